@@ -11,7 +11,7 @@
 //   k_compact_runsum  one wave per run: bytes of the run's tiles
 //   k_compact_scan    one workgroup: exclusive scan over the runs -> run offsets, group byte offsets, total
 //   k_compact_emit    one wave per tile: the bytes
-//   k_unpack_compact  one wave per run, tile in LDS, messages in order (the batched decoder for this format)
+//   k_unpack_compact  one wave per few tiles of a run, tile in LDS, messages in order (the batched decoder for this format)
 #include "vgc_internal.h"
 
 namespace vgc {
@@ -167,26 +167,129 @@ struct CompactArgs {
 };
 
 typedef float f4c __attribute__((ext_vector_type(4)));
+typedef uint16_t us2 __attribute__((ext_vector_type(2)));
 
-__global__ __launch_bounds__(256) void k_unpack_compact(PlanCheck pc, CompactArgs A, const PlanGroup* __restrict__ groups,
-                                                        const PlanRun* __restrict__ runs, uint32_t n_runs, float scale,
-                                                        float* __restrict__ dense, int overwrite) {
+constexpr uint32_t kLaneBytes = 8;                              // bytes of a message a lane decodes per round
+constexpr uint32_t kRoundBytes = 64 * kLaneBytes;
+
+// Inclusive sum over the wave's lanes (DPP row shifts, then the rows' totals broadcast upwards).
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+#define VGC_DPP(ctrl, rows) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xF, false)
+    x += VGC_DPP(0x111, 0xF);
+    x += VGC_DPP(0x112, 0xF);
+    x += VGC_DPP(0x114, 0xF);
+    x += VGC_DPP(0x118, 0xF);
+    x += VGC_DPP(0x142, 0xA);
+    x += VGC_DPP(0x143, 0xC);
+#undef VGC_DPP
+    return x;
+}
+
+// Bits 0..3 of x as bytes of 0x00 or 0xFF.
+__device__ __forceinline__ uint32_t byte_mask(uint32_t x) {
+    const uint32_t y = ((x & 15u) * 0x00204081u) & 0x01010101u;
+    return (y << 8) - y;
+}
+
+// One wave owns tiles_per_wave consecutive tiles of a run (tile in LDS, messages in order).
+//
+// What bounds it: fetched 64 bytes at a time, each fetch waiting for the end of the element before, by one wave per run
+// of 64 tiles, 8 messages of 0.17 x 138 M elements took 2.57 ms, all of it latency (0.79 GB have to move: 0.13 ms).
+// The directory says where every tile's bytes lie, so here a wave can start at any tile of a run, requests the first
+// kRoundBytes of a message's tile while the message before it is decoded, and a lane decodes kLaneBytes consecutive
+// bytes: 0.28 ms (2.8 TB/s), bound by the vector instructions per byte.
+//
+// Whether a lane's bytes begin inside an element follows from two ballots: a byte is the second of an element iff an
+// odd number of bytes with bit 7 set precede it without a gap, so a lane whose bytes all have bit 7 set (an even number
+// of them) passes the state of the lane before it on, and any other lane's outgoing state is the parity of its trailing
+// bytes with bit 7 set.  An element is added at its last byte, up to which its position is the sum of all steps (gap + 1
+// at a first byte, 8 times the value at a second byte); positions are kept in bytes of LDS, two per register.
+// kTiny: some stream is shorter than one 8-byte access; bytes are fetched one by one.
+template <bool kTiny>
+__global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, CompactArgs A, const PlanGroup* __restrict__ groups,
+                                                           const PlanRun* __restrict__ runs, uint32_t n_runs, float scale,
+                                                           float* __restrict__ dense, int overwrite, uint32_t tiles_per_wave) {
+    static_assert(kBatchMax == 8, "a lane per (message, tile of a block of 8)");
     __shared__ __attribute__((aligned(16))) float sh_tile[4][kTile];
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t run = blockIdx.x * 4 + wave;
+    const uint32_t lane = threadIdx.x & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t per_run = (uint32_t)kRunTiles / tiles_per_wave;
+    const uint32_t gw = blockIdx.x * 4 + wave, run = gw / per_run;
     if (run >= n_runs || !plan_ok(pc)) return;
     float* T = sh_tile[wave];
-    const uint32_t k = runs[run].group;
+    const uint32_t k = runs[run].group, first = runs[run].first_tile;
     const PlanGroup pg = groups[k];
     const uint32_t nt_group = (pg.size + kTile - 1) / kTile;
-    const uint32_t t0 = runs[run].first_tile, t1 = min(t0 + (uint32_t)kRunTiles, nt_group);
-    // lane w < p: byte cursor of message w, and the exponent field of the group in that message
-    uint64_t cur = 0;
-    uint32_t expf = 0;
-    if (lane < A.p) {
-        cur = A.run_offsets[lane][run];
-        expf = A.hdrs[lane][k].exp_field;
+    const uint32_t run_end = min(first + (uint32_t)kRunTiles, nt_group);
+    const uint32_t t0 = first + (gw % per_run) * tiles_per_wave;
+    if (t0 >= run_end) return;
+    const uint32_t t1 = min(t0 + tiles_per_wave, run_end);
+
+    // Lanes 8 w .. 8 w + 7 keep message w: where the run's bytes begin, how many bytes the stream has from there (none
+    // past them is read, whatever a damaged directory says), the group's exponent field, and for tile tb + lane % 8 of
+    // the block of 8 tiles being requested: offset inside the run << 13 | bytes (at most 2 kTile a tile).
+    const uint32_t mw = lane >> 3, mj = lane & 7u;
+    const bool mine = mw < A.p;
+    uint64_t run_bytes = 0;
+    uint32_t run_left = 0, expf = 0;
+    const uint16_t* counts = nullptr;
+    if (mine) {
+        const uint64_t at = A.run_offsets[mw][run], n_bytes = A.n_bytes[mw];
+        run_bytes = reinterpret_cast<uint64_t>(A.streams[mw]) + at;
+        run_left = n_bytes > at ? (uint32_t)min(n_bytes - at, (uint64_t)1 << 20) : 0u;
+        expf = A.hdrs[mw][k].exp_field;
+        counts = A.tile_bytes[mw] + pg.first_tile;
     }
+    auto count_of = [&](uint32_t t) { return (mine && t < run_end) ? min((uint32_t)counts[t], 2u * kTile) : 0u; };
+    uint32_t cur = 0;                                           // bytes of the run's tiles before the block
+    for (uint32_t t = first + mj; t < t0; t += 8) cur += count_of(t);
+    cur += (uint32_t)__shfl_xor((int)cur, 1);
+    cur += (uint32_t)__shfl_xor((int)cur, 2);
+    cur += (uint32_t)__shfl_xor((int)cur, 4);
+    uint32_t block = 0, ahead = count_of(t0 + mj);
+    auto next_block = [&](uint32_t tb) {                        // ahead: the counts of the block that begins at tile tb
+        uint32_t incl = ahead;
+#pragma unroll
+        for (int off = 1; off < 8; off <<= 1) {
+            const uint32_t y = (uint32_t)__shfl_up((int)incl, off, 8);
+            if (mj >= (uint32_t)off) incl += y;
+        }
+        block = ((cur + incl - ahead) << 13) | ahead;
+        cur += (uint32_t)__shfl((int)incl, 7, 8);
+        ahead = count_of(tb + 8 + mj);
+    };
+    // bytes off .. off + 7 of the tile's message at S, `left` bytes of which may be read
+    auto fetch = [&](const uint8_t* S, uint32_t off, int left) -> uint2 {
+        uint64_t x = 0;
+        if (kTiny) {
+            for (int i = 0; i < (int)kLaneBytes && (int)off + i < left; ++i) x |= (uint64_t)S[off + i] << (8 * i);
+        } else {
+            const int a = min((int)off, left - (int)kLaneBytes);    // the stream's last bytes: read from before them
+            __builtin_memcpy(&x, (S - kLaneBytes) + (uint32_t)(a + (int)kLaneBytes), sizeof(x));
+            x >>= 8u * (off - (uint32_t)a);
+        }
+        return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+    };
+    // the item (tile, message) requested next, and what has been requested
+    uint32_t tn = t0, wn = 0, nb_n = 0;
+    int left_n = 0;
+    const uint8_t* S_n = nullptr;
+    uint2 x_n = make_uint2(0u, 0u);
+    auto request = [&]() {
+        if (tn >= t1) return;
+        if (wn == 0 && ((tn - t0) & 7u) == 0) next_block(tn);
+        const int src = (int)(wn * 8u);
+        const uint32_t d = (uint32_t)__builtin_amdgcn_readlane((int)block, src + (int)((tn - t0) & 7u));
+        const uint64_t at = ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)(run_bytes >> 32), src) << 32) |
+                            (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)run_bytes, src);
+        left_n = __builtin_amdgcn_readlane((int)run_left, src) - (int)(d >> 13);
+        nb_n = (uint32_t)max(0, min((int)(d & 8191u), left_n));
+        S_n = reinterpret_cast<const uint8_t*>(at) + (d >> 13);
+        if (lane * kLaneBytes < nb_n) x_n = fetch(S_n, lane * kLaneBytes, left_n);
+        if (++wn == A.p) { wn = 0; ++tn; }
+    };
+    if (A.p) request();
+
     for (uint32_t t = t0; t < t1; ++t) {
         const uint32_t start = t * kTile;
         const uint32_t m = min(kTile, pg.size - start);
@@ -203,46 +306,82 @@ __global__ __launch_bounds__(256) void k_unpack_compact(PlanCheck pc, CompactArg
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
         __builtin_amdgcn_wave_barrier();
-        const uint32_t nb_mine = (lane < A.p) ? (uint32_t)A.tile_bytes[lane][(uint64_t)pg.first_tile + t] : 0u;
         for (uint32_t w = 0; w < A.p; ++w) {
-            const uint64_t c0 = ((uint64_t)(uint32_t)__shfl((int)(uint32_t)(cur >> 32), (int)w) << 32) | (uint32_t)__shfl((int)(uint32_t)cur, (int)w);
-            const uint32_t nb = (uint32_t)__shfl((int)nb_mine, (int)w);
-            const uint32_t ef = (uint32_t)__shfl((int)expf, (int)w);
-            const uint8_t* S = A.streams[w] + c0;
-            const uint64_t left = A.n_bytes[w] > c0 ? A.n_bytes[w] - c0 : 0;      // a damaged directory never reads past the stream
-            int32_t pos_base = -1;                              // position of the last element decoded so far
-            uint32_t done = 0;
-            while (done < nb) {                                 // 64 bytes at a time, always starting at an element
-                const uint32_t i = done + lane;
-                const bool valid = i < nb && i < left;
-                const uint32_t byte = valid ? (uint32_t)S[i] : 0u;
-                // a byte starts an element iff the bytes with bit 7 set directly before it are an even number: such a
-                // byte opens a two-byte element when it is itself a start, and is its second byte otherwise
-                const uint64_t L = __ballot(valid && (byte & 0x80u));
-                const uint64_t zeros_below = ~L & lanes_below(lane);
-                const int last_zero = zeros_below ? 63 - __builtin_clzll(zeros_below) : -1;
-                const bool is_start = valid && ((((int)lane - 1 - last_zero) & 1) == 0);
-                const bool is_long = is_start && (byte & 0x80u);
-                const uint32_t next = (uint32_t)__shfl_down((int)byte, 1);
-                const bool cut = is_long && lane == 63u;        // its second byte is in the next 64: leave it for the next round
-                const uint32_t gap = ((byte >> 4) & 7u) | (is_long ? next << 3 : 0u);
-                uint32_t incl = (is_start && !cut) ? gap + 1u : 0u;
+            const uint32_t nb = nb_n;
+            const int left = left_n;
+            const uint8_t* S = S_n;
+            const uint32_t ef = (uint32_t)__builtin_amdgcn_readlane((int)expf, (int)(w * 8u));
+            uint2 x = x_n;
+            request();
+            if (ef == 0 || ef > 254u) continue;                 // nothing of this message can be decoded
+            uint32_t pos0 = ~3u;                                // position of the last element so far (-1: none), in bytes
+            uint32_t inside = 0, last = 0;                      // whether the round begins inside an element, the byte before it
+            for (uint32_t o = 0; o < nb; o += kRoundBytes) {
+                const uint32_t off = o + lane * kLaneBytes;
+                uint2 more = make_uint2(0u, 0u);
+                if (off + kRoundBytes < nb) more = fetch(S, off + kRoundBytes, left);
+                const uint32_t valid = (1u << (off < nb ? min(nb - off, kLaneBytes) : 0u)) - 1u;
+                // bit i: byte i has bit 7 set
+                const uint32_t high = (__builtin_amdgcn_udot4((x.x >> 7) & 0x01010101u, 0x08040201u, 0u, false) |
+                                       __builtin_amdgcn_udot4((x.y >> 7) & 0x01010101u, 0x80402010u, 0u, false)) & valid;
+                const uint64_t stops = __ballot(high != 0xFFu);
+                const uint64_t odd = __ballot((__builtin_clz(~(high << 24)) & 1) != 0);
+                const uint64_t before = stops & lanes_below(lane);
+                const uint32_t in = before ? (uint32_t)(odd >> (63 - __builtin_clzll(before))) & 1u : inside;
+                // second bytes: those after an odd number of set bits, counted from where a run of them begins (the
+                // carry of an addition runs through each run and comes out with its parity)
+                const uint32_t opens = high & ~in;
+                const uint32_t second = (((opens << 1) | 0xAAAAAAAAu) - opens) ^ 0xAAAAAAAAu ^ (high | in);
+                uint32_t ends = valid & (second | ~high);
+                const uint32_t m0 = byte_mask(second), m1 = byte_mask(second >> 4);
+                // the 4-bit value of the element a byte ends: its own, or that of the byte before a second byte
+                const uint32_t prev_lane = (uint32_t)__builtin_amdgcn_update_dpp((int)(last << 24), (int)x.y, 0x138, 0xF, 0xF, false);  // wave_shr:1
+                const uint32_t c0 = (m0 & __builtin_amdgcn_alignbyte(x.x, prev_lane, 3)) | (~m0 & x.x);
+                const uint32_t c1 = (m1 & __builtin_amdgcn_alignbyte(x.y, x.x, 3)) | (~m1 & x.y);
+                // steps, two bytes per register, and their running sums
+                us2 q[4];
+                us2 run_sum = {0, 0};
 #pragma unroll
-                for (int off = 1; off < 64; off <<= 1) {
-                    const uint32_t y = (uint32_t)__shfl_up((int)incl, off);
-                    if (lane >= (uint32_t)off) incl += y;
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t src = i < 2 ? x.x : x.y, msk = i < 2 ? m0 : m1;
+                    const uint32_t h = __builtin_amdgcn_perm(0u, src, (i & 1) ? 0x0C030C02u : 0x0C010C00u);
+                    const uint32_t mm = __builtin_amdgcn_perm(0u, msk, (i & 1) ? 0x03030202u : 0x01010000u);
+                    const uint32_t as_first = ((h >> 2) & 0x001C001Cu) + 0x00040004u, as_second = h << 5;
+                    const uint32_t step = (mm & as_second) | (~mm & as_first);
+                    q[i] = __builtin_bit_cast(us2, step + (step << 16)) + run_sum;
+                    run_sum = (us2){q[i].y, q[i].y};
                 }
-                const int32_t pos = pos_base + (int32_t)incl;
-                const uint32_t d = byte & 7u;
-                if (is_start && !cut && (uint32_t)pos < m && ef > d && ef <= 254u) {
-                    const float val = __uint_as_float(((ef - d) << 23) | ((byte & 8u) << 28));
+                const uint32_t sum = run_sum.x;
+                const uint32_t incl = wave_inclusive_sum(sum);
+                const uint16_t b16 = (uint16_t)(pos0 + incl - sum);
+                if (ef < 8u) {                                  // exponents too small for some of the codes
+#pragma unroll
+                    for (int i = 0; i < (int)kLaneBytes; ++i)
+                        if ((((i < 4 ? c0 : c1) >> (8 * (i & 3))) & 7u) >= ef) ends &= ~(1u << i);
+                }
+                // the elements of one message are distinct: all are read before any is written
+                uint32_t at[kLaneBytes];
+                float old[kLaneBytes];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) {
+                    const uint32_t pair = __builtin_bit_cast(uint32_t, q[i] + (us2){b16, b16}) & (0x00010001u * (4u * (kTile - 1)));
+                    at[2 * i] = pair & 0xFFFFu;
+                    at[2 * i + 1] = pair >> 16;
+                }
+#pragma unroll
+                for (int i = 0; i < (int)kLaneBytes; ++i) old[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(T) + at[i]);
+#pragma unroll
+                for (int i = 0; i < (int)kLaneBytes; ++i) {
+                    const uint32_t c = (i < 4 ? c0 : c1) >> (8 * (i & 3));
+                    const float val = __uint_as_float(((ef - (c & 7u)) << 23) | ((c << 28) & 0x80000000u));
                     const float contrib = scale * val;
-                    T[pos] = T[pos] + contrib;
+                    if ((ends >> i) & 1u) *reinterpret_cast<float*>(reinterpret_cast<char*>(T) + at[i]) = old[i] + contrib;
                 }
-                pos_base += (int32_t)__shfl((int)incl, 63);
-                done += __ballot(cut) ? 63u : 64u;
+                pos0 += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
+                inside = stops ? (uint32_t)(odd >> (63 - __builtin_clzll(stops))) & 1u : inside;
+                last = (uint32_t)__builtin_amdgcn_readlane((int)x.y, 63) >> 24;
+                x = more;
             }
-            if (lane == w) cur += nb;
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
@@ -261,7 +400,8 @@ int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, con
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
                                 const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,
                                 float* dense, hipStream_t stream) {
-    const uint32_t blocks = (uint32_t)((n_runs + 3) / 4);
+    const uint32_t tpw = decode_tiles_per_wave(n_runs);
+    const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;
     for (uint32_t ch = 0; ch < chunks; ++ch) {
         CompactArgs A;
@@ -275,8 +415,13 @@ int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, con
             A.run_offsets[w] = on ? run_offsets[first + w] : nullptr;
             A.hdrs[w] = on ? hdrs[first + w] : nullptr;
         }
-        hipLaunchKernelGGL(k_unpack_compact, dim3(blocks), dim3(256), 0, stream, pc, A, groups, runs, (uint32_t)n_runs, scale, dense,
-                           (overwrite && ch == 0) ? 1 : 0);
+        // the one 8-byte access a lane makes needs a stream of that length; shorter ones are read byte by byte
+        bool tiny = false;
+        for (uint32_t w = 0; w < A.p; ++w) tiny = tiny || A.n_bytes[w] < kLaneBytes;
+        if (tiny) hipLaunchKernelGGL(k_unpack_compact<true>, dim3(blocks), dim3(256), 0, stream, pc, A, groups, runs, (uint32_t)n_runs,
+                                     scale, dense, (overwrite && ch == 0) ? 1 : 0, tpw);
+        else hipLaunchKernelGGL(k_unpack_compact<false>, dim3(blocks), dim3(256), 0, stream, pc, A, groups, runs, (uint32_t)n_runs,
+                                scale, dense, (overwrite && ch == 0) ? 1 : 0, tpw);
     }
     return hip_check(hipGetLastError(), "launch k_unpack_compact");
 }

@@ -78,6 +78,14 @@ struct PlanRun {               // 8 bytes
     uint32_t first_tile;       // index of the run's first tile inside its group
 };
 
+// Tiles one wave of the batched decoders takes: a whole run when there are plenty of runs, fewer (a power of two) when
+// the parameter set is small, so that there are about 16 K waves to spread over the chip.
+inline uint32_t decode_tiles_per_wave(uint64_t n_runs) {
+    uint32_t tpw = kRunTiles;
+    while (tpw > 1 && n_runs * (kRunTiles / tpw) < 16384) tpw /= 2;
+    return tpw;
+}
+
 // Per-tile record in the scratch.  Written by the accumulate kernel (w[0..4]) and completed by
 // the first pack kernel (w[5..7]).
 //   w[0..3]  : hist[0..7], two 16-bit counters per word (low half = even bin)

@@ -309,14 +309,6 @@ __global__ __launch_bounds__(256) void k_unpack_add_batch(PlanCheck pc, BatchArg
     }
 }
 
-// Tiles one wave takes: a whole run when there are plenty of runs, fewer (a power of two) when the parameter
-// set is small, so that there are about 16 K waves to spread over the chip.
-static uint32_t tiles_per_wave(uint64_t n_runs) {
-    uint32_t tpw = kRunTiles;
-    while (tpw > 1 && n_runs * (kRunTiles / tpw) < 16384) tpw /= 2;
-    return tpw;
-}
-
 template <int kMax>
 static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                                   uint32_t first, uint32_t p) {
@@ -334,7 +326,7 @@ static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* 
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                             uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs,
                             float scale, int overwrite, float* dense, hipStream_t stream) {
-    const uint32_t tpw = tiles_per_wave(n_runs);
+    const uint32_t tpw = decode_tiles_per_wave(n_runs);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;     // p == 0: only the optional clear
     for (uint32_t ch = 0; ch < chunks; ++ch) {
@@ -349,7 +341,7 @@ int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64
                         uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale,
                         int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
                         float eps, float* param, float* state1, float* state2, hipStream_t stream) {
-    const uint32_t tpw = tiles_per_wave(n_runs);
+    const uint32_t tpw = decode_tiles_per_wave(n_runs);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const BatchArgs<kApplyMax> A = batch_args<kApplyMax>(words, n_words, hdrs, 0, p);
     UpdateArgs O;

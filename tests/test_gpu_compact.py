@@ -178,3 +178,55 @@ def test_unpack_compact_from_oracle_bytes_with_long_gaps(dev):
                                  [_dev(np.array(chdrs, dtype=vgc.HDR_DTYPE).view(np.uint8), dev)], plan, 0.25, dense, overwrite=True)
     torch.cuda.synchronize()
     assert np.array_equal(_bits(dense.cpu().numpy()), _bits(expect))
+
+
+@pytest.mark.parametrize("case", ["dense", "all_two_byte", "alternating", "one_byte", "two_bytes", "seven_bytes", "small_exponent", "run_end"])
+def test_unpack_compact_at_the_edges_of_a_lane_and_a_round(dev, case):
+    """A lane decodes 8 bytes, a round 512: elements cut by either, tiles of more than one round, streams shorter than a
+    lane's access, exponent fields below the largest code, the tiles around the end of a run; three messages, the second
+    of them shifted so that its bytes begin at other alignments.  Bit-exact against the oracle's decode."""
+    import torch
+    from paper_1802_06058_amd import vgc
+    sizes = [2048 * 66 + 300, 700] if case == "run_end" else [3 * 2048 + 5, 2048]
+    groups = W.groups_from_sizes(sizes)
+    plan = vgc.Plan(groups, dev)
+    rng = np.random.default_rng(len(case))
+    field = 5 if case == "small_exponent" else 120
+    scale = 1.0 if case == "small_exponent" else 1.0 / 3.0
+    expect = np.zeros(plan.n, F32)
+    streams, nb, tb, ro, hd = [], [], [], [], []
+    for w in range(3):
+        idx = []
+        for _, size in groups:
+            if case in ("dense", "small_exponent", "run_end"):
+                i = np.flatnonzero(rng.random(size) < [0.9, 0.4, 0.05][w])
+            elif case == "all_two_byte":
+                i = np.arange(w, size, 9 + w)
+            elif case == "alternating":                          # one- and two-byte elements by turns
+                i = np.cumsum(np.tile([1 + w, 9 + 250 * w], size))
+                i = i[i < size]
+            else:                                                # one to seven bytes in all, in the first group only
+                few = {"one_byte": [3], "two_bytes": [2047], "seven_bytes": [0, 1, 2, 3, 1000, 1001]}[case]
+                i = np.array(few if size > 2048 else [], dtype=np.int64) + (w if case == "seven_bytes" else 0)
+            idx.append(i)
+        code = lambda k: (rng.integers(0, 2, k) << 3 | rng.integers(0, min(8, field), k)).astype(np.uint64)   # d < field: decodable
+        words = np.concatenate([(code(i.size) << np.uint64(28) | i.astype(np.uint64)).astype(U32) for i in idx])
+        counts = [i.size for i in idx]
+        hdrs = [(field if c else 0, c, sum(counts[:k])) for k, c in enumerate(counts)]
+        stream, tile_bytes, run_offsets, chdrs = O.pack_compact(words, hdrs, groups)
+        O.unpack_add(words, hdrs, groups, scale, expect)
+        shift = 5 * w                                            # the stream at an odd address, canary bytes around it
+        whole = np.full(stream.size + 32, 0xFF, np.uint8)
+        whole[shift:shift + stream.size] = stream
+        streams.append(_dev(whole, dev)[shift:shift + stream.size]); nb.append(stream.size)
+        tb.append(_dev(tile_bytes.view(np.int16), dev)); ro.append(_dev(run_offsets.view(np.int64), dev))
+        hd.append(_dev(np.array(chdrs, dtype=vgc.HDR_DTYPE).view(np.uint8), dev))
+    if case == "one_byte":
+        assert nb[0] == 1
+    if case == "seven_bytes":
+        assert nb[0] == 7
+    dense = torch.zeros(plan.n, dtype=torch.float32, device=dev)
+    vgc.unpack_compact_add_batch(streams, nb, tb, ro, hd, plan, scale, dense, overwrite=True)
+    torch.cuda.synchronize()
+    got = dense.cpu().numpy()
+    assert np.array_equal(_bits(got), _bits(expect)), np.flatnonzero(_bits(got) != _bits(expect))[:10]
