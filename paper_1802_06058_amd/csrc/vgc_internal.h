@@ -191,7 +191,7 @@ int launch_sqgrad(int kind, int dtype, const void* X, const void* D, uint32_t B,
 int launch_sqgrad_simple(int kind, int dtype, const void* X, const void* D, uint32_t B, uint32_t P,
                          uint32_t J, uint32_t C, float c, float* g_out, float* s_out, hipStream_t stream);
 
-// LDS-tiled kernels (vgc_sqgrad_tiled.hip, vgc_sqgrad_fc.hip)
+// LDS-tiled kernels (vgc_sqgrad_tiled.hip, vgc_sqgrad_fc.hip, vgc_sqgrad_conv_f32.hip)
 uint32_t conv_splits(uint32_t B, uint32_t J, uint32_t C);
 size_t conv_workspace_bytes(uint32_t B, uint32_t P, uint32_t J, uint32_t C);
 bool conv_taps_supported(uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, uint32_t kh, uint32_t kw, uint32_t sh, uint32_t sw,
@@ -202,7 +202,6 @@ void launch_sqgrad_reduce(const float* ws, uint32_t splits, size_t JC, float cg,
                           hipStream_t stream);
 bool fc_tiled_supported(int dtype, uint32_t B, uint32_t J, uint32_t C);
 bool conv_f32_tiled_supported(uint32_t P, uint32_t J, uint32_t C);
-uint32_t conv_f32_splits(uint32_t B, uint32_t J, uint32_t C);
 size_t conv_f32_workspace_bytes(uint32_t B, uint32_t P, uint32_t J, uint32_t C);
 void launch_sqgrad_reduce_parts(const float* ws, uint32_t B, uint32_t split_p, size_t JC, float cg, float cs, float* g_out,
                                 float* s_out, hipStream_t stream);
@@ -215,8 +214,8 @@ size_t sqgrad_workspace_bytes(int kind, int dtype, uint32_t B, uint32_t P, uint3
 // j = (ky kw + kx) Cin + i is the input element [z, y sh + ky - ph, x sw + kx - pw, i], or zero outside.
 struct ConvGeom {
     uint32_t H, W, Cin, kw, sh, sw, ph, pw, Ho, Wo;
-    uint32_t step_y, step_x; // one chunk of kKC positions further: kKC = step_y * Wo + step_x
-    uint32_t period;         // bf16 kernel, unit strides and Wo = W: chunks after which the column pattern repeats (0: general path)
+    uint32_t step_y, step_x; // one chunk of 32 positions further: 32 = step_y * Wo + step_x
+    uint32_t period;         // unit strides and Wo = W: chunks after which the column pattern repeats (0: general path)
 };
 
 bool conv2d_supported(int dtype, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, uint32_t P);

@@ -1,0 +1,474 @@
+// float32 conv form of the per-parameter sums of Alg. 1 (per sample G_z = U_z^T D_z over the P positions, then
+// g = c sum_z G_z, s = c^2 sum_z G_z . G_z) on the bf16 matrix cores, without giving up float32: every input element is
+// cut into three bf16 pieces that add up to it exactly (hi: its upper 16 bits; mid: the rest rounded to bf16; lo: what is
+// left, at most 8 bits), and of the nine products of two elements' pieces the six that reach 2^-24 of the largest are
+// summed in the float32 accumulators: hi hi, hi mid, mid hi, mid mid, hi lo, lo hi.  The products are exact; what is left
+// out is mid lo, lo mid (2^-26 of the product, of either sign) and lo lo.
+//
+// Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
+// latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.65 ms (98 -> 183 TFLOP/s); the 53 layers
+// of ResNet-50 at batch 32: 3.14 -> 2.35 ms in one batch call.  What bounds it now: the vector instructions that cut the
+// elements (11 per pair) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 43 % busy), and
+// on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
+//
+// The bf16 MFMA adds with truncation: chained over all positions, every instruction would cut off a little of the
+// accumulator, always towards minus infinity.  So the six products of a chunk of 32 positions are summed from zero, where
+// what is cut off is small, and the chunk's sum is added in float32, rounded to nearest; and odd chunks form the negative sum
+// and subtract it, so that what is left of the one-sided error cancels instead of adding up over the samples into g.  Error of s against 64 bits over ResNet-50's layers: 0.52e-7 to 0.81e-7 (with the float32 instruction 0.66e-7
+// to 1.3e-7), of g 0.82e-7 to 1.4e-7 (1.1e-7 to 2.9e-7).
+#include "vgc_internal.h"
+
+namespace vgc {
+
+typedef short s4v __attribute__((ext_vector_type(4)));
+typedef short s8v __attribute__((ext_vector_type(8)));
+typedef __bf16 bf2v __attribute__((ext_vector_type(2)));
+typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
+typedef float f2v __attribute__((ext_vector_type(2)));
+typedef float f4v __attribute__((ext_vector_type(4)));
+typedef uint32_t u2v __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) s4v* lds_s4v_ptr;
+typedef __amdgpu_buffer_rsrc_t rsrc_t;
+
+__device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(base), 0, (int)bytes, 0x00020000);
+}
+
+constexpr int kR32 = 32;                 // positions per LDS stage: one MFMA k-step
+
+// Two floats as three pairs of bf16 whose sum they are.  hi is cut off, not rounded, so that no finite value overflows.
+__device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
+    const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
+    hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
+    const float r0 = x0 - __uint_as_float(u0 & 0xFFFF0000u), r1 = x1 - __uint_as_float(u1 & 0xFFFF0000u);
+    mid = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){r0, r1}, bf2v));
+    const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xFFFF0000u);
+    lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
+}
+
+// One staged chunk in registers: kR32 rows of a BM-wide and of a BN-wide float matrix, PA resp. PB 16-byte
+// pieces per thread of a workgroup of NT threads.  Piece idx of an operand W columns wide sits in row
+// idx / (W / 4), columns 4 (idx % (W / 4)) .. + 3.
+template <int PA, int PB> struct Chunk32 { f4v a[PA], b[PB]; };
+
+// LDS image of one operand's chunk: three planes (hi, mid, lo) of kR32 rows of W bf16.  A transposing read takes one
+// 32-byte unit of rows 0..3, 8..11, 16..19 and 24..27 at once, half of them per pass over the 64 banks: the units of a row are
+// XOR-ed with bits of the row number so that the eight (row, unit) of a pass fall into different banks without padding.
+template <int W> __device__ __forceinline__ constexpr uint32_t lds_swizzle(uint32_t row) {
+    return W >= 128 ? (row & 3u) | ((row >> 1) & 4u) : ((row >> 1) & 1u) | ((row >> 2) & 2u);
+}
+template <int W> __device__ __forceinline__ uint32_t lds_piece(uint32_t row, uint32_t col) {      // byte offset inside a plane
+    return row * (W * 2) + (((col >> 4) ^ lds_swizzle<W>(row)) << 5) + (col & 15u) * 2u;
+}
+
+// X is [B, P, J], D is [B, P, C], samples z_begin .. z_end-1 of this workgroup's split.
+// Input modes other than kPatches: X is the layer's NHWC input [B, H, W, Cin] seen through the geometry G, J = kh kw Cin;
+//         the thread's piece of 4 columns lies inside one filter tap (Cin is a multiple of 4).
+//   kLinear   unit strides, an output as wide as the input: the input element of position p is a constant number of
+//             elements after p's own, so offsets advance by a constant per chunk; whether the column lies inside the
+//             image repeats every W / gcd(W, kR32) <= 32 chunks and is kept as one bit per chunk of that period.
+//   kGeneral  offsets are formed per chunk from the output position of the row, which is kept incrementally.
+// BM x BN: the block tile; WM x WN: the part of it a wave multiplies, in MFMA tiles of 16 x 16.
+enum { kPatches = 0, kLinear = 1, kGeneral = 2 };
+
+template <bool kWantG, int kMode, int BM, int BN, int WM, int WN>
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
+void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t P, uint32_t J, uint32_t C,
+                uint32_t splits, uint32_t split_p, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out,
+                float* __restrict__ ws, ConvGeom G) {
+    constexpr int NT = (BM / WM) * (BN / WN) * 64;                   // threads of the workgroup
+    constexpr int MT = WM / 16, NTL = WN / 16;                       // MFMA tiles of a wave
+    constexpr int PA = kR32 * BM / 4 / NT, PB = kR32 * BN / 4 / NT;  // 16-byte pieces per thread and chunk
+    constexpr int kPlaneA = kR32 * BM * 2, kPlaneB = kR32 * BN * 2;  // bytes
+    static_assert(NT % (BM / 4) == 0 && NT % (BN / 4) == 0, "all pieces of a thread lie in the same columns");
+    __shared__ __attribute__((aligned(16))) uint8_t shA[2][3 * kPlaneA];
+    __shared__ __attribute__((aligned(16))) uint8_t shB[2][3 * kPlaneB];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, wm = wave / (BN / WN), wn = wave % (BN / WN);
+    const uint32_t tiles_c = (C + BN - 1) / BN, tiles_j = (J + BM - 1) / BM;
+    const uint32_t nblk = gridDim.x, per = nblk / 8u, rem = nblk % 8u;
+    const uint32_t xcd = blockIdx.x % 8u, slot = blockIdx.x / 8u;
+    const uint32_t logical = xcd * per + min(xcd, rem) + slot;       // contiguous range of tiles per XCD
+    const uint32_t tile_c = logical % tiles_c, tile_j = (logical / tiles_c) % tiles_j, split = logical / (tiles_c * tiles_j);
+    const uint32_t j0 = tile_j * BM, c0 = tile_c * BN;
+    // split_p > 1: the workgroup owns part `part` of the positions of the single sample split / split_p
+    // and leaves the unsquared partial product in the workspace
+    const uint32_t n_chunks = (P + kR32 - 1) / kR32;
+    const uint32_t part = split_p > 1 ? split % split_p : 0u;
+    const uint32_t chunks_per_part = (n_chunks + split_p - 1) / split_p;
+    const uint32_t c_begin = min(n_chunks, part * chunks_per_part);
+    // sample ranges of the splits differ by at most one sample
+    const uint32_t z_begin = split_p > 1 ? split / split_p : (uint32_t)((uint64_t)split * B / splits);
+    const uint32_t z_end = split_p > 1 ? z_begin + 1u : (uint32_t)((uint64_t)(split + 1u) * B / splits);
+    const uint32_t total = split_p > 1 ? min(n_chunks, c_begin + chunks_per_part) - c_begin : (z_end - z_begin) * n_chunks;
+
+    f4v acc[MT][NTL], s_acc[MT][NTL], g_acc[MT][NTL];
+#pragma unroll
+    for (int a = 0; a < MT; ++a)
+#pragma unroll
+        for (int b = 0; b < NTL; ++b) { acc[a][b] = (f4v){0}; s_acc[a][b] = (f4v){0}; g_acc[a][b] = (f4v){0}; }
+
+    // the thread's pieces lie in the same columns, kRowStep rows apart
+    constexpr uint32_t kRowStepA = NT / (BM / 4), kRowStepB = NT / (BN / 4);
+    const uint32_t rowA = tid / (BM / 4), rowB = tid / (BN / 4), colj = j0 + (tid % (BM / 4)) * 4u;
+    const uint32_t offB = (rowB * C + c0 + (tid % (BN / 4)) * 4u) * 4u;
+    uint32_t offA = (rowA * J + colj) * 4u, offA0 = 0, rowsA = kRowStepA * J * 4u, phase = 0;
+    uint32_t y0A[PA], x0A[PA], yA[PA], xA[PA], outside[PA];
+    int32_t tapX = 0, tapOff = 0;
+    if (kMode != kPatches) {
+        const uint32_t tap = colj / G.Cin, ky = tap / G.kw;
+        const int32_t ty = (int32_t)ky - (int32_t)G.ph;
+        tapX = (int32_t)(tap - ky * G.kw) - (int32_t)G.pw;
+        tapOff = (ty * (int32_t)G.W + tapX) * (int32_t)G.Cin + (int32_t)(colj - tap * G.Cin);
+        if (colj >= J) tapX = -0x400000;                     // a column past J: never inside the input
+    }
+    if (kMode == kLinear) {
+        offA0 = (uint32_t)((int32_t)(rowA * G.Cin) + tapOff) * 4u;
+        offA = offA0 + c_begin * (kR32 * G.Cin * 4u);
+        rowsA = kRowStepA * G.Cin * 4u;
+        phase = c_begin % G.period;
+#pragma unroll
+        for (int i = 0; i < PA; ++i) {
+            uint32_t x = (rowA + kRowStepA * (uint32_t)i) % G.W;
+            outside[i] = 0;
+            for (uint32_t k = 0; k < G.period; ++k) {
+                outside[i] |= ((uint32_t)((int32_t)x + tapX) < G.W ? 0u : 1u) << k;
+                x = (x + kR32) % G.W;
+            }
+        }
+    }
+    if (kMode == kGeneral) {
+#pragma unroll
+        for (int i = 0; i < PA; ++i) {
+            const uint32_t pos0 = c_begin * kR32 + rowA + kRowStepA * (uint32_t)i;    // the row in the workgroup's first chunk
+            y0A[i] = yA[i] = pos0 / G.Wo;
+            x0A[i] = xA[i] = pos0 - y0A[i] * G.Wo;
+        }
+    }
+    Chunk32<PA, PB> R;
+    uint32_t zl = z_begin, pcl = c_begin, issued = 0;
+    // request of piece i of chunk (zl, pcl) (pieces of A, then those of B); past the last chunk the range is empty
+    auto issue_piece = [&](int i) {
+        const bool live = issued < total;
+        const uint32_t zz = live ? zl : z_begin;
+        if (i >= PA) {
+            const rsrc_t rb = make_rsrc(D + ((size_t)zz * P + pcl * kR32) * C, live ? (P - pcl * kR32) * C * 4u : 0u);
+            const uint32_t voff = offB + (uint32_t)(i - PA) * (kRowStepB * C * 4u);
+            R.b[i < PA ? 0 : i - PA] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)voff, 0, 0));
+            return;
+        }
+        const int ia = i < PA ? i : 0;
+        rsrc_t ra;
+        uint32_t voff;
+        if (kMode == kPatches) {
+            ra = make_rsrc(X + ((size_t)zz * P + pcl * kR32) * J, live ? (P - pcl * kR32) * J * 4u : 0u);
+            voff = offA + (uint32_t)ia * rowsA;
+        } else {
+            // rows of the input outside the image give an offset that is negative or past the sample: the load answers with
+            // zeros; columns outside are masked (as are positions past P in the general mode; in the linear one they alias
+            // into pixels of the sample, where the rows of D read as zeros)
+            const uint32_t sample = G.H * G.W * G.Cin;
+            ra = make_rsrc(X + (size_t)zz * sample, live ? sample * 4u : 0u);
+            if (kMode == kLinear) {
+                voff = (offA + (uint32_t)ia * rowsA) | (uint32_t)__builtin_amdgcn_sbfe((int32_t)outside[ia], phase, 1u);
+            } else {
+                const int32_t ys = __mul24((int32_t)yA[ia], (int32_t)G.sh), xs = __mul24((int32_t)xA[ia], (int32_t)G.sw);
+                const bool inside = ((uint32_t)(xs + tapX) < G.W) & (yA[ia] < G.Ho);
+                const int32_t off = __mul24(__mul24(ys, (int32_t)G.W) + xs, (int32_t)G.Cin) + tapOff;
+                voff = ((uint32_t)off << 2) | (inside ? 0u : 0xFFFFFFFFu);
+            }
+        }
+        R.a[ia] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)voff, 0, 0));
+    };
+    auto issue_done = [&]() {                                     // every piece of the chunk is requested: on to the next
+        const bool wrap = (++pcl == n_chunks);
+        if (wrap) { pcl = 0; ++zl; }
+        if (kMode == kLinear) {
+            offA = wrap ? offA0 : offA + kR32 * G.Cin * 4u;
+            phase = wrap || phase + 1u == G.period ? 0u : phase + 1u;
+        }
+        if (kMode == kGeneral) {
+#pragma unroll
+            for (int i = 0; i < PA; ++i) {                        // the row of the next chunk: kR32 positions further
+                const uint32_t x = xA[i] + G.step_x, xw = x - G.Wo;
+                const uint32_t carry = x >= G.Wo ? 1u : 0u;
+                const uint32_t keep = wrap ? 0u : 0xFFFFFFFFu;
+                xA[i] = (min(x, xw) & keep) | (x0A[i] & ~keep);
+                yA[i] = ((yA[i] + G.step_y + carry) & keep) | (y0A[i] & ~keep);
+            }
+        }
+        ++issued;
+    };
+    // piece i of the requested chunk (those of A, then those of B); rows kRowStep apart differ in the swizzle by a constant
+    static_assert(kRowStepA % 8 == 0 && kRowStepB % 8 == 0, "the low bits of the row are the thread's own");
+    const uint32_t toA = lds_piece<BM>(rowA, (tid % (BM / 4)) * 4u), toB = lds_piece<BN>(rowB, (tid % (BN / 4)) * 4u);
+    u2v sh_, sm_, sl_;                                               // the piece's three planes
+    // half h of piece i: two of its four columns; the second half stores the piece and requests the next chunk's
+    auto stage_half = [&](uint32_t buf, int i, int h) {                // buf: the parity of the chunk
+        f4v x = i < PA ? R.a[i < PA ? i : 0] : R.b[i < PA ? 0 : i - PA];
+        if (i < PA && buf) x = -x;
+        uint32_t a, b, c;
+        split_pair(x[2 * h], x[2 * h + 1], a, b, c);
+        sh_[h] = a; sm_[h] = b; sl_[h] = c;
+        if (h == 0) return;
+        // (rowA < kRowStepA: where that is 8, bit 3 of the row is that of i kRowStep alone)
+        uint8_t* p = i < PA ? shA[buf] + (toA ^ (lds_swizzle<BM>((uint32_t)i * kRowStepA) << 5)) + (uint32_t)i * (kRowStepA * BM * 2)
+                            : shB[buf] + (toB ^ (lds_swizzle<BN>((uint32_t)(i - PA) * kRowStepB) << 5)) + (uint32_t)(i - PA) * (kRowStepB * BN * 2);
+        const int plane = i < PA ? kPlaneA : kPlaneB;
+        *reinterpret_cast<u2v*>(p) = sh_;
+        *reinterpret_cast<u2v*>(p + plane) = sm_;
+        *reinterpret_cast<u2v*>(p + 2 * plane) = sl_;
+        issue_piece(i);
+    };
+    constexpr int kValu = 4;
+    constexpr int kHalves = 2 * (PA + PB), kSlots = 3 * MT;          // a chunk's staging is dealt out over so many places in the loop
+    auto stage_slot = [&](uint32_t buf, int s) {
+        // (from and to by arithmetic, so that the unrolled loop has one or two turns and every index is a constant)
+        const int from = (s * kHalves + kSlots - 1) / kSlots, to = ((s + 1) * kHalves + kSlots - 1) / kSlots;
+#pragma unroll
+        for (int k = from; k < to; ++k) stage_half(buf, k >> 1, k & 1);
+        if (s == kSlots - 1) issue_done();
+    };
+
+    // the lane's place in a transposed fragment (ds_read_b64_tr_b16): rows 8 (lane / 16) .. + 7 of the k-step in two reads
+    // of four, of which it addresses row r / 4 (rows r and r + 4 share the swizzle), and the 32-byte unit of the MFMA tile's
+    // 16 columns
+    const uint32_t r16 = lane & 15u, frow = (lane >> 4) * 8u + (r16 >> 2);
+    const uint32_t fA = lds_piece<BM>(frow, wm * (uint32_t)WM + 4u * (r16 & 3u)), fB = lds_piece<BN>(frow, wn * (uint32_t)WN + 4u * (r16 & 3u));
+    auto frag = [&](const uint8_t* p, int pitch) -> bf8v {
+        const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(p));
+        const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(p + 4 * pitch));
+        s8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf8v, v);
+    };
+
+#pragma unroll
+    for (int i = 0; i < PA + PB; ++i) issue_piece(i);
+    issue_done();
+#pragma unroll
+    for (int s = 0; s < kSlots; ++s) stage_slot(0, s);
+#pragma unroll
+    for (int s = 0; s < 3; ++s) stage_slot(1, s);
+    __syncthreads();
+
+    static_assert(MT % 2 == 0, "the fragments' sets go by the row's parity");
+    bf8v a[2][3], b[2][NTL][3];                                      // row m in set m % 2, chunk q's columns in set q % 2
+    auto fetch_a = [&](uint32_t buf, int m, int pl) { a[m & 1][pl] = frag(shA[buf] + pl * kPlaneA + (fA ^ ((uint32_t)m * 32u)), BM * 2); };
+    auto fetch_b = [&](uint32_t buf, int pl) {                       // the unit's XOR with the row is the lane's own: tiles XOR in
+#pragma unroll
+        for (int n = 0; n < NTL; ++n) b[buf][n][pl] = frag(shB[buf] + pl * kPlaneB + (fB ^ ((uint32_t)n * 32u)), BN * 2);
+    };
+#pragma unroll
+    for (int pl = 2; pl >= 0; --pl) { fetch_a(0, 0, pl); fetch_b(0, pl); }
+
+    // Chunk q sits in LDS buffer q % 2.  The two waves of a SIMD pass the barrier together and would all multiply, then all
+    // convert (measured: matrix and vector time added up), so the conversion of the chunks to come is cut into two-column
+    // halves of a thread's pieces and spread between the MFMAs, each slice kept in its place, and a piece is requested
+    // again, two chunks on, as soon as its registers are free.  The fragments of the next MFMA row are fetched during this one,
+    // those of the next chunk during this one's last row.  The one barrier of a chunk stands before its last row: by then the
+    // wave has fetched all of chunk q's fragments and stored its pieces of chunk q + 1; those of chunk q + 2 follow into
+    // chunk q's buffer.
+    uint32_t left = split_p > 1 ? 0u : n_chunks;                     // chunks until the sample's product is complete (0: never)
+    for (uint32_t q0 = 0; q0 < total; q0 += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u > 0 && q0 + (uint32_t)u >= total) break;
+            const uint32_t buf = (uint32_t)u;
+            constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};   // the smallest products first
+            const bool last = --left == 0;                           // sample finished with this chunk: G_z is complete in acc
+            if (last) left = n_chunks;
+#pragma unroll
+            for (int m = 0; m < MT; ++m) {
+                const bool end = m + 1 == MT;
+                const uint32_t fbuf = end ? buf ^ 1u : buf;
+                const int fm = end ? 0 : m + 1;
+                if (end) {
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                }
+                f4v T[NTL];                                          // the chunk's own sum (of -A B for odd chunks, see above)
+#pragma unroll
+                for (int n = 0; n < NTL; ++n) T[n] = (f4v){0};
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) T[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m & 1][kPa[e]], b[u][n][kPb[e]], T[n], 0, 0, 0);
+                    if (e < 3) fetch_a(fbuf, fm, 2 - e);
+                    if (end && e < 3) fetch_b(fbuf, 2 - e);
+                    if (e & 1) {
+                        stage_slot(end ? buf : buf ^ 1u, end ? e / 2 : m * 3 + e / 2 + 3);
+#pragma unroll
+                        for (int k = 0; k < 2 * NTL; ++k) {
+                            __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                            __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
+                        }
+                        __builtin_amdgcn_sched_barrier(0);
+                    }
+                }
+                if (u) {
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) T[n] = -T[n];
+                }
+                if (last) {
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float x = acc[m][n][i] + T[n][i];
+                            s_acc[m][n][i] = __builtin_fmaf(x, x, s_acc[m][n][i]);
+                            if (kWantG) g_acc[m][n][i] += x;
+                        }
+                        acc[m][n] = (f4v){0};
+                    }
+                } else {
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) acc[m][n] = acc[m][n] + T[n];
+                }
+            }
+        }
+    }
+
+    // split_p > 1: the partial product itself, for k_sqgrad_reduce_parts; else the scaled result or unscaled partial sums
+    const bool direct = (splits == 1);
+    const size_t JC = (size_t)J * C;
+    float* so = split_p > 1 ? ws + (size_t)split * JC : direct ? s_out : ws + (size_t)split * 2 * JC;
+    float* go = direct ? g_out : ws + (size_t)split * 2 * JC + JC;
+    const float fs = direct && split_p == 1 ? cs : 1.0f, fg = direct ? cg : 1.0f;
+#pragma unroll
+    for (int m = 0; m < MT; ++m)
+#pragma unroll
+        for (int n = 0; n < NTL; ++n) {
+            const uint32_t col = c0 + wn * (uint32_t)WN + n * 16u + (lane & 15u);
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const uint32_t row = j0 + wm * (uint32_t)WM + m * 16u + 4u * (lane >> 4) + (uint32_t)i;
+                if (row < J && col < C) {
+                    const size_t o = (size_t)row * C + col;
+                    __builtin_nontemporal_store(split_p > 1 ? acc[m][n][i] : fs * s_acc[m][n][i], so + o);
+                    if (kWantG) __builtin_nontemporal_store(fg * g_acc[m][n][i], go + o);
+                }
+            }
+        }
+}
+
+// ------------------------------------------------------------------------------------------------
+// host side
+// ------------------------------------------------------------------------------------------------
+bool conv_f32_tiled_supported(uint32_t P, uint32_t J, uint32_t C) {
+    const uint64_t limit = 0x7FFFFFFFull;
+    return J % 4 == 0 && C % 4 == 0 && (uint64_t)(P + 16) * J * 4 < limit && (uint64_t)(P + 16) * C * 4 < limit;
+}
+
+// Block tile of the float32 conv kernel for a shape: 64 instead of 128 rows (columns) where that wastes at
+// least a fifth fewer of them (J or C at most 64, or just past a multiple of 128).  256 rows were tried: 10 to 15 % faster
+// where every compute unit gets eight samples or more (14 x 14, 256 -> 256, 3 x 3 at batch 256: 315 us against 354), slower
+// below (batch 32: 65 against 60), and s would depend on whether g is asked for, whose accumulators that tile has no room for.
+struct F32Tile { uint32_t bm, bn; };
+static uint32_t f32_tile_edge(uint32_t n) {
+    const uint32_t pad128 = (n + 127) / 128 * 128, pad64 = (n + 63) / 64 * 64;
+    return pad64 * 5 <= pad128 * 4 ? 64u : 128u;
+}
+static F32Tile conv_f32_tile(uint32_t J, uint32_t C) { return F32Tile{f32_tile_edge(J), f32_tile_edge(C)}; }
+static uint64_t conv_f32_tiles(const F32Tile& t, uint32_t J, uint32_t C) {
+    return (uint64_t)((J + t.bm - 1) / t.bm) * ((C + t.bn - 1) / t.bn);
+}
+// Workgroups resident at once: as many as 160 KB of LDS hold at two staged chunks each (one of 128 x 128, two of 128 x 64,
+// three of 64 x 64).
+static uint64_t conv_f32_slots(const F32Tile& t) {
+    const uint64_t lds = 2ull * 3 * kR32 * (t.bm + t.bn) * sizeof(uint16_t);
+    return 256 * ((160ull * 1024) / lds);
+}
+
+// How a shape's work is divided: the samples over `splits` workgroups per tile, or (split_p > 1) every sample's positions
+// over split_p of them, for `slots` workgroups at once and chunks of `chunk` positions.  most: bytes of workspace.
+struct F32Split { uint32_t splits, split_p; };
+static size_t f32_split_bytes(const F32Split& r, uint32_t J, uint32_t C) {
+    const size_t JC = (size_t)J * C * sizeof(float);
+    return r.split_p > 1 ? (size_t)r.splits * JC : r.splits > 1 ? (size_t)r.splits * 2 * JC : 0;
+}
+static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32_t B, uint32_t P, uint32_t J, uint32_t C, size_t most) {
+    const uint32_t n_chunks = (P + chunk - 1) / chunk;
+    F32Split r{1, 1};
+    if (tiles * B * 3 <= slots * 2 && n_chunks >= 256u / chunk) {
+        // up to half a round: as many parts as fill one round; up to two thirds: just under two rounds
+        const uint64_t sp = tiles * B * 2 <= slots ? slots / (tiles * B) : 2 * slots / (tiles * B);
+        r.split_p = (uint32_t)(sp < n_chunks * chunk / 128u ? sp : n_chunks * chunk / 128u);
+        while (r.split_p > 1 && f32_split_bytes(F32Split{B * r.split_p, r.split_p}, J, C) > most) --r.split_p;
+        if (r.split_p > 1) { r.splits = B * r.split_p; return r; }
+        r.split_p = 1;
+    }
+    double best = 1e300;
+    for (uint32_t s = 1; s <= B; ++s) {
+        const uint32_t zper = (B + s - 1) / s, s2 = (B + zper - 1) / zper;
+        if (s2 != s || f32_split_bytes(F32Split{s, 1}, J, C) > most) continue;
+        const uint64_t rounds = (tiles * s2 + slots - 1) / slots;
+        const double cost = (double)rounds * zper + (s2 > 1 ? 0.5 * s2 * (double)tiles / slots + 0.5 : 0.0);
+        if (cost < best - 1e-9) { best = cost; r.splits = s2; }
+    }
+    return r;
+}
+// The workspace a shape asks for, which is also what vgc_sqgrad_noalloc accepts or refuses it by, is a rule of its own: what
+// two, four or six workgroups per compute unit of 128 x 128, 128 x 64 and 64 x 64 tiles would fill.  The kernel has fewer and
+// larger workgroups in flight and needs less for nearly all shapes; where it would need more it splits less.
+size_t conv_f32_workspace_bytes(uint32_t B, uint32_t P, uint32_t J, uint32_t C) {
+    const F32Tile t = conv_f32_tile(J, C);
+    const uint64_t slots = 256 * (t.bm + t.bn == 256 ? 2 : t.bm + t.bn == 192 ? 4 : 6);
+    return f32_split_bytes(f32_split(conv_f32_tiles(t, J, C), slots, 16, B, P, J, C, ~(size_t)0), J, C);
+}
+
+template <int kMode>
+static int launch_conv_f32_any(const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
+                               float* g_out, float* s_out, void* workspace, size_t workspace_bytes, const ConvGeom& G,
+                               hipStream_t stream) {
+    const size_t JC = (size_t)J * C;
+    const F32Tile t = conv_f32_tile(J, C);
+    const size_t asked = conv_f32_workspace_bytes(B, P, J, C);
+    F32Split sp = f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked);
+    if (!workspace || workspace_bytes < asked) sp = F32Split{1, 1};
+    const uint32_t splits = sp.splits, split_p = sp.split_p;
+    // with the positions split the partial products are unsquared: the variant without g serves both
+    const bool with_g = g_out && split_p == 1;
+    const uint64_t nblk = conv_f32_tiles(t, J, C) * splits;
+    if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
+    const float cg = c, cs = c * c;
+    float* ws = static_cast<float*>(workspace);
+    const float* Xf = static_cast<const float*>(X);
+    const float* Df = static_cast<const float*>(D);
+#define VGC_LAUNCH_F32(G_, BM_, BN_, WM_, WN_)                                                                             \
+    hipLaunchKernelGGL((k_conv_f32<G_, kMode, BM_, BN_, WM_, WN_>), dim3((uint32_t)nblk),                              \
+                       dim3((BM_ / WM_) * (BN_ / WN_) * 64), 0, stream, Xf, Df, B, P, J, C, splits, split_p, cg, cs, g_out, s_out, ws, G)
+#define VGC_LAUNCH_F32_TILES(G_)                                                                                           \
+    do {                                                                                                                   \
+        if (t.bm == 128 && t.bn == 128) VGC_LAUNCH_F32(G_, 128, 128, 64, 32);                                              \
+        else if (t.bm == 128) VGC_LAUNCH_F32(G_, 128, 64, 64, 32);                                                         \
+        else if (t.bn == 128) VGC_LAUNCH_F32(G_, 64, 128, 64, 32);                                                         \
+        else VGC_LAUNCH_F32(G_, 64, 64, 32, 32);                                                                           \
+    } while (0)
+    if (with_g) VGC_LAUNCH_F32_TILES(true);
+    else VGC_LAUNCH_F32_TILES(false);
+#undef VGC_LAUNCH_F32_TILES
+#undef VGC_LAUNCH_F32
+    if (split_p > 1) launch_sqgrad_reduce_parts(ws, B, split_p, JC, cg, cs, g_out, s_out, stream);
+    else if (splits > 1) launch_sqgrad_reduce(ws, splits, JC, cg, cs, g_out, s_out, stream);
+    return hip_check(hipGetLastError(), "launch k_conv_f32");
+}
+
+int launch_conv_f32_tiled(const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
+                          float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+    return launch_conv_f32_any<kPatches>(X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, ConvGeom{}, stream);
+}
+
+int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
+                      float* g_out, float* s_out, void* workspace, size_t workspace_bytes, ConvGeom G, hipStream_t stream) {
+    if (G.sh == 1 && G.sw == 1 && G.Wo == G.W) {
+        uint32_t a = G.W, b = kR32 % G.W;
+        while (b) { const uint32_t m = a % b; a = b; b = m; }
+        G.period = G.W / a;
+        if (G.period <= 32) return launch_conv_f32_any<kLinear>(act, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, G, stream);
+    }
+    G.step_y = kR32 / G.Wo;
+    G.step_x = kR32 % G.Wo;
+    return launch_conv_f32_any<kGeneral>(act, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, G, stream);
+}
+
+}  // namespace vgc

@@ -1,0 +1,96 @@
+"""The float32 conv statistic on the bf16 matrix cores (three bf16 pieces per element): every block tile, input mode and
+remainder of its kernel against the float64 oracle; that no bit of a float32 input is lost over the range of exponents;
+and that the sums are not biased although the matrix instruction truncates."""
+import numpy as np
+import pytest
+
+from oracle import vgc_oracle as O
+from test_gpu_sqgrad_conv2d import _patches, _run
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dev():
+    import torch
+    from paper_1802_06058_amd import vgc
+    assert torch.cuda.is_available()
+    vgc.load()
+    return torch.device("cuda:0")
+
+
+SHAPES = [  # B, H, W, Cin, C, k, stride, pad          tile, input mode
+    (4, 4, 8, 60, 60, 1, 1, 0),                      # 64 x 64, 32 positions: one whole chunk
+    (5, 3, 11, 64, 68, 1, 1, 0),                     # 64 x 128 with a ragged column tile, 33 positions
+    (4, 31, 1, 132, 64, 1, 1, 0),                    # 128 x 64, 31 positions, output one column wide
+    (6, 7, 7, 24, 132, 3, 1, 1),                     # 128 x 128, 49 positions, ragged in both directions
+    (4, 9, 14, 36, 128, 3, 2, 1),                    # general mode: stride 2
+    (4, 8, 37, 16, 64, 3, 1, 1),                     # W = 37: a period of 37 chunks does not fit the mask
+    (5, 10, 32, 16, 64, 3, 1, 1),                    # W = 32: a period of one chunk
+    (4, 66, 33, 12, 12, 3, 1, 1),                    # the positions split over workgroups
+    (4, 40, 41, 8, 132, 2, 1, 0),                    # even kernel, output narrower than the input
+    (40, 3, 5, 256, 1024, 1, 1, 0),                  # several samples per workgroup
+]
+
+
+@pytest.mark.parametrize("want_g", [False, True])
+@pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
+def test_shapes(dev, shape, want_g):
+    import torch
+    from paper_1802_06058_amd import vgc
+    B, H, W, Cin, C, k, st, pad = shape
+    rng = np.random.default_rng(B * H + W + C)
+    A = rng.standard_normal((B, H, W, Cin)).astype(np.float32)
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    D = (rng.standard_normal((B, Ho, Wo, C)) * 1e-3).astype(np.float32)
+    U = _patches(A, k, k, (st, st), (pad, pad), Ho, Wo).astype(np.float64)
+    E = D.reshape(B, Ho * Wo, C).astype(np.float64)
+    G = np.matmul(U.transpose(0, 2, 1), E)
+    c = np.float32(1.0 / B)
+    g64, s64 = G.sum(0) * float(c), (G * G).sum(0) * float(c) ** 2
+    mag = np.matmul(np.abs(U).transpose(0, 2, 1), np.abs(E)).sum(0) * float(c)
+    runs = [_run(A, D, k, k, (st, st), (pad, pad), float(c), dev, want_g, use_ws) for use_ws in (True, False)]
+    X = torch.from_numpy(np.ascontiguousarray(U.astype(np.float32))).to(dev)
+    Dd = torch.from_numpy(np.ascontiguousarray(D.reshape(B, Ho * Wo, C))).to(dev)
+    s = torch.empty(U.shape[2], C, device=dev)
+    g = torch.empty(U.shape[2], C, device=dev) if want_g else None
+    vgc.sqgrad(vgc.CONV, X, Dd, float(c), s, g)                      # the patch matrix, no workspace
+    runs.append((g.cpu().numpy() if want_g else None, s.cpu().numpy()))
+    for gv, sv in runs:
+        # |G_z - exact| <= about (P / 32 + 8) roundings of 2^-24 of the magnitudes summed; s doubles it.  The outputs are sums
+        # over at least four samples, so s does not cancel below a hundredth of the magnitudes squared.
+        assert np.all(np.abs(sv - s64) <= 1e-5 * s64)
+        if want_g:
+            assert np.all(np.abs(gv - g64) <= 1e-6 * mag)
+
+
+@pytest.mark.parametrize("exponent", [-100, -60, -1, 0, 60, 126])
+def test_every_bit_of_the_inputs_counts(dev, exponent):
+    """One sample, one position: g is the product of two floats.  The three pieces of each add up to it exactly; with hi cut
+    off (mid < 2^-7 of the leading bit, lo <= 2^-16) the two products mid lo that are left out stay below 2^-22 in all, and
+    the six truncating additions below another 2^-22."""
+    rng = np.random.default_rng(exponent + 200)
+    Cin, C = 64, 64
+    x = np.ldexp(rng.uniform(1, 2, Cin), exponent).astype(np.float32)
+    x[:4] = np.ldexp(np.array([1 + 2.0 ** -23, 2 - 2.0 ** -23, 1 + 2.0 ** -16, 1 + 2.0 ** -8]), exponent).astype(np.float32)
+    x[4:8] = -x[:4]
+    d = rng.uniform(0.5, 1, C).astype(np.float32)
+    d[:2] = [1.0, 1 - 2.0 ** -24]
+    if exponent == 126:
+        x[8] = np.float32(3.4028235e38)                             # the largest float: its upper half must not round to infinity
+    g, _ = _run(x.reshape(1, 1, 1, Cin), d.reshape(1, 1, 1, C), 1, 1, (1, 1), (0, 0), 1.0, dev)
+    want = np.outer(x.astype(np.float64), d.astype(np.float64))
+    assert np.all(np.abs(g - want) <= 2.0 ** -21 * np.abs(want))
+
+
+def test_sums_are_not_biased(dev):
+    """The mean error of g over many outputs: each output errs by at most 1e-6 of its magnitudes, and if the truncation of the
+    matrix instruction did not cancel, all would err to the same side (1e-7 of the magnitudes at 1600 positions)."""
+    rng = np.random.default_rng(5)
+    B, H, Cin, C = 8, 40, 64, 64
+    A = rng.standard_normal((B, H, H, Cin)).astype(np.float32)
+    D = rng.standard_normal((B, H, H, C)).astype(np.float32)
+    g, _ = _run(A, D, 1, 1, (1, 1), (0, 0), 1.0, dev, use_workspace=False)
+    U, E = A.reshape(-1, Cin).astype(np.float64), D.reshape(-1, C).astype(np.float64)
+    err = g - U.T @ E
+    assert abs(err.mean()) <= 2e-9 * (np.abs(U).T @ np.abs(E)).mean()
