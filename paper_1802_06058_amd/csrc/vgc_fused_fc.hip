@@ -8,10 +8,17 @@
 // weight [J, C]: 16 rows x 2048 columns when C is a multiple of 2048 (a tile is a piece of a row), 16 R whole
 // rows when C = 2048 / R (a tile is R rows).  The K = |B| contraction is short, so the operands are read
 // from a pre-transposed copy (K contiguous per row / column: one 16-byte load per MFMA fragment, no LDS) that a
-// small kernel prepares, and all 16 tiles' g and s stay in the accumulators (2 x 64 registers per lane).  They
-// then pass through LDS four tiles at a time, which turns the MFMA layout into the tile order the select
-// pass works in, and each half of the workgroup runs the tile core on one tile at a time while the r and v
-// of the next tile are already in flight.
+// small kernel prepares.  The columns are the M side of the MFMA and the rows its N side, so that a lane holds four
+// consecutive columns of one row; 32 columns of 16 rows at a time are turned through a wave's own LDS so that each access
+// to r and v covers whole 128-byte lines, and finished in registers down to 16 bits per element (sign and exponents of
+// what is sent).  When all 16 tiles are through, these go to LDS in tile order and each wave encodes two tiles from there.
+//
+// What bounds it: r and v read and written, 16 bytes per parameter (25088 x 4096: 1.64 GB, 0.28 ms at the 5.9 TB/s of an
+// in-place stream), and how far the contraction (0.20 ms alone) and that stream overlap.  Keeping all 16 tiles' g and s in
+// accumulators and passing them through LDS into tile order took one workgroup of 131 KB of LDS per compute unit, whose
+// waves contracted, streamed and encoded in step: 0.43 ms.  With 70 KB and 128 registers two workgroups share a compute
+// unit: 0.38 ms.  Loads come back in the order of their request: with r and v requested before the fragments each MFMA
+// waited for HBM (0.50 ms).
 #include "vgc_tile_core.h"
 
 namespace vgc {
@@ -20,13 +27,18 @@ typedef __bf16 bf8v __attribute__((ext_vector_type(8)));
 typedef float f4v __attribute__((ext_vector_type(4)));
 typedef uint32_t u4v __attribute__((ext_vector_type(4)));
 
-// [B, W] row-major -> [W, Kp] with the B values of a column contiguous and zeros up to Kp.  One thread per
-// (column, 16-byte piece of K); neighbouring threads take neighbouring columns, so the reads coalesce.
+// [B, W] row-major -> [W, Kp] with the B values of a column contiguous and zeros up to Kp, for X (W = J) and, in the blocks
+// from blocks_x on, for D (W = C).  One thread per (column, 16-byte piece of K); neighbouring threads take neighbouring
+// columns, so the reads coalesce.
 template <typename T>
-__global__ __launch_bounds__(256) void k_fc_transpose(const T* __restrict__ src, uint32_t B, uint32_t W, uint32_t Kp,
-                                                      T* __restrict__ dst) {
+__global__ __launch_bounds__(256) void k_fc_transpose(const T* __restrict__ X, const T* __restrict__ D, uint32_t B, uint32_t J, uint32_t C,
+                                                      uint32_t Kp, uint32_t blocks_x, T* __restrict__ XT, T* __restrict__ DT) {
     constexpr uint32_t kPer = 16 / sizeof(T);
-    const uint64_t idx = (uint64_t)blockIdx.x * 256 + threadIdx.x;
+    const bool is_x = blockIdx.x < blocks_x;
+    const T* src = is_x ? X : D;
+    T* dst = is_x ? XT : DT;
+    const uint32_t W = is_x ? J : C;
+    const uint64_t idx = (uint64_t)(blockIdx.x - (is_x ? 0u : blocks_x)) * 256 + threadIdx.x;
     const uint32_t pieces = Kp / kPer;
     if (idx >= (uint64_t)W * pieces) return;
     const uint32_t w = (uint32_t)(idx % W), kc = (uint32_t)(idx / W);
@@ -56,7 +68,8 @@ __device__ __forceinline__ u4v sq_bf16x8(u4v x) {
 }
 
 constexpr int kFusedTiles = 16;                     // tiles per workgroup
-constexpr int kLdsPitch = kTile + 8;                // floats per staged tile: slots 2 q and 2 q + 2 start 16 banks apart
+constexpr int kCodePitch = kTile + 64;              // codes per tile in LDS: two tiles start 32 banks apart
+constexpr int kTurnPitch = 32 + 4;                  // floats per row of a wave's 16 x 32 turning buffer
 
 struct FusedArgs {
     const void* XT;          // [J, Kp]
@@ -71,57 +84,31 @@ struct FusedArgs {
     float alpha, zeta;
 };
 
-// One tile of the block as a wave sees it.
-struct TileRef {
-    uint64_t base;           // first element in the flat parameter space
-    uint32_t t;              // tile number in the plan (scratch records)
-    uint32_t in_group;       // tile number inside the group
-    uint32_t m;              // elements
-    bool live;               // false: past the end of the layer (the wave only keeps the barriers company)
-    bool vec;                // whole, 16-byte aligned tile: 16-byte accesses
-};
+// What the encoder has to know of an element, in 16 bits: rounded exponent field (Section 4.4's recipe, 0 .. 256), whether
+// rounding raised it, whether the element is sent, its sign.
+__device__ __forceinline__ uint32_t element_code(uint32_t bits, bool send) {
+    const uint32_t ab = bits & 0x7FFFFFFFu, ernd = (ab + 0x00400000u) >> 23;   // add one at the mantissa's top bit, drop the mantissa
+    return (ernd | ((ernd - (ab >> 23)) << 9) | 0x4000u | ((bits >> 16) & 0x8000u)) & (send ? 0xFFFFu : 0u);
+}
 
-// Alg. 1's loop body on one tile by ONE wave, from g and s staged in LDS (lg, ls: this wave's slot) and r, v in memory.
-// No workgroup barrier inside: the eight waves of a workgroup each run their own tile.  Element e = 4 u + c of a lane
-// is tile element 256 u + 4 lane + c (whole aligned tiles: 16-byte accesses; R4, V4 hold chunks u = 0, 1 on entry, the
-// rest is loaded two chunks ahead), so chunk u is a contiguous range of 256 elements in (lane, c) order.  The slot's g
-// area is reused for the index-ordered staged entries once g has been consumed.
-__device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef& q, float* lg, const float* ls, f4 (&R4)[4], f4 (&V4)[4],
-                                              TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap, uint16_t* __restrict__ staging,
-                                              uint32_t lane) {
-    float* r = A.r + q.base;
-    float* v = A.v + q.base;
-    uint32_t* bm = bitmap + (size_t)q.t * (kTile / 32);
-    uint32_t bits[32];
-    uint32_t sendmask = 0, etr = 0;
+// The second half of the select pass on one tile, by one wave, from the tile's codes in LDS: send bitmap, largest exponent,
+// histogram of the relative codes and the staged entries in index order (which replace the codes).  Chunk u of the tile is
+// elements 256 u + 4 lane + c.
+__device__ __forceinline__ void encode_codes(uint16_t* codes, TileHdr* __restrict__ hdr, uint32_t* __restrict__ bm,
+                                             uint16_t* __restrict__ out, uint32_t lane) {
+    uint2 code[8];
+    uint32_t etr = 0;
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
-        const f4 g4 = reinterpret_cast<const f4*>(lg)[u * 64 + lane];
-        const f4 s4 = reinterpret_cast<const f4*>(ls)[u * 64 + lane];
-        const f4 r4 = R4[u & 3], v4 = V4[u & 3];
-        if (u + 4 < 8) {                                     // chunk u + 4 into the registers chunk u leaves
-            R4[u & 3] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(r) + (u + 4) * 64 + lane);
-            V4[u & 3] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(v) + (u + 4) * 64 + lane);
-        }
-        if (A.g_out) {
-            const size_t o = (size_t)q.in_group * kTile;
-            reinterpret_cast<f4*>(A.g_out + o)[u * 64 + lane] = g4;
-            reinterpret_cast<f4*>(A.s_out + o)[u * 64 + lane] = s4;
-        }
-        f4 ro, vo;
+        code[u] = *reinterpret_cast<const uint2*>(codes + u * 256 + 4 * lane);
         uint32_t nib = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            float a, b;
-            const bool send = alg1_step(g4[c], s4[c], r4[c], v4[c], A.alpha, A.zeta, a, b, bits[u * 4 + c]);
-            ro[c] = a;
-            vo[c] = b;
+            const uint32_t w = ((c < 2 ? code[u].x : code[u].y) >> (16 * (c & 1))) & 0xFFFFu;
+            const bool send = (w & 0x4000u) != 0;
             nib |= (send ? 1u : 0u) << c;
-            if (send) etr = max(etr, (bits[u * 4 + c] & 0x7FFFFFFFu) >> 23);
+            etr = max(etr, send ? (w & 511u) - ((w >> 9) & 1u) : 0u);
         }
-        __builtin_nontemporal_store(ro, reinterpret_cast<f4*>(r) + u * 64 + lane);
-        __builtin_nontemporal_store(vo, reinterpret_cast<f4*>(v) + u * 64 + lane);
-        sendmask |= nib << (4 * u);
         // send bitmap: bit 256 u + 4 lane + c; eight lanes make one word
         uint32_t x = nib << (4 * (lane & 7u));
         x |= (uint32_t)__shfl_xor((int)x, 1);
@@ -131,9 +118,9 @@ __device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef&
     }
 #pragma unroll
     for (int off = 32; off > 0; off >>= 1) etr = max(etr, (uint32_t)__shfl_xor((int)etr, off));
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane's codes are read before entries replace them
+    __builtin_amdgcn_wave_barrier();
 
-    // ---- tile-relative exponent codes (Section 4.4's rounding recipe), histogram, index-ordered compaction ----
-    uint16_t* stage = reinterpret_cast<uint16_t*>(lg);
     uint64_t hist = 0;                                       // nine 6-bit counters (a lane has at most 32 entries)
     uint32_t base = 0;                                       // entries of the chunks before u (uniform)
 #pragma unroll
@@ -141,12 +128,10 @@ __device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef&
         uint32_t entry[4], below = 0, total = 0, st = 0;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            const int e = u * 4 + c;
-            const uint32_t ab = bits[e] & 0x7FFFFFFFu;
-            const uint32_t ernd = (ab + 0x00400000u) >> 23;  // add one at the mantissa's top bit, drop the mantissa
-            const uint32_t rel = etr + 1u - ernd;            // >= 0 for sent elements
-            const bool staged = ((sendmask >> e) & 1u) && ernd >= 1u && rel <= 8u;
-            entry[c] = ((rel & 15u) << 12) | ((bits[e] >> 31) << 11) | (uint32_t)(u * 256 + c) + 4u * lane;
+            const uint32_t w = ((c < 2 ? code[u].x : code[u].y) >> (16 * (c & 1))) & 0xFFFFu;
+            const uint32_t ernd = w & 511u, rel = etr + 1u - ernd;              // >= 0 for sent elements
+            const bool staged = (w & 0x4000u) && ernd >= 1u && rel <= 8u;
+            entry[c] = ((rel & 15u) << 12) | ((w >> 15) << 11) | (uint32_t)(u * 256 + c) + 4u * lane;
             hist += staged ? (1ull << (staged ? 6u * rel : 0u)) : 0ull;
             const uint64_t b = __ballot(staged);
             below += rank_below(b);
@@ -156,7 +141,7 @@ __device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef&
         uint32_t pos = base + below;
 #pragma unroll
         for (int c = 0; c < 4; ++c) {
-            if ((st >> c) & 1u) stage[pos] = (uint16_t)entry[c];
+            if ((st >> c) & 1u) codes[pos] = (uint16_t)entry[c];
             pos += (st >> c) & 1u;
         }
         base += total;
@@ -174,9 +159,8 @@ __device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef&
     }
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
-    uint16_t* out = staging + (size_t)q.t * kTile;
     for (uint32_t piece = lane; piece * 8u < base; piece += 64u)
-        __builtin_nontemporal_store(reinterpret_cast<const uint4v*>(stage)[piece], reinterpret_cast<uint4v*>(out) + piece);
+        __builtin_nontemporal_store(reinterpret_cast<const uint4v*>(codes)[piece], reinterpret_cast<uint4v*>(out) + piece);
     if (lane == 0) {
         uint32_t h[kRelBins];
 #pragma unroll
@@ -185,85 +169,35 @@ __device__ __forceinline__ void wave_tile_vec(const FusedArgs& A, const TileRef&
         for (int j = 5; j < 9; ++j) h[j] = (uint32_t)(h_hi >> (12 * (j - 5))) & 0xFFFu;
         uint4 lo = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
         uint4 hi = make_uint4(h[8] | (etr << 16), 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(hdrs + q.t)[0] = lo;
-        reinterpret_cast<uint4*>(hdrs + q.t)[1] = hi;
+        reinterpret_cast<uint4*>(hdr)[0] = lo;
+        reinterpret_cast<uint4*>(hdr)[1] = hi;
     }
 }
 
-// The same for a tile that is partial or not 16-byte aligned: element e of a lane is tile element 64 e + lane
-// (4-byte accesses, bounds-checked by m), chunk e is a contiguous range of 64 elements in lane order.
-__device__ __forceinline__ void wave_tile_any(const FusedArgs& A, const TileRef& q, float* lg, const float* ls,
-                                              TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap, uint16_t* __restrict__ staging,
-                                              uint32_t lane) {
-    float* r = A.r + q.base;
-    float* v = A.v + q.base;
-    uint32_t* bm = bitmap + (size_t)q.t * (kTile / 32);
-    uint32_t bits[32];
-    uint32_t sendmask = 0, etr = 0;
+// Four consecutive floats, as 16 bytes where they are aligned (`vec`: the same for the whole launch).
+__device__ __forceinline__ f4 load4(const float* p, bool vec) {
+    if (vec) return __builtin_nontemporal_load(reinterpret_cast<const f4*>(p));
+    return (f4){__builtin_nontemporal_load(p), __builtin_nontemporal_load(p + 1), __builtin_nontemporal_load(p + 2), __builtin_nontemporal_load(p + 3)};
+}
+__device__ __forceinline__ void store4(f4 x, float* p, bool vec) {
+    if (vec) { __builtin_nontemporal_store(x, reinterpret_cast<f4*>(p)); return; }
 #pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const uint32_t i = (uint32_t)e * 64u + lane;
-        const bool in = i < q.m;
-        const float g1 = lg[i], s1 = ls[i];
-        const float r1 = in ? __builtin_nontemporal_load(r + i) : 0.f, v1 = in ? __builtin_nontemporal_load(v + i) : 0.f;
-        if (A.g_out && in) {
-            A.g_out[(size_t)q.in_group * kTile + i] = g1;
-            A.s_out[(size_t)q.in_group * kTile + i] = s1;
-        }
-        float a, b;
-        const bool send = alg1_step(g1, s1, r1, v1, A.alpha, A.zeta, a, b, bits[e]) && in;
-        if (in) {
-            __builtin_nontemporal_store(a, r + i);
-            __builtin_nontemporal_store(b, v + i);
-        }
-        sendmask |= (send ? 1u : 0u) << e;
-        if (send) etr = max(etr, (bits[e] & 0x7FFFFFFFu) >> 23);
-        const uint64_t bal = __ballot(send);
-        if (lane == 0) *reinterpret_cast<uint2*>(bm + 2 * e) = make_uint2((uint32_t)bal, (uint32_t)(bal >> 32));
-    }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) etr = max(etr, (uint32_t)__shfl_xor((int)etr, off));
-    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane's reads of lg precede the entries written over it
-    __builtin_amdgcn_wave_barrier();
-    uint16_t* stage = reinterpret_cast<uint16_t*>(lg);
-    uint32_t h[kRelBins];
-#pragma unroll
-    for (int j = 0; j < (int)kRelBins; ++j) h[j] = 0;
-    uint32_t base = 0;
-#pragma unroll
-    for (int e = 0; e < 32; ++e) {
-        const uint32_t ab = bits[e] & 0x7FFFFFFFu;
-        const uint32_t ernd = (ab + 0x00400000u) >> 23;
-        const uint32_t rel = etr + 1u - ernd;
-        const bool staged = ((sendmask >> e) & 1u) && ernd >= 1u && rel <= 8u;
-        const uint32_t entry = ((rel & 15u) << 12) | ((bits[e] >> 31) << 11) | ((uint32_t)e * 64u + lane);
-#pragma unroll
-        for (int j = 0; j < (int)kRelBins; ++j) h[j] += (uint32_t)__popcll(__ballot(staged && rel == (uint32_t)j));
-        const uint64_t b = __ballot(staged);
-        if (staged) stage[base + rank_below(b)] = (uint16_t)entry;
-        base += (uint32_t)__popcll(b);
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    uint16_t* out = staging + (size_t)q.t * kTile;
-    for (uint32_t piece = lane; piece * 8u < base; piece += 64u)
-        __builtin_nontemporal_store(reinterpret_cast<const uint4v*>(stage)[piece], reinterpret_cast<uint4v*>(out) + piece);
-    if (lane == 0) {
-        uint4 lo = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-        uint4 hi = make_uint4(h[8] | (etr << 16), 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(hdrs + q.t)[0] = lo;
-        reinterpret_cast<uint4*>(hdrs + q.t)[1] = hi;
-    }
+    for (int c = 0; c < 4; ++c) __builtin_nontemporal_store(x[c], p + c);
 }
 
 // kR: rows of [J, C] per tile (1: C is a multiple of 2048 and a tile is a piece of a row; 2, 4, 8: C = 2048 / kR).
 template <int kR, bool kBf16>
-__global__ __launch_bounds__(512) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
-                                                         const PlanGroup* __restrict__ groups,
-                                                         TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap,
-                                                         uint16_t* __restrict__ staging) {
-    __shared__ __attribute__((aligned(16))) float lds_g[8][kLdsPitch];
-    __shared__ __attribute__((aligned(16))) float lds_s[8][kLdsPitch];
+__global__ __launch_bounds__(512, 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
+                                                            const PlanGroup* __restrict__ groups,
+                                                            TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap,
+                                                            uint16_t* __restrict__ staging) {
+    // first the waves' turning buffers for g and s and the codes of their first 128 columns, then, when all are through, the
+    // codes of the 16 tiles (of the wave's other 128 columns from registers: 64 would leave a lane with scratch accesses)
+    union Lds {
+        struct { float turn[2][16 * kTurnPitch]; uint2 park[8][64]; } w[8];
+        uint16_t codes[kFusedTiles][kCodePitch];
+    };
+    __shared__ __attribute__((aligned(16))) Lds sh;
 
     const bool ok = plan_ok(pc);
     if (blockIdx.x == 0 && threadIdx.x == 0) flags[0] = ok ? 0u : 1u;
@@ -281,130 +215,145 @@ __global__ __launch_bounds__(512) void k_fused_fc_select(PlanCheck pc, uint32_t*
     const uint32_t colbase = cb * kTile;
     const uint32_t nt_group = (pg.size + kTile - 1) / kTile;
 
-    // The block's 16 tiles pass through LDS eight at a time; wave w runs the tile in slot w.  Accumulator element i of MFMA
-    // tile t of a lane is row 16 rt + 4 lgrp + i, column 16 (ct0 + t) + lrow of the block; it belongs to tile tl = row / kR at
-    // position (row % kR) Cb + column.  For kR = 1 pass p takes elements i = 2 p, 2 p + 1 of every lane (tiles 4 lgrp + i, slot
-    // 2 lgrp + i % 2: all lanes write), otherwise the tiles 8 p .. 8 p + 7.
-    auto ref_of = [&](int p) -> TileRef {
-        const uint32_t tl = kR == 1 ? 4u * (wave >> 1) + 2u * (uint32_t)p + (wave & 1u) : 8u * (uint32_t)p + wave;
-        TileRef q;
-        q.in_group = kR == 1 ? (j0 + tl) * ncb + cb : (uint32_t)blockIdx.x * kFusedTiles + tl;
-        q.live = kR == 1 ? (j0 + tl) < A.J : q.in_group < nt_group;
-        if (!q.live) q.in_group = 0;
-        q.t = pg.first_tile + q.in_group;
-        q.base = pg.offset + (uint64_t)q.in_group * kTile;
-        q.m = min(kTile, pg.size - q.in_group * kTile);
-        q.vec = q.live && q.m == kTile && ((reinterpret_cast<uintptr_t>(A.r + q.base) | reinterpret_cast<uintptr_t>(A.v + q.base)) & 15u) == 0 &&
-                (!A.g_out || ((reinterpret_cast<uintptr_t>(A.g_out) | reinterpret_cast<uintptr_t>(A.s_out)) & 15u) == 0);
-        return q;
-    };
-    // r and v of the first four chunks of a tile, requested early: they arrive while the matrix cores (pass 0) or the
-    // previous tile's compaction (pass 1) are busy
-    f4 R4[4], V4[4];
-    auto prefetch = [&](const TileRef& q) {
-        if (q.vec) {
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-                R4[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(A.r + q.base) + u * 64 + lane);
-                V4[u] = __builtin_nontemporal_load(reinterpret_cast<const f4*>(A.v + q.base) + u * 64 + lane);
-            }
-        }
-    };
-    TileRef q0 = ref_of(0);
-    prefetch(q0);
-
-    // ---- contraction: this wave's 16 MFMA tiles (one row tile, 16 column tiles) ----
+    // ---- this wave's part: one MFMA row tile (16 rows), 256 columns, 32 of them at a time.  Accumulator element i of a lane in
+    // column tile t is row lane % 16, column 16 t + 4 (lane / 16) + i of them; turned through LDS, a lane has the four columns
+    // 4 (lane % 8) .. + 3 of the rows 8 q + lane / 8, q = 0, 1 ----
     const uint32_t rt = (16u * wave) / CT, ct0 = (16u * wave) % CT;
-    f4v acc_g[16], acc_s[16];
+    const uint32_t trow = lane >> 3, tcol = 4u * (lane & 7u);
+    const bool frow_ok = j0 + 16u * rt + lrow < A.J;          // the fragment's row exists
+    const uint32_t row = 16u * rt + trow, rows_left = j0 + row < A.J ? A.J - j0 - row : 0u;   // row of q = 0 in the block; rows from there on
+    // addresses as a part that is the same for the wave and a lane's offset of 32 bits
+    const uint64_t e0 = (uint64_t)(j0 + 16u * rt) * A.C + colbase + 16u * ct0;          // the wave's first element in the layer
+    const uint32_t eoff = trow * A.C + tcol;
+    float* r = A.r + pg.offset + e0;
+    float* v = A.v + pg.offset + e0;
+    const size_t row8 = (size_t)8u * A.C;                     // from q to q + 1
+    const bool vec = ((reinterpret_cast<uintptr_t>(A.r + pg.offset) | reinterpret_cast<uintptr_t>(A.v + pg.offset)) & 15u) == 0;
+    const bool vec_out = ((reinterpret_cast<uintptr_t>(A.g_out) | reinterpret_cast<uintptr_t>(A.s_out)) & 15u) == 0;
+    float* turn_g = sh.w[wave].turn[0];
+    float* turn_s = sh.w[wave].turn[1];
+    constexpr uint32_t kPer = kBf16 ? 8u : 4u;                // K values a lane's 16 bytes hold
+    constexpr uint32_t kStep = 4u * kPer;                     // K values of one fragment
+    const uint32_t es = kBf16 ? 2u : 4u;
+    const uint32_t doff = (lrow * A.Kp + kPer * lgrp) * es, xoff = frow_ok ? doff : 0u;
+    const char* xp = static_cast<const char*>(A.XT) + (size_t)(j0 + 16u * rt < A.J ? j0 + 16u * rt : 0u) * A.Kp * es;
+    const char* dp = static_cast<const char*>(A.DT) + (size_t)(colbase + 16u * ct0) * A.Kp * es;
+    const size_t dstep = (size_t)16u * A.Kp * es;             // one column tile further
+    struct Frags { u4v x, d[2]; };
+    auto fetch = [&](int n, uint32_t k0) -> Frags {
+        Frags F;
+        F.x = *reinterpret_cast<const u4v*>(xp + (size_t)k0 * es + xoff);
+        if (!frow_ok) F.x = (u4v){0u, 0u, 0u, 0u};
 #pragma unroll
-    for (int t = 0; t < 16; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
-    const uint32_t arow = j0 + 16u * rt + lrow;
-    const bool arow_ok = arow < A.J;
-    if (kBf16) {
-        const uint16_t* XT = static_cast<const uint16_t*>(A.XT);
-        const uint16_t* DT = static_cast<const uint16_t*>(A.DT);
-        const uint16_t* ap = XT + (size_t)(arow_ok ? arow : 0u) * A.Kp + 8u * lgrp;
-        const uint16_t* bp = DT + (size_t)(colbase + 16u * ct0 + lrow) * A.Kp + 8u * lgrp;
-        for (uint32_t k0 = 0; k0 < A.Kp; k0 += 32) {
-            u4v a = *reinterpret_cast<const u4v*>(ap + k0);
-            if (!arow_ok) a = (u4v){0u, 0u, 0u, 0u};
-            const u4v a2 = sq_bf16x8(a);
+        for (int t = 0; t < 2; ++t) F.d[t] = *reinterpret_cast<const u4v*>(dp + (size_t)(2 * n + t) * dstep + (size_t)k0 * es + doff);
+        return F;
+    };
+    f4v acc_g[2], acc_s[2];
+    auto multiply = [&](const Frags& F) {
+        if (kBf16) {
+            const u4v x2 = sq_bf16x8(F.x);
 #pragma unroll
-            for (int tb = 0; tb < 16; tb += 8) {
-                u4v b[8];
+            for (int t = 0; t < 2; ++t) {
+                const u4v d2 = sq_bf16x8(F.d[t]);
+                acc_g[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, F.d[t]), __builtin_bit_cast(bf8v, F.x), acc_g[t], 0, 0, 0);
+                acc_s[t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d2), __builtin_bit_cast(bf8v, x2), acc_s[t], 0, 0, 0);
+            }
+        } else {
+            // v_mfma_f32_16x16x4_f32 takes one k per lane group; a lane loads four consecutive k at once and k-step i of
+            // a group of 16 uses element i, so lane group q supplies k = 16 step + 4 q + i (the same assignment for both
+            // operands, every k exactly once)
+            const f4v xf = __builtin_bit_cast(f4v, F.x), x2 = xf * xf;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) b[t] = *reinterpret_cast<const u4v*>(bp + (size_t)(tb + t) * 16u * A.Kp + k0);
+            for (int t = 0; t < 2; ++t) {
+                const f4v df = __builtin_bit_cast(f4v, F.d[t]), d2 = df * df;
 #pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const u4v b2 = sq_bf16x8(b[t]);
-                    acc_g[tb + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a), __builtin_bit_cast(bf8v, b[t]), acc_g[tb + t], 0, 0, 0);
-                    acc_s[tb + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, a2), __builtin_bit_cast(bf8v, b2), acc_s[tb + t], 0, 0, 0);
+                for (int i = 0; i < 4; ++i) {
+                    acc_g[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(df[i], xf[i], acc_g[t], 0, 0, 0);
+                    acc_s[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(d2[i], x2[i], acc_s[t], 0, 0, 0);
                 }
             }
         }
-    } else {
-        // float32: v_mfma_f32_16x16x4_f32 takes one k per lane group; a lane loads four consecutive k at once and
-        // k-step i of a group of 16 uses element i, so lane group q supplies k = 16 step + 4 q + i (the same
-        // assignment for both operands, every k exactly once)
-        const float* XT = static_cast<const float*>(A.XT);
-        const float* DT = static_cast<const float*>(A.DT);
-        const float* ap = XT + (size_t)(arow_ok ? arow : 0u) * A.Kp + 4u * lgrp;
-        const float* bp = DT + (size_t)(colbase + 16u * ct0 + lrow) * A.Kp + 4u * lgrp;
-        for (uint32_t k0 = 0; k0 < A.Kp; k0 += 16) {
-            f4v a = *reinterpret_cast<const f4v*>(ap + k0);
-            if (!arow_ok) a = (f4v){0.f, 0.f, 0.f, 0.f};
-            const f4v a2 = a * a;
+    };
+    // Loads come back in the order of their request (and stores count among them): the first fragments of the next 32 columns are
+    // requested before the r and v of these are waited for and written.
+    Frags F0 = fetch(0, 0), F1 = fetch(0, A.Kp > kStep ? kStep : 0u);
+    uint2 code[8][2];                                         // of columns 32 n + tcol .. + 3, row q (n < 4: parked in LDS meanwhile)
 #pragma unroll
-            for (int tb = 0; tb < 16; tb += 8) {
-                f4v b[8];
+    for (int n = 0; n < 8; ++n) {
+        f4 R4[2], V4[2];
 #pragma unroll
-                for (int t = 0; t < 8; ++t) b[t] = *reinterpret_cast<const f4v*>(bp + (size_t)(tb + t) * 16u * A.Kp + k0);
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const f4v b2 = b[t] * b[t];
-#pragma unroll
-                    for (int i = 0; i < 4; ++i) {
-                        acc_g[tb + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a[i], b[t][i], acc_g[tb + t], 0, 0, 0);
-                        acc_s[tb + t] = __builtin_amdgcn_mfma_f32_16x16x4f32(a2[i], b2[i], acc_s[tb + t], 0, 0, 0);
-                    }
-                }
+        for (int q = 0; q < 2; ++q) {
+            R4[q] = V4[q] = (f4){0.f, 0.f, 0.f, 0.f};
+            if (8u * q < rows_left) {
+                R4[q] = load4(r + q * row8 + 32 * n + eoff, vec);
+                V4[q] = load4(v + q * row8 + 32 * n + eoff, vec);
             }
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+        multiply(F0);
+        if (A.Kp > kStep) multiply(F1);
+#pragma unroll 1
+        for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
+        if (n + 1 < 8) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            *reinterpret_cast<f4v*>(turn_g + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_g[t] * A.cg;
+            *reinterpret_cast<f4v*>(turn_s + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_s[t] * A.cs;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const f4v g4 = *reinterpret_cast<const f4v*>(turn_g + (8 * q + trow) * kTurnPitch + tcol);
+            const f4v s4 = *reinterpret_cast<const f4v*>(turn_s + (8 * q + trow) * kTurnPitch + tcol);
+            const bool live = 8u * q < rows_left;
+            if (A.g_out && live) {
+                store4(__builtin_bit_cast(f4, g4), A.g_out + e0 + q * row8 + 32 * n + eoff, vec_out);
+                store4(__builtin_bit_cast(f4, s4), A.s_out + e0 + q * row8 + 32 * n + eoff, vec_out);
+            }
+            f4 ro, vo;
+            uint32_t w[4];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float a, b;
+                uint32_t bits;
+                const bool send = alg1_step(g4[c], s4[c], R4[q][c], V4[q][c], A.alpha, A.zeta, a, b, bits) & live;
+                ro[c] = a;
+                vo[c] = b;
+                w[c] = element_code(bits, send);
+            }
+            if (live) {
+                store4(ro, r + q * row8 + 32 * n + eoff, vec);
+                store4(vo, v + q * row8 + 32 * n + eoff, vec);
+            }
+            const uint2 cw = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+            if (n < 4) sh.w[wave].park[2 * n + q][lane] = cw;
+            else code[n][q] = cw;
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
     }
 #pragma unroll
-    for (int t = 0; t < 16; ++t) { acc_g[t] = acc_g[t] * A.cg; acc_s[t] = acc_s[t] * A.cs; }
-
+    for (int n = 0; n < 4; ++n)
 #pragma unroll
-    for (int p = 0; p < 2; ++p) {
-        if (p) __syncthreads();                               // every wave is done with the slots of pass 0
-        if (kR == 1) {
+        for (int q = 0; q < 2; ++q) code[n][q] = sh.w[wave].park[2 * n + q][lane];
+    __syncthreads();                                          // the waves' own buffers have been read
 #pragma unroll
-            for (int ii = 0; ii < 2; ++ii)
+    for (int q = 0; q < 2; ++q) {
+        const uint32_t rw = row + 8u * q;
 #pragma unroll
-                for (int t = 0; t < 16; ++t) {
-                    const uint32_t col = 16u * (ct0 + t) + lrow;
-                    lds_g[2u * lgrp + ii][col] = acc_g[t][2 * p + ii];
-                    lds_s[2u * lgrp + ii][col] = acc_s[t][2 * p + ii];
-                }
-        } else {
-#pragma unroll
-            for (int i = 0; i < 4; ++i) {
-                const uint32_t row = 16u * rt + 4u * lgrp + i, tl = row / kR;
-                if ((tl >> 3) == (uint32_t)p) {
-#pragma unroll
-                    for (int t = 0; t < 16; ++t) {
-                        const uint32_t pos = (row % kR) * Cb + 16u * (ct0 + t) + lrow;
-                        lds_g[tl & 7u][pos] = acc_g[t][i];
-                        lds_s[tl & 7u][pos] = acc_s[t][i];
-                    }
-                }
-            }
-        }
-        __syncthreads();
-        const TileRef q = p == 0 ? q0 : ref_of(1);
-        if (p == 1) prefetch(q);
-        if (q.vec) wave_tile_vec(A, q, lds_g[wave], lds_s[wave], R4, V4, hdrs, bitmap, staging, lane);
-        else if (q.live) wave_tile_any(A, q, lds_g[wave], lds_s[wave], hdrs, bitmap, staging, lane);
+        for (int n = 0; n < 8; ++n)
+            *reinterpret_cast<uint2*>(sh.codes[rw / kR] + (rw % kR) * Cb + 16u * ct0 + 32u * n + tcol) = code[n][q];
+    }
+    __syncthreads();
+#pragma unroll 1
+    for (uint32_t q = 0; q < 2; ++q) {
+        const uint32_t tl = 2u * wave + q;
+        const uint32_t in_group = kR == 1 ? (j0 + tl) * ncb + cb : (uint32_t)blockIdx.x * kFusedTiles + tl;
+        if (kR == 1 ? j0 + tl >= A.J : in_group >= nt_group) break;      // past the end of the layer
+        const uint32_t t = pg.first_tile + in_group;
+        encode_codes(sh.codes[tl], hdrs + t, bitmap + (size_t)t * (kTile / 32), staging + (size_t)t * kTile, lane);
     }
 }
 
@@ -438,13 +387,13 @@ int launch_fused_fc_select(PlanCheck pc, uint32_t* flags, int dtype, const void*
     void* DT = ws + (size_t)J * Kp * es;
     const uint32_t per = 16 / (uint32_t)es;
     const uint64_t nx = (uint64_t)J * (Kp / per), nd = (uint64_t)C * (Kp / per);
-    if (dtype == VGC_BF16) {
-        hipLaunchKernelGGL(k_fc_transpose<uint16_t>, dim3((uint32_t)((nx + 255) / 256)), dim3(256), 0, stream, (const uint16_t*)X, B, J, Kp, (uint16_t*)XT);
-        hipLaunchKernelGGL(k_fc_transpose<uint16_t>, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, stream, (const uint16_t*)D, B, C, Kp, (uint16_t*)DT);
-    } else {
-        hipLaunchKernelGGL(k_fc_transpose<float>, dim3((uint32_t)((nx + 255) / 256)), dim3(256), 0, stream, (const float*)X, B, J, Kp, (float*)XT);
-        hipLaunchKernelGGL(k_fc_transpose<float>, dim3((uint32_t)((nd + 255) / 256)), dim3(256), 0, stream, (const float*)D, B, C, Kp, (float*)DT);
-    }
+    const uint32_t bx = (uint32_t)((nx + 255) / 256), bd = (uint32_t)((nd + 255) / 256);
+    if (dtype == VGC_BF16)
+        hipLaunchKernelGGL(k_fc_transpose<uint16_t>, dim3(bx + bd), dim3(256), 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, Kp, bx,
+                           (uint16_t*)XT, (uint16_t*)DT);
+    else
+        hipLaunchKernelGGL(k_fc_transpose<float>, dim3(bx + bd), dim3(256), 0, stream, (const float*)X, (const float*)D, B, J, C, Kp, bx,
+                           (float*)XT, (float*)DT);
     FusedArgs A;
     A.XT = XT; A.DT = DT; A.J = J; A.C = C; A.Kp = Kp; A.cg = c; A.cs = c * c; A.r = r; A.v = v; A.g_out = g_out; A.s_out = s_out;
     A.group = group; A.alpha = alpha; A.zeta = zeta;

@@ -167,3 +167,12 @@ def test_fused_rejects_what_it_cannot_do(dev):
     assert rc == -2
     torch.cuda.synchronize()
     assert float(r.min()) == 1.0 == float(v.max())
+
+
+@pytest.mark.parametrize("B,J,C,prec,front", [
+    (100, 17, 2048, "f32", 12),         # seven k-steps; one row in the last block of 16
+    (3, 17, 256, "bf16", 4),            # one k-step, mostly padding
+    (161, 33, 512, "bf16", 7),          # six k-steps; one row in the last block of 64; 4-byte accesses
+])
+def test_fused_layer_at_the_edges_of_its_blocks(dev, B, J, C, prec, front):
+    test_fused_layer_inside_a_model(dev, B, J, C, prec, front)
