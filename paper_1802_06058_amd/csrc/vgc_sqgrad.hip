@@ -35,15 +35,31 @@ __global__ __launch_bounds__(256) void k_sqgrad_simple(const T* __restrict__ X, 
 
     f16v acc_g = {0}, acc_s = {0};
     if (!kConv) {
-        for (uint32_t z0 = 0; z0 < B; z0 += 2) {
-            const uint32_t z = z0 + kh;
-            float a = 0.f, b = 0.f;
-            if (z < B) {
-                if (va) a = ld<T>(X + (size_t)z * J + ja);
-                if (vb) b = ld<T>(D + (size_t)z * C + cb);
+        // float32: eight k-steps are requested while the eight before them are multiplied (one at a time, 1000 x 10 at batch
+        // 128, 32 waves in all, took 15.1 us and 20001 x 4001 at batch 64 427 us; so 9.6 and 313).  bfloat16: one at a
+        // time, with more waves instead of the registers (9001 x 3001 at batch 128: 198 us, 249 with eight ahead).
+        constexpr int kAhead = sizeof(T) == 4 ? 8 : 1;
+        struct Steps { float a[kAhead], b[kAhead]; };
+        auto request = [&](uint32_t z0) -> Steps {
+            Steps S;
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                const uint32_t z = z0 + 2 * i + kh;
+                S.a[i] = z < B && va ? ld<T>(X + (size_t)z * J + ja) : 0.f;
+                S.b[i] = z < B && vb ? ld<T>(D + (size_t)z * C + cb) : 0.f;
             }
-            acc_g = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc_g, 0, 0, 0);
-            acc_s = __builtin_amdgcn_mfma_f32_32x32x2f32(a * a, b * b, acc_s, 0, 0, 0);
+            return S;
+        };
+        Steps S = request(0);
+        for (uint32_t z0 = 0; z0 < B; z0 += 2 * kAhead) {
+            Steps next;
+            if (kAhead > 1) next = request(z0 + 2 * kAhead);
+#pragma unroll
+            for (int i = 0; i < kAhead; ++i) {
+                if (kAhead == 1 || g_out) acc_g = __builtin_amdgcn_mfma_f32_32x32x2f32(S.a[i], S.b[i], acc_g, 0, 0, 0);
+                acc_s = __builtin_amdgcn_mfma_f32_32x32x2f32(S.a[i] * S.a[i], S.b[i] * S.b[i], acc_s, 0, 0, 0);
+            }
+            S = kAhead > 1 ? next : request(z0 + 2 * kAhead);
         }
     } else {
         for (uint32_t z = 0; z < B; ++z) {

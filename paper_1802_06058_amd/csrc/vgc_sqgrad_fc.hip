@@ -7,7 +7,7 @@
 //   k_fc_f32    float32 inputs, v_mfma_f32_32x32x2_f32 (float32 products and sums, which is what the 1e-5 tolerance
 //               on s needs).
 //
-// Block tile 128 x 128 of [J, C], 4 waves (2 x 2), operands staged through LDS k-major (rows of the
+// Block tile 128 x 128 of [J, C] (k_fc_f32 also 64 x 64), 4 waves (2 x 2), operands staged through LDS k-major (rows of the
 // source matrices as they are in memory).  Rows past the end of the matrix are outside the
 // bounded range of the buffer loads and read as zero.
 #include "vgc_internal.h"
@@ -51,18 +51,20 @@ __device__ __forceinline__ uint32_t square_bf16x2(uint32_t w) {
     return ra | rb;
 }
 
-__device__ __forceinline__ void store_tile(float fs, float fg, const f16v (&s_acc)[2][2], const f16v (&g_acc)[2][2],
+// A wave's MT x MT MFMA tiles, of the quarter (wm, wn) of the block.
+template <int MT>
+__device__ __forceinline__ void store_tile(float fs, float fg, const f16v (&s_acc)[MT][MT], const f16v (&g_acc)[MT][MT],
                                            bool want_g, float* __restrict__ so, float* __restrict__ go,
                                            uint32_t j0, uint32_t c0, uint32_t J, uint32_t C, uint32_t wm, uint32_t wn,
                                            uint32_t lane) {
 #pragma unroll
-    for (int mt = 0; mt < 2; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) {
-            const uint32_t col = c0 + wn * 64 + nt * 32 + (lane & 31u);
+        for (int nt = 0; nt < MT; ++nt) {
+            const uint32_t col = c0 + wn * (MT * 32u) + nt * 32 + (lane & 31u);
 #pragma unroll
             for (int i = 0; i < 16; ++i) {
-                const uint32_t row = j0 + wm * 64 + mt * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
+                const uint32_t row = j0 + wm * (MT * 32u) + mt * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
                 if (row < J && col < C) {
                     const size_t o = (size_t)row * C + col;
                     __builtin_nontemporal_store(fs * s_acc[mt][nt][i], so + o);
@@ -139,82 +141,89 @@ __global__ __launch_bounds__(256, 2) void k_fc_bf16(const uint16_t* __restrict__
             }
         }
     }
-    store_tile(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
+    store_tile<2>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
 // FC, float32
 // ------------------------------------------------------------------------------------------------
 constexpr int kR32 = 16;                 // rows per LDS stage
-constexpr int kPitch32 = kT + 32;        // float row pitch
 
 // Two chains of v_mfma_f32_32x32x2_f32 (float32 products and sums), on the values and on their squares.  A chunk of kR32
-// samples is in registers while the one before it is multiplied from LDS.
-template <bool kWantG>
+// samples is in registers while the one before it is multiplied from LDS.  Four waves (2 x 2) share a block of kE x kE
+// outputs.  kE = 128 where there are tiles enough (the kernel is then bound by writing [J, C] floats); kE = 64 where 128 x 128
+// tiles would leave compute units idle, whose one tile's K = B steps are then all the time there is: 1000 x 1000 at batch 128,
+// 64 tiles of 128 against 256 of 64: 15.8 -> 6.6 us; 4096 x 1000 at batch 64 with g (256 against 1024): 23.6 -> 17.7.
+template <bool kWantG, int kE>
 __global__ __launch_bounds__(256, 2) void k_fc_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t J,
                                                    uint32_t C, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out) {
-    __shared__ __attribute__((aligned(16))) float shA[2][kR32 * kPitch32], shB[2][kR32 * kPitch32];
+    constexpr int kPitch = kE + 32, MT = kE / 64;            // floats per LDS row; 32 x 32 tiles of a wave per direction
+    constexpr int kPieces = kR32 * kE / 4 / 256;             // 16-byte pieces per thread, operand and chunk
+    __shared__ __attribute__((aligned(16))) float shA[2][kR32 * kPitch], shB[2][kR32 * kPitch];
     const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = tid >> 6, wm = wave >> 1, wn = wave & 1u;
-    const uint32_t tiles_c = (C + kT - 1) / kT;
+    const uint32_t tiles_c = (C + kE - 1) / kE;
     const uint32_t nblk = gridDim.x, per = nblk / 8u, rem = nblk % 8u;
     const uint32_t xcd = blockIdx.x % 8u, slot = blockIdx.x / 8u;
     const uint32_t logical = xcd * per + min(xcd, rem) + slot;       // contiguous range of tiles per XCD
-    const uint32_t j0 = (logical / tiles_c) * kT, c0 = (logical % tiles_c) * kT;
+    const uint32_t j0 = (logical / tiles_c) * kE, c0 = (logical % tiles_c) * kE;
     const rsrc_t rx = make_rsrc(X, B * J * 4u), rd = make_rsrc(D, B * C * 4u);
 
-    f16v s_acc[2][2], g_acc[2][2];
+    f16v s_acc[MT][MT], g_acc[MT][MT];
 #pragma unroll
-    for (int a = 0; a < 2; ++a)
+    for (int a = 0; a < MT; ++a)
 #pragma unroll
-        for (int b = 0; b < 2; ++b) { s_acc[a][b] = (f16v){0}; g_acc[a][b] = (f16v){0}; }
+        for (int b = 0; b < MT; ++b) { s_acc[a][b] = (f16v){0}; g_acc[a][b] = (f16v){0}; }
 
-    f4v ra[2], rb[2];
-    auto load = [&](uint32_t z0) {
+    struct Chunk { f4v a[kPieces], b[kPieces]; };
+    auto load = [&](uint32_t z0) -> Chunk {                  // rows past B read as zeros
+        Chunk R;
 #pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t idx = tid + 256u * i, row = idx / (kT / 4), col = (idx % (kT / 4)) * 4u;
-            ra[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(((z0 + row) * J + j0 + col) * 4u), 0, 0));
-            rb[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(((z0 + row) * C + c0 + col) * 4u), 0, 0));
+        for (int i = 0; i < kPieces; ++i) {
+            const uint32_t idx = tid + 256u * i, row = idx / (kE / 4), col = (idx % (kE / 4)) * 4u;
+            R.a[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(((z0 + row) * J + j0 + col) * 4u), 0, 0));
+            R.b[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(((z0 + row) * C + c0 + col) * 4u), 0, 0));
+        }
+        return R;
+    };
+    auto stage = [&](uint32_t buf, const Chunk& R) {
+#pragma unroll
+        for (int i = 0; i < kPieces; ++i) {
+            const uint32_t idx = tid + 256u * i, off = (idx / (kE / 4)) * kPitch + (idx % (kE / 4)) * 4u;
+            *reinterpret_cast<f4v*>(shA[buf] + off) = R.a[i];
+            *reinterpret_cast<f4v*>(shB[buf] + off) = R.b[i];
         }
     };
-    auto stage = [&](uint32_t buf) {
-#pragma unroll
-        for (int i = 0; i < 2; ++i) {
-            const uint32_t idx = tid + 256u * i, off = (idx / (kT / 4)) * kPitch32 + (idx % (kT / 4)) * 4u;
-            *reinterpret_cast<f4v*>(shA[buf] + off) = ra[i];
-            *reinterpret_cast<f4v*>(shB[buf] + off) = rb[i];
-        }
-    };
-    load(0);
-    stage(0);
+    // two chunks are requested ahead: with few tiles their latency is what a chunk costs
+    stage(0, load(0));
+    Chunk next = load(kR32);
     __syncthreads();
     const uint32_t col = lane & 31u, kh = lane >> 5;
     uint32_t buf = 0;
     for (uint32_t z0 = 0; z0 < B; z0 += kR32, buf ^= 1u) {
-        const bool more = z0 + kR32 < B;
-        if (more) load(z0 + kR32);
+        const Chunk far = load(z0 + 2 * kR32);
         const float* A = shA[buf];
         const float* Bm = shB[buf];
 #pragma unroll
         for (int ks = 0; ks < kR32 / 2; ++ks) {
-            float a[2], b[2];
+            float a[MT], b[MT];
 #pragma unroll
-            for (int t = 0; t < 2; ++t) {
-                a[t] = A[(ks * 2 + kh) * kPitch32 + wm * 64 + t * 32 + col];
-                b[t] = Bm[(ks * 2 + kh) * kPitch32 + wn * 64 + t * 32 + col];
+            for (int t = 0; t < MT; ++t) {
+                a[t] = A[(ks * 2 + kh) * kPitch + wm * (kE / 2) + t * 32 + col];
+                b[t] = Bm[(ks * 2 + kh) * kPitch + wn * (kE / 2) + t * 32 + col];
             }
 #pragma unroll
-            for (int mt = 0; mt < 2; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int nt = 0; nt < 2; ++nt) {
+                for (int nt = 0; nt < MT; ++nt) {
                     s_acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mt] * a[mt], b[nt] * b[nt], s_acc[mt][nt], 0, 0, 0);
                     if (kWantG) g_acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mt], b[nt], g_acc[mt][nt], 0, 0, 0);
                 }
         }
-        if (more) stage(buf ^ 1u);
+        stage(buf ^ 1u, next);
+        next = far;
         __syncthreads();
     }
-    store_tile(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
+    store_tile<MT>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -228,15 +237,20 @@ bool fc_tiled_supported(int dtype, uint32_t B, uint32_t J, uint32_t C) {
 
 int launch_fc_tiled(int dtype, const void* X, const void* D, uint32_t B, uint32_t J, uint32_t C, float c,
                     float* g_out, float* s_out, hipStream_t stream) {
-    const uint64_t nblk = (uint64_t)((J + kT - 1) / kT) * ((C + kT - 1) / kT);
+    uint64_t nblk = (uint64_t)((J + kT - 1) / kT) * ((C + kT - 1) / kT);
+    const bool small = dtype == VGC_F32 && nblk < 2 * 256;           // fewer than two 128 x 128 tiles per compute unit
+    if (small) nblk = (uint64_t)((J + 63) / 64) * ((C + 63) / 64);
     if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
     const float cg = c, cs = c * c;
+    const dim3 grid((uint32_t)nblk), block(256);
     if (dtype == VGC_BF16) {
-        if (g_out) hipLaunchKernelGGL(k_fc_bf16<true>, dim3((uint32_t)nblk), dim3(256), 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
-        else hipLaunchKernelGGL(k_fc_bf16<false>, dim3((uint32_t)nblk), dim3(256), 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
+        if (g_out) hipLaunchKernelGGL(k_fc_bf16<true>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
+        else hipLaunchKernelGGL(k_fc_bf16<false>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
     } else {
-        if (g_out) hipLaunchKernelGGL(k_fc_f32<true>, dim3((uint32_t)nblk), dim3(256), 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out);
-        else hipLaunchKernelGGL(k_fc_f32<false>, dim3((uint32_t)nblk), dim3(256), 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out);
+#define VGC_FC_F32(G_, E_) hipLaunchKernelGGL((k_fc_f32<G_, E_>), grid, block, 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out)
+        if (small) { if (g_out) VGC_FC_F32(true, 64); else VGC_FC_F32(false, 64); }
+        else { if (g_out) VGC_FC_F32(true, 128); else VGC_FC_F32(false, 128); }
+#undef VGC_FC_F32
     }
     return hip_check(hipGetLastError(), "launch fc tiled");
 }
