@@ -400,7 +400,7 @@ int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, con
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
                                 const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,
                                 float* dense, hipStream_t stream) {
-    const uint32_t tpw = decode_tiles_per_wave(n_runs);
+    const uint32_t tpw = decode_tiles_per_wave(n_runs, 16384);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;
     for (uint32_t ch = 0; ch < chunks; ++ch) {

@@ -79,10 +79,10 @@ struct PlanRun {               // 8 bytes
 };
 
 // Tiles one wave of the batched decoders takes: a whole run when there are plenty of runs, fewer (a power of two) when
-// the parameter set is small, so that there are about 16 K waves to spread over the chip.
-inline uint32_t decode_tiles_per_wave(uint64_t n_runs) {
+// the parameter set is small, so that there are at least `waves` to spread over the chip.
+inline uint32_t decode_tiles_per_wave(uint64_t n_runs, uint64_t waves) {
     uint32_t tpw = kRunTiles;
-    while (tpw > 1 && n_runs * (kRunTiles / tpw) < 16384) tpw /= 2;
+    while (tpw > 1 && n_runs * (kRunTiles / tpw) < waves) tpw /= 2;
     return tpw;
 }
 

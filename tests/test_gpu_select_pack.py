@@ -449,3 +449,46 @@ def test_plan_of_another_group_list_is_refused_on_the_device(dev):
     vgc.unpack_apply([good.words], [total], [good.hdrs], b, 1.0, dense, m, kind=vgc.MOMENTUM_SGD, lr=1.0, momentum=0.5)
     torch.cuda.synchronize()
     assert float(dense.min()) == 7.0 == float(dense.max()) and float(m.abs().max()) == 0.0
+
+
+@pytest.mark.parametrize("rhos", [(0.05,), (0.0, 0.02), (0.0, 0.17, 0.01), (0.2, 1.0, 0.3, 0.6, "tiles"), ("tiles", 0.03) * 16 + (0.0,)])
+def test_batch_decoder_at_the_edges_of_its_requests(dev, rhos):
+    """The tiled decoders request a tile's words by the densest message of the group (2, 8 or 12 rounds of 64), more if
+    the tile holds more, the next message's ahead; 64 / p lanes look for a cursor.  Densities on both sides of each
+    number, empty messages, messages whose words fill few tiles whole ("tiles"), odd and even p, groups of one tile and
+    of more than 512 (where workgroups are renumbered): bit for bit the oracle's sums in message order."""
+    import torch
+    from paper_1802_06058_amd import vgc
+    sizes = [2047, 2048 * 1200 + 7, 1, 2049]
+    groups = W.groups_from_sizes(sizes)
+    n, p, scale = sum(sizes), len(rhos), 1.0 / 3.0
+    plan = vgc.Plan(groups, dev)
+    rng = np.random.default_rng(p)
+    msgs = []
+    for rho in rhos:
+        words, hdrs, at = [], [], 0
+        for _, size in groups:
+            keep = (np.arange(size) // 2048 % 97 == 5) if rho == "tiles" else rng.random(size) < rho
+            idx = np.flatnonzero(keep).astype(np.uint32)
+            words.append(idx | rng.integers(0, 16, idx.size, dtype=np.uint32) << np.uint32(28))
+            hdrs.append((int(rng.integers(100, 130)), idx.size, at))
+            at += idx.size
+        msgs.append((np.concatenate(words), hdrs))
+    d_words = [_dev(np.append(w, np.uint32(5)).view(np.int32), dev) for w, _ in msgs]
+    d_hdrs = [_dev(np.array(h, dtype=vgc.HDR_DTYPE).view(np.uint8), dev) for _, h in msgs]
+    counts = [w.size for w, _ in msgs]
+    dense0 = rng.standard_normal(n).astype(F32)
+    for overwrite in (False, True):
+        expect = np.zeros(n, F32) if overwrite else dense0.copy()
+        for words, hdrs in msgs:
+            O.unpack_add(words, hdrs, groups, scale, expect)
+        dense = _dev(dense0, dev)
+        vgc.unpack_add_batch(d_words, counts, d_hdrs, plan, scale, dense, overwrite=overwrite)
+        torch.cuda.synchronize()
+        assert np.array_equal(_bits(dense.cpu().numpy()), _bits(expect)), overwrite
+    w, m = (rng.standard_normal(n).astype(F32) for _ in range(2))
+    dw, dm = _dev(w, dev), _dev(m, dev)
+    w, m = O.unpack_apply(msgs, groups, scale, n, "momentum_sgd", w, m, lr=0.05, mu=0.9)
+    vgc.unpack_apply(d_words, counts, d_hdrs, plan, scale, dw, dm, kind=vgc.MOMENTUM_SGD, lr=0.05, momentum=0.9)
+    torch.cuda.synchronize()
+    assert np.array_equal(_bits(dw.cpu().numpy()), _bits(w)) and np.array_equal(_bits(dm.cpu().numpy()), _bits(m))
