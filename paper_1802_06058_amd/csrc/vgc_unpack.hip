@@ -136,16 +136,19 @@ __device__ __forceinline__ uint32_t lane_of(uint32_t x, uint32_t w) {
 
 // Requests min(left, rounds x 64) words of message w.  The range of the buffer resource ends with the last of them: the
 // rounds behind it are answered without memory traffic, and there is no branch, so that the wait for one message's words
-// can be counted past the next message's.
+// can be counted past the next message's.  A round's place is part of the vector offset and there the instruction's own
+// (at most 2816 bytes): the scalar offset is not held against the range.
 template <int kFirst>
 __device__ __forceinline__ void request_words(Request<kFirst>& Q, const Cursor& C, uint32_t w, uint32_t lane) {
     const uint64_t at = (uint64_t)lane_of((uint32_t)C.at, w) | (uint64_t)lane_of((uint32_t)(C.at >> 32), w) << 32;
     Q.n = min(lane_of(C.left, w), lane_of(C.rounds, w) * 64u);
     const __amdgpu_buffer_rsrc_t r =
         __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(at), 0, (int)(Q.n * 4u), 0x00020000);
+    uint32_t at_lane = lane * 4u;
+    asm volatile("" : "+v"(at_lane));                        // or each sum is kept in a register of its own through the loops
 #pragma unroll
     for (int j = 0; j < kFirst; ++j)
-        Q.word[j] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(lane * 4u), j * 256, 0);
+        Q.word[j] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)at_lane + j * 256, 0, 0);
 }
 
 // Adds kRounds x 64 words (the first n of them exist) into the tile; returns how many belong to it.  A message's indices
