@@ -186,6 +186,14 @@ static void check_compute_errors() {
     CHECK(vgc_unpack_apply(wl, nl, hl, VGC_MAX_UPDATE_MESSAGES + 1, g.data(), 2, plan, 1.f, &opt, f, f, f, n, nullptr) == VGC_ERR_SIZE);
 }
 
+// The compact decoder's variant for streams of 1 to 7 bytes: empty streams do not choose it.
+namespace vgc { bool compact_short_streams(const uint64_t* n_bytes, uint32_t p); }
+static void check_dispatch() {
+    const uint64_t dense[3] = {100, 8, 1ull << 40}, empty[3] = {100, 0, 8}, few[3] = {0, 100, 7}, one[1] = {1};
+    CHECK(!vgc::compact_short_streams(dense, 3) && !vgc::compact_short_streams(empty, 3) && !vgc::compact_short_streams(nullptr, 0));
+    CHECK(vgc::compact_short_streams(few, 3) && !vgc::compact_short_streams(few, 2) && vgc::compact_short_streams(one, 1));
+}
+
 int main() {
     const uint32_t T = vgc_tile_size();
     check_plan({1});
@@ -199,6 +207,7 @@ int main() {
     check_plan(many);
     check_group_errors();
     check_compute_errors();
+    check_dispatch();
     if (g_failed) { std::fprintf(stderr, "hostcheck: %d check(s) failed\n", g_failed); return 1; }
     std::printf("hostcheck ok\n");
     return 0;

@@ -165,6 +165,7 @@ int launch_pack_compact(PlanCheck pc, const PlanGroup* groups, const PlanTile* t
                         uint64_t n_runs, uint32_t n_groups, const TileHdr* hdrs, const uint16_t* staging, uint8_t* stream_out,
                         uint64_t stream_cap, uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out,
                         vgc_pack_status* status_out, hipStream_t stream);
+bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
 int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
                                 const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,

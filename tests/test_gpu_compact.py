@@ -230,3 +230,42 @@ def test_unpack_compact_at_the_edges_of_a_lane_and_a_round(dev, case):
     torch.cuda.synchronize()
     got = dense.cpu().numpy()
     assert np.array_equal(_bits(got), _bits(expect)), np.flatnonzero(_bits(got) != _bits(expect))[:10]
+
+
+def _compact(words, hdrs, groups, dev):
+    from paper_1802_06058_amd import vgc
+    stream, tile_bytes, run_offsets, chdrs = O.pack_compact(words, hdrs, groups)
+    return (_dev(np.append(stream, np.zeros(32, np.uint8)), dev)[:stream.size], stream.size, _dev(tile_bytes.view(np.int16), dev),
+            _dev(run_offsets.view(np.int64), dev), _dev(np.array(chdrs, dtype=vgc.HDR_DTYPE).view(np.uint8), dev))
+
+
+def _message(idx, group_size, rng, field=120):
+    """Words and headers of a model of one group whose elements idx are sent."""
+    code = rng.integers(0, 16, idx.size).astype(U32)
+    return code << U32(28) | idx.astype(U32), [(field if idx.size else 0, idx.size, 0)]
+
+
+def test_short_messages_beside_dense_ones(dev):
+    """A worker may send nothing, or a handful of bytes (fewer than a lane reads at once): its message is decoded right
+    wherever it stands among dense ones, and so are they."""
+    import torch
+    from paper_1802_06058_amd import vgc
+    rng = np.random.default_rng(0)
+    n, scale = 2048 * 70 + 100, 0.125
+    groups = W.groups_from_sizes([n])
+    plan = vgc.Plan(groups, dev)
+    few = {0: [], 1: [5], 7: [1, 2, 3, 4, 5, 6, 7], 9: [n - 9 + k for k in range(8)], 5: [2048 * 66 + 9, 2048 * 67, 2048 * 69 + 9]}
+    dense_msgs = [_message(np.flatnonzero(rng.random(n) < rho), n, rng) for rho in (0.3, 0.9, 0.04)]
+    for k, idx in few.items():
+        short = _message(np.array(idx, np.int64), n, rng)
+        for at in (0, 1, 3):
+            msgs = dense_msgs[:at] + [short] + dense_msgs[at:]
+            streams, nb, tb, ro, hd = zip(*(_compact(*m, groups, dev) for m in msgs))
+            assert nb[at] == k
+            dense = torch.zeros(n, dtype=torch.float32, device=dev)
+            vgc.unpack_compact_add_batch(streams, nb, tb, ro, hd, plan, scale, dense, overwrite=True)
+            torch.cuda.synchronize()
+            expect = np.zeros(n, F32)
+            for w, h in msgs:
+                O.unpack_add(w, h, groups, scale, expect)
+            assert np.array_equal(_bits(dense.cpu().numpy()), _bits(expect)), (k, at)
