@@ -94,3 +94,57 @@ def test_sums_are_not_biased(dev):
     U, E = A.reshape(-1, Cin).astype(np.float64), D.reshape(-1, C).astype(np.float64)
     err = g - U.T @ E
     assert abs(err.mean()) <= 2e-9 * (np.abs(U).T @ np.abs(E)).mean()
+
+
+def _float32_results(U, E, c):
+    """g and s from patches U [B, P, J] and gradients E [B, P, C]: which outputs are not finite as float32 arithmetic has it
+    (0 * inf and inf - inf are NaN, what leaves the range is infinite), the finite ones' values in 64 bits."""
+    with np.errstate(all="ignore"):
+        G, G64 = np.einsum("zpj,zpc->zjc", U, E), np.einsum("zpj,zpc->zjc", U.astype(np.float64), E.astype(np.float64))
+        g, s = G.sum(0), (G * G).sum(0)
+        return np.where(np.isfinite(g), G64.sum(0), g) * float(c), np.where(np.isfinite(s), (G64 * G64).sum(0), s) * float(c) ** 2
+
+
+@pytest.mark.parametrize("want_g", [False, True])
+@pytest.mark.parametrize("shape", SHAPES + [(4, 6, 6, 16, 16, 1, 1, 0), (3, 64, 48, 8, 8, 3, 1, 1)], ids=lambda s: "x".join(map(str, s)))
+def test_sums_that_are_not_finite(dev, shape, want_g):
+    """Infinities, NaN and products beyond the range of float32: each output is what float32 arithmetic makes of the inputs it
+    depends on, whatever the elements are cut into, and no other output sees them."""
+    import torch
+    from paper_1802_06058_amd import vgc
+    B, H, W, Cin, C, k, st, pad = shape
+    rng = np.random.default_rng(B + H + W + C)
+    Ho, Wo = (H + 2 * pad - k) // st + 1, (W + 2 * pad - k) // st + 1
+    A = rng.standard_normal((B, H, W, Cin)).astype(np.float32)
+    D = rng.standard_normal((B, Ho, Wo, C)).astype(np.float32)
+    A[0, 0, 0, 1], A[-1, -1, -1, 2], A[B // 2, H // 2, W // 2, 3] = np.inf, -np.inf, np.nan
+    A[1, H - 1, 0, 1] = np.inf                                      # beside the first: inf + inf or inf - inf
+    D[0, 0, 0, 3], D[-1, -1, -1, 2] = np.inf, np.nan
+    A[1, 0, 0, 4], D[1, 0, 0, 4] = 1.7 * 2.0 ** 100, -1.3 * 2.0 ** 100
+    D[1, Ho // 2, Wo // 2, 5], A[..., 5] = 3.4028235e38, 1.0         # in range as a product, not as a square
+    D[2, 0, 0, 6] = 3.4028235e38                                     # rounds up to infinity in 16 bits
+    A[2, :, :, 6] = 2.0 ** -100
+    c = np.float32(1.0 / B)
+    U = _patches(A, k, k, (st, st), (pad, pad), Ho, Wo)
+    E = D.reshape(B, Ho * Wo, C)
+    g64, s64 = _float32_results(U, E, c)
+    runs = [_run(A, D, k, k, (st, st), (pad, pad), float(c), dev, want_g, use_ws) for use_ws in (True, False)]
+    X, Dd = torch.from_numpy(np.ascontiguousarray(U)).to(dev), torch.from_numpy(np.ascontiguousarray(E)).to(dev)
+    s = torch.empty(U.shape[2], C, device=dev)
+    g = torch.empty(U.shape[2], C, device=dev) if want_g else None
+    nb = vgc.sqgrad_workspace_bytes(vgc.CONV, vgc.F32, B, Ho * Wo, U.shape[2], C)
+    ws = torch.empty(nb, dtype=torch.uint8, device=dev) if nb else None
+    vgc.sqgrad(vgc.CONV, X, Dd, float(c), s, g, workspace=ws)
+    runs.append((g.cpu().numpy() if want_g else None, s.cpu().numpy()))
+    assert np.isinf(s64).any() and np.isnan(s64).any() and np.isfinite(s64).any()
+    for gv, sv in runs:
+        for got, want, rtol in ((sv, s64, 1e-5), (gv, g64, None)):
+            if got is None:
+                continue
+            assert np.array_equal(np.isnan(got), np.isnan(want))
+            inf = np.isinf(want)
+            assert np.array_equal(got[inf], want[inf].astype(np.float32))
+            fin = np.isfinite(want)
+            assert np.isfinite(got[fin]).all()
+            if rtol:
+                assert np.all(np.abs(got[fin] - want[fin]) <= rtol * want[fin])
