@@ -1,9 +1,10 @@
 // float32 conv form of the per-parameter sums of Alg. 1 (per sample G_z = U_z^T D_z over the P positions, then
 // g = c sum_z G_z, s = c^2 sum_z G_z . G_z) on the bf16 matrix cores, without giving up float32: every input element is
-// cut into three bf16 pieces that add up to it exactly (hi: its upper 16 bits; mid: the rest rounded to bf16; lo: what is
-// left, at most 8 bits), and of the nine products of two elements' pieces the six that reach 2^-24 of the largest are
-// summed in the float32 accumulators: hi hi, hi mid, mid hi, mid mid, hi lo, lo hi.  The products are exact; what is left
-// out is mid lo, lo mid (2^-26 of the product, of either sign) and lo lo.
+// cut into three bf16 pieces that add up to it exactly (hi: rounded to bf16; mid: the rest rounded to bf16; lo: what is
+// left, at most 8 bits), and of the nine products of two elements' pieces the six largest are summed in the float32
+// accumulators: hi hi, hi mid, mid hi, mid mid, hi lo, lo hi.  The products are exact.  What is left out, mid lo, lo mid and
+// lo lo, is at most 2^-24 of the product (x x with x = 1.0038986), over random mantissas 2^-27.5 in the root mean square; for
+// the same two mantissas it is the same each time.  (With hi cut off instead of rounded: 2^-22 and 2^-25.5.)
 //
 // Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
 // latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.65 ms (98 -> 183 TFLOP/s); the 53 layers
@@ -36,11 +37,11 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
 
 constexpr int kR32 = 32;                 // positions per LDS stage: one MFMA k-step
 
-// Two floats as three pairs of bf16 whose sum they are.  hi is cut off, not rounded, so that no finite value overflows.
+// Two floats as three pairs of bf16 whose sum they are: hi and mid rounded to nearest, lo what is left of 24 bits.  (A magnitude
+// within half a bf16 step of the largest float rounds up to infinity: its sums are formed again at the end.)
 __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uint32_t& mid, uint32_t& lo) {
-    const uint32_t u0 = __float_as_uint(x0), u1 = __float_as_uint(x1);
-    hi = __builtin_amdgcn_perm(u1, u0, 0x07060302u);
-    const float r0 = x0 - __uint_as_float(u0 & 0xFFFF0000u), r1 = x1 - __uint_as_float(u1 & 0xFFFF0000u);
+    hi = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){x0, x1}, bf2v));
+    const float r0 = x0 - __uint_as_float(hi << 16), r1 = x1 - __uint_as_float(hi & 0xFFFF0000u);
     mid = __builtin_bit_cast(uint32_t, __builtin_convertvector((f2v){r0, r1}, bf2v));
     const float l0 = r0 - __uint_as_float(mid << 16), l1 = r1 - __uint_as_float(mid & 0xFFFF0000u);
     lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);

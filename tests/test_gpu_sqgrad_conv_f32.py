@@ -1,6 +1,6 @@
 """The float32 conv statistic on the bf16 matrix cores (three bf16 pieces per element): every block tile, input mode and
 remainder of its kernel against the float64 oracle; that no bit of a float32 input is lost over the range of exponents;
-and that the sums are not biased although the matrix instruction truncates."""
+that the sums are not biased although the matrix instruction truncates; and sums that are not finite."""
 import numpy as np
 import pytest
 
@@ -64,23 +64,30 @@ def test_shapes(dev, shape, want_g):
             assert np.all(np.abs(gv - g64) <= 1e-6 * mag)
 
 
+@pytest.mark.parametrize("swap", [False, True])
 @pytest.mark.parametrize("exponent", [-100, -60, -1, 0, 60, 126])
-def test_every_bit_of_the_inputs_counts(dev, exponent):
-    """One sample, one position: g is the product of two floats.  The three pieces of each add up to it exactly; with hi cut
-    off (mid < 2^-7 of the leading bit, lo <= 2^-16) the two products mid lo that are left out stay below 2^-22 in all, and
-    the six truncating additions below another 2^-22."""
+def test_every_bit_of_the_inputs_counts(dev, exponent, swap):
+    """One sample, one position: g is the product of two floats, one with mantissas that are the hardest to cut, the other
+    around one.  A power of two is a piece of its own, so the other operand must come back bit for bit.  In general the
+    products of pieces that are left out stay below 2^-24 of the product (mid below 2^-8, lo below 2^-17 of the leading bit,
+    mid lo and lo mid), the last addition is cut off at 2^-23 of it, and the five before it at 2^-31."""
     rng = np.random.default_rng(exponent + 200)
-    Cin, C = 64, 64
-    x = np.ldexp(rng.uniform(1, 2, Cin), exponent).astype(np.float32)
-    x[:4] = np.ldexp(np.array([1 + 2.0 ** -23, 2 - 2.0 ** -23, 1 + 2.0 ** -16, 1 + 2.0 ** -8]), exponent).astype(np.float32)
-    x[4:8] = -x[:4]
-    d = rng.uniform(0.5, 1, C).astype(np.float32)
-    d[:2] = [1.0, 1 - 2.0 ** -24]
+    n = 64
+    hard = [1 + 2.0 ** -23, 2 - 2.0 ** -23, 1 + 2.0 ** -16, 1 + 2.0 ** -8, 1.0077972, 1.0038986, 1 + 2.0 ** -8 + 2.0 ** -23]
+    x = np.ldexp(rng.uniform(1, 2, n), exponent).astype(np.float32)
+    x[:len(hard)] = np.ldexp(np.array(hard), exponent).astype(np.float32)
+    x[len(hard):2 * len(hard)] = -x[:len(hard)]
+    d = rng.uniform(0.5, 1, n).astype(np.float32)
+    d[:5] = [1.0, 1 - 2.0 ** -24, 1.0077972, 0.25, 1.0038986]
     if exponent == 126:
-        x[8] = np.float32(3.4028235e38)                             # the largest float: its upper half must not round to infinity
-    g, _ = _run(x.reshape(1, 1, 1, Cin), d.reshape(1, 1, 1, C), 1, 1, (1, 1), (0, 0), 1.0, dev)
-    want = np.outer(x.astype(np.float64), d.astype(np.float64))
-    assert np.all(np.abs(g - want) <= 2.0 ** -21 * np.abs(want))
+        d[2], d[4] = 0.50389862, 0.5019608
+        x[20] = np.float32(3.4028235e38)                            # the largest float: it rounds up to infinity in 16 bits
+    a, b = (d, x) if swap else (x, d)
+    g, _ = _run(a.reshape(1, 1, 1, n), b.reshape(1, 1, 1, n), 1, 1, (1, 1), (0, 0), 1.0, dev)
+    want = np.outer(a.astype(np.float64), b.astype(np.float64))
+    assert np.all(np.abs(g - want) <= (2.0 ** -24 + 2.0 ** -23 + 5 * 2.0 ** -31) * np.abs(want))
+    g = g.T if swap else g
+    assert np.array_equal(g[:, 0], x) and np.array_equal(g[:, 3], x * np.float32(0.25))
 
 
 def test_sums_are_not_biased(dev):
