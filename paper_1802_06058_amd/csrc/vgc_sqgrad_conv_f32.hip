@@ -9,14 +9,16 @@
 // Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
 // latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.65 ms (98 -> 183 TFLOP/s); the 53 layers
 // of ResNet-50 at batch 32: 3.14 -> 2.35 ms in one batch call.  What bounds it now: the vector instructions that cut the
-// elements (11 per pair) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 43 % busy), and
+// elements (13 per pair) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 43 % busy), and
 // on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
 //
 // The bf16 MFMA adds with truncation: chained over all positions, every instruction would cut off a little of the
 // accumulator, always towards minus infinity.  So the six products of a chunk of 32 positions are summed from zero, where
 // what is cut off is small, and the chunk's sum is added in float32, rounded to nearest; and odd chunks form the negative sum
-// and subtract it, so that what is left of the one-sided error cancels instead of adding up over the samples into g.  Error of s against 64 bits over ResNet-50's layers: 0.52e-7 to 0.81e-7 (with the float32 instruction 0.66e-7
-// to 1.3e-7), of g 0.82e-7 to 1.4e-7 (1.1e-7 to 2.9e-7).
+// and subtract it, so that what is left of the one-sided error cancels instead of adding up over the samples into g.  Error
+// of s against 64 bits over ResNet-50's layers: 0.51e-7 to 0.81e-7 (with the float32 instruction 0.66e-7 to 1.3e-7), of g
+// 0.79e-7 to 1.5e-7 (1.1e-7 to 2.9e-7).  Below 16 positions the last truncation shows: at one position g errs by 0.95e-7
+// (0.73e-7), s by 0.62e-7 (0.57e-7).
 #include "vgc_internal.h"
 
 namespace vgc {
@@ -36,6 +38,10 @@ __device__ __forceinline__ rsrc_t make_rsrc(const void* base, uint32_t bytes) {
 }
 
 constexpr int kR32 = 32;                 // positions per LDS stage: one MFMA k-step
+// Elements are cut at 2^24 times their size, so that no piece of any float32 number, subnormal ones included, falls below what
+// bf16 holds in full (without it, lo lost bits of elements below 2^-110); samples' sums are scaled back before the square.
+// The multiplications cost 1 % of ResNet-50's layers.
+constexpr float kUp = 0x1p24f, kDown = 0x1p-48f;
 
 // Two floats as three pairs of bf16 whose sum they are: hi and mid rounded to nearest, lo what is left of 24 bits.  (A magnitude
 // within half a bf16 step of the largest float rounds up to infinity: its sums are formed again at the end.)
@@ -205,10 +211,10 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     u2v sh_, sm_, sl_;                                               // the piece's three planes
     // half h of piece i: two of its four columns; the second half stores the piece and requests the next chunk's
     auto stage_half = [&](uint32_t buf, int i, int h) {                // buf: the parity of the chunk
-        f4v x = i < PA ? R.a[i < PA ? i : 0] : R.b[i < PA ? 0 : i - PA];
-        if (i < PA && buf) x = -x;
+        const f4v x = i < PA ? R.a[i < PA ? i : 0] : R.b[i < PA ? 0 : i - PA];
+        const float up = i < PA && buf ? -kUp : kUp;
         uint32_t a, b, c;
-        split_pair(x[2 * h], x[2 * h + 1], a, b, c);
+        split_pair(x[2 * h] * up, x[2 * h + 1] * up, a, b, c);
         sh_[h] = a; sm_[h] = b; sl_[h] = c;
         if (h == 0) return;
         // (rowA < kRowStepA: where that is 8, bit 3 of the row is that of i kRowStep alone)
@@ -220,7 +226,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         *reinterpret_cast<u2v*>(p + 2 * plane) = sl_;
         issue_piece(i);
     };
-    constexpr int kValu = 4;
+    constexpr int kValu = 10;                                        // vector instructions after an MFMA; 4, 7 and 10: 2.265, 2.257, 2.260 ms
     constexpr int kHalves = 2 * (PA + PB), kSlots = 3 * MT;          // a chunk's staging is dealt out over so many places in the loop
     auto stage_slot = [&](uint32_t buf, int s) {
         // (from and to by arithmetic, so that the unrolled loop has one or two turns and every index is a constant)
@@ -315,7 +321,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
                     for (int n = 0; n < NTL; ++n) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float x = acc[m][n][i] + T[n][i];
+                            const float x = (acc[m][n][i] + T[n][i]) * kDown;
                             s_acc[m][n][i] = __builtin_fmaf(x, x, s_acc[m][n][i]);
                             if (kWantG) g_acc[m][n][i] += x;
                         }
@@ -345,7 +351,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
                 const uint32_t row = j0 + wm * (uint32_t)WM + m * 16u + 4u * (lane >> 4) + (uint32_t)i;
                 if (row < J && col < C) {
                     const size_t o = (size_t)row * C + col;
-                    __builtin_nontemporal_store(split_p > 1 ? acc[m][n][i] : fs * s_acc[m][n][i], so + o);
+                    __builtin_nontemporal_store(split_p > 1 ? kDown * acc[m][n][i] : fs * s_acc[m][n][i], so + o);
                     if (kWantG) __builtin_nontemporal_store(fg * g_acc[m][n][i], go + o);
                 }
             }

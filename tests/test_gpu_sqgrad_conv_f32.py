@@ -65,7 +65,7 @@ def test_shapes(dev, shape, want_g):
 
 
 @pytest.mark.parametrize("swap", [False, True])
-@pytest.mark.parametrize("exponent", [-100, -60, -1, 0, 60, 126])
+@pytest.mark.parametrize("exponent", [-145, -130, -126, -112, -104, -100, -60, -1, 0, 60, 126])
 def test_every_bit_of_the_inputs_counts(dev, exponent, swap):
     """One sample, one position: g is the product of two floats, one with mantissas that are the hardest to cut, the other
     around one.  A power of two is a piece of its own, so the other operand must come back bit for bit.  In general the
@@ -77,17 +77,19 @@ def test_every_bit_of_the_inputs_counts(dev, exponent, swap):
     x = np.ldexp(rng.uniform(1, 2, n), exponent).astype(np.float32)
     x[:len(hard)] = np.ldexp(np.array(hard), exponent).astype(np.float32)
     x[len(hard):2 * len(hard)] = -x[:len(hard)]
+    up = np.float32(2.0 ** max(0, -60 - exponent))                  # tiny (and subnormal) elements: a product in the normal range
     d = rng.uniform(0.5, 1, n).astype(np.float32)
     d[:5] = [1.0, 1 - 2.0 ** -24, 1.0077972, 0.25, 1.0038986]
     if exponent == 126:
         d[2], d[4] = 0.50389862, 0.5019608
         x[20] = np.float32(3.4028235e38)                            # the largest float: it rounds up to infinity in 16 bits
+    d *= up
     a, b = (d, x) if swap else (x, d)
     g, _ = _run(a.reshape(1, 1, 1, n), b.reshape(1, 1, 1, n), 1, 1, (1, 1), (0, 0), 1.0, dev)
     want = np.outer(a.astype(np.float64), b.astype(np.float64))
     assert np.all(np.abs(g - want) <= (2.0 ** -24 + 2.0 ** -23 + 5 * 2.0 ** -31) * np.abs(want))
     g = g.T if swap else g
-    assert np.array_equal(g[:, 0], x) and np.array_equal(g[:, 3], x * np.float32(0.25))
+    assert np.array_equal(g[:, 0], x * up) and np.array_equal(g[:, 3], x * (up / 4))
 
 
 def test_sums_are_not_biased(dev):
