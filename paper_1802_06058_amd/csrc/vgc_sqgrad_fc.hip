@@ -154,8 +154,11 @@ constexpr int kR32 = 16;                 // rows per LDS stage
 // outputs.  kE = 128 where there are tiles enough (the kernel is then bound by writing [J, C] floats); kE = 64 where 128 x 128
 // tiles would leave compute units idle, whose one tile's K = B steps are then all the time there is: 1000 x 1000 at batch 128,
 // 64 tiles of 128 against 256 of 64: 15.8 -> 6.6 us; 4096 x 1000 at batch 64 with g (256 against 1024): 23.6 -> 17.7.
-template <bool kWantG, int kE>
-__global__ __launch_bounds__(256, 2) void k_fc_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t J,
+// kLong: how the chunks to come are held.  In two register sets without copies, the multiplication never waits for a load,
+// but the unrolled loop of the large tile takes registers that are worth a wave per SIMD; with a copy from set to set each
+// chunk waits for the loads of the one after the next, which costs nothing while the writes of [J, C] are the bound.
+template <bool kWantG, int kE, bool kLong>
+__global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t J,
                                                    uint32_t C, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out) {
     constexpr int kPitch = kE + 32, MT = kE / 64;            // floats per LDS row; 32 x 32 tiles of a wave per direction
     constexpr int kPieces = kR32 * kE / 4 / 256;             // 16-byte pieces per thread, operand and chunk
@@ -193,16 +196,8 @@ __global__ __launch_bounds__(256, 2) void k_fc_f32(const float* __restrict__ X, 
             *reinterpret_cast<f4v*>(shB[buf] + off) = R.b[i];
         }
     };
-    // two chunks are requested ahead: with few tiles their latency is what a chunk costs
-    stage(0, load(0));
-    Chunk next = load(kR32);
-    __syncthreads();
     const uint32_t col = lane & 31u, kh = lane >> 5;
-    uint32_t buf = 0;
-    for (uint32_t z0 = 0; z0 < B; z0 += kR32, buf ^= 1u) {
-        const Chunk far = load(z0 + 2 * kR32);
-        const float* A = shA[buf];
-        const float* Bm = shB[buf];
+    auto multiply = [&](const float* A, const float* Bm) {
 #pragma unroll
         for (int ks = 0; ks < kR32 / 2; ++ks) {
             float a[MT], b[MT];
@@ -219,9 +214,35 @@ __global__ __launch_bounds__(256, 2) void k_fc_f32(const float* __restrict__ X, 
                     if (kWantG) g_acc[mt][nt] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[mt], b[nt], g_acc[mt][nt], 0, 0, 0);
                 }
         }
-        stage(buf ^ 1u, next);
-        next = far;
+    };
+    // Chunk q is multiplied from LDS buffer q % 2, and two more are on their way: with few tiles their latency is what a chunk costs.
+    stage(0, load(0));
+    Chunk R[2];
+    R[0] = load(kR32);
+    if (kLong) {
+        // through register set (q + 1) % 2, the loop unrolled over both (a set that is copied is waited for)
+        R[1] = load(2 * kR32);
         __syncthreads();
+        for (uint32_t z0 = 0; z0 < B; z0 += 2 * kR32) {
+#pragma unroll
+            for (uint32_t u = 0; u < 2; ++u) {
+                if (u > 0 && z0 + kR32 >= B) break;
+                multiply(shA[u], shB[u]);
+                stage(u ^ 1u, R[u]);
+                R[u] = load(z0 + (u + 3) * kR32);
+                __syncthreads();
+            }
+        }
+    } else {
+        __syncthreads();
+        uint32_t buf = 0;
+        for (uint32_t z0 = 0; z0 < B; z0 += kR32, buf ^= 1u) {
+            R[1] = load(z0 + 2 * kR32);
+            multiply(shA[buf], shB[buf]);
+            stage(buf ^ 1u, R[0]);
+            R[0] = R[1];
+            __syncthreads();
+        }
     }
     store_tile<MT>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
 }
@@ -247,9 +268,12 @@ int launch_fc_tiled(int dtype, const void* X, const void* D, uint32_t B, uint32_
         if (g_out) hipLaunchKernelGGL(k_fc_bf16<true>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
         else hipLaunchKernelGGL(k_fc_bf16<false>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
     } else {
-#define VGC_FC_F32(G_, E_) hipLaunchKernelGGL((k_fc_f32<G_, E_>), grid, block, 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out)
-        if (small) { if (g_out) VGC_FC_F32(true, 64); else VGC_FC_F32(false, 64); }
-        else { if (g_out) VGC_FC_F32(true, 128); else VGC_FC_F32(false, 128); }
+#define VGC_FC_F32(G_, E_, L_) hipLaunchKernelGGL((k_fc_f32<G_, E_, L_>), grid, block, 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out)
+        if (small) { if (g_out) VGC_FC_F32(true, 64, true); else VGC_FC_F32(false, 64, true); }
+        // the large tile's two forms cross between batches of 200 and 256: 4096 x 4096 with g, copied against in two sets: 117 against
+        // 121 us at 200, 140 against 138 at 256, 1025 against 988 at 2048
+        else if (B >= 256) { if (g_out) VGC_FC_F32(true, 128, true); else VGC_FC_F32(false, 128, true); }
+        else { if (g_out) VGC_FC_F32(true, 128, false); else VGC_FC_F32(false, 128, false); }
 #undef VGC_FC_F32
     }
     return hip_check(hipGetLastError(), "launch fc tiled");

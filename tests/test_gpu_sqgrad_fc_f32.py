@@ -23,6 +23,7 @@ def dev():
 @pytest.mark.parametrize("B,J,C", [
     (16, 64, 64), (17, 68, 60), (1, 4, 132), (33, 132, 4),            # 64 x 64: one tile, ragged tiles, one chunk and more
     (31, 2888, 2884), (16, 4100, 2052),                               # 529 and 561 tiles of 128 x 128: the larger tile, ragged
+    (256, 2888, 2884), (273, 2948, 2820),                             # the larger tile's form for long sums: an even and an odd number of chunks
     (15, 2816, 2944),                                                 # 22 x 23 = 506 of them: still the smaller tile
     (16, 33, 31), (17, 65, 10), (1, 1, 1), (48, 129, 67),             # rows that are not whole 16-byte pieces: the fallback
 ])
