@@ -78,15 +78,22 @@ template <int W> __device__ __forceinline__ uint32_t lds_piece(uint32_t row, uin
 // BM x BN: the block tile; WM x WN: the part of it a wave multiplies, in MFMA tiles of 16 x 16.
 enum { kPatches = 0, kLinear = 1, kGeneral = 2 };
 
-template <bool kWantG, int kMode, int BM, int BN, int WM, int WN>
+// kFew: samples of at most 16 positions.  A chunk is 16 positions then, and the 32 of an MFMA hold two of the six products:
+// lo hi + hi lo, mid mid + mid hi, hi mid + hi hi, with the two halves of a wave reading different planes.  Half the MFMAs and
+// half the elements to cut of a chunk padded to 32 positions: 3 x 3, 512 -> 512 at 4 x 4, batch 64: 89 -> 53 us (80 with the
+// float32 instruction); one position, 512 -> 512, batch 32, without a workspace: 51 -> 32.5 (33).
+template <bool kWantG, int kMode, int BM, int BN, int WM, int WN, bool kFew>
 __global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
 void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t P, uint32_t J, uint32_t C,
                 uint32_t splits, uint32_t split_p, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out,
                 float* __restrict__ ws, ConvGeom G) {
+    static_assert(!kFew || kMode != kLinear, "one chunk per sample: nothing to advance");
+    if (kFew) split_p = 1;
+    constexpr int kRows = kFew ? kR32 / 2 : kR32;                    // positions of a chunk
     constexpr int NT = (BM / WM) * (BN / WN) * 64;                   // threads of the workgroup
     constexpr int MT = WM / 16, NTL = WN / 16;                       // MFMA tiles of a wave
-    constexpr int PA = kR32 * BM / 4 / NT, PB = kR32 * BN / 4 / NT;  // 16-byte pieces per thread and chunk
-    constexpr int kPlaneA = kR32 * BM * 2, kPlaneB = kR32 * BN * 2;  // bytes
+    constexpr int PA = kRows * BM / 4 / NT, PB = kRows * BN / 4 / NT;   // 16-byte pieces per thread and chunk
+    constexpr int kPlaneA = kRows * BM * 2, kPlaneB = kRows * BN * 2;   // bytes
     static_assert(NT % (BM / 4) == 0 && NT % (BN / 4) == 0, "all pieces of a thread lie in the same columns");
     __shared__ __attribute__((aligned(16))) uint8_t shA[2][3 * kPlaneA];
     __shared__ __attribute__((aligned(16))) uint8_t shB[2][3 * kPlaneB];
@@ -99,7 +106,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     const uint32_t j0 = tile_j * BM, c0 = tile_c * BN;
     // split_p > 1: the workgroup owns part `part` of the positions of the single sample split / split_p
     // and leaves the unsquared partial product in the workspace
-    const uint32_t n_chunks = (P + kR32 - 1) / kR32;
+    const uint32_t n_chunks = kFew ? 1u : (P + kR32 - 1) / kR32;
     const uint32_t part = split_p > 1 ? split % split_p : 0u;
     const uint32_t chunks_per_part = (n_chunks + split_p - 1) / split_p;
     const uint32_t c_begin = min(n_chunks, part * chunks_per_part);
@@ -193,7 +200,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
             offA = wrap ? offA0 : offA + kR32 * G.Cin * 4u;
             phase = wrap || phase + 1u == G.period ? 0u : phase + 1u;
         }
-        if (kMode == kGeneral) {
+        if (kMode == kGeneral && !kFew) {
 #pragma unroll
             for (int i = 0; i < PA; ++i) {                        // the row of the next chunk: kR32 positions further
                 const uint32_t x = xA[i] + G.step_x, xw = x - G.Wo;
@@ -239,7 +246,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     // the lane's place in a transposed fragment (ds_read_b64_tr_b16): rows 8 (lane / 16) .. + 7 of the k-step in two reads
     // of four, of which it addresses row r / 4 (rows r and r + 4 share the swizzle), and the 32-byte unit of the MFMA tile's
     // 16 columns
-    const uint32_t r16 = lane & 15u, frow = (lane >> 4) * 8u + (r16 >> 2);
+    // (kFew: the upper half of the wave has the same rows again, of the other plane of a pair)
+    const uint32_t r16 = lane & 15u, frow = ((lane >> 4) & (kFew ? 1u : 3u)) * 8u + (r16 >> 2);
     const uint32_t fA = lds_piece<BM>(frow, wm * (uint32_t)WM + 4u * (r16 & 3u)), fB = lds_piece<BN>(frow, wn * (uint32_t)WN + 4u * (r16 & 3u));
     auto frag = [&](const uint8_t* p, int pitch) -> bf8v {
         const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(p));
@@ -258,14 +266,21 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     __syncthreads();
 
     static_assert(MT % 2 == 0, "the fragments' sets go by the row's parity");
-    bf8v a[2][3], b[2][NTL][3];                                      // row m in set m % 2, chunk q's columns in set q % 2
-    auto fetch_a = [&](uint32_t buf, int m, int pl) { a[m & 1][pl] = frag(shA[buf] + pl * kPlaneA + (fA ^ ((uint32_t)m * 32u)), BM * 2); };
-    auto fetch_b = [&](uint32_t buf, int pl) {                       // the unit's XOR with the row is the lane's own: tiles XOR in
+    // the products' operands, the smallest first: planes, or (kFew) pairs of planes of which the wave's halves read one each
+    constexpr int kProducts = kFew ? 3 : 6, kFragsB = kFew ? 2 : 3;
+    constexpr int kPa[6] = {kFew ? 0 : 2, kFew ? 1 : 0, kFew ? 2 : 1, 1, 0, 0}, kPb[6] = {0, kFew ? 1 : 2, 1, 0, 1, 0};
+    const bool upper = lane >= 32u;
+    const uint32_t planeA[3] = {kFew ? (upper ? 0u : 2u * kPlaneA) : 0u, (uint32_t)kPlaneA, kFew ? 0u : 2u * kPlaneA};
+    const uint32_t planeB[3] = {kFew && upper ? 2u * kPlaneB : 0u, kFew && upper ? 0u : (uint32_t)kPlaneB, 2u * kPlaneB};
+    bf8v a[2][3], b[2][NTL][kFragsB];                                // row m in set m % 2, chunk q's columns in set q % 2
+    auto fetch_a = [&](uint32_t buf, int m, int f) { a[m & 1][f] = frag(shA[buf] + planeA[f] + (fA ^ ((uint32_t)m * 32u)), BM * 2); };
+    auto fetch_b = [&](uint32_t buf, int f) {                        // the unit's XOR with the row is the lane's own: tiles XOR in
 #pragma unroll
-        for (int n = 0; n < NTL; ++n) b[buf][n][pl] = frag(shB[buf] + pl * kPlaneB + (fB ^ ((uint32_t)n * 32u)), BN * 2);
+        for (int n = 0; n < NTL; ++n) b[buf][n][f] = frag(shB[buf] + planeB[f] + (fB ^ ((uint32_t)n * 32u)), BN * 2);
     };
+    auto order = [](int e, int n) { return kFew ? e : n - 1 - e; };  // of the fragments' fetches: as the products use them
 #pragma unroll
-    for (int pl = 2; pl >= 0; --pl) { fetch_a(0, 0, pl); fetch_b(0, pl); }
+    for (int e = 0; e < 3; ++e) { fetch_a(0, 0, order(e, 3)); if (e < kFragsB) fetch_b(0, order(e, kFragsB)); }
 
     // Chunk q sits in LDS buffer q % 2.  The two waves of a SIMD pass the barrier together and would all multiply, then all
     // convert (measured: matrix and vector time added up), so the conversion of the chunks to come is cut into two-column
@@ -280,8 +295,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         for (int u = 0; u < 2; ++u) {
             if (u > 0 && q0 + (uint32_t)u >= total) break;
             const uint32_t buf = (uint32_t)u;
-            constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};   // the smallest products first
-            const bool last = --left == 0;                           // sample finished with this chunk: G_z is complete in acc
+            const bool last = kFew || --left == 0;                           // sample finished with this chunk: G_z is complete in acc
             if (last) left = n_chunks;
 #pragma unroll
             for (int m = 0; m < MT; ++m) {
@@ -297,22 +311,23 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
 #pragma unroll
                 for (int n = 0; n < NTL; ++n) T[n] = (f4v){0};
 #pragma unroll
-                for (int e = 0; e < 6; ++e) {
+                for (int e = 0; e < kProducts; ++e) {
 #pragma unroll
                     for (int n = 0; n < NTL; ++n) T[n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[m & 1][kPa[e]], b[u][n][kPb[e]], T[n], 0, 0, 0);
-                    if (e < 3) fetch_a(fbuf, fm, 2 - e);
-                    if (end && e < 3) fetch_b(fbuf, 2 - e);
-                    if (e & 1) {
-                        stage_slot(end ? buf : buf ^ 1u, end ? e / 2 : m * 3 + e / 2 + 3);
+                    if (e < 3) fetch_a(fbuf, fm, order(e, 3));
+                    if (end && e < kFragsB) fetch_b(fbuf, order(e, kFragsB));
+                    if (kFew || (e & 1)) {
+                        const int slot_ = kFew ? e : e / 2;
+                        stage_slot(end ? buf : buf ^ 1u, end ? slot_ : m * 3 + slot_ + 3);
 #pragma unroll
-                        for (int k = 0; k < 2 * NTL; ++k) {
+                        for (int k = 0; k < (kFew ? 1 : 2) * NTL; ++k) {
                             __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
                             __builtin_amdgcn_sched_group_barrier(0x002, kValu, 0);
                         }
                         __builtin_amdgcn_sched_barrier(0);
                     }
                 }
-                if (u) {
+                if (u && !kFew) {
 #pragma unroll
                     for (int n = 0; n < NTL; ++n) T[n] = -T[n];
                 }
@@ -321,11 +336,11 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
                     for (int n = 0; n < NTL; ++n) {
 #pragma unroll
                         for (int i = 0; i < 4; ++i) {
-                            const float x = (acc[m][n][i] + T[n][i]) * kDown;
+                            const float x = kFew ? T[n][i] * (u ? -kDown : kDown) : (acc[m][n][i] + T[n][i]) * kDown;
                             s_acc[m][n][i] = __builtin_fmaf(x, x, s_acc[m][n][i]);
                             if (kWantG) g_acc[m][n][i] += x;
                         }
-                        acc[m][n] = (f4v){0};
+                        if (!kFew) acc[m][n] = (f4v){0};
                     }
                 } else {
 #pragma unroll
@@ -516,18 +531,22 @@ static int launch_conv_f32_any(const void* X, const void* D, uint32_t B, uint32_
     float* ws = static_cast<float*>(workspace);
     const float* Xf = static_cast<const float*>(X);
     const float* Df = static_cast<const float*>(D);
-#define VGC_LAUNCH_F32(G_, BM_, BN_, WM_, WN_)                                                                             \
-    hipLaunchKernelGGL((k_conv_f32<G_, kMode, BM_, BN_, WM_, WN_>), dim3((uint32_t)nblk),                              \
+#define VGC_LAUNCH_F32(G_, BM_, BN_, WM_, WN_, FEW_)                                                                       \
+    hipLaunchKernelGGL((k_conv_f32<G_, kMode, BM_, BN_, WM_, WN_, FEW_>), dim3((uint32_t)nblk),                        \
                        dim3((BM_ / WM_) * (BN_ / WN_) * 64), 0, stream, Xf, Df, B, P, J, C, splits, split_p, cg, cs, g_out, s_out, ws, G)
-#define VGC_LAUNCH_F32_TILES(G_)                                                                                           \
+#define VGC_LAUNCH_F32_TILES(G_, FEW_)                                                                                     \
     do {                                                                                                                   \
-        if (t.bm == 128 && t.bn == 128) VGC_LAUNCH_F32(G_, 128, 128, 64, 32);                                              \
-        else if (t.bm == 128) VGC_LAUNCH_F32(G_, 128, 64, 64, 32);                                                         \
-        else if (t.bn == 128) VGC_LAUNCH_F32(G_, 64, 128, 64, 32);                                                         \
-        else VGC_LAUNCH_F32(G_, 64, 64, 32, 32);                                                                           \
+        if (t.bm == 128 && t.bn == 128) VGC_LAUNCH_F32(G_, 128, 128, 64, 32, FEW_);                                        \
+        else if (t.bm == 128) VGC_LAUNCH_F32(G_, 128, 64, 64, 32, FEW_);                                                   \
+        else if (t.bn == 128) VGC_LAUNCH_F32(G_, 64, 128, 64, 32, FEW_);                                                   \
+        else VGC_LAUNCH_F32(G_, 64, 64, 32, 32, FEW_);                                                                     \
     } while (0)
-    if (with_g) VGC_LAUNCH_F32_TILES(true);
-    else VGC_LAUNCH_F32_TILES(false);
+    constexpr bool kHasFew = kMode != kLinear;
+    if (kHasFew && P <= kR32 / 2) {
+        if (with_g) VGC_LAUNCH_F32_TILES(true, kHasFew);
+        else VGC_LAUNCH_F32_TILES(false, kHasFew);
+    } else if (with_g) VGC_LAUNCH_F32_TILES(true, false);
+    else VGC_LAUNCH_F32_TILES(false, false);
 #undef VGC_LAUNCH_F32_TILES
 #undef VGC_LAUNCH_F32
     if (split_p > 1) launch_sqgrad_reduce_parts(ws, B, split_p, JC, cg, cs, g_out, s_out, stream);
@@ -542,7 +561,7 @@ int launch_conv_f32_tiled(const void* X, const void* D, uint32_t B, uint32_t P, 
 
 int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
                       float* g_out, float* s_out, void* workspace, size_t workspace_bytes, ConvGeom G, hipStream_t stream) {
-    if (G.sh == 1 && G.sw == 1 && G.Wo == G.W) {
+    if (G.sh == 1 && G.sw == 1 && G.Wo == G.W && P > kR32 / 2) {
         uint32_t a = G.W, b = kR32 % G.W;
         while (b) { const uint32_t m = a % b; a = b; b = m; }
         G.period = G.W / a;

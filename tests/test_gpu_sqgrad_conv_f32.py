@@ -30,6 +30,12 @@ SHAPES = [  # B, H, W, Cin, C, k, stride, pad          tile, input mode
     (4, 66, 33, 12, 12, 3, 1, 1),                    # the positions split over workgroups
     (4, 40, 41, 8, 132, 2, 1, 0),                    # even kernel, output narrower than the input
     (40, 3, 5, 256, 1024, 1, 1, 0),                  # several samples per workgroup
+    (4, 4, 4, 60, 60, 1, 1, 0),                      # at most 16 positions, where two products share an MFMA: 64 x 64, 16 of them
+    (6, 1, 1, 200, 200, 1, 1, 0),                    # 128 x 128, one position
+    (4, 7, 8, 12, 200, 3, 2, 1),                     # 128 x 128, stride 2
+    (4, 2, 2, 200, 60, 2, 1, 1),                     # 128 x 64, 9 positions
+    (35, 3, 4, 60, 200, 1, 1, 0),                    # 64 x 128, 12 positions, an odd number of samples
+    (4, 1, 17, 60, 60, 1, 1, 0),                     # 17: no longer
 ]
 
 
@@ -65,9 +71,10 @@ def test_shapes(dev, shape, want_g):
 
 
 @pytest.mark.parametrize("swap", [False, True])
+@pytest.mark.parametrize("positions", [1, 20])
 @pytest.mark.parametrize("exponent", [-145, -130, -126, -112, -104, -100, -60, -1, 0, 60, 126])
-def test_every_bit_of_the_inputs_counts(dev, exponent, swap):
-    """One sample, one position: g is the product of two floats, one with mantissas that are the hardest to cut, the other
+def test_every_bit_of_the_inputs_counts(dev, exponent, positions, swap):
+    """One sample, one position (or one and zeros): g is the product of two floats, one with mantissas that are the hardest to cut, the other
     around one.  A power of two is a piece of its own, so the other operand must come back bit for bit.  In general the
     products of pieces that are left out stay below 2^-24 of the product (mid below 2^-8, lo below 2^-17 of the leading bit,
     mid lo and lo mid), the last addition is cut off at 2^-23 of it, and the five before it at 2^-31."""
@@ -85,7 +92,8 @@ def test_every_bit_of_the_inputs_counts(dev, exponent, swap):
         x[20] = np.float32(3.4028235e38)                            # the largest float: it rounds up to infinity in 16 bits
     d *= up
     a, b = (d, x) if swap else (x, d)
-    g, _ = _run(a.reshape(1, 1, 1, n), b.reshape(1, 1, 1, n), 1, 1, (1, 1), (0, 0), 1.0, dev)
+    at = lambda v: np.concatenate([v, np.zeros((positions - 1) * n, np.float32)]).reshape(1, 1, positions, n)
+    g, _ = _run(at(a), at(b), 1, 1, (1, 1), (0, 0), 1.0, dev)
     want = np.outer(a.astype(np.float64), b.astype(np.float64))
     assert np.all(np.abs(g - want) <= (2.0 ** -24 + 2.0 ** -23 + 5 * 2.0 ** -31) * np.abs(want))
     g = g.T if swap else g
