@@ -562,10 +562,19 @@ int vgc_pack_compact(uint64_t n, const vgc_group* groups, uint32_t n_groups, con
                                run_offsets_out, hdrs_out, status_out, static_cast<hipStream_t>(stream));
 }
 
-int vgc_unpack_compact_add_batch(const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
-                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
-                                 const vgc_group* groups, uint32_t n_groups, const void* plan, float scale, int overwrite,
-                                 float* dense_out, uint64_t n, void* stream) {
+// The batched decoders with the tiles of a wave given (a power of two up to a run's 64, 0: by the rule).  Not part of the
+// interface: the public calls below pass 0; tests run on small parameter sets what only large ones lead to.
+static bool tiles_ok(uint32_t tiles_per_wave) {
+    if (tiles_per_wave <= kRunTiles && (tiles_per_wave & (tiles_per_wave - 1u)) == 0) return true;
+    set_error("tiles_per_wave = %u is neither 0 nor a power of two up to %u", tiles_per_wave, kRunTiles);
+    return false;
+}
+
+int vgc_tiles_unpack_compact_add_batch(const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
+                                       const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
+                                       const vgc_group* groups, uint32_t n_groups, const void* plan, float scale, int overwrite,
+                                       float* dense_out, uint64_t n, void* stream, uint32_t tiles_per_wave) {
+    if (!tiles_ok(tiles_per_wave)) return VGC_ERR_PARAM;
     if (!plan || !dense_out || (p && (!streams || !stream_bytes || !tile_bytes || !run_offsets || !hdrs))) {
         set_error("vgc_unpack_compact_add_batch: NULL pointer");
         return VGC_ERR_NULL;
@@ -589,7 +598,15 @@ int vgc_unpack_compact_add_batch(const uint8_t* const* streams, const uint64_t* 
     if (p == 0 && !overwrite) return VGC_OK;
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     return launch_unpack_compact_batch(plan_check(plan, gs), streams, stream_bytes, tile_bytes, run_offsets, hdrs, p, pv.groups, pv.runs,
-                                       gs.n_runs, scale, overwrite, dense_out, static_cast<hipStream_t>(stream));
+                                       gs.n_runs, scale, overwrite, dense_out, tiles_per_wave, static_cast<hipStream_t>(stream));
+}
+
+int vgc_unpack_compact_add_batch(const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
+                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
+                                 const vgc_group* groups, uint32_t n_groups, const void* plan, float scale, int overwrite,
+                                 float* dense_out, uint64_t n, void* stream) {
+    return vgc_tiles_unpack_compact_add_batch(streams, stream_bytes, tile_bytes, run_offsets, hdrs, p, groups, n_groups, plan, scale,
+                                              overwrite, dense_out, n, stream, 0);
 }
 
 int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr* hdrs,
@@ -613,15 +630,16 @@ int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr*
         const uint32_t* const wl[1] = {words};
         const uint64_t nl[1] = {n_words};
         const vgc_group_hdr* const hl[1] = {hdrs};
-        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.runs, gs.n_runs, scale, 0, dense_out,
+        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.runs, gs.n_runs, scale, 0, dense_out, 0,
                                        static_cast<hipStream_t>(stream));
     }
     return launch_unpack_add(plan_check(plan, gs), words, n_words, hdrs, pv.groups, n_groups, scale, dense_out, static_cast<hipStream_t>(stream));
 }
 
-int vgc_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                         uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan,
-                         float scale, int overwrite, float* dense_out, uint64_t n, void* stream) {
+int vgc_tiles_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
+                               uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan,
+                               float scale, int overwrite, float* dense_out, uint64_t n, void* stream, uint32_t tiles_per_wave) {
+    if (!tiles_ok(tiles_per_wave)) return VGC_ERR_PARAM;
     if (!plan || !dense_out || (p && (!words || !n_words || !hdrs))) { set_error("vgc_unpack_add_batch: NULL pointer"); return VGC_ERR_NULL; }
     uint64_t n_tiles = 0;
     GroupStats gs;
@@ -636,12 +654,20 @@ int vgc_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_words, 
     if (p == 0 && !overwrite) return VGC_OK;
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     return launch_unpack_add_batch(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.runs, gs.n_runs, scale, overwrite, dense_out,
-                                   static_cast<hipStream_t>(stream));
+                                   tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 
-int vgc_unpack_apply(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                     uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan, float scale,
-                     const vgc_optimizer* opt, float* param, float* state1, float* state2, uint64_t n, void* stream) {
+int vgc_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
+                         uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan,
+                         float scale, int overwrite, float* dense_out, uint64_t n, void* stream) {
+    return vgc_tiles_unpack_add_batch(words, n_words, hdrs, p, groups, n_groups, plan, scale, overwrite, dense_out, n, stream, 0);
+}
+
+int vgc_tiles_unpack_apply(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
+                           uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan, float scale,
+                           const vgc_optimizer* opt, float* param, float* state1, float* state2, uint64_t n, void* stream,
+                           uint32_t tiles_per_wave) {
+    if (!tiles_ok(tiles_per_wave)) return VGC_ERR_PARAM;
     if (!plan || !opt || !param || !state1 || (p && (!words || !n_words || !hdrs))) { set_error("vgc_unpack_apply: NULL pointer"); return VGC_ERR_NULL; }
     if (opt->kind != VGC_OPT_MOMENTUM_SGD && opt->kind != VGC_OPT_ADAM) { set_error("vgc_unpack_apply: unknown optimizer %d", opt->kind); return VGC_ERR_PARAM; }
     if (opt->kind == VGC_OPT_ADAM && !state2) { set_error("vgc_unpack_apply: Adam needs state2"); return VGC_ERR_NULL; }
@@ -674,7 +700,13 @@ int vgc_unpack_apply(const uint32_t* const* words, const uint64_t* n_words, cons
     }
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     return launch_unpack_apply(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.runs, gs.n_runs, scale, opt->kind, opt->lr, mu, b1, b2,
-                               omb1, omb2, bias1, bias2, eps, param, state1, state2, static_cast<hipStream_t>(stream));
+                               omb1, omb2, bias1, bias2, eps, param, state1, state2, tiles_per_wave, static_cast<hipStream_t>(stream));
+}
+
+int vgc_unpack_apply(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
+                     uint32_t p, const vgc_group* groups, uint32_t n_groups, const void* plan, float scale,
+                     const vgc_optimizer* opt, float* param, float* state1, float* state2, uint64_t n, void* stream) {
+    return vgc_tiles_unpack_apply(words, n_words, hdrs, p, groups, n_groups, plan, scale, opt, param, state1, state2, n, stream, 0);
 }
 
 }  // extern "C"

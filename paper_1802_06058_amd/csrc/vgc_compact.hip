@@ -414,8 +414,8 @@ bool compact_short_streams(const uint64_t* n_bytes, uint32_t p) {
 int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
                                 const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,
-                                float* dense, hipStream_t stream) {
-    const uint32_t tpw = decode_tiles_per_wave(n_runs, 16384);
+                                float* dense, uint32_t tiles_per_wave, hipStream_t stream) {
+    const uint32_t tpw = decode_tiles_per_wave(n_runs, 16384, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;
     for (uint32_t ch = 0; ch < chunks; ++ch) {

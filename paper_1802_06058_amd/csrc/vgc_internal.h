@@ -79,8 +79,10 @@ struct PlanRun {               // 8 bytes
 };
 
 // Tiles one wave of the batched decoders takes: a whole run when there are plenty of runs, fewer (a power of two) when
-// the parameter set is small, so that there are at least `waves` to spread over the chip.
-inline uint32_t decode_tiles_per_wave(uint64_t n_runs, uint64_t waves) {
+// the parameter set is small, so that there are at least `waves` to spread over the chip.  given: 0, or the number itself
+// (what a large parameter set leads to can so be run on a small one).
+inline uint32_t decode_tiles_per_wave(uint64_t n_runs, uint64_t waves, uint32_t given) {
+    if (given) return given;
     uint32_t tpw = kRunTiles;
     while (tpw > 1 && n_runs * (kRunTiles / tpw) < waves) tpw /= 2;
     return tpw;
@@ -169,7 +171,7 @@ bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
 int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
                                 const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,
-                                float* dense, hipStream_t stream);
+                                float* dense, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_unpack_add(PlanCheck pc, const uint32_t* words, uint64_t n_words, const vgc_group_hdr* hdrs,
                       const PlanGroup* groups, uint32_t n_groups, float scale, float* dense,
@@ -179,12 +181,12 @@ constexpr int kBatchMax = 8;   // messages one launch of the batched decoder tak
 constexpr int kApplyMax = 64;  // messages the decoder fused with the parameter update takes (one launch; a lane per message)
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                             uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs,
-                            float scale, int overwrite, float* dense, hipStream_t stream);
+                            float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                         uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale,
                         int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
-                        float eps, float* param, float* state1, float* state2, hipStream_t stream);
+                        float eps, float* param, float* state1, float* state2, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_sqgrad(int kind, int dtype, const void* X, const void* D, uint32_t B, uint32_t P,
                   uint32_t J, uint32_t C, float c, float* g_out, float* s_out,

@@ -400,8 +400,8 @@ static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* 
 
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                             uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs,
-                            float scale, int overwrite, float* dense, hipStream_t stream) {
-    const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves);
+                            float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream) {
+    const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;     // p == 0: only the optional clear
     for (uint32_t ch = 0; ch < chunks; ++ch) {
@@ -415,8 +415,8 @@ int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const ui
 int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                         uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale,
                         int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
-                        float eps, float* param, float* state1, float* state2, hipStream_t stream) {
-    const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves);
+                        float eps, float* param, float* state1, float* state2, uint32_t tiles_per_wave, hipStream_t stream) {
+    const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const BatchArgs<kApplyMax> A = batch_args<kApplyMax>(words, n_words, hdrs, 0, p);
     UpdateArgs O;
