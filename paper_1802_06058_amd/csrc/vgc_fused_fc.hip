@@ -187,8 +187,11 @@ __device__ __forceinline__ void store4(f4 x, float* p, bool vec) {
 
 // kR: rows of [J, C] per tile (1: C is a multiple of 2048 and a tile is a piece of a row; 2, 4, 8: C = 2048 / kR).
 // kWaves: waves that share the block's 16 tiles.
-template <int kR, bool kBf16, int kWaves>
-__global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
+// kLong: the contraction over a long K comes first, for all of the wave's columns at once, so that the fragments of X are
+// fetched and squared once instead of once per 32 columns (one vector instruction in three), with two waves on a SIMD and the
+// r and v of two pieces on their way.
+template <int kR, bool kBf16, int kWaves, bool kLong>
+__global__ __launch_bounds__(kWaves * 64, kLong ? 2 : 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
                                                             const PlanGroup* __restrict__ groups,
                                                             TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap,
                                                             uint16_t* __restrict__ staging) {
@@ -279,26 +282,64 @@ __global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc
     };
     // Loads come back in the order of their request (and stores count among them): the first fragments of the next 32 columns are
     // requested before the r and v of these are waited for and written.
-    Frags F0 = fetch(0, 0), F1 = fetch(0, A.Kp > kStep ? kStep : 0u);
+    Frags F0, F1;
+    if (!kLong) { F0 = fetch(0, 0); F1 = fetch(0, A.Kp > kStep ? kStep : 0u); }
+    auto request = [&](int n, f4 (&R)[2], f4 (&V)[2]) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            R[q] = V[q] = (f4){0.f, 0.f, 0.f, 0.f};
+            if (8u * q < rows_left) {
+                R[q] = load4(r + q * row8 + 32 * n + eoff, vec);
+                V[q] = load4(v + q * row8 + 32 * n + eoff, vec);
+            }
+        }
+    };
+    f4 RN[2][2], VN[2][2];                                    // kLong: r and v of the next two pieces
+    if (kLong) request(0, RN[0], VN[0]);
+    f4v long_g[kLong ? 2 * kN : 1], long_s[kLong ? 2 * kN : 1];
+    if (kLong) {
+        static_assert(!kLong || kBf16, "float32 gains nothing from it");
+#pragma unroll
+        for (int t = 0; t < 2 * kN; ++t) { long_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; long_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+        for (uint32_t k0 = 0; k0 < A.Kp; k0 += kStep) {
+            u4v x = *reinterpret_cast<const u4v*>(xp + (size_t)k0 * es + xoff);
+            if (!frow_ok) x = (u4v){0u, 0u, 0u, 0u};
+            const u4v x2 = sq_bf16x8(x);
+#pragma unroll
+            for (int t0 = 0; t0 < 2 * kN; t0 += 8) {
+                u4v d[8];
+#pragma unroll
+                for (int t = 0; t < 8; ++t) d[t] = *reinterpret_cast<const u4v*>(dp + (size_t)(t0 + t) * dstep + (size_t)k0 * es + doff);
+#pragma unroll
+                for (int t = 0; t < 8; ++t) {
+                    const u4v d2 = sq_bf16x8(d[t]);
+                    long_g[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d[t]), __builtin_bit_cast(bf8v, x), long_g[t0 + t], 0, 0, 0);
+                    long_s[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d2), __builtin_bit_cast(bf8v, x2), long_s[t0 + t], 0, 0, 0);
+                }
+            }
+        }
+    }
+    if (kLong) request(1, RN[1], VN[1]);
     uint2 code[kN][2];                                        // of columns 32 n + tcol .. + 3, row q (n < kParked: in LDS meanwhile)
 #pragma unroll
     for (int n = 0; n < kN; ++n) {
         f4 R4[2], V4[2];
+        if (kLong) {
 #pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            R4[q] = V4[q] = (f4){0.f, 0.f, 0.f, 0.f};
-            if (8u * q < rows_left) {
-                R4[q] = load4(r + q * row8 + 32 * n + eoff, vec);
-                V4[q] = load4(v + q * row8 + 32 * n + eoff, vec);
-            }
-        }
+            for (int q = 0; q < 2; ++q) { R4[q] = RN[n & 1][q]; V4[q] = VN[n & 1][q]; }
+            if (n + 2 < kN) request(n + 2, RN[n & 1], VN[n & 1]);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
-        multiply(F0);
-        if (A.Kp > kStep) multiply(F1);
+            for (int t = 0; t < 2; ++t) { acc_g[t] = long_g[kLong ? 2 * n + t : 0]; acc_s[t] = long_s[kLong ? 2 * n + t : 0]; }
+        } else {
+            request(n, R4, V4);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+            multiply(F0);
+            if (A.Kp > kStep) multiply(F1);
 #pragma unroll 1
-        for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
-        if (n + 1 < kN) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
+            for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
+            if (n + 1 < kN) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
+        }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             *reinterpret_cast<f4v*>(turn_g + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_g[t] * A.cg;
@@ -360,6 +401,11 @@ __global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc
     }
 }
 
+// Batches from which on the contraction comes first (bf16; times before it was split off, the short form, the long one):
+// 9216 x 1024 at 128 93, 92 and 94 us, at 160 87, 96 and 91, at 256 125, 134 and 124; 25088 x 4096 at 160 510, 533 and 555,
+// at 256 748, 772 and 762, at 1024 1925, 2393 and 1922.
+constexpr uint32_t kLongK = 128;
+
 // Shapes the fused kernel takes: C a multiple of 2048 (a tile is a piece of a row) or C = 1024, 512, 256 (a tile is
 // 2, 4, 8 whole rows).  0 = not supported.
 static int fused_rows_per_tile(uint32_t C) {
@@ -406,10 +452,15 @@ int launch_fused_fc_select(PlanCheck pc, uint32_t* flags, int dtype, const void*
     // With no more blocks than compute units 16 waves share a block, each with half the columns and one tile to encode: what a
     // wave does in a row is then all the time there is (300 x 2048 in bf16 at batch 64: 31.4 us against 35.0 with eight waves;
     // 1000 x 256 in float32: 41.7 against 49.7).
-#define VGC_FUSED(KR, BF, NW)                                                                                                 \
-    hipLaunchKernelGGL((k_fused_fc_select<KR, BF, NW>), dim3((uint32_t)nblk), dim3(NW * 64), 0, stream, pc, flags, A, groups, \
+#define VGC_FUSED(KR, BF, NW, LG)                                                                                             \
+    hipLaunchKernelGGL((k_fused_fc_select<KR, BF, NW, LG>), dim3((uint32_t)nblk), dim3(NW * 64), 0, stream, pc, flags, A, groups, \
                        hdrs, bitmap, staging)
-#define VGC_FUSED_WAVES(KR, BF) do { if (nblk <= 256) VGC_FUSED(KR, BF, 16); else VGC_FUSED(KR, BF, 8); } while (0)
+#define VGC_FUSED_WAVES(KR, BF)                                                                                               \
+    do {                                                                                                                      \
+        if (BF && Kp > kLongK) VGC_FUSED(KR, BF, 8, BF);                                                                      \
+        else if (nblk <= 256) VGC_FUSED(KR, BF, 16, false);                                                                   \
+        else VGC_FUSED(KR, BF, 8, false);                                                                                     \
+    } while (0)
     const bool bf = dtype == VGC_BF16;
     if (kr == 1) { if (bf) VGC_FUSED_WAVES(1, true); else VGC_FUSED_WAVES(1, false); }
     else if (kr == 2) { if (bf) VGC_FUSED_WAVES(2, true); else VGC_FUSED_WAVES(2, false); }

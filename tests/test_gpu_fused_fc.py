@@ -173,6 +173,9 @@ def test_fused_rejects_what_it_cannot_do(dev):
     (100, 17, 2048, "f32", 12),         # seven k-steps; one row in the last block of 16
     (3, 17, 256, "bf16", 4),            # one k-step, mostly padding
     (161, 33, 512, "bf16", 7),          # six k-steps; one row in the last block of 64; 4-byte accesses
+    (129, 40, 4096, "bf16", 8),         # more than 128 samples in bf16, the contraction first: five k-steps, a tile is half a row
+    (200, 35, 1024, "bf16", 6),         # a tile is two rows; 8-byte aligned state
+    (224, 130, 256, "bf16", 4),         # a tile is eight rows, two live rows in the last block
     (65, 4100, 2048, "bf16", 3),        # 257 blocks: eight waves a block, three k-steps
     (20, 32900, 256, "f32", 4),         # 258 blocks of 128 rows, two k-steps
     (100, 8197, 1024, "f32", 2),        # 257 blocks, seven k-steps
