@@ -124,6 +124,14 @@ size_t vgc_scratch_bitmap_offset(const vgc_group* groups, uint32_t n_groups, uin
  * g_out (may be NULL), s_out: DEVICE float [J, C] row-major (the weight's own layout), 16-byte aligned.
  * Accumulation is in float32.  Errors: NULL, SIZE (a zero dimension, P != 1 for FC), DTYPE, ALIGN, PARAM.
  *
+ * Accuracy of the float32 form.  FC (and shapes whose rows are not whole 16-byte pieces): float32 products and sums.
+ * CONV (and vgc_sqgrad_conv2d beyond first layers): a product of two elements is formed from six products of their
+ * 8-bit pieces, within 2^-24 of it (2^-27.5 in the root mean square over random mantissas); the six are added for up to
+ * 32 positions at a time by an instruction that truncates its sum to 24 bits, so that a single product may err by
+ * 2^-22.4; these sums, the samples' squares and their sums are rounded to nearest in float32.  Over 16 positions and
+ * more the error of g and s against 64 bits is at or below that of float32 products and sums; at a single position it
+ * is up to 1.3 times that.  Every float32 input counts with all its bits, subnormal ones included.
+ *
  * workspace: optional DEVICE buffer (16-byte aligned) of vgc_sqgrad_workspace_bytes() bytes.  When
  * [J, C] has too few tiles to fill the chip the samples are split over more workgroups and the
  * partial sums are added from the workspace in a fixed order (the result does not depend on

@@ -7,10 +7,11 @@
 // the same two mantissas it is the same each time.  (With hi cut off instead of rounded: 2^-22 and 2^-25.5.)
 //
 // Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
-// latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.65 ms (98 -> 183 TFLOP/s); the 53 layers
-// of ResNet-50 at batch 32: 3.14 -> 2.35 ms in one batch call.  What bounds it now: the vector instructions that cut the
-// elements (13 per pair) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 43 % busy), and
-// on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
+// latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.66 ms (98 -> 180 TFLOP/s); the 53 layers
+// of ResNet-50 at batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product).  What bounds it
+// now: the vector instructions that cut the elements (13 per pair, once per filter tap and column tile) and those that add
+// up the chunks share the issue slots with the MFMAs (matrix pipes 26 to 33 % busy on ResNet's layers), and on the small
+// layers a workgroup's 14 chunks take 19 us of its kernel's 31.
 //
 // The bf16 MFMA adds with truncation: chained over all positions, every instruction would cut off a little of the
 // accumulator, always towards minus infinity.  So the six products of a chunk of 32 positions are summed from zero, where

@@ -63,8 +63,9 @@ int launch_unpack_add(PlanCheck pc, const uint32_t* words, uint64_t n_words, con
 // Bound by memory: the words once, the buffer (or the optimizer's arrays) once or twice.  What kept it from there was the
 // search for the cursors, each message's words being asked for only when the one before was done, and words asked for
 // past a tile's end that a non-temporal load did not leave in the cache.  Before and after: 10^9 elements, 8 messages of
-// 17 % overwriting, 2380 -> 1862 us (5.1 TB/s); of 0.2 % over 3 x 10^8, 473 -> 225 us; 25.6 M elements with Adam,
-// 224 -> 158 us; 138 M with momentum SGD and sparse messages, 431 -> 386 us (5.8 TB/s).
+// 17 % overwriting, 2388 -> 1888 us (5.0 TB/s); of 0.2 % over 3 x 10^8, 473 -> 225 us; 25.6 M elements with Adam,
+// 220 -> 163 us; 138 M with momentum SGD and sparse messages, 433 -> 387 us (5.8 TB/s).  The words are read 1.33 (33 %
+// sent) to 1.60 times (19 %): 1.17 to 1.37 times with an eighth of the waves, so the rest are the cursors' searches.
 // ------------------------------------------------------------------------------------------------
 namespace vgc {
 
@@ -381,7 +382,7 @@ __global__ __launch_bounds__(256) void k_unpack_add_batch(PlanCheck pc, BatchArg
 
 // Waves to aim for: 5120 are resident, and the last ones to be placed leave the others idle.  64 K of them against 16 K:
 // 10^9 elements, 8 messages of 17 %, 1.87 against 2.05 ms; 138 M elements, sparse messages with momentum SGD, 384 against
-// 423 us.  With 256 K the search for the cursors and the words requested twice cost more: 2.36 ms and 386 us.
+// 423 us, although each wave's search reads 12 to 16 KB.  With 256 K that costs more: 2.36 ms and 386 us.
 constexpr uint64_t kWaves = 65536;
 
 template <int kMax>
