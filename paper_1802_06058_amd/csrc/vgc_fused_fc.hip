@@ -16,11 +16,13 @@
 // What bounds it: r and v read and written, 16 bytes per parameter (25088 x 4096: 1.64 GB, 0.28 ms at the 5.9 TB/s of an
 // in-place stream), and how far the contraction (0.20 ms alone) and that stream overlap.  Keeping all 16 tiles' g and s in
 // accumulators and passing them through LDS into tile order took one workgroup of 131 KB of LDS per compute unit, whose
-// waves contracted, streamed and encoded in step: 0.43 ms.  With 70 KB and 128 registers (three more spill: 12 bytes of
-// scratch a lane) two workgroups share a compute unit: 0.38 ms.  Loads come back in the order of their request: with r and
-// v requested before the fragments each MFMA waited for HBM (0.50 ms).  Kernel and transposes, before -> now, us: the same
-// layer at batch 8, 32, 64, 128 in bf16 384 -> 365, 388 -> 359, 457 -> 384, 553 -> 511, in float32 428 -> 363, 508 -> 390,
-// 638 -> 533, 901 -> 813.
+// waves contracted, streamed and encoded in step: 0.43 ms.  With 70 KB and at most 128 registers two workgroups share a
+// compute unit: 0.38 ms.  Loads come back in the order of their request: with r and v requested before the fragments each
+// MFMA waited for HBM (0.50 ms).  Kernel and transposes, before -> now, us: the same layer at batch 8, 32, 64, 128 in bf16
+// 384 -> 365, 388 -> 359, 457 -> 384, 553 -> 511, in float32 428 -> 363, 508 -> 390, 638 -> 533, 901 -> 813.  The form before
+// stays for long batches in bf16 (k_fused_fc_select_long).
+#include <type_traits>
+
 #include "vgc_tile_core.h"
 
 namespace vgc {
@@ -189,11 +191,8 @@ __device__ __forceinline__ void store4(f4 x, float* p, bool vec) {
 
 // kR: rows of [J, C] per tile (1: C is a multiple of 2048 and a tile is a piece of a row; 2, 4, 8: C = 2048 / kR).
 // kWaves: waves that share the block's 16 tiles.
-// kLong: the contraction over a long K comes first, for all of the wave's columns at once, so that the fragments of X are
-// fetched and squared once instead of once per 32 columns (one vector instruction in three), with two waves on a SIMD and the
-// r and v of two pieces on their way.
-template <int kR, bool kBf16, int kWaves, bool kLong>
-__global__ __launch_bounds__(kWaves * 64, kLong ? 2 : 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
+template <int kR, bool kBf16, int kWaves>
+__global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
                                                             const PlanGroup* __restrict__ groups,
                                                             TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap,
                                                             uint16_t* __restrict__ staging) {
@@ -284,64 +283,26 @@ __global__ __launch_bounds__(kWaves * 64, kLong ? 2 : 4) void k_fused_fc_select(
     };
     // Loads come back in the order of their request (and stores count among them): the first fragments of the next 32 columns are
     // requested before the r and v of these are waited for and written.
-    Frags F0, F1;
-    if (!kLong) { F0 = fetch(0, 0); F1 = fetch(0, A.Kp > kStep ? kStep : 0u); }
-    auto request = [&](int n, f4 (&R)[2], f4 (&V)[2]) {
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            R[q] = V[q] = (f4){0.f, 0.f, 0.f, 0.f};
-            if (8u * q < rows_left) {
-                R[q] = load4(r + q * row8 + 32 * n + eoff, vec);
-                V[q] = load4(v + q * row8 + 32 * n + eoff, vec);
-            }
-        }
-    };
-    f4 RN[2][2], VN[2][2];                                    // kLong: r and v of the next two pieces
-    if (kLong) request(0, RN[0], VN[0]);
-    f4v long_g[kLong ? 2 * kN : 1], long_s[kLong ? 2 * kN : 1];
-    if (kLong) {
-        static_assert(!kLong || kBf16, "float32 gains nothing from it");
-#pragma unroll
-        for (int t = 0; t < 2 * kN; ++t) { long_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; long_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
-        for (uint32_t k0 = 0; k0 < A.Kp; k0 += kStep) {
-            u4v x = *reinterpret_cast<const u4v*>(xp + (size_t)k0 * es + xoff);
-            if (!frow_ok) x = (u4v){0u, 0u, 0u, 0u};
-            const u4v x2 = sq_bf16x8(x);
-#pragma unroll
-            for (int t0 = 0; t0 < 2 * kN; t0 += 8) {
-                u4v d[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) d[t] = *reinterpret_cast<const u4v*>(dp + (size_t)(t0 + t) * dstep + (size_t)k0 * es + doff);
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const u4v d2 = sq_bf16x8(d[t]);
-                    long_g[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d[t]), __builtin_bit_cast(bf8v, x), long_g[t0 + t], 0, 0, 0);
-                    long_s[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, d2), __builtin_bit_cast(bf8v, x2), long_s[t0 + t], 0, 0, 0);
-                }
-            }
-        }
-    }
-    if (kLong) request(1, RN[1], VN[1]);
+    Frags F0 = fetch(0, 0), F1 = fetch(0, A.Kp > kStep ? kStep : 0u);
     uint2 code[kN][2];                                        // of columns 32 n + tcol .. + 3, row q (n < kParked: in LDS meanwhile)
 #pragma unroll
     for (int n = 0; n < kN; ++n) {
         f4 R4[2], V4[2];
-        if (kLong) {
 #pragma unroll
-            for (int q = 0; q < 2; ++q) { R4[q] = RN[n & 1][q]; V4[q] = VN[n & 1][q]; }
-            if (n + 2 < kN) request(n + 2, RN[n & 1], VN[n & 1]);
-#pragma unroll
-            for (int t = 0; t < 2; ++t) { acc_g[t] = long_g[kLong ? 2 * n + t : 0]; acc_s[t] = long_s[kLong ? 2 * n + t : 0]; }
-        } else {
-            request(n, R4, V4);
-#pragma unroll
-            for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
-            multiply(F0);
-            if (A.Kp > kStep) multiply(F1);
-#pragma unroll 1
-            for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
-            if (n + 1 < kN) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
+        for (int q = 0; q < 2; ++q) {
+            R4[q] = V4[q] = (f4){0.f, 0.f, 0.f, 0.f};
+            if (8u * q < rows_left) {
+                R4[q] = load4(r + q * row8 + 32 * n + eoff, vec);
+                V4[q] = load4(v + q * row8 + 32 * n + eoff, vec);
+            }
         }
+#pragma unroll
+        for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+        multiply(F0);
+        if (A.Kp > kStep) multiply(F1);
+#pragma unroll 1
+        for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
+        if (n + 1 < kN) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
             *reinterpret_cast<f4v*>(turn_g + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_g[t] * A.cg;
@@ -403,9 +364,156 @@ __global__ __launch_bounds__(kWaves * 64, kLong ? 2 : 4) void k_fused_fc_select(
     }
 }
 
-// Batches from which on the contraction comes first (bf16; times before it was split off, the short form, the long one):
-// 9216 x 1024 at 128 93, 92 and 94 us, at 160 87, 96 and 91, at 256 125, 134 and 124; 25088 x 4096 at 160 510, 533 and 555,
-// at 256 748, 772 and 762, at 1024 1925, 2393 and 1922.
+// The same for a long K in bf16: the contraction first, with all 16 tiles' g and s in the accumulators (2 x 64 registers per
+// lane of eight waves, one workgroup per compute unit), which then pass through LDS in tile order, eight tiles at a time, and
+// each wave runs the loop body on one tile while the r and v of its next chunks are on their way.  The fragments of X are
+// fetched and squared once, where the kernel above does it once per 32 columns (one vector instruction in three).
+constexpr int kSlotPitch = kTile + 8;               // floats per tile's slot: slots 2 q and 2 q + 2 start 16 banks apart
+
+template <int kR>
+__global__ __launch_bounds__(512) void k_fused_fc_select_long(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
+                                                              const PlanGroup* __restrict__ groups, TileHdr* __restrict__ hdrs,
+                                                              uint32_t* __restrict__ bitmap, uint16_t* __restrict__ staging) {
+    __shared__ __attribute__((aligned(16))) float lds_g[8][kSlotPitch];
+    __shared__ __attribute__((aligned(16))) float lds_s[8][kSlotPitch];
+
+    const bool ok = plan_ok(pc);
+    if (blockIdx.x == 0 && threadIdx.x == 0) flags[0] = ok ? 0u : 1u;
+    if (!ok) return;
+
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);      // uniform per wave: scalar registers, scalar branches
+    const uint32_t lrow = lane & 15u, lgrp = lane >> 4;
+    const PlanGroup pg = groups[A.group];
+    constexpr uint32_t Cb = kTile / kR, CT = Cb / 16;         // columns of a block, its 16-column MFMA tiles per row tile
+    const uint32_t ncb = kR == 1 ? A.C / kTile : 1u;          // column blocks
+    const uint32_t cb = kR == 1 ? blockIdx.x % ncb : 0u, rb = kR == 1 ? blockIdx.x / ncb : blockIdx.x;
+    const uint32_t j0 = rb * 16u * kR, colbase = cb * kTile;  // first row and column of the block
+    const uint32_t nt_group = (pg.size + kTile - 1) / kTile;
+    const bool vec = ((reinterpret_cast<uintptr_t>(A.r + pg.offset) | reinterpret_cast<uintptr_t>(A.v + pg.offset)) & 15u) == 0;
+    const bool vec_out = ((reinterpret_cast<uintptr_t>(A.g_out) | reinterpret_cast<uintptr_t>(A.s_out)) & 15u) == 0;
+
+    // Wave w runs the tile in slot w of each pass.  Accumulator element i of MFMA tile t of a lane is row 16 rt + 4 lgrp + i,
+    // column 16 (ct0 + t) + lrow of the block; it belongs to tile row / kR.  For kR = 1 pass p takes elements 2 p, 2 p + 1 of
+    // every lane (tiles 4 lgrp + i in slots 2 lgrp + i % 2: all lanes write), otherwise the tiles 8 p .. 8 p + 7.
+    struct TileRef { uint32_t in_group, m; };                 // number inside the group, elements (0: past the end of the layer)
+    auto ref_of = [&](uint32_t p) -> TileRef {
+        const uint32_t tl = kR == 1 ? 4u * (wave >> 1) + 2u * p + (wave & 1u) : 8u * p + wave;
+        const uint32_t in_group = kR == 1 ? (j0 + tl) * ncb + cb : (uint32_t)blockIdx.x * kFusedTiles + tl;
+        const bool live = kR == 1 ? (j0 + tl) < A.J : in_group < nt_group;
+        return TileRef{live ? in_group : 0u, live ? min(kTile, pg.size - in_group * kTile) : 0u};
+    };
+    // chunk u of a tile: elements 256 u + 4 lane + c; rows are whole multiples of 256, so a chunk exists as a whole or not at all
+    f4 R4[4], V4[4];
+    auto request = [&](const TileRef& q, int u, bool whole) {     // whole: all of it exists, 16 bytes at a time
+        if (!whole) R4[u & 3] = V4[u & 3] = (f4){0.f, 0.f, 0.f, 0.f};
+        if (!whole && 256u * u >= q.m) return;
+        const size_t at = pg.offset + (size_t)q.in_group * kTile + 256u * u + 4u * lane;
+        R4[u & 3] = load4(A.r + at, whole || vec);
+        V4[u & 3] = load4(A.v + at, whole || vec);
+    };
+    TileRef q = ref_of(0);
+    if (vec && q.m == kTile) {
+#pragma unroll
+        for (int u = 0; u < 4; ++u) request(q, u, true);      // they arrive while the matrix cores are busy
+    }
+
+    const uint32_t rt = (16u * wave) / CT, ct0 = (16u * wave) % CT;      // the wave's 16 MFMA tiles: one row tile, 16 column tiles
+    f4v acc_g[16], acc_s[16];
+#pragma unroll
+    for (int t = 0; t < 16; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+    const uint32_t row = j0 + 16u * rt + lrow;
+    const bool row_ok = row < A.J;
+    const uint16_t* xp = static_cast<const uint16_t*>(A.XT) + (size_t)(row_ok ? row : 0u) * A.Kp + 8u * lgrp;
+    const uint16_t* dp = static_cast<const uint16_t*>(A.DT) + (size_t)(colbase + 16u * ct0 + lrow) * A.Kp + 8u * lgrp;
+    for (uint32_t k0 = 0; k0 < A.Kp; k0 += 32) {
+        u4v x = *reinterpret_cast<const u4v*>(xp + k0);
+        if (!row_ok) x = (u4v){0u, 0u, 0u, 0u};
+        const u4v x2 = sq_bf16x8(x);
+#pragma unroll
+        for (int t0 = 0; t0 < 16; t0 += 8) {
+            u4v d[8];
+#pragma unroll
+            for (int t = 0; t < 8; ++t) d[t] = *reinterpret_cast<const u4v*>(dp + (size_t)(t0 + t) * 16u * A.Kp + k0);
+#pragma unroll
+            for (int t = 0; t < 8; ++t) {
+                const u4v d2 = sq_bf16x8(d[t]);
+                acc_g[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, x), __builtin_bit_cast(bf8v, d[t]), acc_g[t0 + t], 0, 0, 0);
+                acc_s[t0 + t] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf8v, x2), __builtin_bit_cast(bf8v, d2), acc_s[t0 + t], 0, 0, 0);
+            }
+        }
+    }
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+        if (p) __syncthreads();                               // every wave is done with the slots of the first pass
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (kR == 1 && i / 2 != p) continue;
+            const uint32_t rw = 16u * rt + 4u * lgrp + i, tl = rw / kR;
+            if (kR != 1 && (tl >> 3) != (uint32_t)p) continue;
+            const uint32_t slot = kR == 1 ? 2u * lgrp + (uint32_t)(i & 1) : tl & 7u, at = (rw % kR) * Cb + 16u * ct0 + lrow;
+#pragma unroll
+            for (int t = 0; t < 16; ++t) {
+                lds_g[slot][at + 16u * t] = acc_g[t][i] * A.cg;
+                lds_s[slot][at + 16u * t] = acc_s[t][i] * A.cs;
+            }
+        }
+        __syncthreads();
+        if (p) q = ref_of(1);
+        if (q.m == 0) continue;
+        uint2 code[8];
+        auto run = [&](auto is_whole) __attribute__((always_inline)) {
+            constexpr bool whole = decltype(is_whole)::value;
+            if (p || !whole) {
+#pragma unroll
+                for (int u = 0; u < 4; ++u) request(q, u, whole);
+            }
+#pragma unroll
+            for (int u = 0; u < 8; ++u) {
+                const f4 g4 = reinterpret_cast<const f4*>(lds_g[wave])[u * 64 + lane], s4 = reinterpret_cast<const f4*>(lds_s[wave])[u * 64 + lane];
+                const f4 r4 = R4[u & 3], v4 = V4[u & 3];
+                if (u + 4 < 8) request(q, u + 4, whole);      // into the registers that this chunk leaves
+                const bool live = whole || 256u * u < q.m;
+                const size_t in_layer = (size_t)q.in_group * kTile + 256u * u + 4u * lane;
+                if (A.g_out && live) {
+                    store4(g4, A.g_out + in_layer, vec_out);
+                    store4(s4, A.s_out + in_layer, vec_out);
+                }
+                f4 ro, vo;
+                uint32_t w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float a, b;
+                    uint32_t bits;
+                    const bool send = alg1_step(g4[c], s4[c], r4[c], v4[c], A.alpha, A.zeta, a, b, bits) & live;
+                    ro[c] = a;
+                    vo[c] = b;
+                    w[c] = element_code(bits, send);
+                }
+                if (live) {
+                    store4(ro, A.r + pg.offset + in_layer, whole || vec);
+                    store4(vo, A.v + pg.offset + in_layer, whole || vec);
+                }
+                code[u] = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+            }
+        };
+        if (vec && q.m == kTile) run(std::true_type{});
+        else run(std::false_type{});
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");      // the slot's g has been read: the codes take its place
+        __builtin_amdgcn_wave_barrier();
+        uint16_t* codes = reinterpret_cast<uint16_t*>(lds_g[wave]);
+#pragma unroll
+        for (int u = 0; u < 8; ++u) *reinterpret_cast<uint2*>(codes + u * 256 + 4 * lane) = code[u];
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+        __builtin_amdgcn_wave_barrier();
+        const uint32_t t = pg.first_tile + q.in_group;
+        encode_codes(codes, hdrs + t, bitmap + (size_t)t * (kTile / 32), staging + (size_t)t * kTile, lane);
+    }
+}
+
+// Batches in bf16 above which the contraction comes first (kernel and transposes, interleaved / contraction first, us): 9216 x
+// 1024 at 128 93 / 93, at 160 96 / 87, at 256 134 / 125, at 1024 387 / 309; 25088 x 4096 at 128 511 / 553, at 160 533 / 520, at
+// 256 772 / 764, at 1024 2393 / 1938.  In float32 the squares are one instruction an element and it gains nothing.
 constexpr uint32_t kLongK = 128;
 
 // Shapes the fused kernel takes: C a multiple of 2048 (a tile is a piece of a row) or C = 1024, 512, 256 (a tile is
@@ -454,20 +562,20 @@ int launch_fused_fc_select(PlanCheck pc, uint32_t* flags, int dtype, const void*
     // With no more blocks than compute units 16 waves share a block, each with half the columns and one tile to encode: what a
     // wave does in a row is then all the time there is (300 x 2048 in bf16 at batch 64: 31.4 us against 35.0 with eight waves;
     // 1000 x 256 in float32: 41.7 against 49.7).
-#define VGC_FUSED(KR, BF, NW, LG)                                                                                             \
-    hipLaunchKernelGGL((k_fused_fc_select<KR, BF, NW, LG>), dim3((uint32_t)nblk), dim3(NW * 64), 0, stream, pc, flags, A, groups, \
-                       hdrs, bitmap, staging)
-#define VGC_FUSED_WAVES(KR, BF)                                                                                               \
+#define VGC_FUSED(K_, NW) hipLaunchKernelGGL((K_), dim3((uint32_t)nblk), dim3(NW * 64), 0, stream, pc, flags, A, groups, hdrs, bitmap, staging)
+#define VGC_FUSED_WAVES(KR)                                                                                                   \
     do {                                                                                                                      \
-        if (BF && Kp > kLongK) VGC_FUSED(KR, BF, 8, BF);                                                                      \
-        else if (nblk <= 256) VGC_FUSED(KR, BF, 16, false);                                                                   \
-        else VGC_FUSED(KR, BF, 8, false);                                                                                     \
+        if (bf && Kp > kLongK) VGC_FUSED(k_fused_fc_select_long<KR>, 8);                                                      \
+        else if (bf && nblk <= 256) VGC_FUSED((k_fused_fc_select<KR, true, 16>), 16);                                         \
+        else if (bf) VGC_FUSED((k_fused_fc_select<KR, true, 8>), 8);                                                          \
+        else if (nblk <= 256) VGC_FUSED((k_fused_fc_select<KR, false, 16>), 16);                                              \
+        else VGC_FUSED((k_fused_fc_select<KR, false, 8>), 8);                                                                 \
     } while (0)
     const bool bf = dtype == VGC_BF16;
-    if (kr == 1) { if (bf) VGC_FUSED_WAVES(1, true); else VGC_FUSED_WAVES(1, false); }
-    else if (kr == 2) { if (bf) VGC_FUSED_WAVES(2, true); else VGC_FUSED_WAVES(2, false); }
-    else if (kr == 4) { if (bf) VGC_FUSED_WAVES(4, true); else VGC_FUSED_WAVES(4, false); }
-    else { if (bf) VGC_FUSED_WAVES(8, true); else VGC_FUSED_WAVES(8, false); }
+    if (kr == 1) VGC_FUSED_WAVES(1);
+    else if (kr == 2) VGC_FUSED_WAVES(2);
+    else if (kr == 4) VGC_FUSED_WAVES(4);
+    else VGC_FUSED_WAVES(8);
 #undef VGC_FUSED_WAVES
 #undef VGC_FUSED
     return hip_check(hipGetLastError(), "launch k_fused_fc_select");
