@@ -25,7 +25,7 @@ int hip_check(hipError_t e, const char* what) {
 }
 
 // Validates the group list and counts tiles.  Returns a vgc_status.
-struct GroupStats { uint64_t n_runs; uint32_t n_segs; bool multi_seg; uint64_t hash; };
+struct GroupStats { uint64_t n_runs; uint32_t n_segs; uint32_t max_group_tiles; uint64_t hash; };
 
 static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, uint64_t* n_tiles_out,
                         GroupStats* stats_out = nullptr) {
@@ -33,7 +33,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     if (n == 0 || n_groups == 0) { set_error("n and n_groups must be positive"); return VGC_ERR_SIZE; }
     uint64_t off = 0, tiles = 0, runs = 0, segs = 0;
     uint64_t hash = 0xCBF29CE484222325ull ^ n_groups;       // FNV-1a over the sizes (offsets follow from them)
-    bool multi = false;
+    uint32_t most = 0;
     for (uint32_t k = 0; k < n_groups; ++k) {
         hash = (hash ^ groups[k].size) * 0x100000001B3ull;
         if (groups[k].size == 0) { set_error("group %u is empty", k); return VGC_ERR_SIZE; }
@@ -51,7 +51,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
         tiles += nt;
         runs += (nt + kRunTiles - 1) / kRunTiles;
         segs += (nt + kSegTiles - 1) / kSegTiles;
-        multi = multi || nt > kSegTiles;
+        if (nt > most) most = (uint32_t)nt;
     }
     if (off != n) {
         set_error("groups cover %llu elements, n = %llu", (unsigned long long)off, (unsigned long long)n);
@@ -59,7 +59,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     }
     if (tiles > 0x7FFFFFFFull) { set_error("too many tiles (%llu)", (unsigned long long)tiles); return VGC_ERR_SIZE; }
     if (n_tiles_out) *n_tiles_out = tiles;
-    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->multi_seg = multi; stats_out->hash = hash; }
+    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->max_group_tiles = most; stats_out->hash = hash; }
     return VGC_OK;
 }
 
@@ -521,7 +521,7 @@ int vgc_pack(uint64_t n, const vgc_group* groups, uint32_t n_groups, const void*
     const ScratchLayout L = scratch_layout(n_tiles, n_groups);
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     char* sc = static_cast<char*>(scratch);
-    return launch_pack(plan_check(plan, gs), reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.tiles, pv.segs, n_tiles, n_groups, gs.n_segs, gs.multi_seg,
+    return launch_pack(plan_check(plan, gs), reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.tiles, pv.segs, n_tiles, n_groups, gs.n_segs, gs.max_group_tiles,
                        reinterpret_cast<TileHdr*>(sc + L.tile_hdr_off),
                        reinterpret_cast<SegTmp*>(sc + L.seg_tmp_off),
                        reinterpret_cast<const uint16_t*>(sc + L.staging_off),
@@ -555,7 +555,7 @@ int vgc_pack_compact(uint64_t n, const vgc_group* groups, uint32_t n_groups, con
     char* sc = static_cast<char*>(scratch);
     const PlanCheck pc = plan_check(plan, gs);
     TileHdr* th = reinterpret_cast<TileHdr*>(sc + L.tile_hdr_off);
-    rc = launch_pack_scans(pc, reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.segs, n_groups, gs.n_segs, gs.multi_seg, th,
+    rc = launch_pack_scans(pc, reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.segs, n_groups, gs.n_segs, gs.max_group_tiles, th,
                            reinterpret_cast<SegTmp*>(sc + L.seg_tmp_off), hdrs_out, status_out, ~0ull, static_cast<hipStream_t>(stream));
     if (rc != VGC_OK) return rc;
     return launch_pack_compact(pc, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, n_groups, th,

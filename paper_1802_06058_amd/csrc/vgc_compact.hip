@@ -28,10 +28,10 @@ __device__ __forceinline__ uint32_t encode_tile(const TileHdr* __restrict__ hdrs
     uint32_t w[8];
 #pragma unroll
     for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__shfl((int)hw, i);
-    if (w[7] == 0) return 0;                                   // nothing kept
+    if ((w[7] & 0xFFFFu) == 0) return 0;                                   // nothing kept
     const uint32_t cnt = (w[0] & 0xFFFFu) + (w[0] >> 16) + (w[1] & 0xFFFFu) + (w[1] >> 16) + (w[2] & 0xFFFFu) +
                          (w[2] >> 16) + (w[3] & 0xFFFFu) + (w[3] >> 16) + (w[4] & 0xFFFFu);
-    const uint32_t shift = w[6], lim = 8 - shift;              // kept != 0 implies shift <= 8
+    const uint32_t shift = w[7] >> 16, lim = 8 - shift;              // kept != 0 implies shift <= 8
     const uint16_t* st = staging + t * kTile;
     int32_t prev = -1;                                         // position of the last kept entry so far (uniform)
     uint32_t bytes = 0;
@@ -125,7 +125,7 @@ __global__ __launch_bounds__(256) void k_compact_emit(PlanCheck pc, const PlanGr
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t t = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= n_tiles || !plan_ok(pc)) return;
-    if (hdrs[t].w[7] == 0) return;
+    if ((hdrs[t].w[7] & 0xFFFFu) == 0) return;
     // where the tile's bytes go: the run's offset plus the bytes of the run's earlier tiles
     const PlanTile pt = tiles[t];
     const uint64_t run_first = (uint64_t)groups[pt.group].first_tile + runs[pt.run].first_tile;

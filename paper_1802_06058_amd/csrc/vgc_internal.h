@@ -60,9 +60,10 @@ struct PlanTile {              // 16 bytes
     uint32_t run;              // index of the tile's run in the run table
 };
 
-// A segment is up to kSegTiles consecutive tiles of one group: the unit one workgroup of the scan
-// kernel owns (8 tile records per thread, one pass).  A group of 2^28 elements has 16 of them.
+// A segment is up to kSegTiles consecutive tiles of one group (a group of 2^28 elements has 16 of them), a part up to
+// kPartTiles consecutive tiles of one segment: the unit one workgroup of the scan kernels owns (4 tile records per thread).
 constexpr uint32_t kSegTiles = 8192;
+constexpr uint32_t kPartTiles = 1024;
 struct PlanSeg {               // 16 bytes
     uint32_t group;
     uint32_t first_tile;       // index of the segment's first tile inside its group
@@ -89,12 +90,13 @@ inline uint32_t decode_tiles_per_wave(uint64_t n_runs, uint64_t waves, uint32_t 
 }
 
 // Per-tile record in the scratch.  Written by the accumulate kernel (w[0..4]) and completed by
-// the first pack kernel (w[5..7]).
+// the pack kernels (w[5..7]).
 //   w[0..3]  : hist[0..7], two 16-bit counters per word (low half = even bin)
 //   w[4]     : low half hist[8]; high half = largest truncated exponent field among the tile's sent elements
-//   w[5]     : number of words the segment's earlier tiles produce (exclusive prefix inside the segment)
-//   w[6]     : shift = E_k - tile exponent
-//   w[7]     : words this tile produces
+//   w[5]     : number of words the part's earlier tiles produce (exclusive prefix inside the part); in the part's first
+//              tile, whose prefix is 0, the part's count, and after the header scan the words of the segment's earlier parts
+//   w[6]     : in a part's first tile the largest tile exponent of the part (written only for groups of several parts)
+//   w[7]     : low half words this tile produces; high half shift = E_k - tile exponent (255 if more)
 struct TileHdr { uint32_t w[8]; };
 
 // Staged entry (uint16): rel << 12 | sign << 11 | position in tile, where
@@ -103,7 +105,7 @@ struct TileHdr { uint32_t w[8]; };
 // and the element is encoded iff rel <= 8 - shift.
 
 struct SegTmp {                // 32 bytes, one per segment
-    uint32_t max_e;            // largest tile exponent inside the segment (written only for groups of several segments)
+    uint32_t reserved1;
     uint32_t exp_field;        // E_k of the segment's group
     uint32_t count;            // words the segment produces
     uint32_t reserved;
@@ -154,14 +156,14 @@ int launch_fused_fc_select(PlanCheck pc, uint32_t* flags, int dtype, const void*
                            uint16_t* staging, float alpha, float zeta, void* workspace, float* g_out, float* s_out, hipStream_t stream);
 
 int launch_pack(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanSeg* segs, uint64_t n_tiles,
-                uint32_t n_groups, uint32_t n_segs, bool multi_seg,
+                uint32_t n_groups, uint32_t n_segs, uint32_t max_group_tiles,
                 TileHdr* hdrs, SegTmp* stmp, const uint16_t* staging,
                 uint32_t* words_out, uint64_t words_cap, vgc_group_hdr* hdrs_out,
                 vgc_pack_status* status_out, hipStream_t stream);
 
 // the scans of vgc_pack without the word emission (vgc_pack.hip), and the compressed index format (vgc_compact.hip)
 int launch_pack_scans(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
-                      uint32_t n_segs, bool multi_seg, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
+                      uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
                       vgc_pack_status* status_out, uint64_t words_cap, hipStream_t stream);
 int launch_pack_compact(PlanCheck pc, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles,
                         uint64_t n_runs, uint32_t n_groups, const TileHdr* hdrs, const uint16_t* staging, uint8_t* stream_out,
