@@ -167,7 +167,9 @@ struct CompactArgs {
 };
 
 typedef float f4c __attribute__((ext_vector_type(4)));
-typedef uint16_t us2 __attribute__((ext_vector_type(2)));
+typedef __attribute__((address_space(3))) float* lds_float;
+struct __attribute__((packed)) Unaligned64 { uint64_t x; };
+typedef const __attribute__((address_space(1))) Unaligned64* global_u64;
 
 constexpr uint32_t kLaneBytes = 8;                              // bytes of a message a lane decodes per round
 constexpr uint32_t kRoundBytes = 64 * kLaneBytes;
@@ -188,7 +190,7 @@ __device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
 // Bits 0..3 of x as bytes of 0x00 or 0xFF.
 __device__ __forceinline__ uint32_t byte_mask(uint32_t x) {
     const uint32_t y = ((x & 15u) * 0x00204081u) & 0x01010101u;
-    return (y << 8) - y;
+    return __builtin_amdgcn_perm(0u, 0u, y | 0x0C0C0C0Cu);       // a selector of 12 gives 0x00, one of 13 0xFF
 }
 
 // One wave owns tiles_per_wave consecutive tiles of a run (tile in LDS, messages in order).
@@ -210,13 +212,17 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
                                                            const PlanRun* __restrict__ runs, uint32_t n_runs, float scale,
                                                            float* __restrict__ dense, int overwrite, uint32_t tiles_per_wave) {
     static_assert(kBatchMax == 8, "a lane per (message, tile of a block of 8)");
-    __shared__ __attribute__((aligned(16))) float sh_tile[4][kTile];
+    __shared__ __attribute__((aligned(4 * kTile))) float sh_tile[4][kTile];         // (a tile's address and a place in it are or-ed)
     const uint32_t lane = threadIdx.x & 63u;
     const uint32_t wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t per_run = (uint32_t)kRunTiles / tiles_per_wave;
     const uint32_t gw = blockIdx.x * 4 + wave, run = gw / per_run;
     if (run >= n_runs || !plan_ok(pc)) return;
     float* T = sh_tile[wave];
+    const uint32_t Tb = (uint32_t)(uintptr_t)(lds_float)T;
+    uint32_t in_tile = 4u * (kTile - 1);                        // a mask in a register: and-or is one instruction then
+    asm volatile("" : "+v"(in_tile));
+    const uint32_t neutral = __float_as_uint(scale) >> 31 ? 0u : 0x80808080u;       // scale times this zero is -0
     const uint32_t k = runs[run].group, first = runs[run].first_tile;
     const PlanGroup pg = groups[k];
     const uint32_t nt_group = (pg.size + kTile - 1) / kTile;
@@ -260,25 +266,25 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
         cur += (uint32_t)__shfl((int)incl, 7, 8);
         ahead = count_of(tb + 8 + mj);
     };
-    // bytes off .. off + 7 of the tile's message at S, `left` bytes of which may be read
-    auto fetch = [&](const uint8_t* S, uint32_t off, int left) -> uint2 {
-        uint64_t x;
+    // Bytes off .. off + 7 of the tile's message at S, `left` bytes of which may be read, once shifted down by `down` bits: the
+    // shift is the reader's, who would otherwise wait for the bytes here.
+    struct Bytes { uint64_t x; uint32_t down; };
+    auto fetch = [&](const uint8_t* S, uint32_t off, int left, Bytes& y) {
         const int a = min((int)off, left - (int)kLaneBytes);    // the stream's last bytes: read from before them
-        __builtin_memcpy(&x, (S - kLaneBytes) + (uint32_t)(a + (int)kLaneBytes), sizeof(x));
-        x >>= 8u * (off - (uint32_t)a);
-        return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+        y.x = ((global_u64)((S - kLaneBytes) + (uint32_t)(a + (int)kLaneBytes)))->x;
+        y.down = 8u * (off - (uint32_t)a);
     };
     // the same where the stream has fewer than 8 bytes in all (so the tile has, and off is 0): one by one
-    auto fetch_few = [&](const uint8_t* S, int left) -> uint2 {
-        uint64_t x = 0;
-        for (int i = 0; i < left; ++i) x |= (uint64_t)S[i] << (8 * i);
-        return make_uint2((uint32_t)x, (uint32_t)(x >> 32));
+    auto fetch_few = [&](const uint8_t* S, int left, Bytes& y) {
+        y.x = 0;
+        for (int i = 0; i < left; ++i) y.x |= (uint64_t)S[i] << (8 * i);
+        y.down = 0;
     };
     // the item (tile, message) requested next, and what has been requested
     uint32_t tn = t0, wn = 0, nb_n = 0;
     int left_n = 0;
     const uint8_t* S_n = nullptr;
-    uint2 x_n = make_uint2(0u, 0u);
+    Bytes x_n = {0, 0};
     auto request = [&]() {
         if (tn >= t1) return;
         if (wn == 0 && ((tn - t0) & 7u) == 0) next_block(tn);
@@ -291,7 +297,10 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
         left_n = (int)(kShort ? left_of_run & 0x7FFFFFFFu : left_of_run) - (int)(d >> 13);
         nb_n = (uint32_t)max(0, min((int)(d & 8191u), left_n));
         S_n = reinterpret_cast<const uint8_t*>(at) + (d >> 13);
-        if (lane * kLaneBytes < nb_n) x_n = few ? fetch_few(S_n, left_n) : fetch(S_n, lane * kLaneBytes, left_n);
+        if (lane * kLaneBytes < nb_n) {
+            if (few) fetch_few(S_n, left_n, x_n);
+            else fetch(S_n, lane * kLaneBytes, left_n, x_n);
+        }
         if (++wn == A.p) { wn = 0; ++tn; }
     };
     if (A.p) request();
@@ -317,16 +326,19 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
             const int left = left_n;
             const uint8_t* S = S_n;
             const uint32_t ef = (uint32_t)__builtin_amdgcn_readlane((int)expf, (int)(w * 8u));
-            uint2 x = x_n;
+            Bytes y = x_n;
             request();
             if (ef == 0 || ef > 254u) continue;                 // nothing of this message can be decoded
             uint32_t pos0 = ~3u;                                // position of the last element so far (-1: none), in bytes
             uint32_t inside = 0, last = 0;                      // whether the round begins inside an element, the byte before it
             for (uint32_t o = 0; o < nb; o += kRoundBytes) {
                 const uint32_t off = o + lane * kLaneBytes;
-                uint2 more = make_uint2(0u, 0u);
-                if (off + kRoundBytes < nb) more = fetch(S, off + kRoundBytes, left);
-                const uint32_t valid = (1u << (off < nb ? min(nb - off, kLaneBytes) : 0u)) - 1u;
+                Bytes more = {0, 0};
+                if (off + kRoundBytes < nb) fetch(S, off + kRoundBytes, left, more);
+                const uint32_t here = off < nb ? min(nb - off, kLaneBytes) : 0u, valid = (1u << here) - 1u;
+                const uint64_t there = ~0ull >> ((8u * (kLaneBytes - here)) & 63u);         // (a lane with none: of no consequence)
+                const uint64_t bytes = (y.x >> y.down) & there;
+                const uint2 x = make_uint2((uint32_t)bytes, (uint32_t)(bytes >> 32));
                 // bit i: byte i has bit 7 set
                 const uint32_t high = (__builtin_amdgcn_udot4((x.x >> 7) & 0x01010101u, 0x08040201u, 0u, false) |
                                        __builtin_amdgcn_udot4((x.y >> 7) & 0x01010101u, 0x80402010u, 0u, false)) & valid;
@@ -344,49 +356,59 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
                 const uint32_t prev_lane = (uint32_t)__builtin_amdgcn_update_dpp((int)(last << 24), (int)x.y, 0x138, 0xF, 0xF, false);  // wave_shr:1
                 const uint32_t c0 = (m0 & __builtin_amdgcn_alignbyte(x.x, prev_lane, 3)) | (~m0 & x.x);
                 const uint32_t c1 = (m1 & __builtin_amdgcn_alignbyte(x.y, x.x, 3)) | (~m1 & x.y);
-                // steps, two bytes per register, and their running sums
-                us2 q[4];
-                us2 run_sum = {0, 0};
-#pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t src = i < 2 ? x.x : x.y, msk = i < 2 ? m0 : m1;
-                    const uint32_t h = __builtin_amdgcn_perm(0u, src, (i & 1) ? 0x0C030C02u : 0x0C010C00u);
-                    const uint32_t mm = __builtin_amdgcn_perm(0u, msk, (i & 1) ? 0x03030202u : 0x01010000u);
-                    const uint32_t as_first = ((h >> 2) & 0x001C001Cu) + 0x00040004u, as_second = h << 5;
-                    const uint32_t step = (mm & as_second) | (~mm & as_first);
-                    q[i] = __builtin_bit_cast(us2, step + (step << 16)) + run_sum;
-                    run_sum = (us2){q[i].y, q[i].y};
-                }
-                const uint32_t sum = run_sum.x;
-                const uint32_t incl = wave_inclusive_sum(sum);
-                const uint16_t b16 = (uint16_t)(pos0 + incl - sum);
                 if (ef < 8u) {                                  // exponents too small for some of the codes
 #pragma unroll
                     for (int i = 0; i < (int)kLaneBytes; ++i)
                         if ((((i < 4 ? c0 : c1) >> (8 * (i & 3))) & 7u) >= ef) ends &= ~(1u << i);
                 }
-                // the elements of one message are distinct: all are read before any is written
+                // the first bytes' steps (gap + 1, low bits) and the second bytes' values; a sum over bytes is a dot product, with
+                // the position in bytes of LDS 4 times the one and 32 times the other
+                const uint32_t f0 = ((((x.x >> 4) & 0x07070707u) + 0x01010101u) & (uint32_t)there) & ~m0, s0 = x.x & m0;
+                const uint32_t f1 = ((((x.y >> 4) & 0x07070707u) + 0x01010101u) & (uint32_t)(there >> 32)) & ~m1, s1 = x.y & m1;
+                const uint32_t half = __builtin_amdgcn_udot4(s0, 0x20202020u, __builtin_amdgcn_udot4(f0, 0x04040404u, 0u, false), false);
+                const uint32_t sum = __builtin_amdgcn_udot4(s1, 0x20202020u, __builtin_amdgcn_udot4(f1, 0x04040404u, half, false), false);
+                const uint32_t incl = wave_inclusive_sum(sum);
+                const uint32_t p0 = pos0 + incl - sum, p1 = p0 + half;
                 uint32_t at[kLaneBytes];
-                float old[kLaneBytes];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) {
-                    const uint32_t pair = __builtin_bit_cast(uint32_t, q[i] + (us2){b16, b16}) & (0x00010001u * (4u * (kTile - 1)));
-                    at[2 * i] = pair & 0xFFFFu;
-                    at[2 * i + 1] = pair >> 16;
+                for (int i = 0; i < 3; ++i) {
+                    const uint32_t four = 0x04040404u >> (24 - 8 * i), eight = 0x20202020u >> (24 - 8 * i);     // of the bytes up to i
+                    at[i] = __builtin_amdgcn_udot4(s0, eight, __builtin_amdgcn_udot4(f0, four, p0, false), false);
+                    at[4 + i] = __builtin_amdgcn_udot4(s1, eight, __builtin_amdgcn_udot4(f1, four, p1, false), false);
                 }
+                at[3] = p1;
+                at[7] = p0 + sum;
 #pragma unroll
-                for (int i = 0; i < (int)kLaneBytes; ++i) old[i] = *reinterpret_cast<const float*>(reinterpret_cast<const char*>(T) + at[i]);
+                for (int i = 0; i < (int)kLaneBytes; ++i) at[i] = (at[i] & in_tile) | Tb;
+                // the elements' values, sign and exponent (which reaches into the third byte), put together four at a time.  A byte
+                // that ends no element gets the zero that leaves any float as it is when scaled and added, so no byte needs a
+                // branch: what it rewrites belongs to no element of the message (the first byte of two lies between its element and
+                // the one before), or, behind the message's end, to its last one, which the same lane writes after it.
+                uint32_t hi[2], lo[2];
 #pragma unroll
-                for (int i = 0; i < (int)kLaneBytes; ++i) {
-                    const uint32_t c = (i < 4 ? c0 : c1) >> (8 * (i & 3));
-                    const float val = __uint_as_float(((ef - (c & 7u)) << 23) | ((c << 28) & 0x80000000u));
-                    const float contrib = scale * val;
-                    if ((ends >> i) & 1u) *reinterpret_cast<float*>(reinterpret_cast<char*>(T) + at[i]) = old[i] + contrib;
+                for (int h = 0; h < 2; ++h) {
+                    const uint32_t e = byte_mask(h ? ends >> 4 : ends), c = (h ? c1 : c0) & e;
+                    const uint32_t exps = ef * 0x01010101u - (c & 0x07070707u);
+                    hi[h] = ((((exps >> 1) & 0x7F7F7F7Fu) | ((c << 4) & 0x80808080u)) & e) | (neutral & ~e);
+                    lo[h] = (exps << 7) & 0x80808080u & e;
+                }
+                if (off < nb) {
+                    // the elements of one message are distinct: all are read before any is written
+                    float old[kLaneBytes];
+#pragma unroll
+                    for (int i = 0; i < (int)kLaneBytes; ++i) old[i] = *(lds_float)(uintptr_t)at[i];
+#pragma unroll
+                    for (int i = (int)kLaneBytes - 1; i >= 0; --i) {
+                        const uint32_t sel = 0x04000C0Cu + 0x01010000u * (uint32_t)(i & 3);
+                        const float val = __uint_as_float(__builtin_amdgcn_perm(hi[i >> 2], lo[i >> 2], sel));
+                        const float contrib = scale * val;
+                        *(lds_float)(uintptr_t)at[i] = old[i] + contrib;
+                    }
                 }
                 pos0 += (uint32_t)__builtin_amdgcn_readlane((int)incl, 63);
                 inside = stops ? (uint32_t)(odd >> (63 - __builtin_clzll(stops))) & 1u : inside;
                 last = (uint32_t)__builtin_amdgcn_readlane((int)x.y, 63) >> 24;
-                x = more;
+                y = more;
             }
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
