@@ -554,13 +554,11 @@ int vgc_pack_compact(uint64_t n, const vgc_group* groups, uint32_t n_groups, con
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     char* sc = static_cast<char*>(scratch);
     const PlanCheck pc = plan_check(plan, gs);
-    TileHdr* th = reinterpret_cast<TileHdr*>(sc + L.tile_hdr_off);
-    rc = launch_pack_scans(pc, reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.segs, n_groups, gs.n_segs, gs.max_group_tiles, th,
-                           reinterpret_cast<SegTmp*>(sc + L.seg_tmp_off), hdrs_out, status_out, ~0ull, static_cast<hipStream_t>(stream));
-    if (rc != VGC_OK) return rc;
-    return launch_pack_compact(pc, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, n_groups, th,
-                               reinterpret_cast<const uint16_t*>(sc + L.staging_off), stream_out, stream_cap, tile_bytes_out,
-                               run_offsets_out, hdrs_out, status_out, static_cast<hipStream_t>(stream));
+    return launch_pack_compact(pc, reinterpret_cast<const uint32_t*>(sc + L.flags_off), pv.groups, pv.tiles, pv.runs, pv.segs, n_tiles,
+                               gs.n_runs, n_groups, gs.n_segs, gs.max_group_tiles, reinterpret_cast<TileHdr*>(sc + L.tile_hdr_off),
+                               reinterpret_cast<SegTmp*>(sc + L.seg_tmp_off), reinterpret_cast<const uint16_t*>(sc + L.staging_off),
+                               stream_out, stream_cap, tile_bytes_out, run_offsets_out, hdrs_out, status_out,
+                               static_cast<hipStream_t>(stream));
 }
 
 // The batched decoders with the tiles of a wave given (a power of two up to a run's 64, 0: by the rule).  Not part of the

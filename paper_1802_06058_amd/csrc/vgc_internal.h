@@ -161,14 +161,26 @@ int launch_pack(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, co
                 uint32_t* words_out, uint64_t words_cap, vgc_group_hdr* hdrs_out,
                 vgc_pack_status* status_out, hipStream_t stream);
 
-// the scans of vgc_pack without the word emission (vgc_pack.hip), and the compressed index format (vgc_compact.hip)
-int launch_pack_scans(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
-                      uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
-                      vgc_pack_status* status_out, uint64_t words_cap, hipStream_t stream);
-int launch_pack_compact(PlanCheck pc, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles,
-                        uint64_t n_runs, uint32_t n_groups, const TileHdr* hdrs, const uint16_t* staging, uint8_t* stream_out,
-                        uint64_t stream_cap, uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out,
-                        vgc_pack_status* status_out, hipStream_t stream);
+// The scans of vgc_pack (vgc_pack.hip): the parts' scans, then the scan over parts, segments and groups, which with a directory
+// given also turns the tiles' bytes of the compressed index format (vgc_compact.hip) into the runs' and groups' byte offsets.
+struct CompactDirectory {
+    const PlanTile* tiles;
+    const PlanRun* runs;
+    uint64_t n_runs;
+    const uint16_t* tile_bytes;
+    uint64_t* run_offsets;
+    uint64_t stream_cap;
+};
+int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_segs, uint32_t max_group_tiles,
+                      TileHdr* hdrs, SegTmp* stmp, hipStream_t stream);
+int launch_header_scan(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
+                       uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
+                       vgc_pack_status* status_out, uint64_t words_cap, const CompactDirectory* compact, hipStream_t stream);
+int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs,
+                        const PlanSeg* segs, uint64_t n_tiles, uint64_t n_runs, uint32_t n_groups, uint32_t n_segs, uint32_t max_group_tiles,
+                        TileHdr* hdrs, SegTmp* stmp, const uint16_t* staging, uint8_t* stream_out, uint64_t stream_cap,
+                        uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out, vgc_pack_status* status_out,
+                        hipStream_t stream);
 bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
 int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,

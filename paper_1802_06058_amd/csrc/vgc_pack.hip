@@ -199,14 +199,36 @@ __device__ __forceinline__ void empty_message(uint32_t threads, uint32_t n_group
     }
 }
 
+// Bytes of a run of the compressed index format: the sum over its tiles (at most 64, of at most 2 kTile bytes each).
+struct __attribute__((packed, aligned(2))) EightCounts { uint32_t w[4]; };
+__device__ __forceinline__ uint32_t run_bytes(const uint16_t* __restrict__ tile_bytes, uint32_t n) {
+    static_assert(kRunTiles == 64, "eight loads of eight tiles");
+    EightCounts x[8];
+    uint16_t y[7];
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q) x[q] = 8 * q + 8 <= n ? reinterpret_cast<const EightCounts*>(tile_bytes + 8 * q)[0] : EightCounts{{0, 0, 0, 0}};
+#pragma unroll
+    for (uint32_t i = 0; i < 7; ++i) y[i] = (n & ~7u) + i < n ? tile_bytes[(n & ~7u) + i] : (uint16_t)0;
+    uint32_t sum = 0;
+#pragma unroll
+    for (uint32_t q = 0; q < 8; ++q)
+#pragma unroll
+        for (uint32_t i = 0; i < 4; ++i) sum += (x[q].w[i] & 0xFFFFu) + (x[q].w[i] >> 16);
+#pragma unroll
+    for (uint32_t i = 0; i < 7; ++i) sum += y[i];
+    return sum;
+}
+
 // One workgroup: the parts' counts become their places inside the segment, an exclusive scan over the segments gives their
-// places in the message, and from these follow headers and status.
+// places in the message, and from these follow headers and status.  kCompact: the message is one with compressed indexes; the
+// same scan over the runs' bytes gives run offsets, and the groups' offsets and the total are in bytes.
+template <bool kCompact>
 __global__ __launch_bounds__(1024) void k_header_scan(PlanCheck pc, const uint32_t* __restrict__ flags,
                                                       const PlanGroup* __restrict__ groups, const PlanSeg* __restrict__ segs,
                                                       TileHdr* __restrict__ hdrs, SegTmp* __restrict__ stmp,
                                                       uint32_t n_groups, uint32_t n_segs, uint32_t parts_per_seg,
                                                       vgc_group_hdr* __restrict__ hdrs_out,
-                                                      vgc_pack_status* __restrict__ status, uint64_t words_cap) {
+                                                      vgc_pack_status* __restrict__ status, uint64_t words_cap, CompactDirectory dir) {
     constexpr uint32_t kParts = kSegTiles / kPartTiles;
     __shared__ uint32_t sh[16];
     if (!plan_ok(pc) || flags[0] != 0u) {
@@ -242,6 +264,23 @@ __global__ __launch_bounds__(1024) void k_header_scan(PlanCheck pc, const uint32
         }
         running += (uint64_t)tot_lo + ((uint64_t)tot_hi << 16);
     }
+    if (kCompact) {
+        running = 0;
+        for (uint64_t base = 0; base < dir.n_runs; base += 1024) {
+            const uint64_t q = base + threadIdx.x;
+            uint32_t bytes = 0;
+            if (q < dir.n_runs) {
+                const PlanRun pr = dir.runs[q];
+                const PlanGroup pg = groups[pr.group];
+                const uint32_t tiles = (pg.size + kTile - 1) / kTile - pr.first_tile;
+                bytes = run_bytes(dir.tile_bytes + pg.first_tile + pr.first_tile, min(tiles, kRunTiles));
+            }
+            uint32_t total;                                  // (1024 runs hold at most 2^28 bytes)
+            const uint32_t incl = block_scan<16>(bytes, sh, total);
+            if (q < dir.n_runs) dir.run_offsets[q] = running + incl - bytes;
+            running += total;
+        }
+    }
     __threadfence_block();
     __syncthreads();
     for (uint32_t i = threadIdx.x; i < n_segs; i += 1024) {
@@ -252,12 +291,13 @@ __global__ __launch_bounds__(1024) void k_header_scan(PlanCheck pc, const uint32
         h.word_offset = stmp[i].base;
         h.count = (uint32_t)(stmp[last].base + stmp[last].count - h.word_offset);
         h.exp_field = h.count ? stmp[i].exp_field : 0u;
+        if (kCompact) h.word_offset = dir.run_offsets[dir.tiles[groups[ps.group].first_tile].run];
         hdrs_out[ps.group] = h;
     }
     if (threadIdx.x == 0) {
         vgc_pack_status st;
         st.total_words = running;
-        st.overflow = running > words_cap ? 1u : 0u;
+        st.overflow = running > (kCompact ? dir.stream_cap : words_cap) ? 1u : 0u;
         st.plan_mismatch = 0;
         *status = st;
     }
@@ -419,17 +459,27 @@ static uint32_t parts_per_seg(uint32_t max_group_tiles) {
     return parts < kSegTiles / kPartTiles ? parts : kSegTiles / kPartTiles;
 }
 
-int launch_pack_scans(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
-                      uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
-                      vgc_pack_status* status_out, uint64_t words_cap, hipStream_t stream) {
+int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_segs, uint32_t max_group_tiles,
+                      TileHdr* hdrs, SegTmp* stmp, hipStream_t stream) {
     // (at most n_tiles / 1024 + 8 n_groups workgroups)
     const uint32_t pps = parts_per_seg(max_group_tiles);
     if (max_group_tiles > kOwnMaxTiles)
         hipLaunchKernelGGL(k_part_max, dim3(n_segs * pps), dim3(kScanThreads), 0, stream, pc, groups, segs, hdrs, pps);
     hipLaunchKernelGGL(k_part_scan, dim3(n_segs * pps), dim3(kScanThreads), 0, stream, pc, groups, segs, hdrs, stmp, pps);
-    hipLaunchKernelGGL(k_header_scan, dim3(1), dim3(1024), 0, stream, pc, flags, groups, segs, hdrs, stmp, n_groups, n_segs, pps, hdrs_out,
-                       status_out, words_cap);
-    return hip_check(hipGetLastError(), "launch pack scans");
+    return hip_check(hipGetLastError(), "launch part scans");
+}
+
+int launch_header_scan(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
+                       uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
+                       vgc_pack_status* status_out, uint64_t words_cap, const CompactDirectory* compact, hipStream_t stream) {
+    const uint32_t pps = parts_per_seg(max_group_tiles);
+    if (compact)
+        hipLaunchKernelGGL(k_header_scan<true>, dim3(1), dim3(1024), 0, stream, pc, flags, groups, segs, hdrs, stmp, n_groups, n_segs, pps,
+                           hdrs_out, status_out, words_cap, *compact);
+    else
+        hipLaunchKernelGGL(k_header_scan<false>, dim3(1), dim3(1024), 0, stream, pc, flags, groups, segs, hdrs, stmp, n_groups, n_segs, pps,
+                           hdrs_out, status_out, words_cap, CompactDirectory{});
+    return hip_check(hipGetLastError(), "launch k_header_scan");
 }
 
 int launch_pack(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanSeg* segs, uint64_t n_tiles,
@@ -443,7 +493,9 @@ int launch_pack(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, co
                            words_out, words_cap, hdrs_out, status_out);
         return hip_check(hipGetLastError(), "launch k_pack_small");
     }
-    const int rc = launch_pack_scans(pc, flags, groups, segs, n_groups, n_segs, max_group_tiles, hdrs, stmp, hdrs_out, status_out, words_cap, stream);
+    int rc = launch_part_scans(pc, groups, segs, n_segs, max_group_tiles, hdrs, stmp, stream);
+    if (rc == VGC_OK)
+        rc = launch_header_scan(pc, flags, groups, segs, n_groups, n_segs, max_group_tiles, hdrs, stmp, hdrs_out, status_out, words_cap, nullptr, stream);
     if (rc != VGC_OK) return rc;
     hipLaunchKernelGGL(k_emit, dim3(blocks), dim3(256), 0, stream, pc, tiles, n_tiles, hdrs, staging,
                        stmp, words_out, words_cap);
