@@ -631,7 +631,7 @@ int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr*
         const uint32_t* const wl[1] = {words};
         const uint64_t nl[1] = {n_words};
         const vgc_group_hdr* const hl[1] = {hdrs};
-        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.runs, gs.n_runs, scale, 0, dense_out, 0,
+        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, 0, dense_out, 0,
                                        static_cast<hipStream_t>(stream));
     }
     return launch_unpack_add(plan_check(plan, gs), words, n_words, hdrs, pv.groups, n_groups, scale, dense_out, static_cast<hipStream_t>(stream));
@@ -654,7 +654,7 @@ int vgc_tiles_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_w
     if (!std::isfinite(scale)) { set_error("vgc_unpack_add_batch: scale is not finite"); return VGC_ERR_PARAM; }
     if (p == 0 && !overwrite) return VGC_OK;
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
-    return launch_unpack_add_batch(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.runs, gs.n_runs, scale, overwrite, dense_out,
+    return launch_unpack_add_batch(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, overwrite, dense_out,
                                    tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 
@@ -700,7 +700,7 @@ int vgc_tiles_unpack_apply(const uint32_t* const* words, const uint64_t* n_words
         bias2 = (float)(1.0 - std::pow((double)b2, (double)opt->step));
     }
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
-    return launch_unpack_apply(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.runs, gs.n_runs, scale, opt->kind, opt->lr, mu, b1, b2,
+    return launch_unpack_apply(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, opt->kind, opt->lr, mu, b1, b2,
                                omb1, omb2, bias1, bias2, eps, param, state1, state2, tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 

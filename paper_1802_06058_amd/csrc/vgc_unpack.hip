@@ -380,10 +380,215 @@ __global__ __launch_bounds__(256) void k_unpack_add_batch(PlanCheck pc, BatchArg
     else decode_tiles<8, kMode>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
 }
 
+// ------------------------------------------------------------------------------------------------
+// The same for parameter sets too small to give every unit of the chip several waves of a tile each: a workgroup per tile.
+// One wave a tile is then bound by a chain: cursors (six dependent loads), then every message's words asked for while the one
+// before it is added.  Here the four waves look for a quarter of the messages' cursors each, with four times the lanes a
+// message, the words of eight messages are requested at once, 256 a round, and a barrier keeps the messages' order.
+// 1.8 M elements, 8 messages of 17 %, momentum SGD: 26.6 -> 18.2 us from a cold cache, Adam 37.8 -> 26.4; 16 messages of 30 %
+// 54.6 -> 33.2; 20,000 elements 28.8 -> 14.3.
+// ------------------------------------------------------------------------------------------------
+template <int kRounds, int kMode>
+__device__ __forceinline__ void decode_tile(uint32_t p, const uint64_t* cur_at, const uint32_t* cur_left, const uint32_t* cur_exp, uint32_t* more,
+                                            const PlanGroup& pg, uint32_t start, float scale, float* __restrict__ dense, int overwrite,
+                                            const UpdateArgs& O, float* T, uint32_t tid) {
+    const uint32_t m = min(kTile, pg.size - start);
+    const uint64_t e0 = pg.offset + start;
+    float* base = (kMode == kToDense) ? dense + e0 : O.w + e0;
+    bool vec = (m == kTile) && ((reinterpret_cast<uintptr_t>(base) & 15u) == 0);
+    if (kMode != kToDense)
+        vec = vec && ((reinterpret_cast<uintptr_t>(O.s1 + e0) & 15u) == 0) &&
+              (kMode != kAdam || (reinterpret_cast<uintptr_t>(O.s2 + e0) & 15u) == 0);
+    const bool fresh = overwrite || kMode != kToDense;
+    // a thread's elements: two groups of four (vec), else eight, 256 apart
+    f4u W4[2], S1[2], S2[2];
+    uint32_t word[8][kRounds];
+    auto request = [&](uint32_t w, uint32_t first, uint32_t* x) -> uint32_t {      // words first .. of message w; how many there are
+        const uint32_t left = w < p ? cur_left[w] : 0u, n = left > first ? min(left - first, (uint32_t)kRounds * 256u) : 0u;
+        const uint64_t at = w < p ? cur_at[w] + 4ull * first : 0ull;
+        const uint32_t n_u = __builtin_amdgcn_readfirstlane(n);
+        const uint32_t at_lo = __builtin_amdgcn_readfirstlane((uint32_t)at), at_hi = __builtin_amdgcn_readfirstlane((uint32_t)(at >> 32));   // (it returns an int)
+        const uint64_t at_u = (uint64_t)at_lo | (uint64_t)at_hi << 32;
+        const __amdgpu_buffer_rsrc_t r = __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(at_u), 0, (int)(n_u * 4u), 0x00020000);
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) x[j] = __builtin_amdgcn_raw_buffer_load_b32(r, (int)(tid * 4u) + j * 1024, 0, 0);
+        return n_u;
+    };
+    auto add = [&](const uint32_t* x, uint32_t n, uint32_t w) {
+        const uint32_t ef = __builtin_amdgcn_readfirstlane(cur_exp[w]);
+        float old[kRounds];
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) old[j] = T[min((x[j] & 0x0FFFFFFFu) - start, kTile - 1u)];
+#pragma unroll
+        for (int j = 0; j < kRounds; ++j) {
+            const uint32_t i = (uint32_t)j * 256u + tid, idx = x[j] & 0x0FFFFFFFu, d = (x[j] >> 28) & 7u;
+            const bool in_tile = i < n && idx < start + m;
+            // a well-formed message has idx >= start here and exp_field > d; anything else is skipped
+            if (in_tile && idx >= start && ef > d && ef <= 254u) {
+                const float val = __uint_as_float(((ef - d) << 23) | (x[j] & 0x80000000u));
+                const float contrib = scale * val;
+                T[idx - start] = old[j] + contrib;
+            }
+            if (in_tile && i == (uint32_t)kRounds * 256u - 1u) more[w] += 1u;      // the last of those requested: there may be others
+        }
+    };
+    for (uint32_t w0 = 0; w0 == 0 || w0 < p; w0 += 8) {
+        uint32_t n[8];
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) n[u] = request(w0 + u, 0, word[u]);
+        if (w0 == 0) {
+            // the tile and the optimizer's arrays: behind the words, and used when those have been added
+            if (vec) {
+#pragma unroll
+                for (int q = 0; q < 2; ++q) {
+                    if (kMode != kToDense || !fresh) W4[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(base) + q * 256 + tid);
+                    if (kMode != kToDense) S1[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s1 + e0) + q * 256 + tid);
+                    if (kMode == kAdam) S2[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s2 + e0) + q * 256 + tid);
+                }
+            }
+            if (!fresh) {
+                if (vec) {
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) reinterpret_cast<f4u*>(T)[q * 256 + tid] = W4[q];
+                } else {
+                    for (uint32_t i = tid; i < kTile; i += 256) T[i] = (i < m) ? base[i] : 0.f;
+                }
+                __syncthreads();
+            }
+        }
+#pragma unroll
+        for (uint32_t u = 0; u < 8; ++u) {
+            if (w0 + u >= p) break;
+            if (n[u] == 0) continue;
+            add(word[u], n[u], w0 + u);
+            __syncthreads();
+            if (n[u] == (uint32_t)kRounds * 256u) {
+                uint32_t rounds = 1;
+                while (more[w0 + u] == rounds) {
+                    uint32_t x[kRounds];
+                    const uint32_t k = request(w0 + u, rounds * (uint32_t)kRounds * 256u, x);
+                    __syncthreads();                                 // (all have read the count)
+                    if (k == 0) break;
+                    add(x, k, w0 + u);
+                    __syncthreads();
+                    ++rounds;
+                }
+            }
+        }
+    }
+    if (vec) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) {
+            const f4u G = reinterpret_cast<f4u*>(T)[q * 256 + tid];
+            if (kMode == kToDense) {
+                __builtin_nontemporal_store(G, reinterpret_cast<f4u*>(base) + q * 256 + tid);
+                continue;
+            }
+            f4u w4 = W4[q], a4 = S1[q], b4 = S2[q];
+#pragma unroll
+            for (int c = 0; c < 4; ++c) {
+                float w = w4[c], a = a4[c], b = kMode == kAdam ? b4[c] : 0.f;
+                update_element<kMode>(O, G[c], w, a, b);
+                w4[c] = w; a4[c] = a; b4[c] = b;
+            }
+            __builtin_nontemporal_store(w4, reinterpret_cast<f4u*>(O.w + e0) + q * 256 + tid);
+            __builtin_nontemporal_store(a4, reinterpret_cast<f4u*>(O.s1 + e0) + q * 256 + tid);
+            if (kMode == kAdam) __builtin_nontemporal_store(b4, reinterpret_cast<f4u*>(O.s2 + e0) + q * 256 + tid);
+        }
+        return;
+    }
+    for (uint32_t i = tid; i < m; i += 256) {
+        if (kMode == kToDense) {
+            base[i] = T[i];
+            continue;
+        }
+        float w = O.w[e0 + i], a = O.s1[e0 + i], b = (kMode == kAdam) ? O.s2[e0 + i] : 0.f;
+        update_element<kMode>(O, T[i], w, a, b);
+        O.w[e0 + i] = w;
+        O.s1[e0 + i] = a;
+        if (kMode == kAdam) O.s2[e0 + i] = b;
+    }
+}
+
+template <int kMax, int kMode>
+__global__ __launch_bounds__(256) void k_unpack_tile(PlanCheck pc, BatchArgs<kMax> A, const PlanGroup* __restrict__ groups,
+                                                     const PlanTile* __restrict__ tiles, uint32_t n_tiles, float scale,
+                                                     float* __restrict__ dense, int overwrite, UpdateArgs O) {
+    __shared__ __attribute__((aligned(16))) float T[kTile];
+    __shared__ uint64_t cur_at[kMax];
+    __shared__ uint32_t cur_left[kMax], cur_exp[kMax], more[kMax], rounds_of[4];
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    // (neighbours share an L2, as above)
+    const uint32_t in_block = blockIdx.x & 127u, block0 = blockIdx.x - in_block;
+    const uint32_t t = block0 + 128u <= gridDim.x ? block0 + (in_block & 7u) * 16u + (in_block >> 3) : blockIdx.x;
+    if (t >= n_tiles || !plan_ok(pc)) return;
+    const PlanTile pt = tiles[t];
+    const PlanGroup pg = groups[pt.group];
+    const uint32_t first = pt.start;
+
+    // The cursors: wave v finds those of messages v, v + 4, .., with 64 >> lg lanes for each (a power of two).
+    const uint32_t mine_p = (A.p + 3u - wave) / 4u;                  // messages of the wave
+    uint32_t lg = 6;
+    while (lg > 0 && (64u >> lg) < mine_p) --lg;
+    const uint32_t w = wave + 4u * (lane >> lg), sub = lane & ((1u << lg) - 1u);
+    uint32_t rounds = 0;
+    if (mine_p) {
+        uint64_t at = 0;
+        uint32_t left = 0, ef = 0;
+        if (w < A.p) {
+            const vgc_group_hdr h = A.hdrs[w][pt.group];
+            const float mu = (float)h.count * ((float)kTile / (float)pg.size);
+            rounds = (uint32_t)fminf((mu + 3.0f * sqrtf(mu)) * (1.0f / 256.0f), 8.0f) + 1u;
+            uint64_t lo = h.word_offset, hi = h.word_offset + h.count;
+            if (hi > A.n_words[w]) hi = A.n_words[w];
+            if (lo > hi) lo = hi;
+            at = reinterpret_cast<uint64_t>(A.words[w]) + 4ull * lo;
+            left = (uint32_t)min(hi - lo, (uint64_t)0xFFFFFFFFu);
+            ef = h.exp_field;
+        }
+        uint32_t lo = 0, hi = first != 0 ? left : 0u;
+        const uint32_t* W = reinterpret_cast<const uint32_t*>(at);
+        while (__ballot(lo < hi)) {
+            const uint64_t n = lo < hi ? hi - lo : 0;
+            const bool less = n != 0 && (W[lo + (uint32_t)((n * (2u * sub + 1u)) >> (lg + 1u))] & 0x0FFFFFFFu) < first;
+            const uint64_t of_message = (__ballot(less) >> ((lane >> lg) << lg)) & (~0ull >> (64u - (1u << lg)));
+            const uint32_t c = (uint32_t)__popcll(of_message);
+            if (n != 0) {
+                const uint32_t below = lo + (uint32_t)((n * (2u * c - 1u)) >> (lg + 1u)) + 1u;
+                const uint32_t above = lo + (uint32_t)((n * (2u * c + 1u)) >> (lg + 1u));
+                if (c != (1u << lg)) hi = above;
+                if (c != 0) lo = min(below, hi);                     // (a damaged message may answer in no order)
+            }
+        }
+        if (w < A.p && sub == 0) {
+            cur_at[w] = at + 4ull * lo;
+            cur_left[w] = left - lo;
+            cur_exp[w] = ef;
+            more[w] = 0;
+        }
+    }
+    const uint32_t rounds_w = __ballot(rounds > 2) ? 4u : __ballot(rounds > 1) ? 2u : 1u;
+    if (lane == 0) rounds_of[wave] = rounds_w;
+    if (overwrite || kMode != kToDense) {
+#pragma unroll
+        for (int q = 0; q < 2; ++q) reinterpret_cast<f4u*>(T)[q * 256 + tid] = (f4u){0.f, 0.f, 0.f, 0.f};
+    }
+    __syncthreads();
+    const uint32_t most = __builtin_amdgcn_readfirstlane(max(max(rounds_of[0], rounds_of[1]), max(rounds_of[2], rounds_of[3])));
+    if (most == 1) decode_tile<1, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+    else if (most == 2) decode_tile<2, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+    else decode_tile<4, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+}
+
 // Waves to aim for: 5120 are resident, and the last ones to be placed leave the others idle.  64 K of them against 16 K:
 // 10^9 elements, 8 messages of 17 %, 1.87 against 2.05 ms; 138 M elements, sparse messages with momentum SGD, 384 against
 // 423 us, although each wave's search reads 12 to 16 KB.  With 256 K that costs more: 2.36 ms and 386 us.
 constexpr uint64_t kWaves = 65536;
+
+// Up to so many tiles a workgroup takes each: as many workgroups as are resident at once (five per compute unit).  2.5 M elements
+// (1221 tiles), 8 messages of 17 %: 22.7 -> 20.2 us overwriting, 38.0 -> 28.2 with Adam; 3 M (1465) 23.8 -> 28.2 and 45.0 -> 35.0;
+// 4 M 24.9 -> 30.4 and 39.0 -> 38.9; beyond, the search for the cursors of every tile costs what it gives or more.
+constexpr uint64_t kFewTiles = 1280;
 
 template <int kMax>
 static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
@@ -400,13 +605,19 @@ static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* 
 }
 
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                            uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs,
+                            uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs,
                             float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream) {
+    const bool by_tile = tiles_per_wave == 0 && n_tiles <= kFewTiles;
     const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;     // p == 0: only the optional clear
     for (uint32_t ch = 0; ch < chunks; ++ch) {
         const BatchArgs<kBatchMax> A = batch_args<kBatchMax>(words, n_words, hdrs, ch * kBatchMax, p);
+        if (by_tile) {
+            hipLaunchKernelGGL((k_unpack_tile<kBatchMax, kToDense>), dim3((uint32_t)n_tiles), dim3(256), 0, stream, pc, A, groups, tiles,
+                               (uint32_t)n_tiles, scale, dense, (overwrite && ch == 0) ? 1 : 0, UpdateArgs{});
+            continue;
+        }
         hipLaunchKernelGGL((k_unpack_add_batch<kBatchMax, kToDense>), dim3(blocks), dim3(256), 0, stream, pc, A, groups, runs,
                            (uint32_t)n_runs, scale, dense, (overwrite && ch == 0) ? 1 : 0, UpdateArgs{}, tpw);
     }
@@ -414,7 +625,7 @@ int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const ui
 }
 
 int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                        uint32_t p, const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale,
+                        uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, float scale,
                         int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
                         float eps, float* param, float* state1, float* state2, uint32_t tiles_per_wave, hipStream_t stream) {
     const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
@@ -423,6 +634,15 @@ int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64
     UpdateArgs O;
     O.w = param; O.s1 = state1; O.s2 = state2;
     O.lr = lr; O.mu = mu; O.b1 = b1; O.b2 = b2; O.omb1 = omb1; O.omb2 = omb2; O.bias1 = bias1; O.bias2 = bias2; O.eps = eps;
+    if (tiles_per_wave == 0 && n_tiles <= kFewTiles) {
+        if (kind == VGC_OPT_ADAM)
+            hipLaunchKernelGGL((k_unpack_tile<kApplyMax, kAdam>), dim3((uint32_t)n_tiles), dim3(256), 0, stream, pc, A, groups, tiles,
+                               (uint32_t)n_tiles, scale, static_cast<float*>(nullptr), 1, O);
+        else
+            hipLaunchKernelGGL((k_unpack_tile<kApplyMax, kMomentumSgd>), dim3((uint32_t)n_tiles), dim3(256), 0, stream, pc, A, groups, tiles,
+                               (uint32_t)n_tiles, scale, static_cast<float*>(nullptr), 1, O);
+        return hip_check(hipGetLastError(), "launch k_unpack_tile (update)");
+    }
     if (kind == VGC_OPT_ADAM)
         hipLaunchKernelGGL((k_unpack_add_batch<kApplyMax, kAdam>), dim3(blocks), dim3(256), 0, stream, pc, A, groups, runs,
                            (uint32_t)n_runs, scale, static_cast<float*>(nullptr), 1, O, tpw);
