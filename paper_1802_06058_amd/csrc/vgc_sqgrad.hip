@@ -35,9 +35,8 @@ __global__ __launch_bounds__(256) void k_sqgrad_simple(const T* __restrict__ X, 
 
     f16v acc_g = {0}, acc_s = {0};
     if (!kConv) {
-        // float32: eight k-steps are requested while the eight before them are multiplied (one at a time, 1000 x 10 at batch
-        // 128, 32 waves in all, took 15.1 us and 20001 x 4001 at batch 64 427 us; so 9.6 and 313).  bfloat16: one at a
-        // time, with more waves instead of the registers (9001 x 3001 at batch 128: 198 us, 249 with eight ahead).
+        // (only for operands of 2^31 bytes or elements and more; the others go through LDS, vgc_sqgrad_fc.hip)  float32: eight
+        // k-steps are requested while the eight before them are multiplied; bfloat16: one at a time, with more waves instead.
         constexpr int kAhead = sizeof(T) == 4 ? 8 : 1;
         struct Steps { float a[kAhead], b[kAhead]; };
         auto request = [&](uint32_t z0) -> Steps {
@@ -103,7 +102,7 @@ int launch_sqgrad(int kind, int dtype, const void* X, const void* D, uint32_t B,
         return launch_conv_f32_tiled(X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, stream);
     if (kind == VGC_FC && fc_tiled_supported(dtype, B, J, C))
         return launch_fc_tiled(dtype, X, D, B, J, C, c, g_out, s_out, stream);
-    // shapes the tiled kernels do not take (row lengths that are not a multiple of 16 bytes)
+    // what the tiled kernels do not take: conv rows that are not whole 16-byte pieces, operands beyond 32-bit offsets
     return launch_sqgrad_simple(kind, dtype, X, D, B, P, J, C, c, g_out, s_out, stream);
 }
 

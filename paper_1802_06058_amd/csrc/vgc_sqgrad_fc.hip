@@ -51,8 +51,9 @@ __device__ __forceinline__ uint32_t square_bf16x2(uint32_t w) {
     return ra | rb;
 }
 
-// A wave's MT x MT MFMA tiles, of the quarter (wm, wn) of the block.
-template <int MT>
+// A wave's MT x MT MFMA tiles, of the quarter (wm, wn) of the block.  kAnyRow: rows of the output begin anywhere in a cache line, so
+// lines are written by two tiles, and have to meet in the cache (25087 x 4095 at batch 8: 285 us with non-temporal stores, 145 so).
+template <int MT, bool kAnyRow>
 __device__ __forceinline__ void store_tile(float fs, float fg, const f16v (&s_acc)[MT][MT], const f16v (&g_acc)[MT][MT],
                                            bool want_g, float* __restrict__ so, float* __restrict__ go,
                                            uint32_t j0, uint32_t c0, uint32_t J, uint32_t C, uint32_t wm, uint32_t wn,
@@ -67,8 +68,12 @@ __device__ __forceinline__ void store_tile(float fs, float fg, const f16v (&s_ac
                 const uint32_t row = j0 + wm * (MT * 32u) + mt * 32 + 8 * (i >> 2) + 4 * (lane >> 5) + (i & 3);
                 if (row < J && col < C) {
                     const size_t o = (size_t)row * C + col;
-                    __builtin_nontemporal_store(fs * s_acc[mt][nt][i], so + o);
-                    if (want_g) __builtin_nontemporal_store(fg * g_acc[mt][nt][i], go + o);
+                    if (kAnyRow) so[o] = fs * s_acc[mt][nt][i];
+                    else __builtin_nontemporal_store(fs * s_acc[mt][nt][i], so + o);
+                    if (want_g) {
+                        if (kAnyRow) go[o] = fg * g_acc[mt][nt][i];
+                        else __builtin_nontemporal_store(fg * g_acc[mt][nt][i], go + o);
+                    }
                 }
             }
         }
@@ -141,7 +146,7 @@ __global__ __launch_bounds__(256, 2) void k_fc_bf16(const uint16_t* __restrict__
             }
         }
     }
-    store_tile<2>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
+    store_tile<2, false>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -157,9 +162,40 @@ constexpr int kR32 = 16;                 // rows per LDS stage
 // kLong: how the chunks to come are held.  In two register sets without copies, the multiplication never waits for a load,
 // but the unrolled loop of the large tile takes registers that are worth a wave per SIMD; with a copy from set to set each
 // chunk waits for the loads of the one after the next, which costs nothing while the writes of [J, C] are the bound.
-template <bool kWantG, int kE, bool kLong>
-__global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t J,
+//
+// T, kAnyRow: float rows whose length is a multiple of four are read by bounded buffer loads; rows of any other length, and
+// bfloat16 ones that k_fc_bf16 does not take (widened exactly, the squares then float32's), by loads at the elements' own
+// alignment, the last piece of the matrix element by element.  Before, such
+// shapes went without LDS, a wave's loads a step or eight ahead: 25087 x 4095 at batch 64, float32, s alone 271 -> 186 us, with
+// g 417 -> 312; bfloat16 477 -> 235 and 589 -> 329; 1000 x 10 at batch 128 10.4 -> 8.0 and (bfloat16) 20.0 -> 10.0.
+template <typename T> struct Piece;                          // four elements as they are in memory
+template <> struct Piece<float> {
+    f4v x;
+    __device__ __forceinline__ f4v value() const { return x; }
+};
+template <> struct Piece<uint16_t> {
+    uint32_t x[2];
+    __device__ __forceinline__ f4v value() const {
+        return (f4v){__uint_as_float(x[0] << 16), __uint_as_float(x[0] & 0xFFFF0000u), __uint_as_float(x[1] << 16), __uint_as_float(x[1] & 0xFFFF0000u)};
+    }
+};
+template <typename T> struct __attribute__((packed, aligned(sizeof(T)))) AtElement { Piece<T> p; };
+
+// Elements at .. at + 3 of a matrix of `total`; those past its end, and all of them unless `live`, are zeros.
+template <typename T>
+__device__ __forceinline__ Piece<T> load_any(const T* __restrict__ M, uint32_t total, uint32_t at, bool live) {
+    union { T e[4]; Piece<T> p; } u = {{0, 0, 0, 0}};
+    if (live && at + 4u <= total) u.p = reinterpret_cast<const AtElement<T>*>(M + at)->p;
+    else if (live)
+        for (uint32_t i = 0; i < 4; ++i)
+            if (at + i < total) u.e[i] = M[at + i];
+    return u.p;
+}
+
+template <bool kWantG, int kE, bool kLong, typename T, bool kAnyRow>
+__global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const T* __restrict__ X, const T* __restrict__ D, uint32_t B, uint32_t J,
                                                    uint32_t C, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out) {
+    static_assert(kAnyRow || sizeof(T) == 4, "bounded loads are of floats");
     constexpr int kPitch = kE + 32, MT = kE / 64;            // floats per LDS row; 32 x 32 tiles of a wave per direction
     constexpr int kPieces = kR32 * kE / 4 / 256;             // 16-byte pieces per thread, operand and chunk
     __shared__ __attribute__((aligned(16))) float shA[2][kR32 * kPitch], shB[2][kR32 * kPitch];
@@ -177,14 +213,21 @@ __global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const float* __re
 #pragma unroll
         for (int b = 0; b < MT; ++b) { s_acc[a][b] = (f16v){0}; g_acc[a][b] = (f16v){0}; }
 
-    struct Chunk { f4v a[kPieces], b[kPieces]; };
+    struct Chunk { Piece<T> a[kPieces], b[kPieces]; };
     auto load = [&](uint32_t z0) -> Chunk {                  // rows past B read as zeros
         Chunk R;
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             const uint32_t idx = tid + 256u * i, row = idx / (kE / 4), col = (idx % (kE / 4)) * 4u;
-            R.a[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(((z0 + row) * J + j0 + col) * 4u), 0, 0));
-            R.b[i] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(((z0 + row) * C + c0 + col) * 4u), 0, 0));
+            // (columns past the matrix edge are those of the next row: they feed outputs that are not stored)
+            const uint32_t atx = (z0 + row) * J + j0 + col, atd = (z0 + row) * C + c0 + col;
+            if constexpr (kAnyRow) {
+                R.a[i] = load_any<T>(X, B * J, atx, z0 + row < B);
+                R.b[i] = load_any<T>(D, B * C, atd, z0 + row < B);
+            } else {
+                R.a[i].x = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rx, (int)(atx * 4u), 0, 0));
+                R.b[i].x = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rd, (int)(atd * 4u), 0, 0));
+            }
         }
         return R;
     };
@@ -192,8 +235,8 @@ __global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const float* __re
 #pragma unroll
         for (int i = 0; i < kPieces; ++i) {
             const uint32_t idx = tid + 256u * i, off = (idx / (kE / 4)) * kPitch + (idx % (kE / 4)) * 4u;
-            *reinterpret_cast<f4v*>(shA[buf] + off) = R.a[i];
-            *reinterpret_cast<f4v*>(shB[buf] + off) = R.b[i];
+            *reinterpret_cast<f4v*>(shA[buf] + off) = R.a[i].value();
+            *reinterpret_cast<f4v*>(shB[buf] + off) = R.b[i].value();
         }
     };
     const uint32_t col = lane & 31u, kh = lane >> 5;
@@ -244,38 +287,57 @@ __global__ __launch_bounds__(256, kLong ? 2 : 3) void k_fc_f32(const float* __re
             __syncthreads();
         }
     }
-    store_tile<MT>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
+    store_tile<MT, kAnyRow>(cs, cg, s_acc, g_acc, kWantG, s_out, g_out, j0, c0, J, C, wm, wn, lane);
 }
 
 // ------------------------------------------------------------------------------------------------
 // host side
 // ------------------------------------------------------------------------------------------------
+// Rows of whole 16-byte pieces, which bounded loads can take.
+static bool fc_whole_pieces(int dtype, uint32_t J, uint32_t C) {
+    const uint32_t per = dtype == VGC_BF16 ? 8 : 4;
+    return J % per == 0 && C % per == 0;
+}
 bool fc_tiled_supported(int dtype, uint32_t B, uint32_t J, uint32_t C) {
     const uint64_t limit = 0x7FFFFFFFull;                            // buffer ranges and offsets are 32-bit
-    if (dtype == VGC_BF16) return J % 8 == 0 && C % 8 == 0 && (uint64_t)(B + 32) * J * 2 < limit && (uint64_t)(B + 32) * C * 2 < limit;
-    return J % 4 == 0 && C % 4 == 0 && (uint64_t)(B + 16) * J * 4 < limit && (uint64_t)(B + 16) * C * 4 < limit;
+    const uint32_t size = dtype == VGC_BF16 ? 2 : 4, ahead = dtype == VGC_BF16 ? 32 : 16;
+    if (fc_whole_pieces(dtype, J, C)) return (uint64_t)(B + ahead) * J * size < limit && (uint64_t)(B + ahead) * C * size < limit;
+    return (uint64_t)(B + 64) * (J + 128ull) < limit && (uint64_t)(B + 64) * (C + 128ull) < limit;
+}
+
+template <typename T, bool kAnyRow>
+static void launch_fc_f32(const void* X, const void* D, uint32_t B, uint32_t J, uint32_t C, float c, float* g_out, float* s_out,
+                          bool small, dim3 grid, hipStream_t stream) {
+    const float cg = c, cs = c * c;
+    const dim3 block(256);
+#define VGC_FC_F32(G_, E_, L_) hipLaunchKernelGGL((k_fc_f32<G_, E_, L_, T, kAnyRow>), grid, block, 0, stream, (const T*)X, (const T*)D, B, J, C, cg, cs, g_out, s_out)
+    if (small) { if (g_out) VGC_FC_F32(true, 64, true); else VGC_FC_F32(false, 64, true); }
+    // the large tile's two forms cross between batches of 200 and 256: 4096 x 4096 with g, copied against in two sets: 117 against
+    // 121 us at 200, 140 against 138 at 256, 1025 against 988 at 2048
+    else if (g_out) {
+        if constexpr (!kAnyRow) { if (B >= 256) VGC_FC_F32(true, 128, true); else VGC_FC_F32(true, 128, false); }
+    } else if (B >= 256) VGC_FC_F32(false, 128, true);
+    else VGC_FC_F32(false, 128, false);
+#undef VGC_FC_F32
 }
 
 int launch_fc_tiled(int dtype, const void* X, const void* D, uint32_t B, uint32_t J, uint32_t C, float c,
                     float* g_out, float* s_out, hipStream_t stream) {
+    const bool whole = fc_whole_pieces(dtype, J, C), bf16 = dtype == VGC_BF16 && whole;
     uint64_t nblk = (uint64_t)((J + kT - 1) / kT) * ((C + kT - 1) / kT);
-    const bool small = dtype == VGC_F32 && nblk < 2 * 256;           // fewer than two 128 x 128 tiles per compute unit
+    // Small tiles where there are fewer than two of 128 x 128 per compute unit, and for rows of any length with g: the large tile
+    // spills there or is down to two waves per SIMD (25087 x 4095, float32 at batch 64: 425 us, 312 with the small one).
+    const bool small = !bf16 && (nblk < 2 * 256 || (!whole && g_out));
     if (small) nblk = (uint64_t)((J + 63) / 64) * ((C + 63) / 64);
     if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
-    const float cg = c, cs = c * c;
     const dim3 grid((uint32_t)nblk), block(256);
-    if (dtype == VGC_BF16) {
+    if (bf16) {
+        const float cg = c, cs = c * c;
         if (g_out) hipLaunchKernelGGL(k_fc_bf16<true>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
         else hipLaunchKernelGGL(k_fc_bf16<false>, grid, block, 0, stream, (const uint16_t*)X, (const uint16_t*)D, B, J, C, cg, cs, g_out, s_out);
-    } else {
-#define VGC_FC_F32(G_, E_, L_) hipLaunchKernelGGL((k_fc_f32<G_, E_, L_>), grid, block, 0, stream, (const float*)X, (const float*)D, B, J, C, cg, cs, g_out, s_out)
-        if (small) { if (g_out) VGC_FC_F32(true, 64, true); else VGC_FC_F32(false, 64, true); }
-        // the large tile's two forms cross between batches of 200 and 256: 4096 x 4096 with g, copied against in two sets: 117 against
-        // 121 us at 200, 140 against 138 at 256, 1025 against 988 at 2048
-        else if (B >= 256) { if (g_out) VGC_FC_F32(true, 128, true); else VGC_FC_F32(false, 128, true); }
-        else { if (g_out) VGC_FC_F32(true, 128, false); else VGC_FC_F32(false, 128, false); }
-#undef VGC_FC_F32
-    }
+    } else if (dtype == VGC_BF16) launch_fc_f32<uint16_t, true>(X, D, B, J, C, c, g_out, s_out, small, grid, stream);
+    else if (whole) launch_fc_f32<float, false>(X, D, B, J, C, c, g_out, s_out, small, grid, stream);
+    else launch_fc_f32<float, true>(X, D, B, J, C, c, g_out, s_out, small, grid, stream);
     return hip_check(hipGetLastError(), "launch fc tiled");
 }
 
