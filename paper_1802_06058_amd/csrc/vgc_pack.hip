@@ -334,7 +334,7 @@ __device__ __forceinline__ void emit_tile(const uint16_t* __restrict__ st, uint3
             const uint32_t word = (((e[j] >> 11) & 1u) << 31) | (d << 28) | (start + (e[j] & 0x7FFu));
             const uint64_t b = __ballot(keep);
             const uint64_t pos = out + rank_below64(b);
-            if (keep && pos < words_cap) __builtin_nontemporal_store(word, words + pos);
+            if (keep && pos < words_cap) words[pos] = word;
             out += (uint32_t)__popcll(b);
         }
     }
