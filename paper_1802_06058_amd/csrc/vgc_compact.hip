@@ -277,13 +277,16 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
         const uint32_t start = t * kTile;
         const uint32_t m = min(kTile, pg.size - start);
         float* base = dense + pg.offset + start;
-        const bool vec = (m == kTile) && ((reinterpret_cast<uintptr_t>(base) & 15u) == 0);
+        const bool vec = m == kTile, whole = (reinterpret_cast<uintptr_t>(base) & 15u) == 0;
         if (overwrite) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) reinterpret_cast<f4c*>(T)[q * 64 + lane] = (f4c){0.f, 0.f, 0.f, 0.f};
+        } else if (vec && whole) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) reinterpret_cast<f4c*>(T)[q * 64 + lane] = load_four<true>(base + 4 * (q * 64 + lane));
         } else if (vec) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q) reinterpret_cast<f4c*>(T)[q * 64 + lane] = __builtin_nontemporal_load(reinterpret_cast<const f4c*>(base) + q * 64 + lane);
+            for (int q = 0; q < 8; ++q) reinterpret_cast<f4c*>(T)[q * 64 + lane] = load_four<false>(base + 4 * (q * 64 + lane));
         } else {
             for (uint32_t i = lane; i < kTile; i += 64) T[i] = (i < m) ? base[i] : 0.f;
         }
@@ -381,10 +384,12 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
             __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
             __builtin_amdgcn_wave_barrier();
         }
-        if (vec) {
+        if (vec && whole) {
 #pragma unroll
-            for (int q = 0; q < 8; ++q)
-                __builtin_nontemporal_store(reinterpret_cast<f4c*>(T)[q * 64 + lane], reinterpret_cast<f4c*>(base) + q * 64 + lane);
+            for (int q = 0; q < 8; ++q) store_four<true>(reinterpret_cast<f4c*>(T)[q * 64 + lane], base + 4 * (q * 64 + lane));
+        } else if (vec) {
+#pragma unroll
+            for (int q = 0; q < 8; ++q) store_four<false>(reinterpret_cast<f4c*>(T)[q * 64 + lane], base + 4 * (q * 64 + lane));
         } else {
             for (uint32_t i = lane; i < m; i += 64) base[i] = T[i];
         }

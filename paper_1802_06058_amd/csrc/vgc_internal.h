@@ -53,6 +53,20 @@ struct PlanGroup {             // 16 bytes
     uint32_t first_tile;       // would overflow only beyond 2^43 parameters
 };
 
+// Four consecutive floats.  kWhole: at a multiple of 16 bytes, and past the cache, as whole lines that are touched once.  Else at
+// any element: a group that begins anywhere (4-byte accesses before: 50 M elements in ragged groups, 8 messages
+// of 2 % added 197 -> 127 us, with Adam 351 -> 273) shares its lines between accesses, which have to meet in the cache.
+typedef float any4 __attribute__((ext_vector_type(4), aligned(4)));
+typedef float four __attribute__((ext_vector_type(4)));
+template <bool kWhole> __device__ __forceinline__ four load_four(const float* p) {
+    if (kWhole) return __builtin_nontemporal_load(reinterpret_cast<const four*>(p));
+    return *reinterpret_cast<const any4*>(p);
+}
+template <bool kWhole> __device__ __forceinline__ void store_four(four x, float* p) {
+    if (kWhole) __builtin_nontemporal_store(x, reinterpret_cast<four*>(p));
+    else *reinterpret_cast<any4*>(p) = x;
+}
+
 struct PlanTile {              // 16 bytes
     uint32_t group;
     uint32_t start;            // element offset of the tile inside its group (multiple of kTile)

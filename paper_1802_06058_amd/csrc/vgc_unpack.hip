@@ -2,6 +2,8 @@
 // message into the dense gradient buffer.  Indices inside a message are distinct, so plain
 // read-modify-write is race free and the float32 result does not depend on scheduling; messages
 // are ordered by the stream.
+#include <type_traits>
+
 #include "vgc_internal.h"
 
 namespace vgc {
@@ -117,6 +119,13 @@ __device__ __forceinline__ void update_element(const UpdateArgs& O, float ghat, 
 
 typedef float f4u __attribute__((ext_vector_type(4)));
 
+// Whether the group's elements begin at a multiple of 16 bytes in every array that is read or written.
+template <int kMode>
+__device__ __forceinline__ bool whole_group(const float* dense, const UpdateArgs& O, const PlanGroup& pg) {
+    auto at = [&](const float* p) { return (reinterpret_cast<uintptr_t>(p + pg.offset) & 15u) == 0; };
+    return kMode == kToDense ? at(dense) : at(O.w) && at(O.s1) && (kMode != kAdam || at(O.s2));
+}
+
 // The first words of one message's tile, on their way: `n` of them, 64 to a round.
 template <int kFirst>
 struct Request {
@@ -212,7 +221,8 @@ __device__ __forceinline__ void add_message(const Request<kFirst>& Q, Cursor& C,
 
 // The tiles [t0, t1) of one wave.  While a message is added, the next one's words (after the last message: the next
 // tile's first) are on their way; an odd number of messages is made even with one that has no words.
-template <int kFirst, int kMode>
+// kWhole: the group's first element lies at a multiple of 16 bytes in every array, and so do its whole tiles.
+template <int kFirst, int kMode, bool kWhole>
 __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGroup& pg, uint32_t t0, uint32_t t1, float scale,
                                              float* __restrict__ dense, int overwrite, const UpdateArgs& O, float* T, uint32_t lane) {
     const uint32_t pe = p < 2 ? 2u : (p + 1u) & ~1u;
@@ -224,10 +234,7 @@ __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGro
         const uint32_t m = min(kTile, pg.size - start);
         const uint64_t e0 = pg.offset + start;
         float* base = (kMode == kToDense) ? dense + e0 : O.w + e0;
-        bool vec = (m == kTile) && ((reinterpret_cast<uintptr_t>(base) & 15u) == 0);
-        if (kMode != kToDense)
-            vec = vec && ((reinterpret_cast<uintptr_t>(O.s1 + e0) & 15u) == 0) &&
-                  (kMode != kAdam || (reinterpret_cast<uintptr_t>(O.s2 + e0) & 15u) == 0);
+        const bool vec = m == kTile;
         // ---- tile -> LDS ----
         if (overwrite || kMode != kToDense) {
 #pragma unroll
@@ -235,7 +242,7 @@ __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGro
         } else if (vec) {
             f4u x[8];
 #pragma unroll
-            for (int q = 0; q < 8; ++q) x[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(base) + q * 64 + lane);
+            for (int q = 0; q < 8; ++q) x[q] = load_four<kWhole>(base + 4 * (q * 64 + lane));
 #pragma unroll
             for (int q = 0; q < 8; ++q) reinterpret_cast<f4u*>(T)[q * 64 + lane] = x[q];
         } else {
@@ -249,9 +256,9 @@ __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGro
         if (kMode != kToDense && vec) {
 #pragma unroll
             for (int q = 0; q < 8; ++q) {
-                W4[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.w + e0) + q * 64 + lane);
-                S1[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s1 + e0) + q * 64 + lane);
-                if (kMode == kAdam) S2[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s2 + e0) + q * 64 + lane);
+                W4[q] = load_four<kWhole>(O.w + e0 + 4 * (q * 64 + lane));
+                S1[q] = load_four<kWhole>(O.s1 + e0 + 4 * (q * 64 + lane));
+                if (kMode == kAdam) S2[q] = load_four<kWhole>(O.s2 + e0 + 4 * (q * 64 + lane));
             }
         }
 
@@ -270,8 +277,7 @@ __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGro
         if (kMode == kToDense) {
             if (vec) {
 #pragma unroll
-                for (int q = 0; q < 8; ++q)
-                    __builtin_nontemporal_store(reinterpret_cast<f4u*>(T)[q * 64 + lane], reinterpret_cast<f4u*>(base) + q * 64 + lane);
+                for (int q = 0; q < 8; ++q) store_four<kWhole>(reinterpret_cast<f4u*>(T)[q * 64 + lane], base + 4 * (q * 64 + lane));
             } else {
                 for (uint32_t i = lane; i < m; i += 64) base[i] = T[i];
             }
@@ -286,9 +292,9 @@ __device__ __forceinline__ void decode_tiles(Cursor C, uint32_t p, const PlanGro
                     update_element<kMode>(O, G[c], w, a, b);
                     w4[c] = w; a4[c] = a; b4[c] = b;
                 }
-                __builtin_nontemporal_store(w4, reinterpret_cast<f4u*>(O.w + e0) + q * 64 + lane);
-                __builtin_nontemporal_store(a4, reinterpret_cast<f4u*>(O.s1 + e0) + q * 64 + lane);
-                if (kMode == kAdam) __builtin_nontemporal_store(b4, reinterpret_cast<f4u*>(O.s2 + e0) + q * 64 + lane);
+                store_four<kWhole>(w4, O.w + e0 + 4 * (q * 64 + lane));
+                store_four<kWhole>(a4, O.s1 + e0 + 4 * (q * 64 + lane));
+                if (kMode == kAdam) store_four<kWhole>(b4, O.s2 + e0 + 4 * (q * 64 + lane));
             }
         } else {
             for (uint32_t i = lane; i < m; i += 64) {
@@ -374,10 +380,15 @@ __global__ __launch_bounds__(256) void k_unpack_add_batch(PlanCheck pc, BatchArg
     // The rounds of a first request follow from the densest message: one that is not needed still costs an issue slot, one
     // that is missing is waited for.  The 12 are for densities from a fifth on (138 M elements, 3 messages of 30 % added:
     // 300 us, 326 with 8); next to the optimizer's arrays they cost a wave per SIMD.
-    if (__ballot(C.rounds > 2) == 0) decode_tiles<2, kMode>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
-    else if (kMode == kToDense && __ballot(C.rounds > 8) != 0)
-        decode_tiles<kMode == kToDense ? 12 : 8, kMode>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
-    else decode_tiles<8, kMode>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
+    auto decode = [&](auto W) {
+        constexpr bool kWhole = decltype(W)::value;
+        if (__ballot(C.rounds > 2) == 0) decode_tiles<2, kMode, kWhole>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
+        else if (kMode == kToDense && __ballot(C.rounds > 8) != 0)
+            decode_tiles<kMode == kToDense ? 12 : 8, kMode, kWhole>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
+        else decode_tiles<8, kMode, kWhole>(C, A.p, pg, t0, t1, scale, dense, overwrite, O, T, lane);
+    };
+    if (whole_group<kMode>(dense, O, pg)) decode(std::true_type{});
+    else decode(std::false_type{});
 }
 
 // ------------------------------------------------------------------------------------------------
@@ -388,17 +399,14 @@ __global__ __launch_bounds__(256) void k_unpack_add_batch(PlanCheck pc, BatchArg
 // 1.8 M elements, 8 messages of 17 %, momentum SGD: 26.6 -> 18.2 us from a cold cache, Adam 37.8 -> 26.4; 16 messages of 30 %
 // 54.6 -> 33.2; 20,000 elements 28.8 -> 14.3.
 // ------------------------------------------------------------------------------------------------
-template <int kRounds, int kMode>
+template <int kRounds, int kMode, bool kWhole>
 __device__ __forceinline__ void decode_tile(uint32_t p, const uint64_t* cur_at, const uint32_t* cur_left, const uint32_t* cur_exp, uint32_t* more,
                                             const PlanGroup& pg, uint32_t start, float scale, float* __restrict__ dense, int overwrite,
                                             const UpdateArgs& O, float* T, uint32_t tid) {
     const uint32_t m = min(kTile, pg.size - start);
     const uint64_t e0 = pg.offset + start;
     float* base = (kMode == kToDense) ? dense + e0 : O.w + e0;
-    bool vec = (m == kTile) && ((reinterpret_cast<uintptr_t>(base) & 15u) == 0);
-    if (kMode != kToDense)
-        vec = vec && ((reinterpret_cast<uintptr_t>(O.s1 + e0) & 15u) == 0) &&
-              (kMode != kAdam || (reinterpret_cast<uintptr_t>(O.s2 + e0) & 15u) == 0);
+    const bool vec = m == kTile;
     const bool fresh = overwrite || kMode != kToDense;
     // a thread's elements: two groups of four (vec), else eight, 256 apart
     f4u W4[2], S1[2], S2[2];
@@ -441,9 +449,9 @@ __device__ __forceinline__ void decode_tile(uint32_t p, const uint64_t* cur_at, 
             if (vec) {
 #pragma unroll
                 for (int q = 0; q < 2; ++q) {
-                    if (kMode != kToDense || !fresh) W4[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(base) + q * 256 + tid);
-                    if (kMode != kToDense) S1[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s1 + e0) + q * 256 + tid);
-                    if (kMode == kAdam) S2[q] = __builtin_nontemporal_load(reinterpret_cast<const f4u*>(O.s2 + e0) + q * 256 + tid);
+                    if (kMode != kToDense || !fresh) W4[q] = load_four<kWhole>(base + 4 * (q * 256 + tid));
+                    if (kMode != kToDense) S1[q] = load_four<kWhole>(O.s1 + e0 + 4 * (q * 256 + tid));
+                    if (kMode == kAdam) S2[q] = load_four<kWhole>(O.s2 + e0 + 4 * (q * 256 + tid));
                 }
             }
             if (!fresh) {
@@ -481,7 +489,7 @@ __device__ __forceinline__ void decode_tile(uint32_t p, const uint64_t* cur_at, 
         for (int q = 0; q < 2; ++q) {
             const f4u G = reinterpret_cast<f4u*>(T)[q * 256 + tid];
             if (kMode == kToDense) {
-                __builtin_nontemporal_store(G, reinterpret_cast<f4u*>(base) + q * 256 + tid);
+                store_four<kWhole>(G, base + 4 * (q * 256 + tid));
                 continue;
             }
             f4u w4 = W4[q], a4 = S1[q], b4 = S2[q];
@@ -491,9 +499,9 @@ __device__ __forceinline__ void decode_tile(uint32_t p, const uint64_t* cur_at, 
                 update_element<kMode>(O, G[c], w, a, b);
                 w4[c] = w; a4[c] = a; b4[c] = b;
             }
-            __builtin_nontemporal_store(w4, reinterpret_cast<f4u*>(O.w + e0) + q * 256 + tid);
-            __builtin_nontemporal_store(a4, reinterpret_cast<f4u*>(O.s1 + e0) + q * 256 + tid);
-            if (kMode == kAdam) __builtin_nontemporal_store(b4, reinterpret_cast<f4u*>(O.s2 + e0) + q * 256 + tid);
+            store_four<kWhole>(w4, O.w + e0 + 4 * (q * 256 + tid));
+            store_four<kWhole>(a4, O.s1 + e0 + 4 * (q * 256 + tid));
+            if (kMode == kAdam) store_four<kWhole>(b4, O.s2 + e0 + 4 * (q * 256 + tid));
         }
         return;
     }
@@ -575,9 +583,14 @@ __global__ __launch_bounds__(256) void k_unpack_tile(PlanCheck pc, BatchArgs<kMa
     }
     __syncthreads();
     const uint32_t most = __builtin_amdgcn_readfirstlane(max(max(rounds_of[0], rounds_of[1]), max(rounds_of[2], rounds_of[3])));
-    if (most == 1) decode_tile<1, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
-    else if (most == 2) decode_tile<2, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
-    else decode_tile<4, kMode>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+    auto decode = [&](auto W) {
+        constexpr bool kWhole = decltype(W)::value;
+        if (most == 1) decode_tile<1, kMode, kWhole>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+        else if (most == 2) decode_tile<2, kMode, kWhole>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+        else decode_tile<4, kMode, kWhole>(A.p, cur_at, cur_left, cur_exp, more, pg, first, scale, dense, overwrite, O, T, tid);
+    };
+    if (whole_group<kMode>(dense, O, pg)) decode(std::true_type{});
+    else decode(std::false_type{});
 }
 
 // Waves to aim for: 5120 are resident, and the last ones to be placed leave the others idle.  64 K of them against 16 K:
