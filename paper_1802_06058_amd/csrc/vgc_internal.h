@@ -44,7 +44,9 @@ struct PlanCheck {
     uint64_t hash;             // of the host group list of this call
 };
 __device__ __forceinline__ bool plan_ok(const PlanCheck& pc) {
-    return pc.header->magic == kPlanMagic && pc.header->groups_hash == pc.hash;
+    uint64_t magic = pc.header->magic, hash = pc.header->groups_hash;
+    asm("" : "+s"(magic), "+s"(hash));                       // requested together: every kernel begins by waiting for them
+    return magic == kPlanMagic && hash == pc.hash;
 }
 
 struct PlanGroup {             // 16 bytes
