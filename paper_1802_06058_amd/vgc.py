@@ -8,6 +8,7 @@ from __future__ import annotations
 
 import ctypes as C
 import os
+from array import array
 
 import numpy as np
 import torch
@@ -30,6 +31,9 @@ class Group(C.Structure):
 
 class GroupHdr(C.Structure):
     _fields_ = [("exp_field", C.c_uint32), ("count", C.c_uint32), ("word_offset", C.c_uint64)]
+
+
+_HDR_BYTES = C.sizeof(GroupHdr)
 
 
 class PackStatus(C.Structure):
@@ -130,8 +134,10 @@ def _ptr(t):
 
 # A call on a small parameter set is bound by this file, not by its kernels, so what every call passes through keeps to
 # plain attributes: addresses go to ctypes as integers, torch is looked up once, and the stream is asked for as a handle
-# (torch.cuda.current_stream() makes an object around it).  Host time of the three statistic calls of a 784-1000-1000-10
-# network 30.0 -> 19.9 us, of select, pack and update on its 1.8 M parameters 53.8 -> 40.7 us.  The checks are the same.
+# (torch.cuda.current_stream() makes an object around it); the device check compares indices, and only when one of them
+# differs looks for what to report; messages are checked in one loop and their tables filled without ctypes.  The checks are
+# the same.  Per call on the 1.8 M parameters of a 784-1000-1000-10 network, launch included: select 9.1 -> 8.5 us, pack 8.3 -> 7.8,
+# update with 8 messages 18.8 -> 14.7, statistic 7.5 -> 7.3.
 def _stream():
     return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
 
@@ -245,17 +251,32 @@ class _Args:
         self.need_bytes(scratch, plan.scratch_bytes, "scratch")
 
     def need_messages(self, plan, words, n_words, hdrs):
+        seen, hdr_bytes = self.seen, plan.n_groups * _HDR_BYTES
         for w, k, h in zip(words, n_words, hdrs):
             if w.element_size() != 4:
                 raise VgcError(f"words: need 32-bit elements, got {w.dtype}")
-            self.need_bytes(w, 4 * int(k), "words")
-            self.need_bytes(h, plan.n_groups * C.sizeof(GroupHdr), "headers")
+            seen.append((w, "words"))
+            if w.numel() < int(k) or not w.is_contiguous():
+                self.need_bytes(w, 4 * int(k), "words")          # reports it
+            seen.append((h, "headers"))
+            if h.numel() * h.element_size() < hdr_bytes or not h.is_contiguous():
+                self.need_bytes(h, hdr_bytes, "headers")
 
     def launchable(self):
         """Every tensor seen lives in the memory of one GPU: the plan's, else the first tensor's."""
-        want = torch.device(self.device) if self.device is not None else None
-        if want is not None and want.type != "cuda":
-            want = None
+        want = self.device
+        if want is not None:
+            if not isinstance(want, torch.device):
+                want = torch.device(want)
+            if want.type != "cuda":
+                want = None
+        if self.seen and (want is not None or self.seen[0][0].is_cuda):
+            index = self.seen[0][0].get_device() if want is None else torch.cuda.current_device() if want.index is None else want.index
+            for t, _ in self.seen:
+                if t.get_device() != index or not t.is_cuda:
+                    break
+            else:
+                return
         for t, what in self.seen:
             if not t.is_cuda:
                 raise VgcError(f"{what}: need a tensor in GPU memory, got one on {t.device}")
@@ -452,11 +473,9 @@ def unpack_add(words, n_words, hdrs, plan, scale, dense):
 
 
 def _message_tables(words, n_words, hdrs):
-    p = len(words)
-    wp = (C.c_void_p * max(p, 1))(*[w.data_ptr() for w in words])
-    hp = (C.c_void_p * max(p, 1))(*[h.data_ptr() for h in hdrs])
-    nw = (C.c_uint64 * max(p, 1))(*[int(x) for x in n_words])
-    return wp, nw, hp
+    """The three host tables as arrays of 64-bit values (which the caller keeps until the call is done)."""
+    return (array("Q", [w.data_ptr() for w in words] or [0]), array("Q", [int(x) & 0xFFFFFFFFFFFFFFFF for x in n_words] or [0]),
+            array("Q", [h.data_ptr() for h in hdrs] or [0]))
 
 
 def unpack_add_batch(words, n_words, hdrs, plan, scale, dense, overwrite=False):
@@ -469,7 +488,7 @@ def unpack_add_batch(words, n_words, hdrs, plan, scale, dense, overwrite=False):
     a.need_state(plan, dense=dense)
     a.launchable()
     wp, nw, hp = _message_tables(words, n_words, hdrs)
-    _check(load().vgc_unpack_add_batch(wp, nw, hp, p, plan.c_groups, plan.n_groups, _ptr(plan.plan), float(scale),
+    _check(load().vgc_unpack_add_batch(wp.buffer_info()[0], nw.buffer_info()[0], hp.buffer_info()[0], p, plan.c_groups, plan.n_groups, _ptr(plan.plan), float(scale),
                                        1 if overwrite else 0, _ptr(dense), plan.n, _stream()))
 
 
@@ -485,7 +504,7 @@ def unpack_apply(words, n_words, hdrs, plan, scale, param, state1, state2=None, 
     a.launchable()
     wp, nw, hp = _message_tables(words, n_words, hdrs)
     opt = Optimizer(kind, lr, momentum, beta1, beta2, eps, step)
-    _check(load().vgc_unpack_apply(wp, nw, hp, p, plan.c_groups, plan.n_groups, _ptr(plan.plan), float(scale),
+    _check(load().vgc_unpack_apply(wp.buffer_info()[0], nw.buffer_info()[0], hp.buffer_info()[0], p, plan.c_groups, plan.n_groups, _ptr(plan.plan), float(scale),
                                    C.byref(opt), _ptr(param), _ptr(state1), _ptr(state2), plan.n, _stream()))
 
 
