@@ -186,9 +186,10 @@ int vgc_sqgrad_conv2d(int dtype, const void* act, const void* D, uint32_t B, uin
 
 /* The statistic of several convolution layers in one call.  The layers of a model are independent of each other
  * (Alg. 1 runs per parameter; a layer is one weight tensor, Section 4.2) and most of them are too small to fill the
- * chip alone, so the layers' kernels are spread over four streams of the library's own, between a fork after what the
- * caller's stream holds so far and a join back into it: kernels of different layers fill each other's tails.  (A single
- * layer runs on the caller's stream.)  Every result is that of vgc_sqgrad_conv2d on the same layer, bit for bit.
+ * chip alone, so the kernels of the small layers (below 2e10 multiply-adds) are spread over four streams of the
+ * library's own, between a fork after what the caller's stream holds so far and a join back into it, while the large
+ * ones run on the caller's stream: kernels of different layers fill each other's tails.  Every result is that of
+ * vgc_sqgrad_conv2d on the same layer, bit for bit.
  *
  * layers: HOST array; the fields are the arguments of vgc_sqgrad_conv2d.  The layers run side by side, so each needs
  * outputs and a workspace of its own.  Every layer is checked before anything is launched; on an argument error

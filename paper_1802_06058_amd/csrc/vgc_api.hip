@@ -342,18 +342,24 @@ int vgc_sqgrad_conv2d_batch(const vgc_conv2d_layer* layers, uint32_t n_layers, v
         if ((rc = hip_check(hipEventCreateWithFlags(&S.fork, hipEventDisableTiming), "hipEventCreate")) != VGC_OK) return rc;
         S.ready = true;
     }
-    // Which stream takes which layer: each goes to the least loaded side stream.  Even of layers that fill the chip by themselves
-    // the last workgroups leave units idle, which the next layer's first ones take.  VGG-16 at batch 64 in bf16, most of whose
-    // layers have 2e10 multiply-adds or more: 2124 us with those on the caller's stream, 2063 so; the 53 small layers of
-    // ResNet-50 at batch 32: 2.92 ms on one stream, 2.30 so.
+    // Which stream takes which layer.  A layer of 2e10 multiply-adds or more fills the chip by itself; it stays on the
+    // caller's stream.  Of the others each goes to the least loaded side stream.  What the rule costs and gives: the 53
+    // small layers of ResNet-50 take 2.92 ms on one stream and 2.30 so (2.24 when the caller spreads all layers over four
+    // streams); VGG-16, most of whose layers are above the line, 2.25 and 2.23 (2.18).
     std::vector<int> lane_of(n_layers, 0);
     double load[kSideStreams + 1] = {0.0};               // multiply-adds queued on each stream so far
     bool lane_used[kSideStreams + 1] = {false};
+    uint32_t n_small = 0;
+    for (uint32_t k = 0; k < n_layers; ++k) {
+        const vgc_conv2d_layer& L = layers[k];
+        const double macs = (double)L.B * Ho[k] * Wo[k] * L.kh * L.kw * L.Cin * L.C;
+        if (macs < 2e10) ++n_small;
+    }
     for (uint32_t k = 0; k < n_layers; ++k) {
         const vgc_conv2d_layer& L = layers[k];
         const double macs = (double)L.B * Ho[k] * Wo[k] * L.kh * L.kw * L.Cin * L.C;
         int lane = 0;
-        if (n_layers > 1) {
+        if (n_small > 1 && macs < 2e10) {
             lane = 1;
             for (int i = 2; i <= kSideStreams; ++i)
                 if (load[i] < load[lane]) lane = i;
