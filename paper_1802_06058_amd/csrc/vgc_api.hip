@@ -623,12 +623,15 @@ int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr*
     }
     if (!std::isfinite(scale)) { set_error("vgc_unpack_add: scale is not finite"); return VGC_ERR_PARAM; }
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
-    // A message that touches most cache lines of the buffer anyway (an eighth of the elements or more, going by
-    // n_words) is decoded tile by tile like a batch of one: the same additions, the buffer streamed once instead of
-    // read and written line by line under 64 scattered lanes.  By words / by tiles, us: 25.6 M parameters 26 / 37 at 4.6 %,
-    // 33 / 38 at 8 %, 38 / 38.5 at 11 %; 138 M parameters 73 / 182 at 2 %, 184 / 186 at 4.6 %, 235 / 194 at 11 % (where
-    // the buffer is larger than the last-level cache the lines cross earlier).
-    if (n_words && n_words >= n / 8) {
+    // A message that touches most cache lines of the buffer anyway (going by n_words) is decoded tile by tile like a
+    // batch of one: the same additions, the buffer streamed once instead of read and written line by line under 64
+    // scattered lanes.  The line is an eighth of the elements, and a sixteenth from twice the last-level cache on (512 MB),
+    // where the scattered lines come from memory also when the buffer has just been written.  By words / by tiles, us, on a
+    // buffer just written (on a cold one): 25 M parameters 37 / 43 (45 / 47) at 6.5 %, 43 / 43 (47 / 47) at 10 %; 75 M 89 / 107
+    // (112 / 114) and 108 / 108 (119 / 115); 138 M 173 / 191 (158 / 198) at 4 %, 223 / 191 (201 / 206) at 6.5 %, 231 / 192
+    // (210 / 209) at 8 %; 400 M 507 / 531 (485 / 552) at 4 %, 630 / 541 (604 / 575) at 6.5 %, 685 / 542 (675 / 598) at 10 %.
+    const uint64_t dense_words = n >= (1ull << 27) ? n / 16 : n / 8;
+    if (n_words && n_words >= dense_words) {
         const uint32_t* const wl[1] = {words};
         const uint64_t nl[1] = {n_words};
         const vgc_group_hdr* const hl[1] = {hdrs};
