@@ -167,13 +167,13 @@ __device__ __forceinline__ uint32_t byte_mask(uint32_t x) {
 // of 64 tiles, 8 messages of 0.17 x 138 M elements took 2.57 ms, all of it latency (0.79 GB have to move: 0.13 ms).
 // The directory says where every tile's bytes lie, so here a wave can start at any tile of a run, requests the first
 // kRoundBytes of a message's tile while the message before it is decoded, and a lane decodes kLaneBytes consecutive
-// bytes: 0.28 ms (2.8 TB/s), bound by the vector instructions per byte.
+// bytes: 0.28 ms, and 0.19 ms (4.1 TB/s) since no byte takes a branch; bound by the vector instructions per byte.
 //
 // Whether a lane's bytes begin inside an element follows from two ballots: a byte is the second of an element iff an
 // odd number of bytes with bit 7 set precede it without a gap, so a lane whose bytes all have bit 7 set (an even number
 // of them) passes the state of the lane before it on, and any other lane's outgoing state is the parity of its trailing
 // bytes with bit 7 set.  An element is added at its last byte, up to which its position is the sum of all steps (gap + 1
-// at a first byte, 8 times the value at a second byte); positions are kept in bytes of LDS, two per register.
+// at a first byte, 8 times the value at a second byte); positions are kept in bytes of LDS.
 // kShort: some stream is shorter than a lane's access (1 to 7 bytes); its bytes are fetched one by one.
 template <bool kShort>
 __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, CompactArgs A, const PlanGroup* __restrict__ groups,
@@ -190,7 +190,6 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
     const uint32_t Tb = (uint32_t)(uintptr_t)(lds_float)T;
     uint32_t in_tile = 4u * (kTile - 1);                        // a mask in a register: and-or is one instruction then
     asm volatile("" : "+v"(in_tile));
-    const uint32_t neutral = __float_as_uint(scale) >> 31 ? 0u : 0x80808080u;       // scale times this zero is -0
     const uint32_t k = runs[run].group, first = runs[run].first_tile;
     const PlanGroup pg = groups[k];
     const uint32_t nt_group = (pg.size + kTile - 1) / kTile;
@@ -321,49 +320,62 @@ __global__ __launch_bounds__(256, 5) void k_unpack_compact(PlanCheck pc, Compact
                 // carry of an addition runs through each run and comes out with its parity)
                 const uint32_t opens = high & ~in;
                 const uint32_t second = (((opens << 1) | 0xAAAAAAAAu) - opens) ^ 0xAAAAAAAAu ^ (high | in);
-                uint32_t ends = valid & (second | ~high);
+                const uint32_t ends = valid & (second | ~high);
+                // the bytes that add their element: its last one, and the first of two in the same lane as well (see below)
+                const uint32_t adds = ends | (second >> 1 & valid >> 1);
                 const uint32_t m0 = byte_mask(second), m1 = byte_mask(second >> 4);
                 // the 4-bit value of the element a byte ends: its own, or that of the byte before a second byte
                 const uint32_t prev_lane = (uint32_t)__builtin_amdgcn_update_dpp((int)(last << 24), (int)x.y, 0x138, 0xF, 0xF, false);  // wave_shr:1
                 const uint32_t c0 = (m0 & __builtin_amdgcn_alignbyte(x.x, prev_lane, 3)) | (~m0 & x.x);
                 const uint32_t c1 = (m1 & __builtin_amdgcn_alignbyte(x.y, x.x, 3)) | (~m1 & x.y);
-                if (ef < 8u) {                                  // exponents too small for some of the codes
-#pragma unroll
-                    for (int i = 0; i < (int)kLaneBytes; ++i)
-                        if ((((i < 4 ? c0 : c1) >> (8 * (i & 3))) & 7u) >= ef) ends &= ~(1u << i);
-                }
                 // the first bytes' steps (gap + 1, low bits) and the second bytes' values; a sum over bytes is a dot product, with
-                // the position in bytes of LDS 4 times the one and 32 times the other
+                // the position in bytes of LDS 4 times the one and 32 times the other.  A second byte's value is counted at the
+                // first byte before it (`lead`: that one is in the lane before), which so has its element's position already.
                 const uint32_t f0 = ((((x.x >> 4) & 0x07070707u) + 0x01010101u) & (uint32_t)there) & ~m0, s0 = x.x & m0;
                 const uint32_t f1 = ((((x.y >> 4) & 0x07070707u) + 0x01010101u) & (uint32_t)(there >> 32)) & ~m1, s1 = x.y & m1;
-                const uint32_t half = __builtin_amdgcn_udot4(s0, 0x20202020u, __builtin_amdgcn_udot4(f0, 0x04040404u, 0u, false), false);
-                const uint32_t sum = __builtin_amdgcn_udot4(s1, 0x20202020u, __builtin_amdgcn_udot4(f1, 0x04040404u, half, false), false);
+                const uint32_t q0 = __builtin_amdgcn_alignbyte(s1, s0, 1), q1 = s1 >> 8;
+                const uint32_t lead = __builtin_amdgcn_udot4(s0, 0x00000020u, 0u, false);
+                const uint32_t half = __builtin_amdgcn_udot4(q0, 0x20202020u, __builtin_amdgcn_udot4(f0, 0x04040404u, lead, false), false);
+                const uint32_t sum = __builtin_amdgcn_udot4(q1, 0x20202020u, __builtin_amdgcn_udot4(f1, 0x04040404u, half, false), false);
                 const uint32_t incl = wave_inclusive_sum(sum);
-                const uint32_t p0 = pos0 + incl - sum, p1 = p0 + half;
+                const uint32_t p = pos0 + incl - sum, p0 = p + lead, p1 = p + half;
                 uint32_t at[kLaneBytes];
 #pragma unroll
                 for (int i = 0; i < 3; ++i) {
                     const uint32_t four = 0x04040404u >> (24 - 8 * i), eight = 0x20202020u >> (24 - 8 * i);     // of the bytes up to i
-                    at[i] = __builtin_amdgcn_udot4(s0, eight, __builtin_amdgcn_udot4(f0, four, p0, false), false);
-                    at[4 + i] = __builtin_amdgcn_udot4(s1, eight, __builtin_amdgcn_udot4(f1, four, p1, false), false);
+                    at[i] = __builtin_amdgcn_udot4(q0, eight, __builtin_amdgcn_udot4(f0, four, p0, false), false);
+                    at[4 + i] = __builtin_amdgcn_udot4(q1, eight, __builtin_amdgcn_udot4(f1, four, p1, false), false);
                 }
                 at[3] = p1;
-                at[7] = p0 + sum;
+                at[7] = adds & 0x80u ? p + sum : at[6];
 #pragma unroll
                 for (int i = 0; i < (int)kLaneBytes; ++i) at[i] = (at[i] & in_tile) | Tb;
-                // the elements' values, sign and exponent (which reaches into the third byte), put together four at a time.  A byte
-                // that ends no element gets the zero that leaves any float as it is when scaled and added, so no byte needs a
-                // branch: what it rewrites belongs to no element of the message (the first byte of two lies between its element and
-                // the one before), or, behind the message's end, to its last one, which the same lane writes after it.
+                // No byte needs a branch: each of a lane's eight writes its element's sum, or what the lane itself overwrites.  The
+                // first byte of two writes the same as the second; one whose second is in the next lane writes where byte 6 does, and
+                // the bytes behind the message's end where its last one does, both of which come later.  That leaves a message
+                // that is cut inside an element, and exponents too small for some of the codes: there each byte is looked at.
+                const bool by_byte = ef < 8u || ((adds ^ valid) & 0x7Fu) != 0u;
+                if (by_byte) {
+#pragma unroll
+                    for (int i = 0; i < (int)kLaneBytes; ++i) {
+                        const uint32_t c = (i < 4 ? c0 : c1) >> (8 * (i & 3)), d = c & 7u;
+                        if ((ends >> i & 1u) && d < ef) {
+                            const float val = __uint_as_float((ef - d) << 23 | (c << 28 & 0x80000000u));
+                            const float contrib = scale * val;
+                            const lds_float e = (lds_float)(uintptr_t)at[i];
+                            *e = *e + contrib;
+                        }
+                    }
+                }
+                // the elements' values, sign and exponent (which reaches into the third byte), put together four at a time
                 uint32_t hi[2], lo[2];
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
-                    const uint32_t e = byte_mask(h ? ends >> 4 : ends), c = (h ? c1 : c0) & e;
-                    const uint32_t exps = ef * 0x01010101u - (c & 0x07070707u);
-                    hi[h] = ((((exps >> 1) & 0x7F7F7F7Fu) | ((c << 4) & 0x80808080u)) & e) | (neutral & ~e);
-                    lo[h] = (exps << 7) & 0x80808080u & e;
+                    const uint32_t c = h ? c1 : c0, exps = ef * 0x01010101u - (c & 0x07070707u);
+                    hi[h] = ((exps >> 1) & 0x7F7F7F7Fu) | ((c << 4) & 0x80808080u);
+                    lo[h] = (exps << 7) & 0x80808080u;
                 }
-                if (off < nb) {
+                if (off < nb && !by_byte) {
                     // the elements of one message are distinct: all are read before any is written
                     float old[kLaneBytes];
 #pragma unroll
