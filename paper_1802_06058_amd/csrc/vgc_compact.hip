@@ -110,7 +110,7 @@ int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* gr
                         uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out, vgc_pack_status* status_out,
                         hipStream_t stream) {
     const uint32_t tb = (uint32_t)((n_tiles + 3) / 4);
-    const int rc = launch_part_scans(pc, groups, segs, n_segs, max_group_tiles, hdrs, stmp, stream);
+    const int rc = launch_part_scans(pc, groups, tiles, segs, n_tiles, n_segs, max_group_tiles, hdrs, stmp, stream);
     if (rc != VGC_OK) return rc;
     hipLaunchKernelGGL(k_compact_count, dim3(tb), dim3(256), 0, stream, pc, n_tiles, hdrs, staging, tile_bytes_out);
     const CompactDirectory dir = {tiles, runs, n_runs, tile_bytes_out, run_offsets_out, stream_cap};

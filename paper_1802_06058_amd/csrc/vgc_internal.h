@@ -187,8 +187,8 @@ struct CompactDirectory {
     uint64_t* run_offsets;
     uint64_t stream_cap;
 };
-int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_segs, uint32_t max_group_tiles,
-                      TileHdr* hdrs, SegTmp* stmp, hipStream_t stream);
+int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanTile* tiles, const PlanSeg* segs, uint64_t n_tiles, uint32_t n_segs,
+                      uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, hipStream_t stream);
 int launch_header_scan(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_groups,
                        uint32_t n_segs, uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, vgc_group_hdr* hdrs_out,
                        vgc_pack_status* status_out, uint64_t words_cap, const CompactDirectory* compact, hipStream_t stream);

@@ -58,20 +58,37 @@ __device__ __forceinline__ uint32_t block_max(uint32_t e, uint32_t* sh /*[kWaves
     return e;
 }
 
-// Part blockIdx.x % parts_per_seg of segment blockIdx.x / parts_per_seg: its tile records and how many there are (0: none).
+// The part of a workgroup: its tile records and how many there are (0: none).  Workgroup i < n_segs has the first part of segment
+// i.  The other parts begin at least kPartTiles tiles apart, each behind a part of the same segment: workgroup n_segs + j has
+// the one that begins among the tiles from j kPartTiles on, if any, and that is one of the segment of the first of these.  (A
+// workgroup for as many parts as the largest group's segments have, of every segment: 100,000 groups of 700 elements and one of
+// 20 M, vgc_pack 1760 us; so 787, and 707 without the large one.)
 struct Part {
     uint32_t seg, index, cnt, group_tiles;
     uint64_t first, group_first;           // its first tile; its group's first tile
 };
-__device__ __forceinline__ Part part_of_block(const PlanGroup* __restrict__ groups, const PlanSeg* __restrict__ segs, uint32_t parts_per_seg) {
+__device__ __forceinline__ Part part_of_block(const PlanGroup* __restrict__ groups, const PlanTile* __restrict__ tiles, const PlanSeg* __restrict__ segs,
+                                              uint32_t n_segs) {
     Part q;
-    q.seg = blockIdx.x / parts_per_seg;
-    q.index = blockIdx.x - q.seg * parts_per_seg;
-    const PlanSeg ps = segs[q.seg];
-    const PlanGroup pg = groups[ps.group];
+    uint32_t group, in_group;
+    if (blockIdx.x < n_segs) {
+        q.seg = blockIdx.x;
+        q.index = 0;
+        const PlanSeg ps = segs[q.seg];
+        group = ps.group;
+        in_group = ps.first_tile;
+    } else {
+        const PlanTile pt = tiles[(uint64_t)(blockIdx.x - n_segs) * kPartTiles];
+        const uint32_t tile = pt.start >> kTileShift, in_seg = tile % kSegTiles;
+        q.seg = pt.seg;
+        q.index = (in_seg + kPartTiles - 1) / kPartTiles;
+        group = pt.group;
+        in_group = tile - in_seg + q.index * kPartTiles;
+        if (q.index == 0 || q.index == kSegTiles / kPartTiles) in_group = ~0u;      // a segment's first part: not here
+    }
+    const PlanGroup pg = groups[group];
     q.group_tiles = (pg.size + kTile - 1) / kTile;
     q.group_first = pg.first_tile;
-    const uint32_t in_group = ps.first_tile + q.index * kPartTiles;
     q.first = (uint64_t)pg.first_tile + in_group;
     q.cnt = in_group < q.group_tiles ? min(kPartTiles, q.group_tiles - in_group) : 0u;
     return q;
@@ -99,11 +116,11 @@ constexpr uint32_t kOwnMaxTiles = 2 * kPartTiles;
 
 // Only for groups of more than kOwnMaxTiles tiles: the largest tile exponent of every part into w[6] of its first record, so that the
 // scan kernel's workgroups can each derive E_k of the whole group.
-__global__ __launch_bounds__(kScanThreads) void k_part_max(PlanCheck pc, const PlanGroup* __restrict__ groups, const PlanSeg* __restrict__ segs,
-                                                  TileHdr* __restrict__ hdrs, uint32_t parts_per_seg) {
+__global__ __launch_bounds__(kScanThreads) void k_part_max(PlanCheck pc, const PlanGroup* __restrict__ groups, const PlanTile* __restrict__ tiles,
+                                                  const PlanSeg* __restrict__ segs, TileHdr* __restrict__ hdrs, uint32_t n_segs) {
     __shared__ uint32_t sh[kScanThreads / 64];
     if (!plan_ok(pc)) return;
-    const Part q = part_of_block(groups, segs, parts_per_seg);
+    const Part q = part_of_block(groups, tiles, segs, n_segs);
     if (q.cnt == 0 || q.group_tiles <= kOwnMaxTiles) return;            // the scan kernel finds E_k itself
     const TileHdr* H = hdrs + q.first;
     uint32_t w[kPartTiles / kScanThreads], e = 0;
@@ -121,12 +138,12 @@ __global__ __launch_bounds__(kScanThreads) void k_part_max(PlanCheck pc, const P
 // One workgroup per part: E_k, then per tile the number of words it keeps and its exclusive prefix inside the part (the first
 // tile's, which is 0, gives its place to the part's count).  Each thread owns consecutive tile records: they are loaded
 // together, scanned in registers, and only the per-thread totals go through the workgroup scan.
-__global__ __launch_bounds__(kScanThreads) void k_part_scan(PlanCheck pc, const PlanGroup* __restrict__ groups, const PlanSeg* __restrict__ segs,
-                                                   TileHdr* __restrict__ hdrs, SegTmp* __restrict__ stmp, uint32_t parts_per_seg) {
+__global__ __launch_bounds__(kScanThreads) void k_part_scan(PlanCheck pc, const PlanGroup* __restrict__ groups, const PlanTile* __restrict__ tiles,
+                                                   const PlanSeg* __restrict__ segs, TileHdr* __restrict__ hdrs, SegTmp* __restrict__ stmp, uint32_t n_segs) {
     constexpr uint32_t kPer = kPartTiles / kScanThreads;
     __shared__ uint32_t sh[kScanThreads / 64];
     if (!plan_ok(pc)) return;
-    const Part q = part_of_block(groups, segs, parts_per_seg);
+    const Part q = part_of_block(groups, tiles, segs, n_segs);
     if (q.cnt == 0) return;
     TileHdr* H = hdrs + q.first;
     const uint32_t tid = threadIdx.x;
@@ -459,13 +476,12 @@ static uint32_t parts_per_seg(uint32_t max_group_tiles) {
     return parts < kSegTiles / kPartTiles ? parts : kSegTiles / kPartTiles;
 }
 
-int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanSeg* segs, uint32_t n_segs, uint32_t max_group_tiles,
-                      TileHdr* hdrs, SegTmp* stmp, hipStream_t stream) {
-    // (at most n_tiles / 1024 + 8 n_groups workgroups)
-    const uint32_t pps = parts_per_seg(max_group_tiles);
+int launch_part_scans(PlanCheck pc, const PlanGroup* groups, const PlanTile* tiles, const PlanSeg* segs, uint64_t n_tiles, uint32_t n_segs,
+                      uint32_t max_group_tiles, TileHdr* hdrs, SegTmp* stmp, hipStream_t stream) {
+    const uint32_t blocks = n_segs + (max_group_tiles > kPartTiles ? (uint32_t)((n_tiles + kPartTiles - 1) / kPartTiles) : 0u);
     if (max_group_tiles > kOwnMaxTiles)
-        hipLaunchKernelGGL(k_part_max, dim3(n_segs * pps), dim3(kScanThreads), 0, stream, pc, groups, segs, hdrs, pps);
-    hipLaunchKernelGGL(k_part_scan, dim3(n_segs * pps), dim3(kScanThreads), 0, stream, pc, groups, segs, hdrs, stmp, pps);
+        hipLaunchKernelGGL(k_part_max, dim3(blocks), dim3(kScanThreads), 0, stream, pc, groups, tiles, segs, hdrs, n_segs);
+    hipLaunchKernelGGL(k_part_scan, dim3(blocks), dim3(kScanThreads), 0, stream, pc, groups, tiles, segs, hdrs, stmp, n_segs);
     return hip_check(hipGetLastError(), "launch part scans");
 }
 
@@ -493,7 +509,7 @@ int launch_pack(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, co
                            words_out, words_cap, hdrs_out, status_out);
         return hip_check(hipGetLastError(), "launch k_pack_small");
     }
-    int rc = launch_part_scans(pc, groups, segs, n_segs, max_group_tiles, hdrs, stmp, stream);
+    int rc = launch_part_scans(pc, groups, tiles, segs, n_tiles, n_segs, max_group_tiles, hdrs, stmp, stream);
     if (rc == VGC_OK)
         rc = launch_header_scan(pc, flags, groups, segs, n_groups, n_segs, max_group_tiles, hdrs, stmp, hdrs_out, status_out, words_cap, nullptr, stream);
     if (rc != VGC_OK) return rc;
