@@ -35,7 +35,7 @@ __global__ __launch_bounds__(256) void k_sqgrad_simple(const T* __restrict__ X, 
 
     f16v acc_g = {0}, acc_s = {0};
     if (!kConv) {
-        // (only for operands of 2^31 bytes or elements and more; the others go through LDS, vgc_sqgrad_fc.hip)  float32: eight
+        // (operands of 2^31 bytes or elements and more, and where fc_by_waves says so: the others go through LDS)  float32: eight
         // k-steps are requested while the eight before them are multiplied; bfloat16: one at a time, with more waves instead.
         constexpr int kAhead = sizeof(T) == 4 ? 8 : 1;
         struct Steps { float a[kAhead], b[kAhead]; };
@@ -100,9 +100,9 @@ int launch_sqgrad(int kind, int dtype, const void* X, const void* D, uint32_t B,
         return launch_conv_tiled(dtype, X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, stream);
     if (kind == VGC_CONV && dtype == VGC_F32 && conv_f32_tiled_supported(P, J, C))
         return launch_conv_f32_tiled(X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, stream);
-    if (kind == VGC_FC && fc_tiled_supported(dtype, B, J, C))
+    if (kind == VGC_FC && fc_tiled_supported(dtype, B, J, C) && !fc_by_waves(dtype, B, J, C, g_out != nullptr))
         return launch_fc_tiled(dtype, X, D, B, J, C, c, g_out, s_out, stream);
-    // what the tiled kernels do not take: conv rows that are not whole 16-byte pieces, operands beyond 32-bit offsets
+    // what the tiled kernels do not take (conv rows that are not whole 16-byte pieces, operands beyond 32-bit offsets) or take longer for
     return launch_sqgrad_simple(kind, dtype, X, D, B, P, J, C, c, g_out, s_out, stream);
 }
 

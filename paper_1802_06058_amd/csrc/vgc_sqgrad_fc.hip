@@ -4,12 +4,12 @@
 //   k_fc_bf16   bf16 inputs.  The squares are taken in float32 and rounded to bf16 (2^-9 relative per factor, well
 //               inside the 1e-2 budget for bf16 inputs); v_mfma_f32_32x32x16_bf16, float32 accumulate.
 //               With K this small the kernel is bound by writing [J, C] floats, not by the matrix cores.
-//   k_fc_f32    float32 inputs, v_mfma_f32_32x32x2_f32 (float32 products and sums, which is what the 1e-5 tolerance
-//               on s needs).
+//   k_fc_f32    float32 inputs, and bf16 ones whose rows are not whole 16-byte pieces (widened); v_mfma_f32_32x32x2_f32
+//               (float32 products and sums, which is what the 1e-5 tolerance on s needs).
 //
-// Block tile 128 x 128 of [J, C] (k_fc_f32 also 64 x 64), 4 waves (2 x 2), operands staged through LDS k-major (rows of the
-// source matrices as they are in memory).  Rows past the end of the matrix are outside the
-// bounded range of the buffer loads and read as zero.
+// Block tile 128 x 128 of [J, C] (k_fc_f32 also 64 x 64, and for rows of any length only that), 4 waves (2 x 2), operands staged
+// through LDS k-major (rows of the source matrices as they are in memory).  Rows past the end of the matrix are outside the
+// bounded range of the buffer loads and read as zero; rows of any length are read by load_any, which checks the end itself.
 #include "vgc_internal.h"
 
 namespace vgc {
@@ -305,6 +305,19 @@ bool fc_tiled_supported(int dtype, uint32_t B, uint32_t J, uint32_t C) {
     return (uint64_t)(B + 64) * (J + 128ull) < limit && (uint64_t)(B + 64) * (C + 128ull) < limit;
 }
 
+// Shapes the tiled kernel takes, but a wave per 32 x 32 outputs without LDS (vgc_sqgrad.hip; the same bits) is faster with: few
+// rows of 16-bit elements, whose way through LDS is not worth it (2049 x 1001 at batch 8: 7.7 us tiled, 6.4 by waves; with g 9.9
+// and 8.2; at batch 16 they meet, and so they do once the outputs, which it stores element by element, outgrow the caches), and
+// matrices so thin that half of a 64 x 64 tile is padding, once there are enough of them to fill the chip (100001 x 9: float32 at
+// batch 16 8.3 and 6.9, with g 10.9 and 8.7, with g at batch 512 122 and 95; bfloat16 at batch 16 8.7 and 7.7).  From batch 64 on
+// the tiled kernel catches up there without g (14.7 and 13.6), and in bfloat16 (16.8 and 23.2).
+bool fc_by_waves(int dtype, uint32_t B, uint32_t J, uint32_t C, bool want_g) {
+    if (fc_whole_pieces(dtype, J, C) || J > 65535u * 64u) return false;
+    const uint64_t tiles = (uint64_t)((J + 63) / 64) * ((C + 63) / 64), out = (uint64_t)J * C * (want_g ? 8 : 4);
+    if (dtype == VGC_BF16 && B <= 8 && out <= (64ull << 20)) return true;
+    return (J < C ? J : C) <= 32 && tiles >= 2 * 256 && (B < 64 || (want_g && dtype == VGC_F32));
+}
+
 template <typename T, bool kAnyRow>
 static void launch_fc_f32(const void* X, const void* D, uint32_t B, uint32_t J, uint32_t C, float c, float* g_out, float* s_out,
                           bool small, dim3 grid, hipStream_t stream) {
@@ -314,10 +327,10 @@ static void launch_fc_f32(const void* X, const void* D, uint32_t B, uint32_t J, 
     if (small) { if (g_out) VGC_FC_F32(true, 64, true); else VGC_FC_F32(false, 64, true); }
     // the large tile's two forms cross between batches of 200 and 256: 4096 x 4096 with g, copied against in two sets: 117 against
     // 121 us at 200, 140 against 138 at 256, 1025 against 988 at 2048
-    else if (g_out) {
-        if constexpr (!kAnyRow) { if (B >= 256) VGC_FC_F32(true, 128, true); else VGC_FC_F32(true, 128, false); }
-    } else if (B >= 256) VGC_FC_F32(false, 128, true);
-    else VGC_FC_F32(false, 128, false);
+    else if constexpr (!kAnyRow) {
+        if (B >= 256) { if (g_out) VGC_FC_F32(true, 128, true); else VGC_FC_F32(false, 128, true); }
+        else { if (g_out) VGC_FC_F32(true, 128, false); else VGC_FC_F32(false, 128, false); }
+    }
 #undef VGC_FC_F32
 }
 
@@ -325,9 +338,12 @@ int launch_fc_tiled(int dtype, const void* X, const void* D, uint32_t B, uint32_
                     float* g_out, float* s_out, hipStream_t stream) {
     const bool whole = fc_whole_pieces(dtype, J, C), bf16 = dtype == VGC_BF16 && whole;
     uint64_t nblk = (uint64_t)((J + kT - 1) / kT) * ((C + kT - 1) / kT);
-    // Small tiles where there are fewer than two of 128 x 128 per compute unit, and for rows of any length with g: the large tile
-    // spills there or is down to two waves per SIMD (25087 x 4095, float32 at batch 64: 425 us, 312 with the small one).
-    const bool small = !bf16 && (nblk < 2 * 256 || (!whole && g_out));
+    // Small tiles where there are fewer than two of 128 x 128 per compute unit, and for rows of any length: with g the large tile
+    // spills there or is down to two waves per SIMD (25087 x 4095, float32 at batch 64: 425 us, 312 with the small one), and without
+    // it is the slower one as well wherever its last wave of workgroups or its edges leave much of it idle (float32 at batch 64:
+    // 25087 x 4095 184 -> 174 us, 129 x 100001 52 -> 35; at best, 4095 x 4095 in
+    // bfloat16 at batch 128, the large one is 8 % ahead).
+    const bool small = !bf16 && (nblk < 2 * 256 || !whole);
     if (small) nblk = (uint64_t)((J + 63) / 64) * ((C + 63) / 64);
     if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
     const dim3 grid((uint32_t)nblk), block(256);
