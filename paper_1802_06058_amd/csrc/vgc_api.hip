@@ -25,7 +25,7 @@ int hip_check(hipError_t e, const char* what) {
 }
 
 // Validates the group list and counts tiles.  Returns a vgc_status.
-struct GroupStats { uint64_t n_runs; uint32_t n_segs; uint32_t max_group_tiles; uint64_t hash; };
+struct GroupStats { uint64_t n_runs; uint32_t n_segs; uint32_t max_group_tiles; bool whole_tiles; uint64_t hash; };
 
 static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, uint64_t* n_tiles_out,
                         GroupStats* stats_out = nullptr) {
@@ -33,7 +33,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     if (n == 0 || n_groups == 0) { set_error("n and n_groups must be positive"); return VGC_ERR_SIZE; }
     uint64_t off = 0, tiles = 0, runs = 0, segs = 0;
     uint64_t hash = 0xCBF29CE484222325ull ^ n_groups;       // FNV-1a over the sizes (offsets follow from them)
-    uint32_t most = 0;
+    uint32_t most = 0, ragged = 0;
     for (uint32_t k = 0; k < n_groups; ++k) {
         hash = (hash ^ groups[k].size) * 0x100000001B3ull;
         if (groups[k].size == 0) { set_error("group %u is empty", k); return VGC_ERR_SIZE; }
@@ -52,6 +52,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
         runs += (nt + kRunTiles - 1) / kRunTiles;
         segs += (nt + kSegTiles - 1) / kSegTiles;
         if (nt > most) most = (uint32_t)nt;
+        ragged |= groups[k].size % kTile;
     }
     if (off != n) {
         set_error("groups cover %llu elements, n = %llu", (unsigned long long)off, (unsigned long long)n);
@@ -59,7 +60,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     }
     if (tiles > 0x7FFFFFFFull) { set_error("too many tiles (%llu)", (unsigned long long)tiles); return VGC_ERR_SIZE; }
     if (n_tiles_out) *n_tiles_out = tiles;
-    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->max_group_tiles = most; stats_out->hash = hash; }
+    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->max_group_tiles = most; stats_out->whole_tiles = ragged == 0; stats_out->hash = hash; }
     return VGC_OK;
 }
 
@@ -635,7 +636,7 @@ int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr*
         const uint32_t* const wl[1] = {words};
         const uint64_t nl[1] = {n_words};
         const vgc_group_hdr* const hl[1] = {hdrs};
-        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, 0, dense_out, 0,
+        return launch_unpack_add_batch(plan_check(plan, gs), wl, nl, hl, 1, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, gs.whole_tiles, scale, 0, dense_out, 0,
                                        static_cast<hipStream_t>(stream));
     }
     return launch_unpack_add(plan_check(plan, gs), words, n_words, hdrs, pv.groups, n_groups, scale, dense_out, static_cast<hipStream_t>(stream));
@@ -658,7 +659,7 @@ int vgc_tiles_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_w
     if (!std::isfinite(scale)) { set_error("vgc_unpack_add_batch: scale is not finite"); return VGC_ERR_PARAM; }
     if (p == 0 && !overwrite) return VGC_OK;
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
-    return launch_unpack_add_batch(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, overwrite, dense_out,
+    return launch_unpack_add_batch(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, gs.whole_tiles, scale, overwrite, dense_out,
                                    tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 
@@ -704,7 +705,7 @@ int vgc_tiles_unpack_apply(const uint32_t* const* words, const uint64_t* n_words
         bias2 = (float)(1.0 - std::pow((double)b2, (double)opt->step));
     }
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
-    return launch_unpack_apply(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, scale, opt->kind, opt->lr, mu, b1, b2,
+    return launch_unpack_apply(plan_check(plan, gs), words, n_words, hdrs, p, pv.groups, pv.tiles, pv.runs, n_tiles, gs.n_runs, gs.whole_tiles, scale, opt->kind, opt->lr, mu, b1, b2,
                                omb1, omb2, bias1, bias2, eps, param, state1, state2, tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 

@@ -211,11 +211,11 @@ constexpr int kBatchMax = 8;   // messages one launch of the batched decoder tak
 constexpr int kApplyMax = 64;  // messages the decoder fused with the parameter update takes (one launch; a lane per message)
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                             uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs,
-                            float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream);
+                            bool whole_tiles, float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                        uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, float scale,
-                        int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
+                        uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, bool whole_tiles,
+                        float scale, int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
                         float eps, float* param, float* state1, float* state2, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_sqgrad(int kind, int dtype, const void* X, const void* D, uint32_t B, uint32_t P,

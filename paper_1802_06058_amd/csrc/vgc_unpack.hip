@@ -601,7 +601,18 @@ constexpr uint64_t kWaves = 65536;
 // Up to so many tiles a workgroup takes each: as many workgroups as are resident at once (five per compute unit).  2.5 M elements
 // (1221 tiles), 8 messages of 17 %: 22.7 -> 20.2 us overwriting, 38.0 -> 28.2 with Adam; 3 M (1465) 23.8 -> 28.2 and 45.0 -> 35.0;
 // 4 M 24.9 -> 30.4 and 39.0 -> 38.9; beyond, the search for the cursors of every tile costs what it gives or more.
-constexpr uint64_t kFewTiles = 1280;
+// Where every group is whole tiles (and the update is not Adam) waves have no last tile that they do element by element, the one
+// all others wait for, and the line comes earlier unless there are many words to a tile.  By tile / by waves, us, buffers in the
+// cache, 16 messages of 3 % added: 512 tiles 16.5 / 16.7, 768 19.5 / 17.3, 1024 21.9 / 18.1, but 1026 and a ragged one 22.1 / 27.1;
+// 8 messages of 17 %, 1024 tiles, 12.8 / 14.5; momentum SGD, 16 of 3 %: 12.6 / 13.1, 14.2 / 13.7, 16.0 / 14.6, 15.9 / 18.2.
+constexpr uint64_t kFewTiles = 1280, kFewWholeTiles = 512;
+static bool few_tiles(uint64_t n_tiles, bool whole_tiles, const uint64_t* n_words, uint32_t p) {
+    if (!whole_tiles || n_tiles <= kFewWholeTiles) return n_tiles <= kFewTiles;
+    const uint64_t n = n_tiles * kTile;
+    uint64_t total = 0;
+    for (uint32_t w = 0; w < p; ++w) total += n_words[w] < n ? n_words[w] : n;
+    return n_tiles <= kFewTiles && total >= n && total >= p * (n / 8);
+}
 
 template <int kMax>
 static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
@@ -619,8 +630,8 @@ static BatchArgs<kMax> batch_args(const uint32_t* const* words, const uint64_t* 
 
 int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
                             uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs,
-                            float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream) {
-    const bool by_tile = tiles_per_wave == 0 && n_tiles <= kFewTiles;
+                            bool whole_tiles, float scale, int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream) {
+    const bool by_tile = tiles_per_wave == 0 && few_tiles(n_tiles, whole_tiles, n_words, p);
     const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
     const uint32_t chunks = p ? (p + kBatchMax - 1) / kBatchMax : 1;     // p == 0: only the optional clear
@@ -638,8 +649,8 @@ int launch_unpack_add_batch(PlanCheck pc, const uint32_t* const* words, const ui
 }
 
 int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64_t* n_words, const vgc_group_hdr* const* hdrs,
-                        uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, float scale,
-                        int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
+                        uint32_t p, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, bool whole_tiles,
+                        float scale, int kind, float lr, float mu, float b1, float b2, float omb1, float omb2, float bias1, float bias2,
                         float eps, float* param, float* state1, float* state2, uint32_t tiles_per_wave, hipStream_t stream) {
     const uint32_t tpw = decode_tiles_per_wave(n_runs, kWaves, tiles_per_wave);
     const uint32_t blocks = (uint32_t)((n_runs * (kRunTiles / tpw) + 3) / 4);
@@ -647,7 +658,7 @@ int launch_unpack_apply(PlanCheck pc, const uint32_t* const* words, const uint64
     UpdateArgs O;
     O.w = param; O.s1 = state1; O.s2 = state2;
     O.lr = lr; O.mu = mu; O.b1 = b1; O.b2 = b2; O.omb1 = omb1; O.omb2 = omb2; O.bias1 = bias1; O.bias2 = bias2; O.eps = eps;
-    if (tiles_per_wave == 0 && n_tiles <= kFewTiles) {
+    if (tiles_per_wave == 0 && few_tiles(n_tiles, whole_tiles && kind != VGC_OPT_ADAM, n_words, p)) {
         if (kind == VGC_OPT_ADAM)
             hipLaunchKernelGGL((k_unpack_tile<kApplyMax, kAdam>), dim3((uint32_t)n_tiles), dim3(256), 0, stream, pc, A, groups, tiles,
                                (uint32_t)n_tiles, scale, static_cast<float*>(nullptr), 1, O);
