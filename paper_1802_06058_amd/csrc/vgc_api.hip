@@ -25,7 +25,7 @@ int hip_check(hipError_t e, const char* what) {
 }
 
 // Validates the group list and counts tiles.  Returns a vgc_status.
-struct GroupStats { uint64_t n_runs; uint32_t n_segs; uint32_t max_group_tiles; bool whole_tiles; uint64_t hash; };
+struct GroupStats { uint64_t n_runs; uint32_t n_segs; uint32_t max_group_tiles; bool whole_tiles, whole_lines; uint64_t hash; };
 
 static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, uint64_t* n_tiles_out,
                         GroupStats* stats_out = nullptr) {
@@ -33,7 +33,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     if (n == 0 || n_groups == 0) { set_error("n and n_groups must be positive"); return VGC_ERR_SIZE; }
     uint64_t off = 0, tiles = 0, runs = 0, segs = 0;
     uint64_t hash = 0xCBF29CE484222325ull ^ n_groups;       // FNV-1a over the sizes (offsets follow from them)
-    uint32_t most = 0, ragged = 0;
+    uint32_t most = 0, ragged = 0, odd = 0;
     for (uint32_t k = 0; k < n_groups; ++k) {
         hash = (hash ^ groups[k].size) * 0x100000001B3ull;
         if (groups[k].size == 0) { set_error("group %u is empty", k); return VGC_ERR_SIZE; }
@@ -53,6 +53,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
         segs += (nt + kSegTiles - 1) / kSegTiles;
         if (nt > most) most = (uint32_t)nt;
         ragged |= groups[k].size % kTile;
+        odd |= (uint32_t)groups[k].offset % 4;               // (not whole 16-byte pieces of a float buffer)
     }
     if (off != n) {
         set_error("groups cover %llu elements, n = %llu", (unsigned long long)off, (unsigned long long)n);
@@ -60,7 +61,7 @@ static int check_groups(const vgc_group* groups, uint32_t n_groups, uint64_t n, 
     }
     if (tiles > 0x7FFFFFFFull) { set_error("too many tiles (%llu)", (unsigned long long)tiles); return VGC_ERR_SIZE; }
     if (n_tiles_out) *n_tiles_out = tiles;
-    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->max_group_tiles = most; stats_out->whole_tiles = ragged == 0; stats_out->hash = hash; }
+    if (stats_out) { stats_out->n_runs = runs; stats_out->n_segs = (uint32_t)segs; stats_out->max_group_tiles = most; stats_out->whole_tiles = ragged == 0; stats_out->whole_lines = odd == 0; stats_out->hash = hash; }
     return VGC_OK;
 }
 
@@ -626,12 +627,16 @@ int vgc_unpack_add(const uint32_t* words, uint64_t n_words, const vgc_group_hdr*
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     // A message that touches most cache lines of the buffer anyway (going by n_words) is decoded tile by tile like a
     // batch of one: the same additions, the buffer streamed once instead of read and written line by line under 64
-    // scattered lanes.  The line is an eighth of the elements, and a sixteenth from twice the last-level cache on (512 MB),
-    // where the scattered lines come from memory also when the buffer has just been written.  By words / by tiles, us, on a
-    // buffer just written (on a cold one): 25 M parameters 37 / 43 (45 / 47) at 6.5 %, 43 / 43 (47 / 47) at 10 %; 75 M 89 / 107
-    // (112 / 114) and 108 / 108 (119 / 115); 138 M 173 / 191 (158 / 198) at 4 %, 223 / 191 (201 / 206) at 6.5 %, 231 / 192
-    // (210 / 209) at 8 %; 400 M 507 / 531 (485 / 552) at 4 %, 630 / 541 (604 / 575) at 6.5 %, 685 / 542 (675 / 598) at 10 %.
-    const uint64_t dense_words = n >= (1ull << 27) ? n / 16 : n / 8;
+    // scattered lanes.  The line is an eighth of the elements, and from twice the last-level cache on (512 MB), where the
+    // scattered lines come from memory also when the buffer has just been written, a sixteenth, or a twelfth where groups begin
+    // anywhere and tiles are read in pieces of lines.  By words / by tiles, us, on a buffer just written (on a cold one):
+    // 25 M parameters 37 / 43 (45 / 47) at 6.5 %, 43 / 43 (47 / 47) at 10 %; 75 M 89 / 107 (112 / 114) and 108 / 108 (119 / 115);
+    // 138 M 173 / 191 (158 / 198) at 4 %, 223 / 191 (201 / 206) at 6.5 %, 231 / 192 (210 / 209) at 8 %; 400 M 507 / 531 (485 / 552)
+    // at 4 %, 630 / 541 (604 / 575) at 6.5 %, 685 / 542 (675 / 598) at 10 %.  With groups that begin anywhere 138 M 214 / 218
+    // (201 / 214) at 6.25 %, 225 / 219 (210 / 214) at 7.5 %, 232 / 222 (218 / 217) at 9 %; 268 M 421 / 436 (402 / 431), 439 / 441
+    // (420 / 436), 454 / 448 (438 / 440).
+    const bool whole = gs.whole_lines && aligned(dense_out, 16);
+    const uint64_t dense_words = n < (1ull << 27) ? n / 8 : whole ? n / 16 : n / 12;
     if (n_words && n_words >= dense_words) {
         const uint32_t* const wl[1] = {words};
         const uint64_t nl[1] = {n_words};

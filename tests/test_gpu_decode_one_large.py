@@ -14,7 +14,7 @@ def test_one_message_at_the_rules_edge(n, below):
     import torch
     from paper_1802_06058_amd import vgc
     gen = torch.Generator(device="cuda").manual_seed(n + below)
-    sizes = [5, (1 << 24) - 3] + [1 << 24] * 7
+    sizes = [8, (1 << 24) - 4] + [1 << 24] * 7                 # (all begin at a multiple of 16 bytes)
     sizes[-1] += n - sum(sizes)
     groups = W.groups_from_sizes(sizes)
     plan = vgc.Plan(groups, "cuda")
