@@ -84,7 +84,7 @@ struct PlanSeg {               // 16 bytes
     uint32_t group;
     uint32_t first_tile;       // index of the segment's first tile inside its group
     uint32_t seg_in_group;
-    uint32_t group_first_seg;  // index of the group's first segment in the table
+    uint32_t group_first_seg;  // index of the group's first segment in the table (no kernel reads it: it is there so that plans keep their bytes)
 };
 
 // A run is up to kRunTiles consecutive tiles of one group: the unit one wave of the batched

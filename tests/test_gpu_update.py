@@ -96,7 +96,7 @@ def test_adam_steps_match_oracle(dev, p):
 
 
 def test_update_on_unaligned_views(dev):
-    """param / state pointers that are only 4-byte aligned take the element-wise path."""
+    """param / state pointers that are only 4-byte aligned: 16-byte accesses at the elements' own alignment."""
     import torch
     from paper_1802_06058_amd import vgc
     sizes = [2048 * 5, 777]
