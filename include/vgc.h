@@ -339,13 +339,16 @@ int vgc_unpack_add_batch(const uint32_t* const* words, const uint64_t* n_words,
  * group after group) and the byte stream.  One or two bytes per element instead of four; with the directory
  * (2 bytes per tile, 8 per run) it is the smaller format once a message holds one element per tile on average.
  *
+ * The encoder writes the one-byte form wherever it fits; the decoder takes the two-byte form with any gap.
+ *
  * vgc_pack_compact consumes the scratch left by vgc_accumulate_select exactly as vgc_pack does (either or both may
  * follow one accumulate call).  stream_out: DEVICE uint8[stream_cap], never written past stream_cap (2 * n bytes
  * cannot overflow); tile_bytes_out: DEVICE uint16[vgc_tile_count()]; run_offsets_out: DEVICE uint64[vgc_run_count()];
  * status_out->total_words is the stream's length in BYTES, overflow and plan_mismatch as for vgc_pack.
  *
  * vgc_unpack_compact_add_batch is vgc_unpack_add_batch for such messages (HOST arrays of p DEVICE pointers;
- * stream_bytes: HOST array of the streams' lengths, beyond which nothing is read): same sums, bit for bit, as
+ * stream_bytes: HOST array of the streams' lengths, beyond which nothing is read; an element that lies partly beyond is not
+ * decoded): same sums, bit for bit, as
  * decoding the messages in the plain format in message order. */
 uint64_t vgc_run_count(const vgc_group* groups, uint32_t n_groups, uint64_t n);
 int vgc_pack_compact(uint64_t n, const vgc_group* groups, uint32_t n_groups, const void* plan, void* scratch,
