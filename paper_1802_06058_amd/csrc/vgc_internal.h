@@ -231,8 +231,11 @@ bool conv_taps_supported(uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, uint3
                          uint32_t ph, uint32_t pw);
 size_t conv_taps_workspace_bytes(uint32_t B, uint32_t P, uint32_t Cin, uint32_t C);
 bool conv_tiled_supported(int dtype, uint32_t P, uint32_t J, uint32_t C);
+// What a split leaves in the workspace: its sums of s and of g (kSplits), of s alone, to be added by pairs (kPairs), or of s and g
+// over two splits of those (kPairsDone).
+enum class ReducePlanes { kSplits, kPairs, kPairsDone };
 void launch_sqgrad_reduce(const float* ws, uint32_t splits, size_t JC, float cg, float cs, float* g_out, float* s_out,
-                          hipStream_t stream);
+                          hipStream_t stream, ReducePlanes planes = ReducePlanes::kSplits);
 bool fc_tiled_supported(int dtype, uint32_t B, uint32_t J, uint32_t C);
 bool fc_by_waves(int dtype, uint32_t B, uint32_t J, uint32_t C, bool want_g);
 bool conv_f32_tiled_supported(uint32_t P, uint32_t J, uint32_t C);

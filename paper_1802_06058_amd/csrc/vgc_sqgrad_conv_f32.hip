@@ -8,10 +8,10 @@
 //
 // Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
 // latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.66 ms (98 -> 180 TFLOP/s); the 53 layers
-// of ResNet-50 at batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product).  What bounds it
-// now: the vector instructions that cut the elements (13 per pair, once per filter tap and column tile) and those that add
-// up the chunks share the issue slots with the MFMAs (matrix pipes 26 to 33 % busy on ResNet's layers), and on the small
-// layers a workgroup's 14 chunks take 19 us of its kernel's 31.
+// of ResNet-50 at batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product), 2.17 with
+// k_conv_taps_f32 below.  What bounds it now: the vector instructions that cut the elements (13 per pair, once per filter tap and
+// column tile) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 26 to 33 % busy on ResNet's
+// layers), and on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
 //
 // The bf16 MFMA adds with truncation: chained over all positions, every instruction would cut off a little of the
 // accumulator, always towards minus infinity.  So the six products of a chunk of 32 positions are summed from zero, where
@@ -67,6 +67,55 @@ template <int W> __device__ __forceinline__ constexpr uint32_t lds_swizzle(uint3
 }
 template <int W> __device__ __forceinline__ uint32_t lds_piece(uint32_t row, uint32_t col) {      // byte offset inside a plane
     return row * (W * 2) + (((col >> 4) ^ lds_swizzle<W>(row)) << 5) + (col & 15u) * 2u;
+}
+
+// The pieces of an infinity add up to NaN, as do products beyond the range of float32 whose pieces differ in sign, and a pixel
+// may reach taps that do not use it, by way of positions past P (in the linear mode of k_conv_f32, and between the rows and the
+// samples of k_conv_taps_f32).  So an MFMA tile with a sum that is not finite is formed again with the float32 instruction,
+// element by element of its own operands from memory, and gets what float32 arithmetic gives.  Where all of a tile's sums are NaN
+// already, as they are throughout once a network has diverged, nothing more can change and the walk ends.  3 x 3, 256 -> 256 at
+// 14 x 14, batch 32, through k_conv_f32: 78 us; with an infinity among the activations 181, among the gradients 328, with nothing but NaN 87.
+// x_at(z, p), d_at(z, p): the operands of the lane's row and column (lane % 16) at a position, zero outside; valid(r), at(r):
+// whether row r of the tile is an output in the lane's column, and where it lies.
+template <bool kWantG, typename FX, typename FD, typename FV, typename FO>
+__device__ __forceinline__ void form_again(FX x_at, FD d_at, FV valid, FO at, uint32_t z_begin, uint32_t z_end, uint32_t p_begin,
+                                           uint32_t p_end, bool parts, float fs, float fg, float* __restrict__ so, float* __restrict__ go) {
+    const uint32_t lane = threadIdx.x & 63u;
+    // whether the sums at the lane's outputs are all NaN
+    auto settled = [&](const f4v& v) {
+        bool s = true;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s = s && (v[i] != v[i] || !valid(4u * (lane >> 4) + (uint32_t)i));
+        return __ballot(!s) == 0;
+    };
+    f4v sum = (f4v){0}, s4 = (f4v){0}, g4 = (f4v){0};
+#pragma unroll 1
+    for (uint32_t z = z_begin; z < z_end && !settled(s4); ++z) {
+        sum = (f4v){0};
+#pragma unroll 1
+        for (uint32_t p0 = p_begin; p0 < p_end && !settled(sum); p0 += 16) {
+            float x[4], d[4];
+#pragma unroll
+            for (uint32_t k = 0; k < 4; ++k) {
+                x[k] = x_at(z, p0 + 4u * k + (lane >> 4));
+                d[k] = d_at(z, p0 + 4u * k + (lane >> 4));
+            }
+#pragma unroll
+            for (int k = 0; k < 4; ++k) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(x[k], d[k], sum, 0, 0, 0);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i) s4[i] = __builtin_fmaf(sum[i], sum[i], s4[i]);
+        g4 = g4 + sum;
+    }
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        const uint32_t r = 4u * (lane >> 4) + (uint32_t)i;
+        if (valid(r)) {
+            const size_t o = at(r);
+            __builtin_nontemporal_store(parts ? sum[i] : fs * s4[i], so + o);
+            if (kWantG) __builtin_nontemporal_store(fg * g4[i], go + o);
+        }
+    }
 }
 
 // X is [B, P, J], D is [B, P, C], samples z_begin .. z_end-1 of this workgroup's split.
@@ -373,12 +422,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
             }
         }
 
-    // The pieces of an infinity add up to NaN, as do products beyond the range of float32 whose pieces differ in sign, and in the
-    // linear mode a pixel may reach taps that do not use it, by way of positions past P.  So an MFMA tile with a sum that is not
-    // finite is formed again with the float32 instruction, element by element of its own operands from memory, and gets what
-    // float32 arithmetic gives.  Where all of a tile's sums are NaN already, as they are throughout once a network has
-    // diverged, nothing more can change and the walk ends.  3 x 3, 256 -> 256 at 14 x 14, batch 32: 78 us; with an infinity among
-    // the activations 181, among the gradients 328, with nothing but NaN 87.  The look at the sums costs 0.6 % of ResNet-50's layers.
+    // Tiles with a sum that is not finite are formed again (see form_again); the look at the sums costs 0.6 % of ResNet-50's layers.
     auto top = [](float x) { return __float_as_uint(x) & 0x7FFFFFFFu; };
     uint32_t most = 0;
 #pragma unroll
@@ -404,48 +448,415 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         const uint32_t tile = (uint32_t)__builtin_ctz(again), m = tile / NTL, n = tile % NTL;
         const uint32_t jt = j0 + wm * (uint32_t)WM + m * 16u, j = jt + (lane & 15u), col = c0 + wn * (uint32_t)WN + n * 16u + (lane & 15u);
         const uint32_t tap = kMode == kPatches ? 0u : j / G.Cin, ky = kMode == kPatches ? 0u : tap / G.kw, kx = tap - ky * G.kw;
-        auto x_at = [&](uint32_t z, uint32_t p) -> float {
-            if (j >= J || p >= p_end) return 0.f;
-            if (kMode == kPatches) return X[((size_t)z * P + p) * J + j];
-            const uint32_t y = p / G.Wo, iy = y * G.sh + ky - G.ph, ix = (p - y * G.Wo) * G.sw + kx - G.pw;
-            return iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + (j - tap * G.Cin)] : 0.f;
-        };
-        auto d_at = [&](uint32_t z, uint32_t p) -> float { return col < C && p < p_end ? D[((size_t)z * P + p) * C + col] : 0.f; };
-        // whether the sums at the lane's outputs are all NaN
-        auto settled = [&](const f4v& v) {
-            bool s = true;
+        form_again<kWantG>(
+            [&](uint32_t z, uint32_t p) -> float {
+                if (j >= J || p >= p_end) return 0.f;
+                if (kMode == kPatches) return X[((size_t)z * P + p) * J + j];
+                const uint32_t y = p / G.Wo, iy = y * G.sh + ky - G.ph, ix = (p - y * G.Wo) * G.sw + kx - G.pw;
+                return iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + (j - tap * G.Cin)] : 0.f;
+            },
+            [&](uint32_t z, uint32_t p) -> float { return col < C && p < p_end ? D[((size_t)z * P + p) * C + col] : 0.f; },
+            [&](uint32_t r) { return jt + r < J && col < C; },
+            [&](uint32_t r) -> size_t { return (size_t)(jt + r) * C + col; },
+            z_begin, z_end, p_begin, p_end, split_p > 1, fs, fg, so, go);
+    }
+}
+
+// ------------------------------------------------------------------------------------------------
+// 3 x 3 filters with unit stride and padding 1.  In the kernel above every element is fetched, cut and stored into LDS once per
+// filter tap and column tile, and the instructions that do so take the issue slots that the matrix instructions leave: beyond
+// two vector instructions per MFMA the two add up (measured: 7.4 ns a SIMD and MFMA with two, 10.4 with four, 13 with six).  Here
+// a workgroup owns all nine taps of 64 input channels times 64 output channels (576 x 64 outputs), and cuts every input pixel
+// once: pixels go through a ring in LDS, and the fragment of tap (ky, kx) is read from it at a shift.
+//
+// For the shift to be the same for all positions, rows are W + 1 pixels long here, the last one a zero: it is the padding to the
+// right of its row and to the left of the next.  Position q = y (W + 1) + x of a sample reads ring pixel q + (ky - 1)(W + 1) +
+// kx - 1; at x = W the output gradient is zero.  That costs 1 / W more positions (none in whole chunks of 32 at 14 x 14 and 7 x 7).
+// A step multiplies 32 positions and takes in 32 pixels, kLead ahead; samples follow each other in the ring with at least
+// W + 2 zeros between their last and first pixels, which pad one's bottom and the other's top.
+//
+// Eight waves: wave w has channels 16 (w % 4) .. + 15 of the block and one half of the columns: nine MFMA tiles of rows times two
+// of columns.  Pieces, products, signs and the sum of a chunk are those of the kernel above; the sign turns on the output
+// gradient, since a pixel belongs to several chunks.  With g, whose sums would not fit the registers otherwise, 32 input channels
+// and a quarter of the columns a wave.  So that there are as many workgroups then, each takes two of the groups of samples that
+// the call without g is split into; the squares of a group are summed by themselves and groups by pairs, here or in the
+// reduction: s is the same with g and without.
+//
+// s alone, batch 32, us before and now: 64 channels at 56 x 56 68 -> 57, 128 at 28 x 28 80 -> 53, 256 at 14 x 14 66 -> 57, 512 at
+// 7 x 7 105 -> 67; 512 at 14 x 14, batch 64, 395 -> 275 (215 TFLOP/s); ResNet-50 in one call 2349 -> 2173.  A step takes 2.3 us, the
+// MFMAs alone 1.7 at the 2.05 GHz that they leave the clock; layers with one or two samples a workgroup are bound by its
+// beginning and end (17 us at 14 x 14) and by the planes of the split.
+constexpr int kTapsRing = 248, kTapsMirror = 34;         // pixels; the first ones again at the end, so that a fragment's reads do not wrap
+constexpr uint32_t kTapsMaxW = 78;                       // a step's window, the block taken in meanwhile and the pixels between samples fit the ring
+
+// How a sample lies in the ring: n_chunks steps of 32, then `extra` (0 .. 4) pixels more, so that the gap to the next is wide enough.
+// A step reads the block of 32 pixels it begins with and the `ahead` next ones.
+constexpr uint32_t kTapsAhead = (2 * (kTapsMaxW + 2) + kR32 - 1) / kR32;
+static_assert(kR32 * (kTapsAhead + 2) + 4 <= kTapsRing, "what is read and what is taken in are different pixels of the ring");
+struct TapsGeom { uint32_t H, W, Cin, n_chunks, extra, ahead; };
+
+template <bool kWantG>
+__global__ __launch_bounds__(512, 2)
+void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t C, uint32_t splits, uint32_t split_p,
+                     float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out, float* __restrict__ ws, TapsGeom G) {
+    constexpr int kCh = kWantG ? 32 : 64, NTL = kWantG ? 1 : 2;      // input channels of the tile; MFMA tiles of columns of a wave
+    // bytes of a pixel, of a position: three planes of bf16, consecutive ones 32 bytes apart in the banks (modulo 256)
+    constexpr int kPlaneX = kCh * 2, kPitchX = 3 * kPlaneX + 32, kPlaneD = 128, kPitchD = 3 * kPlaneD + 32;
+    static_assert(kPitchX % 64 == 32 && kPitchD % 64 == 32, "eight consecutive ones begin in different banks");
+    __shared__ __attribute__((aligned(16))) uint8_t shX[(kTapsRing + kTapsMirror) * kPitchX];
+    __shared__ __attribute__((aligned(16))) uint8_t shD[2][kR32 * kPitchD];
+    __shared__ f4v shS[kWantG ? 9 * 512 : 1];                        // the first group's sums of s (each thread's own)
+    const uint32_t tid = threadIdx.x, lane = tid & 63u;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6), wc = kWantG ? wave & 1u : wave & 3u, wn = kWantG ? wave >> 1 : wave >> 2;
+    const uint32_t tiles_c = (C + 63u) / 64u, tiles_i = (G.Cin + kCh - 1u) / kCh, J = 9u * G.Cin, Wp = G.W + 1u;
+    const uint32_t nblk = gridDim.x, per = nblk / 8u, rem = nblk % 8u;
+    const uint32_t xcd = blockIdx.x % 8u, slot_x = blockIdx.x / 8u;
+    const uint32_t logical = xcd * per + min(xcd, rem) + slot_x;     // contiguous range of tiles per XCD
+    const uint32_t tile_c = logical % tiles_c, tile_i = (logical / tiles_c) % tiles_i, split = logical / (tiles_c * tiles_i);
+    const uint32_t i0 = tile_i * kCh, c0 = tile_c * 64u;
+    const uint32_t n_chunks = G.n_chunks;
+    const uint32_t part = split_p > 1 ? split % split_p : 0u;
+    const uint32_t chunks_per_part = (n_chunks + split_p - 1) / split_p;
+    const uint32_t c_begin = min(n_chunks, part * chunks_per_part);
+    const auto z_of = [&](uint32_t g) { return (uint32_t)((uint64_t)min(g, splits) * B / splits); };
+    const uint32_t z_begin = split_p > 1 ? split / split_p : z_of(kWantG ? 2u * split : split);
+    const uint32_t z_end = split_p > 1 ? z_begin + 1u : z_of(kWantG ? 2u * split + 2u : split + 1u);
+    const uint32_t total = split_p > 1 ? min(n_chunks, c_begin + chunks_per_part) - c_begin : (z_end - z_begin) * n_chunks;
+
+    f4v acc[9][NTL], s_acc[9][NTL], g_acc[9][NTL];
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s = s && (v[i] != v[i] || jt + 4u * (lane >> 4) + (uint32_t)i >= J || col >= C);
-            return __ballot(!s) == 0;
-        };
-        f4v sum = (f4v){0}, s4 = (f4v){0}, g4 = (f4v){0};
-#pragma unroll 1
-        for (uint32_t z = z_begin; z < z_end && !settled(s4); ++z) {
-            sum = (f4v){0};
-#pragma unroll 1
-            for (uint32_t p0 = p_begin; p0 < p_end && !settled(sum); p0 += 16) {
-                float x[4], d[4];
+    for (int a = 0; a < 9; ++a)
 #pragma unroll
-                for (uint32_t k = 0; k < 4; ++k) {
-                    x[k] = x_at(z, p0 + 4u * k + (lane >> 4));
-                    d[k] = d_at(z, p0 + 4u * k + (lane >> 4));
+        for (int b = 0; b < NTL; ++b) { acc[a][b] = (f4v){0}; s_acc[a][b] = (f4v){0}; g_acc[a][b] = (f4v){0}; }
+
+    // the sign of the first chunk's sum, by its number in the batch, so that it does not depend on where the workgroup begins
+    const float sign = ((z_begin * n_chunks + c_begin) & 1u) ? -1.0f : 1.0f;
+
+    // ---- what the thread takes in: pixel row_ of a block of 32, four channels; position row_ of a chunk, four columns ----
+    const uint32_t prow = tid / (kCh / 4), quad = tid % (kCh / 4), drow = tid >> 4, dquad = tid & 15u;
+    const bool has_x = kCh == 64 || wave < 4u;
+    const uint32_t xch = i0 + quad * 4u, dcol = c0 + dquad * 4u;
+    const uint32_t x_off = (uint32_t)(xch < G.Cin) - 1u, d_off = (uint32_t)(dcol < C) - 1u;      // all ones where there is nothing
+    // (y, x) of the pixel (position) that the thread requests next; 32 pixels further is step_y rows and step_x columns
+    const uint32_t step_y = (uint32_t)kR32 / Wp, step_x = (uint32_t)kR32 - step_y * Wp;
+    const uint32_t back_y = n_chunks * kR32 / Wp, back_x = n_chunks * kR32 - back_y * Wp;
+    const uint32_t lead = G.W + 2u;
+    uint32_t py, px, dy, dx;
+    {   // pixel c_begin 32 + prow - lead, from two rows above the image on (lead <= 2 Wp)
+        const uint32_t at = c_begin * kR32 + prow + 2u * Wp - lead;
+        py = at / Wp;
+        px = at - py * Wp;
+        py -= 2u;
+        const uint32_t pos = c_begin * kR32 + drow;
+        dy = pos / Wp;
+        dx = pos - dy * Wp;
+    }
+    auto advance = [&](uint32_t& y, uint32_t& x) {
+        x += step_x;
+        const uint32_t xw = x - Wp;
+        y += step_y + (x >= Wp ? 1u : 0u);
+        x = min(x, xw);
+    };
+    auto rewind = [&](uint32_t& y, uint32_t& x) {                    // to the start of a sample
+        y -= back_y + (x < back_x ? 1u : 0u);
+        x = x < back_x ? x + Wp - back_x : x - back_x;
+    };
+    const uint32_t x_bytes = G.H * G.W * G.Cin * 4u, d_bytes = G.H * G.W * C * 4u;
+    uint32_t zx = z_begin, bx = c_begin, zd = z_begin, bd = c_begin; // sample and block (chunk) requested next
+    auto operand = [&](const float* base, uint32_t bytes, uint32_t z) {
+        return make_rsrc(base + (size_t)(z < z_end ? z : z_begin) * (bytes / 4u), z < z_end ? bytes : 0u);
+    };
+    rsrc_t rx = operand(X, x_bytes, z_begin), rd = operand(D, d_bytes, z_begin);
+    f4v RX = {0}, RD = {0}, RE = {0};
+    auto load_at = [&](rsrc_t r, uint32_t y, uint32_t x, uint32_t ch, uint32_t width, uint32_t off) -> f4v {
+        const uint32_t at = (uint32_t)__mul24(__mul24((int)y, (int)G.W) + (int)x, (int)width) + ch;
+        const bool inside = (y < G.H) & (x < G.W);
+        return __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(r, (int)((at << 2) | off | (inside ? 0u : 0xFFFFFFFFu)), 0, 0));
+    };
+    auto request_x = [&]() {
+        if (has_x) RX = load_at(rx, py, px, xch, G.Cin, x_off);
+        advance(py, px);
+        if (++bx == n_chunks) {
+            // the pixels beyond the sample's last block, by the first wave: thread row 0 .. 3 stands at exactly those
+            if (G.extra && wave == 0u) RE = load_at(rx, py, px, xch, G.Cin, x_off | ((uint32_t)(prow < G.extra) - 1u));
+            bx = 0;
+            rx = operand(X, x_bytes, ++zx);
+            rewind(py, px);
+        }
+    };
+    auto request_d = [&]() {
+        RD = load_at(rd, dy, dx, dcol, C, d_off);
+        advance(dy, dx);
+        if (++bd == n_chunks) { bd = 0; rd = operand(D, d_bytes, ++zd); rewind(dy, dx); }
+    };
+    // ---- into LDS ----
+    uint32_t slot_w = 0, bw = c_begin;                               // ring slot of the block stored next, and its number in the sample
+    auto store_pixel = [&](uint32_t slot, u2v h, u2v m, u2v l) {
+        uint8_t* p = shX + slot * kPitchX + quad * 8u;
+        *reinterpret_cast<u2v*>(p) = h;
+        *reinterpret_cast<u2v*>(p + kPlaneX) = m;
+        *reinterpret_cast<u2v*>(p + 2 * kPlaneX) = l;
+    };
+    auto cut = [&](const f4v& v, float up, u2v& h, u2v& m, u2v& l) {
+        uint32_t a, b, c;
+        split_pair(v[0] * up, v[1] * up, a, b, c);
+        h[0] = a; m[0] = b; l[0] = c;
+        split_pair(v[2] * up, v[3] * up, a, b, c);
+        h[1] = a; m[1] = b; l[1] = c;
+    };
+    auto put_x = [&](uint32_t first, const f4v& v) {                 // pixel prow of those from ring slot `first` on
+        if (!has_x) return;
+        u2v h, m, l;
+        cut(v, kUp, h, m, l);
+        uint32_t slot = first + prow;
+        slot = min(slot, slot - (uint32_t)kTapsRing);
+        store_pixel(slot, h, m, l);
+        if (first < (uint32_t)kTapsMirror || first + kR32 > (uint32_t)kTapsRing)
+            if (slot < (uint32_t)kTapsMirror) store_pixel(slot + kTapsRing, h, m, l);
+    };
+    auto ring = [](uint32_t s) { return s >= (uint32_t)kTapsRing ? s - (uint32_t)kTapsRing : s; };
+    auto stage_x = [&]() {
+        put_x(slot_w, RX);
+        slot_w = ring(slot_w + kR32);
+        if (++bw == n_chunks) {
+            bw = 0;
+            if (G.extra) {
+                if (wave == 0u && prow < G.extra) put_x(slot_w, RE);
+                slot_w = ring(slot_w + G.extra);
+            }
+        }
+        request_x();
+    };
+    auto put_d = [&](uint32_t buf, float up) {
+        u2v h, m, l;
+        cut(RD, up, h, m, l);
+        uint8_t* p = shD[buf] + drow * kPitchD + dquad * 8u;
+        *reinterpret_cast<u2v*>(p) = h;
+        *reinterpret_cast<u2v*>(p + kPlaneD) = m;
+        *reinterpret_cast<u2v*>(p + 2 * kPlaneD) = l;
+    };
+
+    // ---- fragments: lanes 16 g .. + 15 have k = 8 g .. + 7, which are positions 4 g .. + 3 and 16 + 4 g .. + 3 of the chunk: a
+    // transposing read then takes eight consecutive rows per pass over the banks ----
+    const uint32_t r16 = lane & 15u, frow = (lane >> 4) * 4u + (r16 >> 2);
+    const uint32_t fX = frow * kPitchX + wc * 32u + 8u * (r16 & 3u);
+    const uint32_t fD = frow * kPitchD + wn * (uint32_t)(NTL * 32) + 8u * (r16 & 3u);
+    auto frag = [&](const uint8_t* p, int pitch) -> bf8v {
+        const s4v lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(p));
+        const s4v hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_s4v_ptr)(p + 16 * pitch));
+        s8v v = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+        return __builtin_bit_cast(bf8v, v);
+    };
+    uint32_t slot_r = 0, br = c_begin;                               // ring slot of the step's first pixel; the step's number in the sample
+    uint32_t at[3];                                                  // the lane's byte offset in the ring for filter row ky
+    auto place = [&]() {
+#pragma unroll
+        for (uint32_t ky = 0; ky < 3; ++ky) at[ky] = fX + __builtin_amdgcn_readfirstlane(ring(slot_r + ky * Wp)) * kPitchX;
+    };
+    // Taps are multiplied one at a time, or with one column of tiles two at a time, for two independent chains of MFMAs.
+    constexpr int kGroup = 2 / NTL, kGroups = (9 + kGroup - 1) / kGroup;
+    static_assert(kGroups % 2 == 1, "the fragments' sets change places from step to step");
+    bf8v a[2][kGroup][3], b[NTL][3];
+    auto fetch_a = [&](int set, int group, int f) {
+#pragma unroll
+        for (int k = 0; k < kGroup; ++k) {
+            const int tap = group * kGroup + k;
+            if (tap < 9) a[set][k][f] = frag(shX + at[tap / 3 % 3] + (tap % 3) * kPitchX + f * kPlaneX, kPitchX);
+        }
+    };
+    auto fetch_b = [&](uint32_t buf, int f) {
+#pragma unroll
+        for (int n = 0; n < NTL; ++n) b[n][f] = frag(shD[buf] + fD + n * 32 + f * kPlaneD, kPitchD);
+    };
+
+    // ---- the blocks that the first step needs, all requested before the first is waited for ----
+    {
+        constexpr int kMost = (int)kTapsAhead;
+        f4v first[kMost + 1], extra[kMost + 1];
+#pragma unroll
+        for (int i = 0; i <= kMost; ++i)
+            if ((uint32_t)i <= G.ahead) { request_x(); first[i] = RX; extra[i] = RE; }
+        request_d();
+        const f4v d0 = RD;
+        request_x();
+        request_d();
+        const f4v nextx = RX, nexte = RE, nextd = RD;
+#pragma unroll
+        for (int i = 0; i <= kMost; ++i)
+            if ((uint32_t)i <= G.ahead) {
+                put_x(slot_w, first[i]);
+                slot_w = ring(slot_w + kR32);
+                if (++bw == n_chunks) {
+                    bw = 0;
+                    if (G.extra) {
+                        if (wave == 0u && prow < G.extra) put_x(slot_w, extra[i]);
+                        slot_w = ring(slot_w + G.extra);
+                    }
                 }
-#pragma unroll
-                for (int k = 0; k < 4; ++k) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(x[k], d[k], sum, 0, 0, 0);
             }
+        RX = nextx; RE = nexte;
+        RD = d0;
+        put_d(0, sign * kUp);
+        RD = nextd;
+    }
+    __syncthreads();
+    place();
+    constexpr int kPa[6] = {2, 0, 1, 1, 0, 0}, kPb[6] = {0, 2, 1, 0, 1, 0};   // the smallest products first
+    constexpr int kOrder[3] = {2, 0, 1};                             // planes in the order in which the products use them
 #pragma unroll
-            for (int i = 0; i < 4; ++i) s4[i] = __builtin_fmaf(sum[i], sum[i], s4[i]);
-            g4 = g4 + sum;
-        }
+    for (int e = 0; e < 3; ++e) { fetch_a(0, 0, kOrder[e]); fetch_b(0, e); }
+
+    // Step q multiplies chunk q from D buffer q % 2 and takes in the next step's pixels and positions.  The fragments of the next
+    // tap are fetched during this one.  The one barrier of a step stands before its last tap: by then the wave has fetched all
+    // of the step's fragments and stored its share of the next step's input; the fragments of the next step's first tap follow.
+    // the sums, the products of a part, or the scaled result go here; the lane's output i of tile (t, n)
+    const bool direct = (splits <= (kWantG ? 2u : 1u) && split_p == 1);
+    const size_t JC = (size_t)J * C;
+    float* so = direct ? s_out : ws + (size_t)split * (kWantG ? 2 : 1) * JC;
+    float* go = direct ? g_out : ws + (size_t)split * 2 * JC + JC;
+    const float fs = direct ? cs : 1.0f, fg = direct ? cg : 1.0f;
+    const uint32_t out_ch = i0 + wc * 16u + 4u * (lane >> 4), out_col = c0 + wn * (uint32_t)(NTL * 16) + (lane & 15u);
+    auto each_out = [&](auto f) __attribute__((always_inline)) {
+        uint32_t ch = out_ch;
+        asm("" : "+v"(ch));                                          // or the addresses are kept in registers through the loop
 #pragma unroll
-        for (int i = 0; i < 4; ++i) {
-            const uint32_t row = jt + 4u * (lane >> 4) + (uint32_t)i;
-            if (row < J && col < C) {
-                const size_t o = (size_t)row * C + col;
-                __builtin_nontemporal_store(split_p > 1 ? sum[i] : fs * s4[i], so + o);
-                if (kWantG) __builtin_nontemporal_store(fg * g4[i], go + o);
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int n = 0; n < NTL; ++n)
+#pragma unroll
+                for (int i = 0; i < 4; ++i)
+                    if (ch + (uint32_t)i < G.Cin && out_col + (uint32_t)n * 16u < C)
+                        f(t, n, i, (size_t)((uint32_t)t * G.Cin + ch + (uint32_t)i) * C + out_col + (uint32_t)n * 16u);
+    };
+
+    f4v T[2][kGroup][NTL];                                           // this group's sums and those of the one before it
+    uint32_t left = split_p > 1 ? 0u : n_chunks;                     // steps until the sample's product is complete (0: never)
+    int32_t to_second = kWantG ? (int32_t)(z_of(2u * split + 1u) - z_begin) : 1;   // samples until the second group; then at most 0
+    // from four samples a group on, g is summed by groups too (16 samples in a row, 512 -> 512 at 7 x 7: error 9.3e-8, 8.2e-8 so; 6 us)
+    const bool halve_g = to_second >= 4;
+    for (uint32_t q0 = 0; q0 < total; q0 += 2) {
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+            if (u > 0 && q0 + (uint32_t)u >= total) break;
+            const bool last = --left == 0;
+            if (last) left = n_chunks;
+            auto add = [&](int group) {
+                const float turn = u ? -sign : sign;
+#pragma unroll
+                for (int k = 0; k < kGroup; ++k) {
+                    const int t = group * kGroup + k;
+                    if (t >= 9) break;
+                    f4v (&V)[NTL] = T[group & 1][k];
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n)
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) acc[t][n][i] = __builtin_fmaf(V[n][i], turn, acc[t][n][i]);
+                    if (!last) continue;
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) {
+#pragma unroll
+                        for (int i = 0; i < 4; ++i) {
+                            const float x = acc[t][n][i] * kDown;
+                            s_acc[t][n][i] = __builtin_fmaf(x, x, s_acc[t][n][i]);
+                            if (kWantG) g_acc[t][n][i] += x;
+                        }
+                        acc[t][n] = (f4v){0};
+                    }
+                }
+            };
+#pragma unroll
+            for (int h = 0; h < kGroups; ++h) {
+                const int set = (h + u) & 1;
+                if (h == kGroups / 3) stage_x();
+                if (h == kGroups * 2 / 3) { put_d(u ^ 1u, (u ? sign : -sign) * kUp); request_d(); }
+                if (h == kGroups - 1) {
+                    slot_r += kR32;
+                    if (++br == n_chunks) { br = 0; slot_r += G.extra; }
+                    slot_r = ring(slot_r);
+                    place();
+                    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+                    __builtin_amdgcn_s_barrier();
+                    asm volatile("" ::: "memory");
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                f4v (&V)[kGroup][NTL] = T[h & 1];
+#pragma unroll
+                for (int k = 0; k < kGroup; ++k)
+#pragma unroll
+                    for (int n = 0; n < NTL; ++n) V[k][n] = (f4v){0};
+#pragma unroll
+                for (int e = 0; e < 6; ++e) {
+#pragma unroll
+                    for (int k = 0; k < kGroup; ++k)
+#pragma unroll
+                        for (int n = 0; n < NTL; ++n)
+                            if (h * kGroup + k < 9) V[k][n] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[set][k][kPa[e]], b[n][kPb[e]], V[k][n], 0, 0, 0);
+                    if (e < 3) fetch_a(set ^ 1, h == kGroups - 1 ? 0 : h + 1, kOrder[e]);
+                    if (h == kGroups - 1) {                          // each plane of the positions after its last use
+                        if (e == 1) fetch_b(u ^ 1u, 2);
+                        if (e == 4) fetch_b(u ^ 1u, 1);
+                        if (e == 5) fetch_b(u ^ 1u, 0);
+                    }
+                    __builtin_amdgcn_sched_barrier(0);
+                    // a group's sums are added while the next one's products run
+                    if (e == 2 && h > 0) { add(h - 1); __builtin_amdgcn_sched_barrier(0); }
+                }
+            }
+            add(kGroups - 1);
+            if (kWantG && last && --to_second == 0) {                // the first group's sums of s wait in LDS, those of g in memory
+#pragma unroll
+                for (int t = 0; t < 9; ++t) { shS[t * 512 + tid] = s_acc[t][0]; s_acc[t][0] = (f4v){0}; }
+                if (halve_g) {
+                    each_out([&](int t, int n, int i, size_t o) { go[o] = g_acc[t][n][i]; });
+#pragma unroll
+                    for (int t = 0; t < 9; ++t) g_acc[t][0] = (f4v){0};
+                }
             }
         }
+    }
+
+    if (kWantG && to_second <= 0) {
+#pragma unroll
+        for (int t = 0; t < 9; ++t) s_acc[t][0] = shS[t * 512 + tid] + s_acc[t][0];
+        if (halve_g) each_out([&](int t, int n, int i, size_t o) { g_acc[t][n][i] = go[o] + g_acc[t][n][i]; });
+    }
+    each_out([&](int t, int n, int i, size_t o) {
+        const float out = split_p > 1 ? kDown * acc[t][n][i] : fs * s_acc[t][n][i];
+        if (direct) __builtin_nontemporal_store(out, so + o);
+        else so[o] = out;                                            // read again at once by the reduction
+        if (kWantG) {
+            if (direct) __builtin_nontemporal_store(fg * g_acc[t][n][i], go + o);
+            else go[o] = fg * g_acc[t][n][i];
+        }
+    });
+    uint32_t again = 0;                                              // one bit per tile with a sum that is not finite
+#pragma unroll
+    for (int t = 0; t < 9; ++t)
+#pragma unroll
+        for (int n = 0; n < NTL; ++n) {
+            uint32_t most = 0;
+#pragma unroll
+            for (int i = 0; i < 4; ++i) most = max(most, __float_as_uint(split_p > 1 ? acc[t][n][i] : s_acc[t][n][i]) & 0x7FFFFFFFu);
+            again |= (__ballot(most >= 0x7F800000u) ? 1u : 0u) << (t * NTL + n);
+        }
+    if (again == 0) return;
+    const uint32_t q_begin = c_begin * kR32, q_end = min((uint32_t)(G.H * Wp), split_p > 1 ? (c_begin + total) * kR32 : G.H * Wp);
+#pragma unroll 1
+    for (; again; again &= again - 1u) {
+        const uint32_t tile = (uint32_t)__builtin_ctz(again), t = tile / NTL, n = tile % NTL, ky = t / 3u, kx = t - 3u * ky;
+        const uint32_t chm = i0 + wc * 16u, colm = c0 + wn * (uint32_t)(NTL * 16) + n * 16u, ch = chm + (lane & 15u), col = colm + (lane & 15u);
+        form_again<kWantG>(
+            [&](uint32_t z, uint32_t q) -> float {
+                const uint32_t y = q / Wp, x = q - y * Wp, iy = y + ky - 1u, ix = x + kx - 1u;
+                return ch < G.Cin && q < q_end && x < G.W && iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + ch] : 0.f;
+            },
+            [&](uint32_t z, uint32_t q) -> float {
+                const uint32_t y = q / Wp, x = q - y * Wp;
+                return col < C && q < q_end && x < G.W ? D[(((size_t)z * G.H + y) * G.W + x) * C + col] : 0.f;
+            },
+            [&](uint32_t r) { return chm + r < G.Cin && col < C; },
+            [&](uint32_t r) -> size_t { return (size_t)(t * G.Cin + chm + r) * C + col; },
+            z_begin, z_end, q_begin, q_end, split_p > 1, fs, fg, so, go);
     }
 }
 
@@ -478,27 +889,29 @@ static uint64_t conv_f32_slots(const F32Tile& t) {
 }
 
 // How a shape's work is divided: the samples over `splits` workgroups per tile, or (split_p > 1) every sample's positions
-// over split_p of them, for `slots` workgroups at once and chunks of `chunk` positions.  most: bytes of workspace.
+// over split_p of them, for `slots` workgroups at once and chunks of `chunk` positions.  most: bytes of workspace; pairs: a
+// split of the samples leaves one plane of [J, C] in it, or with g a pair of them two (see k_conv_taps_f32), else each two.
 struct F32Split { uint32_t splits, split_p; };
-static size_t f32_split_bytes(const F32Split& r, uint32_t J, uint32_t C) {
+static size_t f32_split_bytes(const F32Split& r, uint32_t J, uint32_t C, bool pairs) {
     const size_t JC = (size_t)J * C * sizeof(float);
-    return r.split_p > 1 ? (size_t)r.splits * JC : r.splits > 1 ? (size_t)r.splits * 2 * JC : 0;
+    return r.split_p > 1 ? (size_t)r.splits * JC : r.splits > 1 ? (size_t)(pairs ? r.splits + r.splits % 2 : r.splits * 2) * JC : 0;
 }
-static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32_t B, uint32_t P, uint32_t J, uint32_t C, size_t most) {
+static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32_t B, uint32_t P, uint32_t J, uint32_t C, size_t most,
+                          bool pairs = false) {
     const uint32_t n_chunks = (P + chunk - 1) / chunk;
     F32Split r{1, 1};
     if (tiles * B * 3 <= slots * 2 && n_chunks >= 256u / chunk) {
         // up to half a round: as many parts as fill one round; up to two thirds: just under two rounds
         const uint64_t sp = tiles * B * 2 <= slots ? slots / (tiles * B) : 2 * slots / (tiles * B);
         r.split_p = (uint32_t)(sp < n_chunks * chunk / 128u ? sp : n_chunks * chunk / 128u);
-        while (r.split_p > 1 && f32_split_bytes(F32Split{B * r.split_p, r.split_p}, J, C) > most) --r.split_p;
+        while (r.split_p > 1 && f32_split_bytes(F32Split{B * r.split_p, r.split_p}, J, C, pairs) > most) --r.split_p;
         if (r.split_p > 1) { r.splits = B * r.split_p; return r; }
         r.split_p = 1;
     }
     double best = 1e300;
     for (uint32_t s = 1; s <= B; ++s) {
         const uint32_t zper = (B + s - 1) / s, s2 = (B + zper - 1) / zper;
-        if (s2 != s || f32_split_bytes(F32Split{s, 1}, J, C) > most) continue;
+        if (s2 != s || f32_split_bytes(F32Split{s, 1}, J, C, pairs) > most) continue;
         const uint64_t rounds = (tiles * s2 + slots - 1) / slots;
         const double cost = (double)rounds * zper + (s2 > 1 ? 0.5 * s2 * (double)tiles / slots + 0.5 : 0.0);
         if (cost < best - 1e-9) { best = cost; r.splits = s2; }
@@ -511,7 +924,7 @@ static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32
 size_t conv_f32_workspace_bytes(uint32_t B, uint32_t P, uint32_t J, uint32_t C) {
     const F32Tile t = conv_f32_tile(J, C);
     const uint64_t slots = 256 * (t.bm + t.bn == 256 ? 2 : t.bm + t.bn == 192 ? 4 : 6);
-    return f32_split_bytes(f32_split(conv_f32_tiles(t, J, C), slots, 16, B, P, J, C, ~(size_t)0), J, C);
+    return f32_split_bytes(f32_split(conv_f32_tiles(t, J, C), slots, 16, B, P, J, C, ~(size_t)0), J, C, false);
 }
 
 template <int kMode>
@@ -555,6 +968,63 @@ static int launch_conv_f32_any(const void* X, const void* D, uint32_t B, uint32_
     return hip_check(hipGetLastError(), "launch k_conv_f32");
 }
 
+// ---- 3 x 3, unit stride, padding 1: k_conv_taps_f32 ----
+static TapsGeom taps_geom(uint32_t H, uint32_t W, uint32_t Cin) {
+    const uint32_t span = H * (W + 1) - 1, lead = W + 2;                 // from the first to the last pixel; zeros needed between samples
+    TapsGeom G{H, W, Cin, (span + kR32 - 1) / kR32, 0, (2 * lead + kR32 - 1) / kR32};
+    const uint32_t room = G.n_chunks * kR32;
+    if (span + lead > room) {
+        if (span + lead - room <= 4) G.extra = span + lead - room;       // (14 x 14: 225 and 224)
+        else G.n_chunks = (span + lead + kR32 - 1) / kR32;
+    }
+    return G;
+}
+// About how long a shape takes, in us: 3.5 and rounds of workgroups, each of which begins and ends in 6.5 and takes `step` a chunk, and
+// the planes of a split, written and read again at 5 TB/s with a launch of 4.
+static double f32_us(uint64_t tiles, uint64_t slots, uint32_t n_chunks, double step, uint32_t B, const F32Split& s, uint32_t J, uint32_t C) {
+    const uint64_t rounds = (tiles * s.splits + slots - 1) / slots;
+    const uint64_t chunks = s.split_p > 1 ? (n_chunks + s.split_p - 1) / s.split_p : (uint64_t)((B + s.splits - 1) / s.splits) * n_chunks;
+    return 3.5 + (double)rounds * (6.5 + (double)chunks * step) + (s.splits > 1 ? 4.0 + (double)s.splits * J * C * 8.0 / 5e6 : 0.0);
+}
+
+// 0 or an error: launched; 1: k_conv_f32 takes the shape.  Which of the two is faster follows from that estimate, whose steps
+// were measured: 1.45 us a chunk with 128 x 128 tiles, 1.55 with two workgroups of half of that per compute unit, 2.35 for the
+// 576 x 64 of k_conv_taps_f32.  Estimated and measured times, k_conv_f32 / k_conv_taps_f32, batch 32: 512 channels at 7 x 7
+// 118 / 67 and 104 / 68; 256 at 14 x 14 71 / 62 and 67 / 58; 128 at 28 x 28 90 / 62 and 81 / 55; 64 at 56 x 56 71 / 65 and 69 / 58; what goes to
+// k_conv_f32: 256 at 14 x 14, batch 33 71 / 74 and 63 / 67; 192 -> 160 at 14 x 14 51 / 54 and 50 / 51; 256 at 8 x 8, batch 64
+// 50 / 57 and 47 / 57; 128 at 14 x 14, batch 7 26 / 32 and 21 / 28.  With g, which has to take the same way, so that s is the same, the
+// shapes above that come here gain as much or more (256 at 14 x 14, the least, 70 and 67).
+static int launch_conv_taps_f32(const void* X, const void* D, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, float c,
+                                float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+    if (W > kTapsMaxW || H * W <= kR32 / 2) return 1;
+    const TapsGeom G = taps_geom(H, W, Cin);
+    const uint32_t J = 9 * Cin, P = H * W, tiles_i = (Cin + 63) / 64;
+    const uint64_t tiles = (uint64_t)tiles_i * ((C + 63) / 64);
+    const F32Tile t = conv_f32_tile(J, C);
+    const size_t JC = (size_t)J * C, asked = conv_f32_workspace_bytes(B, P, J, C);
+    const bool space = workspace && workspace_bytes >= asked;
+    const F32Split none{1, 1}, sp = space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, asked, true) : none;
+    const F32Split other = space ? f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked) : none;
+    if (f32_us(tiles, 256, G.n_chunks, 2.35, B, sp, J, C) >
+        0.94 * f32_us(conv_f32_tiles(t, J, C), conv_f32_slots(t), (P + kR32 - 1) / kR32, t.bm + t.bn == 256 ? 1.45 : 1.55, B, other, J, C))
+        return 1;
+    const bool with_g = g_out && sp.split_p == 1;
+    const uint32_t blocks = with_g ? (sp.splits + 1) / 2 : sp.splits;
+    const uint64_t nblk = (uint64_t)(with_g ? (Cin + 31) / 32 : tiles_i) * ((C + 63) / 64) * blocks;
+    if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
+    const float cg = c, cs = c * c;
+    float* ws = static_cast<float*>(workspace);
+#define VGC_LAUNCH_TAPS(G_)                                                                                                \
+    hipLaunchKernelGGL((k_conv_taps_f32<G_>), dim3((uint32_t)nblk), dim3(512), 0, stream, static_cast<const float*>(X), \
+                       static_cast<const float*>(D), B, C, sp.splits, sp.split_p, cg, cs, g_out, s_out, ws, G)
+    if (with_g) VGC_LAUNCH_TAPS(true);
+    else VGC_LAUNCH_TAPS(false);
+#undef VGC_LAUNCH_TAPS
+    if (sp.split_p > 1) launch_sqgrad_reduce_parts(ws, B, sp.split_p, JC, cg, cs, g_out, s_out, stream);
+    else if (blocks > 1) launch_sqgrad_reduce(ws, blocks, JC, cg, cs, g_out, s_out, stream, with_g ? ReducePlanes::kPairsDone : ReducePlanes::kPairs);
+    return hip_check(hipGetLastError(), "launch k_conv_taps_f32");
+}
+
 int launch_conv_f32_tiled(const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
                           float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
     return launch_conv_f32_any<kPatches>(X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, ConvGeom{}, stream);
@@ -562,6 +1032,10 @@ int launch_conv_f32_tiled(const void* X, const void* D, uint32_t B, uint32_t P, 
 
 int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
                       float* g_out, float* s_out, void* workspace, size_t workspace_bytes, ConvGeom G, hipStream_t stream) {
+    if (G.kw == 3 && J == 9 * G.Cin && G.sh == 1 && G.sw == 1 && G.ph == 1 && G.pw == 1) {
+        const int rc = launch_conv_taps_f32(act, D, B, G.H, G.W, G.Cin, C, c, g_out, s_out, workspace, workspace_bytes, stream);
+        if (rc <= 0) return rc;
+    }
     if (G.sh == 1 && G.sw == 1 && G.Wo == G.W && P > kR32 / 2) {
         uint32_t a = G.W, b = kR32 % G.W;
         while (b) { const uint32_t m = a % b; a = b; b = m; }

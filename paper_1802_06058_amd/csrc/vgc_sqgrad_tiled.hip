@@ -478,7 +478,8 @@ template <int kV> __device__ __forceinline__ void store_vec(float* p, const Floa
 // Adds the per-split partial sums in a fixed order and applies the scale factors.  `lanes` (1 or 4) threads
 // share kV consecutive outputs: thread (outputs, lane q) takes splits q, q + lanes, ..., and the lanes' sums are
 // added in lane order.  A workgroup owns 256 / lanes * kV consecutive outputs; JC is a multiple of kV.
-template <int kV>
+// kPairs: the planes are those of s alone, and two neighbours are added to each other first.
+template <int kV, bool kPairs>
 __global__ __launch_bounds__(256) void k_sqgrad_reduce(const float* __restrict__ ws, uint32_t splits, size_t JC,
                                                        float cg, float cs, float* __restrict__ g_out,
                                                        float* __restrict__ s_out, uint32_t lanes) {
@@ -487,7 +488,15 @@ __global__ __launch_bounds__(256) void k_sqgrad_reduce(const float* __restrict__
     const size_t i = ((size_t)blockIdx.x * opb + il) * kV;
     FloatVec<kV> s = {}, g = {};
     if (i < JC) {
-        for (uint32_t k = q; k < splits; k += lanes) {
+        for (uint32_t k = q; kPairs && k < splits / 2; k += lanes) {
+            const FloatVec<kV> a = load_vec<kV>(ws + (size_t)k * 2 * JC + i), b = load_vec<kV>(ws + (size_t)k * 2 * JC + JC + i);
+            for (int e = 0; e < kV; ++e) s.v[e] += a.v[e] + b.v[e];
+        }
+        if (kPairs && (splits & 1u) && splits / 2 % lanes == q) {
+            const FloatVec<kV> a = load_vec<kV>(ws + (size_t)(splits - 1u) * JC + i);
+            for (int e = 0; e < kV; ++e) s.v[e] += a.v[e];
+        }
+        for (uint32_t k = q; !kPairs && k < splits; k += lanes) {
             const FloatVec<kV> ps = load_vec<kV>(ws + (size_t)k * 2 * JC + i);
             for (int e = 0; e < kV; ++e) s.v[e] += ps.v[e];
             if (g_out) {
@@ -522,7 +531,7 @@ static ConvTile conv_tile(uint32_t J, uint32_t C) {
 
 // Sums the parts of every sample's product, then squares and sums over the samples, in a fixed order: a
 // workgroup owns 16 kV consecutive outputs; thread (outputs, lane q) takes samples q, q + 16, ..., and the 16
-// lanes' sums are added in lane order.  JC is a multiple of kV.
+// lanes' sums are added by fours, in lane order.  JC is a multiple of kV.
 template <int kV>
 __global__ __launch_bounds__(256) void k_sqgrad_reduce_parts(const float* __restrict__ ws, uint32_t B, uint32_t split_p, size_t JC,
                                                              float cg, float cs, float* __restrict__ g_out,
@@ -547,8 +556,11 @@ __global__ __launch_bounds__(256) void k_sqgrad_reduce_parts(const float* __rest
     __syncthreads();
     if (q == 0 && i < JC) {
         FloatVec<kV> st = {}, gt = {};
-        for (int k = 0; k < 16; ++k)
-            for (int e = 0; e < kV; ++e) { st.v[e] += sh_s[k][il].v[e]; gt.v[e] += sh_g[k][il].v[e]; }
+        for (int k = 0; k < 16; k += 4)                  // (by fours: half the roundings that a sum meets in a row)
+            for (int e = 0; e < kV; ++e) {
+                st.v[e] += (sh_s[k][il].v[e] + sh_s[k + 1][il].v[e]) + (sh_s[k + 2][il].v[e] + sh_s[k + 3][il].v[e]);
+                gt.v[e] += (sh_g[k][il].v[e] + sh_g[k + 1][il].v[e]) + (sh_g[k + 2][il].v[e] + sh_g[k + 3][il].v[e]);
+            }
         for (int e = 0; e < kV; ++e) { st.v[e] *= cs; gt.v[e] *= cg; }
         store_vec<kV>(s_out + i, st);
         if (g_out) store_vec<kV>(g_out + i, gt);
@@ -637,15 +649,17 @@ void launch_sqgrad_reduce_parts(const float* ws, uint32_t B, uint32_t split_p, s
 }
 
 void launch_sqgrad_reduce(const float* ws, uint32_t splits, size_t JC, float cg, float cs, float* g_out, float* s_out,
-                          hipStream_t stream) {
-    const uint32_t lanes = splits <= 4 ? 1u : 4u;        // (16 lanes for more than 16 splits read 256-byte runs: 15 against 12.5 us on 32 planes of 1 MB)
+                          hipStream_t stream, ReducePlanes planes) {
+    const bool pairs = planes == ReducePlanes::kPairs;
+    const uint32_t sums = pairs ? (splits + 1) / 2 : splits, lanes = sums <= (planes == ReducePlanes::kSplits ? 4u : 2u) ? 1u : 4u;        // (16 lanes for more than 16 splits read 256-byte runs: 15 against 12.5 us on 32 planes of 1 MB)
     const uint32_t opb = 256u / lanes;
-    if (reduce_vec4(ws, JC, g_out, s_out))
-        hipLaunchKernelGGL(k_sqgrad_reduce<4>, dim3((uint32_t)((JC / 4 + opb - 1) / opb)), dim3(256), 0, stream, ws, splits, JC, cg,
-                           cs, g_out, s_out, lanes);
-    else
-        hipLaunchKernelGGL(k_sqgrad_reduce<1>, dim3((uint32_t)((JC + opb - 1) / opb)), dim3(256), 0, stream, ws, splits, JC, cg, cs,
-                           g_out, s_out, lanes);
+    const bool vec = reduce_vec4(ws, JC, g_out, s_out);
+    const dim3 grid((uint32_t)(((vec ? JC / 4 : JC) + opb - 1) / opb));
+#define VGC_REDUCE(V_, PAIRS_) hipLaunchKernelGGL((k_sqgrad_reduce<V_, PAIRS_>), grid, dim3(256), 0, stream, ws, splits, JC, cg, cs, g_out, s_out, lanes)
+    if (vec) { if (pairs) VGC_REDUCE(4, true); else VGC_REDUCE(4, false); }
+    else if (pairs) VGC_REDUCE(1, true);
+    else VGC_REDUCE(1, false);
+#undef VGC_REDUCE
 }
 
 // ------------------------------------------------------------------------------------------------
