@@ -174,8 +174,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     // the thread's pieces lie in the same columns, kRowStep rows apart
     constexpr uint32_t kRowStepA = NT / (BM / 4), kRowStepB = NT / (BN / 4);
     const uint32_t rowA = tid / (BM / 4), rowB = tid / (BN / 4), colj = j0 + (tid % (BM / 4)) * 4u;
-    const uint32_t offB = (rowB * C + c0 + (tid % (BN / 4)) * 4u) * 4u;
-    uint32_t offA = (rowA * J + colj) * 4u, offA0 = 0, rowsA = kRowStepA * J * 4u, phase = 0;
+    const uint32_t offB0 = (rowB * C + c0 + (tid % (BN / 4)) * 4u) * 4u;
+    uint32_t offA = 0, offA0 = (rowA * J + colj) * 4u, rowsA = kRowStepA * J * 4u, phase = 0;
     uint32_t y0A[PA], x0A[PA], yA[PA], xA[PA], outside[PA];
     int32_t tapX = 0, tapOff = 0;
     if (kMode != kPatches) {
@@ -209,29 +209,32 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         }
     }
     Chunk32<PA, PB> R;
-    uint32_t zl = z_begin, pcl = c_begin, issued = 0;
-    // request of piece i of chunk (zl, pcl) (pieces of A, then those of B); past the last chunk the range is empty
+    // The operands of the sample that is requested, kept as descriptors: formed per piece they were a quarter of the loop's
+    // instructions.  `to_event` chunks from now the requests leave the sample, or the last chunk has been requested.
+    const uint32_t bytesA = kMode == kPatches ? P * J * 4u : G.H * G.W * G.Cin * 4u, bytesB = P * C * 4u;
+    const uint32_t stepA = (kMode == kPatches ? J : G.Cin) * (kR32 * 4u), stepB = C * (kR32 * 4u);
+    uint32_t zl = z_begin, todo = total, to_event = min(n_chunks - c_begin, total);
+    auto operand = [&](const float* base, uint32_t bytes, uint32_t z, bool live) {
+        return make_rsrc(base + (size_t)z * (bytes / 4u), live ? bytes : 0u);
+    };
+    rsrc_t ra = operand(X, bytesA, z_begin, total > 0u), rb = operand(D, bytesB, z_begin, total > 0u);
+    uint32_t offB = offB0 + c_begin * stepB;
+    if (kMode == kPatches) offA = offA0 + c_begin * stepA;
+    // request of piece i of the chunk (pieces of A, then those of B); past the last chunk the range is empty
     auto issue_piece = [&](int i) {
-        const bool live = issued < total;
-        const uint32_t zz = live ? zl : z_begin;
         if (i >= PA) {
-            const rsrc_t rb = make_rsrc(D + ((size_t)zz * P + pcl * kR32) * C, live ? (P - pcl * kR32) * C * 4u : 0u);
             const uint32_t voff = offB + (uint32_t)(i - PA) * (kRowStepB * C * 4u);
             R.b[i < PA ? 0 : i - PA] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)voff, 0, 0));
             return;
         }
         const int ia = i < PA ? i : 0;
-        rsrc_t ra;
         uint32_t voff;
         if (kMode == kPatches) {
-            ra = make_rsrc(X + ((size_t)zz * P + pcl * kR32) * J, live ? (P - pcl * kR32) * J * 4u : 0u);
             voff = offA + (uint32_t)ia * rowsA;
         } else {
             // rows of the input outside the image give an offset that is negative or past the sample: the load answers with
             // zeros; columns outside are masked (as are positions past P in the general mode; in the linear one they alias
             // into pixels of the sample, where the rows of D read as zeros)
-            const uint32_t sample = G.H * G.W * G.Cin;
-            ra = make_rsrc(X + (size_t)zz * sample, live ? sample * 4u : 0u);
             if (kMode == kLinear) {
                 voff = (offA + (uint32_t)ia * rowsA) | (uint32_t)__builtin_amdgcn_sbfe((int32_t)outside[ia], phase, 1u);
             } else {
@@ -244,23 +247,33 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         R.a[ia] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)voff, 0, 0));
     };
     auto issue_done = [&]() {                                     // every piece of the chunk is requested: on to the next
-        const bool wrap = (++pcl == n_chunks);
-        if (wrap) { pcl = 0; ++zl; }
-        if (kMode == kLinear) {
-            offA = wrap ? offA0 : offA + kR32 * G.Cin * 4u;
-            phase = wrap || phase + 1u == G.period ? 0u : phase + 1u;
-        }
+        offB += stepB;
+        if (kMode != kGeneral) offA += stepA;
+        if (kMode == kLinear) phase = phase + 1u == G.period ? 0u : phase + 1u;
+        const bool event = --to_event == 0u;
         if (kMode == kGeneral && !kFew) {
 #pragma unroll
             for (int i = 0; i < PA; ++i) {                        // the row of the next chunk: kR32 positions further
                 const uint32_t x = xA[i] + G.step_x, xw = x - G.Wo;
-                const uint32_t carry = x >= G.Wo ? 1u : 0u;
-                const uint32_t keep = wrap ? 0u : 0xFFFFFFFFu;
-                xA[i] = (min(x, xw) & keep) | (x0A[i] & ~keep);
-                yA[i] = ((yA[i] + G.step_y + carry) & keep) | (y0A[i] & ~keep);
+                yA[i] += G.step_y + (x >= G.Wo ? 1u : 0u);
+                xA[i] = min(x, xw);
             }
         }
-        ++issued;
+        if (event) {
+            todo -= min(todo, n_chunks);                          // (a part of a sample is within one)
+            offB = offB0;
+            if (kMode != kGeneral) offA = offA0;
+            phase = 0;
+            if (kMode == kGeneral) {
+#pragma unroll
+                for (int i = 0; i < PA; ++i) { xA[i] = x0A[i]; yA[i] = y0A[i]; }
+            }
+            ++zl;
+            const bool live = todo > 0u;
+            to_event = live ? min(n_chunks, todo) : 0x7FFFFFFFu;
+            ra = operand(X, bytesA, live ? zl : z_begin, live);
+            rb = operand(D, bytesB, live ? zl : z_begin, live);
+        }
     };
     // piece i of the requested chunk (those of A, then those of B); rows kRowStep apart differ in the swizzle by a constant
     static_assert(kRowStepA % 8 == 0 && kRowStepB % 8 == 0, "the low bits of the row are the thread's own");
