@@ -54,6 +54,11 @@ __device__ __forceinline__ void split_pair(float x0, float x1, uint32_t& hi, uin
     lo = __builtin_amdgcn_perm(__float_as_uint(l1), __float_as_uint(l0), 0x07060302u);
 }
 
+// The first sample of group k of `groups`: k B / groups (in 32 bits where that is enough: a division of 64 takes a workgroup 0.2 us).
+__device__ __forceinline__ uint32_t first_sample(uint32_t k, uint32_t B, uint32_t groups) {
+    return B < 65536u ? k * B / groups : (uint32_t)((uint64_t)k * B / groups);
+}
+
 // One staged chunk in registers: kR32 rows of a BM-wide and of a BN-wide float matrix, PA resp. PB 16-byte
 // pieces per thread of a workgroup of NT threads.  Piece idx of an operand W columns wide sits in row
 // idx / (W / 4), columns 4 (idx % (W / 4)) .. + 3.
@@ -133,7 +138,7 @@ enum { kPatches = 0, kLinear = 1, kGeneral = 2 };
 // half the elements to cut of a chunk padded to 32 positions: 3 x 3, 512 -> 512 at 4 x 4, batch 64: 89 -> 53 us (80 with the
 // float32 instruction); one position, 512 -> 512, batch 32, without a workspace: 51 -> 32.5 (33).
 template <bool kWantG, int kMode, int BM, int BN, int WM, int WN, bool kFew>
-__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, 2)
+__global__ __launch_bounds__((BM / WM) * (BN / WN) * 64, kFew && !kWantG ? 4 : 2)      // (one register above 128: 512 -> 512 at 4 x 4 53 -> 64 us)
 void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32_t B, uint32_t P, uint32_t J, uint32_t C,
                 uint32_t splits, uint32_t split_p, float cg, float cs, float* __restrict__ g_out, float* __restrict__ s_out,
                 float* __restrict__ ws, ConvGeom G) {
@@ -161,8 +166,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     const uint32_t chunks_per_part = (n_chunks + split_p - 1) / split_p;
     const uint32_t c_begin = min(n_chunks, part * chunks_per_part);
     // sample ranges of the splits differ by at most one sample
-    const uint32_t z_begin = split_p > 1 ? split / split_p : (uint32_t)((uint64_t)split * B / splits);
-    const uint32_t z_end = split_p > 1 ? z_begin + 1u : (uint32_t)((uint64_t)(split + 1u) * B / splits);
+    const uint32_t z_begin = split_p > 1 ? split / split_p : first_sample(split, B, splits);
+    const uint32_t z_end = split_p > 1 ? z_begin + 1u : first_sample(split + 1u, B, splits);
     const uint32_t total = split_p > 1 ? min(n_chunks, c_begin + chunks_per_part) - c_begin : (z_end - z_begin) * n_chunks;
 
     f4v acc[MT][NTL], s_acc[MT][NTL], g_acc[MT][NTL];
@@ -196,7 +201,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
             outside[i] = 0;
             for (uint32_t k = 0; k < G.period; ++k) {
                 outside[i] |= ((uint32_t)((int32_t)x + tapX) < G.W ? 0u : 1u) << k;
-                x = (x + kR32) % G.W;
+                x += G.step_x;                                       // kR32 modulo W
+                x = min(x, x - G.W);
             }
         }
     }
@@ -221,10 +227,10 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     uint32_t offB = offB0 + c_begin * stepB;
     if (kMode == kPatches) offA = offA0 + c_begin * stepA;
     // request of piece i of the chunk (pieces of A, then those of B); past the last chunk the range is empty
-    auto issue_piece = [&](int i) {
+    auto issue_into = [&](Chunk32<PA, PB>& Q, int i) {
         if (i >= PA) {
             const uint32_t voff = offB + (uint32_t)(i - PA) * (kRowStepB * C * 4u);
-            R.b[i < PA ? 0 : i - PA] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)voff, 0, 0));
+            Q.b[i < PA ? 0 : i - PA] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(rb, (int)voff, 0, 0));
             return;
         }
         const int ia = i < PA ? i : 0;
@@ -244,7 +250,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
                 voff = ((uint32_t)off << 2) | (inside ? 0u : 0xFFFFFFFFu);
             }
         }
-        R.a[ia] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)voff, 0, 0));
+        Q.a[ia] = __builtin_bit_cast(f4v, __builtin_amdgcn_raw_buffer_load_b128(ra, (int)voff, 0, 0));
     };
     auto issue_done = [&]() {                                     // every piece of the chunk is requested: on to the next
         offB += stepB;
@@ -280,8 +286,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
     const uint32_t toA = lds_piece<BM>(rowA, (tid % (BM / 4)) * 4u), toB = lds_piece<BN>(rowB, (tid % (BN / 4)) * 4u);
     u2v sh_, sm_, sl_;                                               // the piece's three planes
     // half h of piece i: two of its four columns; the second half stores the piece and requests the next chunk's
-    auto stage_half = [&](uint32_t buf, int i, int h) {                // buf: the parity of the chunk
-        const f4v x = i < PA ? R.a[i < PA ? i : 0] : R.b[i < PA ? 0 : i - PA];
+    auto stage_half = [&](uint32_t buf, int i, int h, const Chunk32<PA, PB>& Q, bool next) {     // buf: the parity of the chunk
+        const f4v x = i < PA ? Q.a[i < PA ? i : 0] : Q.b[i < PA ? 0 : i - PA];
         const float up = i < PA && buf ? -kUp : kUp;
         uint32_t a, b, c;
         split_pair(x[2 * h] * up, x[2 * h + 1] * up, a, b, c);
@@ -294,7 +300,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         *reinterpret_cast<u2v*>(p) = sh_;
         *reinterpret_cast<u2v*>(p + plane) = sm_;
         *reinterpret_cast<u2v*>(p + 2 * plane) = sl_;
-        issue_piece(i);
+        if (next) issue_into(R, i);
     };
     constexpr int kValu = 10;                                        // vector instructions after an MFMA; 4, 7 and 10: 2.265, 2.257, 2.260 ms
     constexpr int kHalves = 2 * (PA + PB), kSlots = 3 * MT;          // a chunk's staging is dealt out over so many places in the loop
@@ -302,7 +308,7 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         // (from and to by arithmetic, so that the unrolled loop has one or two turns and every index is a constant)
         const int from = (s * kHalves + kSlots - 1) / kSlots, to = ((s + 1) * kHalves + kSlots - 1) / kSlots;
 #pragma unroll
-        for (int k = from; k < to; ++k) stage_half(buf, k >> 1, k & 1);
+        for (int k = from; k < to; ++k) stage_half(buf, k >> 1, k & 1, R, true);
         if (s == kSlots - 1) issue_done();
     };
 
@@ -319,11 +325,18 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         return __builtin_bit_cast(bf8v, v);
     };
 
+    // the first two chunks are requested before the first is waited for
+    {
+        Chunk32<PA, PB> first;
 #pragma unroll
-    for (int i = 0; i < PA + PB; ++i) issue_piece(i);
-    issue_done();
+        for (int i = 0; i < PA + PB; ++i) issue_into(first, i);
+        issue_done();
 #pragma unroll
-    for (int s = 0; s < kSlots; ++s) stage_slot(0, s);
+        for (int i = 0; i < PA + PB; ++i) issue_into(R, i);
+        issue_done();
+#pragma unroll
+        for (int k = 0; k < kHalves; ++k) stage_half(0, k >> 1, k & 1, first, false);
+    }
 #pragma unroll
     for (int s = 0; s < 3; ++s) stage_slot(1, s);
     __syncthreads();
@@ -531,7 +544,7 @@ void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, u
     const uint32_t part = split_p > 1 ? split % split_p : 0u;
     const uint32_t chunks_per_part = (n_chunks + split_p - 1) / split_p;
     const uint32_t c_begin = min(n_chunks, part * chunks_per_part);
-    const auto z_of = [&](uint32_t g) { return (uint32_t)((uint64_t)min(g, splits) * B / splits); };
+    const auto z_of = [&](uint32_t g) { return first_sample(min(g, splits), B, splits); };
     const uint32_t z_begin = split_p > 1 ? split / split_p : z_of(kWantG ? 2u * split : split);
     const uint32_t z_end = split_p > 1 ? z_begin + 1u : z_of(kWantG ? 2u * split + 2u : split + 1u);
     const uint32_t total = split_p > 1 ? min(n_chunks, c_begin + chunks_per_part) - c_begin : (z_end - z_begin) * n_chunks;
@@ -1053,6 +1066,7 @@ int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, ui
         uint32_t a = G.W, b = kR32 % G.W;
         while (b) { const uint32_t m = a % b; a = b; b = m; }
         G.period = G.W / a;
+        G.step_x = kR32 % G.W;
         if (G.period <= 32) return launch_conv_f32_any<kLinear>(act, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, G, stream);
     }
     G.step_y = kR32 / G.Wo;
