@@ -32,7 +32,7 @@ __device__ __forceinline__ uint32_t encode_tile(const TileHdr* __restrict__ hdrs
     const uint32_t hw = (lane < 8) ? hdrs[t].w[lane] : 0u;
     uint32_t w[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__shfl((int)hw, i);
+    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)hw, i);
     if ((w[7] & 0xFFFFu) == 0) return 0;                       // nothing kept
     found();
     const uint32_t cnt = min((w[0] & 0xFFFFu) + (w[0] >> 16) + (w[1] & 0xFFFFu) + (w[1] >> 16) + (w[2] & 0xFFFFu) +
@@ -64,7 +64,7 @@ __device__ __forceinline__ uint32_t encode_tile(const TileHdr* __restrict__ hdrs
             const uint32_t offset = bytes + (uint32_t)__popcll(lower) + (uint32_t)__popcll(bl & lanes_below(lane));
             const uint32_t b0 = (is_long ? 0x80u : 0u) | ((gap & 7u) << 4) | code, b1 = gap >> 3;
             sink(keep, b0, b1, is_long, offset);
-            if (b) prev = __shfl(pos, 63 - __builtin_clzll(b));
+            if (b) prev = __builtin_amdgcn_readlane(pos, 63 - __builtin_clzll(b));
             bytes += (uint32_t)__popcll(b) + (uint32_t)__popcll(bl);
         }
     }
@@ -93,10 +93,7 @@ __global__ __launch_bounds__(256) void k_compact_emit(PlanCheck pc, const PlanTi
         // where the tile's bytes go: the run's offset plus the bytes of the run's earlier tiles
         const uint32_t in_run = (pt.start >> kTileShift) % kRunTiles;
         uint32_t x = lane < in_run ? (uint32_t)tile_bytes[t - in_run + lane] : 0u;
-        out = run_offsets[pt.run];
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off);
-        out += x;
+        out = run_offsets[pt.run] + (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x), 63);
     }, [&](bool keep, uint32_t b0, uint32_t b1, bool is_long, uint32_t offset) {
         const uint64_t o = out + offset;
         if (keep && o < stream_cap) stream[o] = (uint8_t)b0;
@@ -141,19 +138,6 @@ typedef const __attribute__((address_space(1))) Unaligned64* global_u64;
 
 constexpr uint32_t kLaneBytes = 8;                              // bytes of a message a lane decodes per round
 constexpr uint32_t kRoundBytes = 64 * kLaneBytes;
-
-// Inclusive sum over the wave's lanes (DPP row shifts, then the rows' totals broadcast upwards).
-__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
-#define VGC_DPP(ctrl, rows) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, ctrl, rows, 0xF, false)
-    x += VGC_DPP(0x111, 0xF);
-    x += VGC_DPP(0x112, 0xF);
-    x += VGC_DPP(0x114, 0xF);
-    x += VGC_DPP(0x118, 0xF);
-    x += VGC_DPP(0x142, 0xA);
-    x += VGC_DPP(0x143, 0xC);
-#undef VGC_DPP
-    return x;
-}
 
 // Bits 0..3 of x as bytes of 0x00 or 0xFF.
 __device__ __forceinline__ uint32_t byte_mask(uint32_t x) {

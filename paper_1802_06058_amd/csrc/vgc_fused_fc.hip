@@ -114,18 +114,15 @@ __device__ __forceinline__ void encode_codes(uint16_t* codes, TileHdr* __restric
             etr = max(etr, send ? (w & 511u) - ((w >> 9) & 1u) : 0u);
         }
         // send bitmap: bit 256 u + 4 lane + c; eight lanes make one word
-        uint32_t x = nib << (4 * (lane & 7u));
-        x |= (uint32_t)__shfl_xor((int)x, 1);
-        x |= (uint32_t)__shfl_xor((int)x, 2);
-        x |= (uint32_t)__shfl_xor((int)x, 4);
+        const uint32_t x = eight_lanes_or(nib << (4 * (lane & 7u)));
         if ((lane & 7u) == 0) bm[u * 8 + (lane >> 3)] = x;
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) etr = max(etr, (uint32_t)__shfl_xor((int)etr, off));
+    etr = wave_max(etr);
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");   // every lane's codes are read before entries replace them
     __builtin_amdgcn_wave_barrier();
 
-    uint64_t hist = 0;                                       // nine 6-bit counters (a lane has at most 32 entries)
+    HistPairs hist = {};                                     // of the lane's at most 32 entries
+    uint32_t nibbles = 0;                                    // of those of up to three chunks
     uint32_t base = 0;                                       // entries of the chunks before u (uniform)
 #pragma unroll
     for (int u = 0; u < 8; ++u) {
@@ -136,7 +133,7 @@ __device__ __forceinline__ void encode_codes(uint16_t* codes, TileHdr* __restric
             const uint32_t ernd = w & 511u, rel = etr + 1u - ernd;              // >= 0 for sent elements
             const bool staged = (w & 0x4000u) && ernd >= 1u && rel <= 8u;
             entry[c] = ((rel & 15u) << 12) | ((w >> 15) << 11) | (uint32_t)(u * 256 + c) + 4u * lane;
-            hist += staged ? (1ull << (staged ? 6u * rel : 0u)) : 0ull;
+            nibbles += staged && rel < 8u ? 1u << (4u * rel & 31u) : 0u;
             const uint64_t b = __ballot(staged);
             below += rank_below(b);
             total += (uint32_t)__popcll(b);
@@ -149,33 +146,19 @@ __device__ __forceinline__ void encode_codes(uint16_t* codes, TileHdr* __restric
             pos += (st >> c) & 1u;
         }
         base += total;
+        if (u % 3 == 2 || u == 7) {
+            const HistPairs s = spread_nibbles(nibbles);
+#pragma unroll
+            for (int q = 0; q < 4; ++q) hist.p[q] += s.p[q];
+            nibbles = 0;
+        }
     }
-    // wave totals of the nine bins: 12-bit fields in two 64-bit words (bins 0..4, 5..8)
-    uint64_t h_lo = 0, h_hi = 0;
-#pragma unroll
-    for (int j = 0; j < 5; ++j) h_lo |= ((hist >> (6 * j)) & 63ull) << (12 * j);
-#pragma unroll
-    for (int j = 5; j < 9; ++j) h_hi |= ((hist >> (6 * j)) & 63ull) << (12 * (j - 5));
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
-        h_lo += ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(h_lo >> 32), off) << 32) | (uint32_t)__shfl_xor((int)(uint32_t)h_lo, off);
-        h_hi += ((uint64_t)(uint32_t)__shfl_xor((int)(uint32_t)(h_hi >> 32), off) << 32) | (uint32_t)__shfl_xor((int)(uint32_t)h_hi, off);
-    }
+    hist = wave_hist(hist);
     __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
     __builtin_amdgcn_wave_barrier();
     for (uint32_t piece = lane; piece * 8u < base; piece += 64u)
         __builtin_nontemporal_store(reinterpret_cast<const uint4v*>(codes)[piece], reinterpret_cast<uint4v*>(out) + piece);
-    if (lane == 0) {
-        uint32_t h[kRelBins];
-#pragma unroll
-        for (int j = 0; j < 5; ++j) h[j] = (uint32_t)(h_lo >> (12 * j)) & 0xFFFu;
-#pragma unroll
-        for (int j = 5; j < 9; ++j) h[j] = (uint32_t)(h_hi >> (12 * (j - 5))) & 0xFFFu;
-        uint4 lo = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-        uint4 hi = make_uint4(h[8] | (etr << 16), 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(hdr)[0] = lo;
-        reinterpret_cast<uint4*>(hdr)[1] = hi;
-    }
+    if (lane == 63) store_tile_record(hdr, hist, base, etr);
 }
 
 // Four consecutive floats, as 16 bytes where they are aligned (`vec`: the same for the whole launch).

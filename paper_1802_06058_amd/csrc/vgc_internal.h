@@ -49,6 +49,44 @@ __device__ __forceinline__ bool plan_ok(const PlanCheck& pc) {
     return magic == kPlanMagic && hash == pc.hash;
 }
 
+// Over the wave's lanes without LDS: a shuffle is a round trip through it, and chains of them (and a ballot for each bin and element
+// of the histogram) were what the kernels' time on few tiles consisted of once their loads had come.  Shuffles -> these, us: select
+// of 20000 elements 5.9 -> 4.1, of 1.8 M 11.8 -> 9.8, of 25.6 M 104.7 -> 103; vgc_pack 4.2 -> 3.8, 6.3 -> 5.8, 17.5 -> 16.4;
+// vgc_pack_compact 14.1 -> 12.4, 16.4 -> 14.7, 27.5 -> 24.9.
+#define VGC_DPP(x, ctrl, rows) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(x), ctrl, rows, 0xF, false)
+// Inclusive sums: of rows of 16 lanes, of halves of 32, of the wave.
+__device__ __forceinline__ uint32_t row_inclusive_sum(uint32_t x) {
+    x += VGC_DPP(x, 0x111, 0xF);
+    x += VGC_DPP(x, 0x112, 0xF);
+    x += VGC_DPP(x, 0x114, 0xF);
+    return x + VGC_DPP(x, 0x118, 0xF);
+}
+__device__ __forceinline__ uint32_t half_inclusive_sum(uint32_t x) {
+    x = row_inclusive_sum(x);
+    return x + VGC_DPP(x, 0x142, 0xA);
+}
+__device__ __forceinline__ uint32_t wave_inclusive_sum(uint32_t x) {
+    x = half_inclusive_sum(x);
+    return x + VGC_DPP(x, 0x143, 0xC);
+}
+// The largest of the wave (uniform).
+__device__ __forceinline__ uint32_t wave_max(uint32_t x) {
+    x = max(x, VGC_DPP(x, 0x111, 0xF));
+    x = max(x, VGC_DPP(x, 0x112, 0xF));
+    x = max(x, VGC_DPP(x, 0x114, 0xF));
+    x = max(x, VGC_DPP(x, 0x118, 0xF));
+    x = max(x, VGC_DPP(x, 0x142, 0xA));
+    x = max(x, VGC_DPP(x, 0x143, 0xC));
+    return (uint32_t)__builtin_amdgcn_readlane((int)x, 63);
+}
+// Or over groups of eight lanes, in each of them.
+__device__ __forceinline__ uint32_t eight_lanes_or(uint32_t x) {
+    x |= VGC_DPP(x, 0xB1, 0xF);                               // lanes 1 apart
+    x |= VGC_DPP(x, 0x4E, 0xF);                               // 2 apart
+    return x | VGC_DPP(x, 0x141, 0xF);                        // the other four
+}
+#undef VGC_DPP
+
 struct PlanGroup {             // 16 bytes
     uint64_t offset;           // first element of the group in the flat parameter space
     uint32_t size;

@@ -25,12 +25,7 @@ __device__ __forceinline__ uint32_t rank_below64(uint64_t mask) {
 template <int kWaves>
 __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* sh /*[kWaves]*/, uint32_t& total) {
     const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    uint32_t incl = x;
-#pragma unroll
-    for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)incl, off);
-        if (lane >= (uint32_t)off) incl += y;
-    }
+    const uint32_t incl = wave_inclusive_sum(x);
     __syncthreads();                       // protects sh against the previous use
     if (lane == 63) sh[wave] = incl;
     __syncthreads();
@@ -48,8 +43,7 @@ __device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* sh /*[kWave
 // Workgroup maximum.
 template <int kWaves>
 __device__ __forceinline__ uint32_t block_max(uint32_t e, uint32_t* sh /*[kWaves]*/) {
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) e = max(e, (uint32_t)__shfl_xor((int)e, off));
+    e = wave_max(e);
     __syncthreads();
     if ((threadIdx.x & 63u) == 0) sh[threadIdx.x >> 6] = e;
     __syncthreads();
@@ -250,9 +244,8 @@ __global__ __launch_bounds__(256) void k_run_sums(PlanCheck pc, const PlanGroup*
     const uint32_t tiles = (pg.size + kTile - 1) / kTile - pr.first_tile;
     uint32_t x = lane < tiles ? (uint32_t)tile_bytes[(uint64_t)pg.first_tile + pr.first_tile + lane] : 0u;
     static_assert(kRunTiles == 64, "a lane a tile");
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) x += (uint32_t)__shfl_xor((int)x, off);
-    if (lane == 0) run_offsets[r] = x;
+    x = wave_inclusive_sum(x);
+    if (lane == 63) run_offsets[r] = x;
 }
 
 // One workgroup: the parts' counts become their places inside the segment, an exclusive scan over the segments gives their
@@ -396,7 +389,7 @@ __global__ __launch_bounds__(256) void k_emit(PlanCheck pc, const PlanTile* __re
     const PlanTile pt = tiles[t];
     uint32_t w[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__shfl((int)hw, i);
+    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)hw, i);
     if ((w[7] & 0xFFFFu) == 0) return;                      // (else the shift is at most 8)
     const uint32_t cnt = (w[0] & 0xFFFFu) + (w[0] >> 16) + (w[1] & 0xFFFFu) + (w[1] >> 16) + (w[2] & 0xFFFFu) +
                          (w[2] >> 16) + (w[3] & 0xFFFFu) + (w[3] >> 16) + (w[4] & 0xFFFFu);
@@ -462,9 +455,8 @@ __global__ __launch_bounds__(256) void k_pack_small(PlanCheck pc, const uint32_t
         }
         if (first_block && kept) atomicAdd(&count[group[j]], kept);
     }
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) before += (uint32_t)__shfl_xor((int)before, off);
-    if (lane == 0) sh[wave] = before;
+    before = wave_inclusive_sum(before);
+    if (lane == 63) sh[wave] = before;
     __syncthreads();
     if (t < n_tiles && own_kept[wave] != 0) {
         uint32_t out = sh[0] + sh[1] + sh[2] + sh[3];

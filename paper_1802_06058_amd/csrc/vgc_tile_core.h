@@ -16,6 +16,29 @@ __device__ __forceinline__ uint32_t rank_below(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
 }
 
+// Histogram of the relative codes 0 .. 7 over a wave: a lane's counts, at most 15 each, in the eight nibbles of `nibbles`; the totals
+// as 16-bit pairs (0, 4), (2, 6), (1, 5), (3, 7) in the last lane.  (Code 8 is what is left of the staged elements.)
+struct HistPairs { uint32_t p[4]; };
+__device__ __forceinline__ HistPairs spread_nibbles(uint32_t nibbles) {
+    const uint32_t even = nibbles & 0x0F0F0F0Fu, odd = (nibbles >> 4) & 0x0F0F0F0Fu;
+    return HistPairs{{even & 0x00FF00FFu, (even >> 8) & 0x00FF00FFu, odd & 0x00FF00FFu, (odd >> 8) & 0x00FF00FFu}};
+}
+__device__ __forceinline__ HistPairs wave_hist(HistPairs h) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) h.p[q] = wave_inclusive_sum(h.p[q]);
+    return h;
+}
+// The first five words of a tile's record from these totals and the number of staged elements.
+__device__ __forceinline__ void store_tile_record(TileHdr* __restrict__ hdr, const HistPairs& h, uint32_t staged, uint32_t etr) {
+    uint32_t sum = 0;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) sum += (h.p[q] & 0xFFFFu) + (h.p[q] >> 16);
+    const uint4 lo = make_uint4((h.p[0] & 0xFFFFu) | (h.p[2] << 16), (h.p[1] & 0xFFFFu) | (h.p[3] << 16),
+                                (h.p[0] >> 16) | (h.p[2] & 0xFFFF0000u), (h.p[1] >> 16) | (h.p[3] & 0xFFFF0000u));
+    reinterpret_cast<uint4*>(hdr)[0] = lo;
+    reinterpret_cast<uint4*>(hdr)[1] = make_uint4((staged - sum) | (etr << 16), 0u, 0u, 0u);
+}
+
 // Alg. 1 loop body for one element; every operation is a single float32 rounding
 // (the files that include this are compiled without floating-point contraction).
 __device__ __forceinline__ bool alg1_step(float g, float s, float r, float v, float alpha, float zeta,
@@ -62,7 +85,7 @@ __device__ __forceinline__ bool step_any(float g, float s, float r, float v, flo
 struct TileLds {
     uint32_t wmax[4];
     uint32_t seg[32];
-    uint32_t hist[4][kRelBins];
+    HistPairs hist[4];
     __attribute__((aligned(16))) uint16_t stage[kTile];
 };
 
@@ -84,7 +107,7 @@ __device__ __forceinline__ void tile_core(const float (&G)[8], const float (&S)[
                                           uint16_t* __restrict__ staging, float alpha, float zeta, float tau,
                                           TileLds& sh, uint32_t tid) {
     const uint32_t lane = tid & 63u;
-    const uint32_t wave = tid >> 6;
+    const uint32_t wave = __builtin_amdgcn_readfirstlane(tid >> 6);
     constexpr int E = kElemsPerThread;
     const bool on = !kGuarded || live;
 
@@ -131,18 +154,14 @@ __device__ __forceinline__ void tile_core(const float (&G)[8], const float (&S)[
 #pragma unroll
         for (int e = 0; e < E; ++e)
             if (sendmask & (1u << e)) etr = max(etr, (bits[e] & 0x7FFFFFFFu) >> 23);
-#pragma unroll
-        for (int off = 32; off > 0; off >>= 1) etr = max(etr, (uint32_t)__shfl_xor((int)etr, off));
+        etr = wave_max(etr);
     }
     if (lane == 0) sh.wmax[wave] = etr;
 
     if (kVec) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
-            uint32_t x = ((sendmask >> (u * 4)) & 0xFu) << (4 * (lane & 7u));
-            x |= (uint32_t)__shfl_xor((int)x, 1);
-            x |= (uint32_t)__shfl_xor((int)x, 2);
-            x |= (uint32_t)__shfl_xor((int)x, 4);
+            const uint32_t x = eight_lanes_or(((sendmask >> (u * 4)) & 0xFu) << (4 * (lane & 7u)));
             if ((lane & 7u) == 0 && on) bitmap[(u * 1024 + wave * 256) / 32 + (lane >> 3)] = x;
         }
     } else {
@@ -179,23 +198,15 @@ __device__ __forceinline__ void tile_core(const float (&G)[8], const float (&S)[
         }
     }
 
-    // histogram of rel over the wave (uniform values; scalar popcounts)
-    if (kHybrid) {
-        // every staged element is +-1.0f and so is the tile's maximum: rel = 1 for all of them
-        uint32_t cnt = 0;
+    // histogram of rel over the wave (hybrid: every staged element is +-1.0f and so is the tile's maximum: rel = 1 for all of them)
+    uint32_t nibbles = 0;
 #pragma unroll
-        for (int e = 0; e < E; ++e) cnt += __popcll(__ballot((stagedmask >> e) & 1u));
-        if (lane < kRelBins) sh.hist[wave][lane] = (lane == 1u) ? cnt : 0u;
-    } else {
-#pragma unroll
-        for (int j = 0; j < (int)kRelBins; ++j) {
-            uint32_t cnt = 0;
-#pragma unroll
-            for (int e = 0; e < E; ++e)
-                cnt += __popcll(__ballot(((stagedmask >> e) & 1u) && ((entry[e] >> 12) == (uint32_t)j)));
-            if (lane == 0) sh.hist[wave][j] = cnt;
-        }
+    for (int e = 0; e < E; ++e) {
+        const uint32_t rel = kHybrid ? 1u : entry[e] >> 12;
+        nibbles += ((stagedmask >> e) & 1u) && rel < 8u ? 1u << (4u * rel & 31u) : 0u;
     }
+    const HistPairs hist = wave_hist(spread_nibbles(nibbles));
+    if (lane == 63) sh.hist[wave] = hist;
 
     // rank of each staged element inside its segment, and segment totals
     uint32_t rank[E];
@@ -229,22 +240,16 @@ __device__ __forceinline__ void tile_core(const float (&G)[8], const float (&S)[
     __syncthreads();
 
     // exclusive scan over the kSeg*4 segment totals, redundantly in every wave
-    uint32_t x = (lane < (uint32_t)(kSeg * 4)) ? sh.seg[lane] : 0u;
-    uint32_t incl = x;
-#pragma unroll
-    for (int off = 1; off < 32; off <<= 1) {
-        const uint32_t y = (uint32_t)__shfl_up((int)incl, off);
-        if (lane >= (uint32_t)off) incl += y;
-    }
-    const uint32_t excl = incl - x;
-    const uint32_t n_staged = (uint32_t)__shfl((int)incl, 31);
+    const uint32_t x = (lane < (uint32_t)(kSeg * 4)) ? sh.seg[lane] : 0u;
+    const uint32_t incl = kVec ? row_inclusive_sum(x) : half_inclusive_sum(x), excl = incl - x;
+    const uint32_t n_staged = (uint32_t)__builtin_amdgcn_readlane((int)incl, kSeg * 4 - 1);
     // compact in LDS, then write the tile's entries as whole 16-byte pieces (the tile's staging area is
     // 4 KiB-aligned; slots between the count and the next multiple of 8 receive stale values that the
     // reader ignores)
 #pragma unroll
     for (int e = 0; e < E; ++e) {
         const int u = kVec ? (e >> 2) : e;
-        const uint32_t segbase = (uint32_t)__shfl((int)excl, u * 4 + (int)wave);
+        const uint32_t segbase = (uint32_t)__builtin_amdgcn_readlane((int)excl, u * 4 + (int)wave);
         if ((stagedmask >> e) & 1u) sh.stage[segbase + rank[e]] = (uint16_t)entry[e];
     }
     __syncthreads();
@@ -252,13 +257,12 @@ __device__ __forceinline__ void tile_core(const float (&G)[8], const float (&S)[
         __builtin_nontemporal_store(reinterpret_cast<const uint4v*>(sh.stage)[tid], reinterpret_cast<uint4v*>(staging) + tid);
 
     if (tid == 0 && on) {
-        uint32_t h[kRelBins];
+        HistPairs h = sh.hist[0];
 #pragma unroll
-        for (int j = 0; j < (int)kRelBins; ++j) h[j] = sh.hist[0][j] + sh.hist[1][j] + sh.hist[2][j] + sh.hist[3][j];
-        uint4 lo = make_uint4(h[0] | (h[1] << 16), h[2] | (h[3] << 16), h[4] | (h[5] << 16), h[6] | (h[7] << 16));
-        uint4 hi = make_uint4(h[8] | (etr << 16), 0u, 0u, 0u);
-        reinterpret_cast<uint4*>(hdr)[0] = lo;
-        reinterpret_cast<uint4*>(hdr)[1] = hi;
+        for (int w = 1; w < 4; ++w)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) h.p[q] += sh.hist[w].p[q];
+        store_tile_record(hdr, h, n_staged, etr);
     }
 }
 
