@@ -19,7 +19,7 @@
 // waves contracted, streamed and encoded in step: 0.43 ms.  With 70 KB and at most 128 registers two workgroups share a
 // compute unit: 0.38 ms.  Loads come back in the order of their request: with r and v requested before the fragments each
 // MFMA waited for HBM (0.50 ms).  Kernel and transposes, before -> now, us: the same layer at batch 8, 32, 64, 128 in bf16
-// 384 -> 365, 388 -> 359, 457 -> 384, 553 -> 511, in float32 428 -> 363, 508 -> 390, 638 -> 533, 901 -> 813.  The form before
+// 384 -> 353, 388 -> 350, 457 -> 383, 553 -> 511, in float32 428 -> 355, 508 -> 390, 638 -> 530, 901 -> 813.  The form before
 // stays for long batches in bf16 (k_fused_fc_select_long).
 #include <type_traits>
 
@@ -174,7 +174,8 @@ __device__ __forceinline__ void store4(f4 x, float* p, bool vec) {
 
 // kR: rows of [J, C] per tile (1: C is a multiple of 2048 and a tile is a piece of a row; 2, 4, 8: C = 2048 / kR).
 // kWaves: waves that share the block's 16 tiles.
-template <int kR, bool kBf16, int kWaves>
+// kSteps: fragments that Kp has (1 or 2), 0: any number.
+template <int kR, bool kBf16, int kWaves, int kSteps>
 __global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc, uint32_t* __restrict__ flags, FusedArgs A,
                                                             const PlanGroup* __restrict__ groups,
                                                             TileHdr* __restrict__ hdrs, uint32_t* __restrict__ bitmap,
@@ -265,65 +266,92 @@ __global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc
         }
     };
     // Loads come back in the order of their request (and stores count among them): the first fragments of the next 32 columns are
-    // requested before the r and v of these are waited for and written.
-    Frags F0 = fetch(0, 0), F1 = fetch(0, A.Kp > kStep ? kStep : 0u);
+    // requested before the r and v of these are waited for and written.  The wait for one of them is counted past those requested
+    // after it where the number of these is known: with kWhole (all 16 rows exist, r and v lie at 16 bytes, g and s are not asked
+    // for) and kSteps no branch is left around a load.  With them in branches each of these waits was for everything, the r and v
+    // just requested among it.  In bf16, us: 25088 x 4096 at batch 32 363 -> 352, at batch 64 387 -> 385, 9216 x 1024 at 64
+    // 72.3 -> 69.6, 4096 x 4096 80.5 -> 77.4, 5000 x 256 at 40 33.2 -> 30.2, 1001 x 512 at 20 29.1 -> 25.6; float32, 25088 x 4096
+    // at 16, 367 -> 357.  With two fragments of float32 it is slower (25088 x 4096 at 32: 391 -> 398): they stay in branches.  With one fragment there are registers left to request the r and v, too, 32 columns ahead (bf16, batch 32:
+    // 354 -> 351; with two: 387 -> 401, spilled).
+    constexpr bool kAhead = kSteps == 1;
     uint2 code[kN][2];                                        // of columns 32 n + tcol .. + 3, row q (n < kParked: in LDS meanwhile)
+    auto pass = [&](auto whole_) __attribute__((always_inline)) {
+        constexpr bool kWhole = decltype(whole_)::value;
+        auto fetch_first = [&](int n, Frags& F0, Frags& F1) {
+            F0 = fetch(n, 0);
+            if (kSteps != 1) F1 = fetch(n, kSteps == 2 || A.Kp > kStep ? kStep : 0u);
+        };
+        f4 R4[2][2], V4[2][2];                                // of these columns and of the next
+        auto request = [&](int n) {
+            f4 (&R)[2] = R4[n & 1], (&V)[2] = V4[n & 1];
 #pragma unroll
-    for (int n = 0; n < kN; ++n) {
-        f4 R4[2], V4[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            R4[q] = V4[q] = (f4){0.f, 0.f, 0.f, 0.f};
-            if (8u * q < rows_left) {
-                R4[q] = load4(r + q * row8 + 32 * n + eoff, vec);
-                V4[q] = load4(v + q * row8 + 32 * n + eoff, vec);
+            for (int q = 0; q < 2; ++q) {
+                if (!kWhole) R[q] = V[q] = (f4){0.f, 0.f, 0.f, 0.f};
+                if (kWhole || 8u * q < rows_left) {
+                    R[q] = load4(r + q * row8 + 32 * n + eoff, kWhole || vec);
+                    V[q] = load4(v + q * row8 + 32 * n + eoff, kWhole || vec);
+                }
             }
-        }
+        };
+        Frags F0, F1;
+        fetch_first(0, F0, F1);
+        if (kWhole && kAhead) request(0);
 #pragma unroll
-        for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
-        multiply(F0);
-        if (A.Kp > kStep) multiply(F1);
+        for (int n = 0; n < kN; ++n) {
+            if (!kWhole || !kAhead) request(n);
+#pragma unroll
+            for (int t = 0; t < 2; ++t) { acc_g[t] = (f4v){0.f, 0.f, 0.f, 0.f}; acc_s[t] = (f4v){0.f, 0.f, 0.f, 0.f}; }
+            multiply(F0);
+            if (kSteps == 2 || (kSteps == 0 && A.Kp > kStep)) multiply(F1);
+            if (kSteps == 0) {
 #pragma unroll 1
-        for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
-        if (n + 1 < kN) { F0 = fetch(n + 1, 0); F1 = fetch(n + 1, A.Kp > kStep ? kStep : 0u); }
+                for (uint32_t k0 = 2u * kStep; k0 < A.Kp; k0 += kStep) multiply(fetch(n, k0));
+            }
+            if (n + 1 < kN) {
+                fetch_first(n + 1, F0, F1);
+                if (kWhole && kAhead) request(n + 1);
+            }
 #pragma unroll
-        for (int t = 0; t < 2; ++t) {
-            *reinterpret_cast<f4v*>(turn_g + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_g[t] * A.cg;
-            *reinterpret_cast<f4v*>(turn_s + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_s[t] * A.cs;
+            for (int t = 0; t < 2; ++t) {
+                *reinterpret_cast<f4v*>(turn_g + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_g[t] * A.cg;
+                *reinterpret_cast<f4v*>(turn_s + lrow * kTurnPitch + 16 * t + 4 * lgrp) = acc_s[t] * A.cs;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int q = 0; q < 2; ++q) {
+                const f4v g4 = *reinterpret_cast<const f4v*>(turn_g + (8 * q + trow) * kTurnPitch + tcol);
+                const f4v s4 = *reinterpret_cast<const f4v*>(turn_s + (8 * q + trow) * kTurnPitch + tcol);
+                const bool live = kWhole || 8u * q < rows_left;
+                if (!kWhole && A.g_out && live) {
+                    store4(__builtin_bit_cast(f4, g4), A.g_out + e0 + q * row8 + 32 * n + eoff, vec_out);
+                    store4(__builtin_bit_cast(f4, s4), A.s_out + e0 + q * row8 + 32 * n + eoff, vec_out);
+                }
+                f4 ro, vo;
+                uint32_t w[4];
+#pragma unroll
+                for (int c = 0; c < 4; ++c) {
+                    float a, b;
+                    uint32_t bits;
+                    const bool send = alg1_step(g4[c], s4[c], R4[n & 1][q][c], V4[n & 1][q][c], A.alpha, A.zeta, a, b, bits) & live;
+                    ro[c] = a;
+                    vo[c] = b;
+                    w[c] = element_code(bits, send);
+                }
+                if (live) {
+                    store4(ro, r + q * row8 + 32 * n + eoff, kWhole || vec);
+                    store4(vo, v + q * row8 + 32 * n + eoff, kWhole || vec);
+                }
+                const uint2 cw = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
+                if (n < kParked) sh.w[wave].park[2 * n + q][lane] = cw;
+                else code[n][q] = cw;
+            }
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
+            __builtin_amdgcn_wave_barrier();
         }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const f4v g4 = *reinterpret_cast<const f4v*>(turn_g + (8 * q + trow) * kTurnPitch + tcol);
-            const f4v s4 = *reinterpret_cast<const f4v*>(turn_s + (8 * q + trow) * kTurnPitch + tcol);
-            const bool live = 8u * q < rows_left;
-            if (A.g_out && live) {
-                store4(__builtin_bit_cast(f4, g4), A.g_out + e0 + q * row8 + 32 * n + eoff, vec_out);
-                store4(__builtin_bit_cast(f4, s4), A.s_out + e0 + q * row8 + 32 * n + eoff, vec_out);
-            }
-            f4 ro, vo;
-            uint32_t w[4];
-#pragma unroll
-            for (int c = 0; c < 4; ++c) {
-                float a, b;
-                uint32_t bits;
-                const bool send = alg1_step(g4[c], s4[c], R4[q][c], V4[q][c], A.alpha, A.zeta, a, b, bits) & live;
-                ro[c] = a;
-                vo[c] = b;
-                w[c] = element_code(bits, send);
-            }
-            if (live) {
-                store4(ro, r + q * row8 + 32 * n + eoff, vec);
-                store4(vo, v + q * row8 + 32 * n + eoff, vec);
-            }
-            const uint2 cw = make_uint2(w[0] | (w[1] << 16), w[2] | (w[3] << 16));
-            if (n < kParked) sh.w[wave].park[2 * n + q][lane] = cw;
-            else code[n][q] = cw;
-        }
-        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront", "local");
-        __builtin_amdgcn_wave_barrier();
-    }
+    };
+    if (kSteps != 0 && vec && !A.g_out && j0 + 16u * rt + 16u <= A.J) pass(std::true_type{});    // (uniform per wave)
+    else pass(std::false_type{});
 #pragma unroll
     for (int n = 0; n < kParked; ++n)
 #pragma unroll
@@ -546,20 +574,28 @@ int launch_fused_fc_select(PlanCheck pc, uint32_t* flags, int dtype, const void*
     // wave does in a row is then all the time there is (300 x 2048 in bf16 at batch 64: 31.4 us against 35.0 with eight waves;
     // 1000 x 256 in float32: 41.7 against 49.7).
 #define VGC_FUSED(K_, NW) hipLaunchKernelGGL((K_), dim3((uint32_t)nblk), dim3(NW * 64), 0, stream, pc, flags, A, groups, hdrs, bitmap, staging)
+#define VGC_FUSED_STEPS(KR, BF, NW)                                                                                           \
+    do {                                                                                                                      \
+        if (steps == 1) VGC_FUSED((k_fused_fc_select<KR, BF, NW, 1>), NW);                                                    \
+        else if (BF && steps == 2) VGC_FUSED((k_fused_fc_select<KR, BF, NW, BF ? 2 : 0>), NW);                                \
+        else VGC_FUSED((k_fused_fc_select<KR, BF, NW, 0>), NW);                                                               \
+    } while (0)
 #define VGC_FUSED_WAVES(KR)                                                                                                   \
     do {                                                                                                                      \
         if (bf && Kp > kLongK) VGC_FUSED(k_fused_fc_select_long<KR>, 8);                                                      \
-        else if (bf && nblk <= 256) VGC_FUSED((k_fused_fc_select<KR, true, 16>), 16);                                         \
-        else if (bf) VGC_FUSED((k_fused_fc_select<KR, true, 8>), 8);                                                          \
-        else if (nblk <= 256) VGC_FUSED((k_fused_fc_select<KR, false, 16>), 16);                                              \
-        else VGC_FUSED((k_fused_fc_select<KR, false, 8>), 8);                                                                 \
+        else if (bf && nblk <= 256) VGC_FUSED_STEPS(KR, true, 16);                                                            \
+        else if (bf) VGC_FUSED_STEPS(KR, true, 8);                                                                            \
+        else if (nblk <= 256) VGC_FUSED_STEPS(KR, false, 16);                                                                 \
+        else VGC_FUSED_STEPS(KR, false, 8);                                                                                   \
     } while (0)
     const bool bf = dtype == VGC_BF16;
+    const uint32_t steps = Kp / (bf ? 32u : 16u);
     if (kr == 1) VGC_FUSED_WAVES(1);
     else if (kr == 2) VGC_FUSED_WAVES(2);
     else if (kr == 4) VGC_FUSED_WAVES(4);
     else VGC_FUSED_WAVES(8);
 #undef VGC_FUSED_WAVES
+#undef VGC_FUSED_STEPS
 #undef VGC_FUSED
     return hip_check(hipGetLastError(), "launch k_fused_fc_select");
 }

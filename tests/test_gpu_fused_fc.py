@@ -182,3 +182,18 @@ def test_fused_rejects_what_it_cannot_do(dev):
 ])
 def test_fused_layer_at_the_edges_of_its_blocks(dev, B, J, C, prec, front):
     test_fused_layer_inside_a_model(dev, B, J, C, prec, front)
+
+
+@pytest.mark.parametrize("B,J,C,prec,front", [
+    (32, 4100, 2048, "bf16", 4),        # exactly one fragment; eight waves a block; whole blocks and one with four rows
+    (33, 16400, 512, "bf16", 8),        # the first batch with two; 16 rows in the last block of 64
+    (64, 32, 4096, "bf16", 12),         # exactly two, sixteen waves a block, whole blocks only
+    (16, 16, 2048, "f32", 4),           # exactly one in float32, one block
+    (17, 32, 2048, "f32", 4),           # two in float32: the form for any number
+    (9, 32777, 256, "f32", 4),          # one, eight waves a block, nine live rows in the last block of 128
+    (31, 48, 2048, "bf16", 2),          # one, state at 8 bytes
+])
+def test_fused_layer_of_one_or_two_fragments(dev, B, J, C, prec, front):
+    """Its waves with 16 rows run with every load unconditional, the others and those that write g and s do not: the call
+    without the optional outputs has to give the state and message of the call with them."""
+    test_fused_layer_inside_a_model(dev, B, J, C, prec, front)
