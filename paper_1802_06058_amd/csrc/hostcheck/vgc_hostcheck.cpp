@@ -186,12 +186,19 @@ static void check_compute_errors() {
     CHECK(vgc_unpack_apply(wl, nl, hl, VGC_MAX_UPDATE_MESSAGES + 1, g.data(), 2, plan, 1.f, &opt, f, f, f, n, nullptr) == VGC_ERR_SIZE);
 }
 
-// The compact decoder's variant for streams of 1 to 7 bytes: empty streams do not choose it.
-namespace vgc { bool compact_short_streams(const uint64_t* n_bytes, uint32_t p); }
+// The compact decoder's variant for streams of 1 to 7 bytes: empty streams do not choose it.  The one that decodes several messages
+// at once: none above 200 bytes a tile.
+namespace vgc {
+bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
+bool compact_thin_streams(const uint64_t* n_bytes, uint32_t p, uint64_t n_tiles);
+}
 static void check_dispatch() {
     const uint64_t dense[3] = {100, 8, 1ull << 40}, empty[3] = {100, 0, 8}, few[3] = {0, 100, 7}, one[1] = {1};
     CHECK(!vgc::compact_short_streams(dense, 3) && !vgc::compact_short_streams(empty, 3) && !vgc::compact_short_streams(nullptr, 0));
     CHECK(vgc::compact_short_streams(few, 3) && !vgc::compact_short_streams(few, 2) && vgc::compact_short_streams(one, 1));
+    const uint64_t thin[3] = {2000, 0, 1999}, thick[3] = {8, 2001, 0};
+    CHECK(vgc::compact_thin_streams(thin, 3, 10) && !vgc::compact_thin_streams(thick, 3, 10) && !vgc::compact_thin_streams(thin, 1, 10));
+    CHECK(!vgc::compact_thin_streams(nullptr, 0, 10) && !vgc::compact_thin_streams(dense, 3, ~0u));
 }
 
 int main() {

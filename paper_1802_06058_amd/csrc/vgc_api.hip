@@ -600,7 +600,7 @@ int vgc_tiles_unpack_compact_add_batch(const uint8_t* const* streams, const uint
     if (p == 0 && !overwrite) return VGC_OK;
     const PlanView pv = plan_view(plan, n_tiles, n_groups);
     return launch_unpack_compact_batch(plan_check(plan, gs), streams, stream_bytes, tile_bytes, run_offsets, hdrs, p, pv.groups, pv.runs,
-                                       gs.n_runs, scale, overwrite, dense_out, tiles_per_wave, static_cast<hipStream_t>(stream));
+                                       n_tiles, gs.n_runs, scale, overwrite, dense_out, tiles_per_wave, static_cast<hipStream_t>(stream));
 }
 
 int vgc_unpack_compact_add_batch(const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,

@@ -236,10 +236,11 @@ int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* gr
                         uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out, vgc_pack_status* status_out,
                         hipStream_t stream);
 bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
+bool compact_thin_streams(const uint64_t* n_bytes, uint32_t p, uint64_t n_tiles);
 int launch_unpack_compact_batch(PlanCheck pc, const uint8_t* const* streams, const uint64_t* stream_bytes, const uint16_t* const* tile_bytes,
                                 const uint64_t* const* run_offsets, const vgc_group_hdr* const* hdrs, uint32_t p,
-                                const PlanGroup* groups, const PlanRun* runs, uint64_t n_runs, float scale, int overwrite,
-                                float* dense, uint32_t tiles_per_wave, hipStream_t stream);
+                                const PlanGroup* groups, const PlanRun* runs, uint64_t n_tiles, uint64_t n_runs, float scale,
+                                int overwrite, float* dense, uint32_t tiles_per_wave, hipStream_t stream);
 
 int launch_unpack_add(PlanCheck pc, const uint32_t* words, uint64_t n_words, const vgc_group_hdr* hdrs,
                       const PlanGroup* groups, uint32_t n_groups, float scale, float* dense,
