@@ -13,30 +13,41 @@
 // The encoder waits on memory, for a few entries per tile: what counts is how many loads depend on one another.  Entries asked
 // for before it is known how many there are, a tile's place found from two tables instead of four, and the runs scanned where
 // the segments are: 3 % of 138 M elements 80.5 -> 56 us, 30 % 180 -> 139.
+//   k_compact_count_small, k_compact_emit_small   all of it in two launches, for parameter sets of few tiles
 //   k_unpack_compact  one wave per few tiles of a run, tile in LDS, messages in order (the batched decoder for this format)
 #include <algorithm>
 
-#include "vgc_internal.h"
+#include "vgc_scan.h"
 
 namespace vgc {
 
 __device__ __forceinline__ uint64_t lanes_below(uint32_t lane) { return (1ull << lane) - 1ull; }
 
+// What is read of tile t (a wave) before it is known whether it has anything: its record and the first two rounds of 64 entries.  A
+// tile owns kTile staging slots; what lies behind its count is ignored.
+struct TileAhead { uint32_t record, entries[2]; };
+__device__ __forceinline__ TileAhead tile_ahead(const TileHdr* __restrict__ hdrs, const uint16_t* __restrict__ staging, uint64_t t, uint32_t lane) {
+    const uint16_t* st = staging + t * kTile;
+    TileAhead a;
+    a.entries[0] = st[lane];
+    a.entries[1] = st[64 + lane];
+    a.record = (lane < 8) ? hdrs[t].w[lane] : 0u;
+    return a;
+}
+
 // The staged entries of tile t (a wave) that the group keeps, 64 at a time, as (first byte, second byte, two bytes?, byte
 // offset inside the tile).  Calls `sink(keep, b0, b1, is_long, offset)` once per round in every lane; returns the
-// tile's bytes.  `found` is called once the tile is known to have some.  A tile owns kTile staging slots, so the first two
-// rounds are requested before its count is known (what lies behind it is ignored), and from then on two while two are encoded.
+// tile's bytes.  `found(w)` is given the record and says whether the tile has some (it may complete w[7]).  Two rounds are
+// requested while the two before are encoded.
 template <class Found, class Sink>
-__device__ __forceinline__ uint32_t encode_tile(const TileHdr* __restrict__ hdrs, const uint16_t* __restrict__ staging,
+__device__ __forceinline__ uint32_t encode_tile(const TileAhead& a, const uint16_t* __restrict__ staging,
                                                 uint64_t t, uint32_t lane, Found found, Sink sink) {
     const uint16_t* st = staging + t * kTile;
-    uint32_t ahead[2] = {st[lane], st[64 + lane]};
-    const uint32_t hw = (lane < 8) ? hdrs[t].w[lane] : 0u;
+    uint32_t ahead[2] = {a.entries[0], a.entries[1]};
     uint32_t w[8];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)hw, i);
-    if ((w[7] & 0xFFFFu) == 0) return 0;                       // nothing kept
-    found();
+    for (int i = 0; i < 8; ++i) w[i] = (uint32_t)__builtin_amdgcn_readlane((int)a.record, i);
+    if (!found(w)) return 0;
     const uint32_t cnt = min((w[0] & 0xFFFFu) + (w[0] >> 16) + (w[1] & 0xFFFFu) + (w[1] >> 16) + (w[2] & 0xFFFFu) +
                              (w[2] >> 16) + (w[3] & 0xFFFFu) + (w[3] >> 16) + (w[4] & 0xFFFFu), kTile);
     const uint32_t shift = w[7] >> 16, lim = 8 - shift;        // kept != 0 implies shift <= 8
@@ -78,7 +89,8 @@ __global__ __launch_bounds__(256) void k_compact_count(PlanCheck pc, uint64_t n_
     const uint32_t lane = threadIdx.x & 63u;
     const uint64_t t = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
     if (t >= n_tiles || !plan_ok(pc)) return;
-    const uint32_t bytes = encode_tile(hdrs, staging, t, lane, []() {}, [](bool, uint32_t, uint32_t, bool, uint32_t) {});
+    const uint32_t bytes = encode_tile(tile_ahead(hdrs, staging, t, lane), staging, t, lane, [](const uint32_t* w) { return (w[7] & 0xFFFFu) != 0; },
+                                       [](bool, uint32_t, uint32_t, bool, uint32_t) {});
     if (lane == 0) tile_bytes[t] = (uint16_t)bytes;
 }
 
@@ -91,16 +103,135 @@ __global__ __launch_bounds__(256) void k_compact_emit(PlanCheck pc, const PlanTi
     if (t >= n_tiles || !plan_ok(pc)) return;
     const PlanTile pt = tiles[t];
     uint64_t out = 0;
-    encode_tile(hdrs, staging, t, lane, [&]() {
+    encode_tile(tile_ahead(hdrs, staging, t, lane), staging, t, lane, [&](const uint32_t* w) {
+        if ((w[7] & 0xFFFFu) == 0) return false;
         // where the tile's bytes go: the run's offset plus the bytes of the run's earlier tiles
         const uint32_t in_run = (pt.start >> kTileShift) % kRunTiles;
         uint32_t x = lane < in_run ? (uint32_t)tile_bytes[t - in_run + lane] : 0u;
         out = run_offsets[pt.run] + (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x), 63);
+        return true;
     }, [&](bool keep, uint32_t b0, uint32_t b1, bool is_long, uint32_t offset) {
         const uint64_t o = out + offset;
         if (keep && o < stream_cap) stream[o] = (uint8_t)b0;
         if (is_long && o + 1 < stream_cap) stream[o + 1] = (uint8_t)b1;
     });
+}
+
+// The same for parameter sets of at most kSmallTiles tiles, where the kernels are chains of a few us and the launches between
+// them what counts: every workgroup reads all tile records and finds its groups' exponents by itself (k_compact_count_small), then
+// all tiles' bytes and finds its own place (k_compact_emit_small, whose first workgroup also writes directory, headers and
+// status).  us a call before -> now at few and at many sent: 20,000 elements 12.5 -> 7.2, 17.5 -> 11.3; 1.8 M 14.8 -> 9.9, 19.6 -> 14.0;
+// 4.19 M (2046 tiles) 17.6 -> 15.7, 22.5 -> 19.7: what every workgroup reads grows with the set, and there its registers end it.
+__global__ __launch_bounds__(256) void k_compact_count_small(PlanCheck pc, const uint32_t* __restrict__ flags, const PlanTile* __restrict__ tiles,
+                                                             uint32_t n_tiles, uint32_t n_groups, TileHdr* __restrict__ hdrs,
+                                                             const uint16_t* __restrict__ staging, uint16_t* __restrict__ tile_bytes) {
+    constexpr uint32_t kPer = kSmallTiles / 256;
+    __shared__ uint32_t max_e[kSmallGroups];
+    if (!plan_ok(pc) || flags[0] != 0u) return;
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), t = blockIdx.x * 4 + wave;
+    const uint32_t mine = min(t, n_tiles - 1);
+    const TileAhead ahead = tile_ahead(hdrs, staging, mine, lane);
+    const uint32_t own_group = tiles[mine].group;
+    uint32_t w4[kPer], group[kPer];
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t i = j * 256 + tid;
+        w4[j] = i < n_tiles ? hdrs[i].w[4] : 0u;
+        group[j] = i < n_tiles ? tiles[i].group : 0u;
+    }
+    for (uint32_t k = tid; k < n_groups; k += 256) max_e[k] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j)
+        if (w4[j] >> 16) atomicMax(&max_e[group[j]], w4[j] >> 16);
+    __syncthreads();
+    if (t >= n_tiles) return;
+    const uint32_t E = max_e[own_group];
+    uint32_t w7 = 0;
+    const uint32_t bytes = encode_tile(ahead, staging, t, lane, [&](uint32_t* w) {
+        uint32_t shift;
+        const uint32_t kept = kept_words(make_uint4(w[0], w[1], w[2], w[3]), w[4], E, shift);
+        w[7] = w7 = kept | min(shift, 255u) << 16;
+        return kept != 0;
+    }, [](bool, uint32_t, uint32_t, bool, uint32_t) {});
+    if (lane == 0) {
+        tile_bytes[t] = (uint16_t)bytes;
+        hdrs[t].w[7] = w7;
+    }
+}
+
+__global__ __launch_bounds__(256) void k_compact_emit_small(PlanCheck pc, const uint32_t* __restrict__ flags, const PlanTile* __restrict__ tiles,
+                                                            uint32_t n_tiles, uint32_t n_groups, const TileHdr* __restrict__ hdrs,
+                                                            const uint16_t* __restrict__ staging, const uint16_t* __restrict__ tile_bytes,
+                                                            uint64_t* __restrict__ run_offsets, uint8_t* __restrict__ stream, uint64_t stream_cap,
+                                                            vgc_group_hdr* __restrict__ hdrs_out, vgc_pack_status* __restrict__ status) {
+    constexpr uint32_t kPer = kSmallTiles / 256;
+    __shared__ uint32_t max_e[kSmallGroups], count[kSmallGroups], place[kSmallGroups], sh[4], own[4];
+    if (!plan_ok(pc) || flags[0] != 0u) {
+        if (blockIdx.x == 0) empty_message(256, n_groups, hdrs_out, status);
+        return;
+    }
+    const uint32_t tid = threadIdx.x, lane = tid & 63u, wave = __builtin_amdgcn_readfirstlane(tid >> 6), t0 = blockIdx.x * 4, t = t0 + wave;
+    const TileAhead ahead = tile_ahead(hdrs, staging, min(t, n_tiles - 1), lane);
+    uint32_t bytes[kPer], sum = 0, before = 0;              // of a thread's consecutive tiles; those before the workgroup's
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t i = tid * kPer + j;
+        bytes[j] = i < n_tiles ? (uint32_t)tile_bytes[i] : 0u;
+    }
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t i = tid * kPer + j;
+        if (i < t0) before += bytes[j];
+        if (i - t0 < 4u) own[i - t0] = bytes[j];
+        sum += bytes[j];
+    }
+    before = wave_inclusive_sum(before);
+    if (lane == 63) sh[wave] = before;
+    __syncthreads();
+    if (t < n_tiles) {
+        uint32_t out = sh[0] + sh[1] + sh[2] + sh[3];       // (2048 tiles have at most 2^23 bytes)
+        for (uint32_t q = 0; q < wave; ++q) out += own[q];
+        encode_tile(ahead, staging, t, lane, [](const uint32_t* w) { return (w[7] & 0xFFFFu) != 0; },
+                    [&](bool keep, uint32_t b0, uint32_t b1, bool is_long, uint32_t offset) {
+            const uint64_t o = (uint64_t)out + offset;
+            if (keep && o < stream_cap) stream[o] = (uint8_t)b0;
+            if (is_long && o + 1 < stream_cap) stream[o + 1] = (uint8_t)b1;
+        });
+    }
+    if (blockIdx.x != 0) return;
+    uint32_t total;
+    uint32_t at = block_scan<4>(sum, sh, total) - sum;
+    for (uint32_t k = tid; k < n_groups; k += 256) max_e[k] = count[k] = place[k] = 0;
+    __syncthreads();
+#pragma unroll
+    for (uint32_t j = 0; j < kPer; ++j) {
+        const uint32_t i = tid * kPer + j;
+        if (i < n_tiles) {
+            const PlanTile pt = tiles[i];
+            const uint32_t w4 = hdrs[i].w[4], kept = hdrs[i].w[7] & 0xFFFFu;
+            if (w4 >> 16) atomicMax(&max_e[pt.group], w4 >> 16);
+            if (kept) atomicAdd(&count[pt.group], kept);
+            if (pt.start == 0) place[pt.group] = at;
+            if ((pt.start >> kTileShift) % kRunTiles == 0) run_offsets[pt.run] = at;
+        }
+        at += bytes[j];
+    }
+    __syncthreads();
+    for (uint32_t k = tid; k < n_groups; k += 256) {
+        vgc_group_hdr h;
+        h.exp_field = count[k] ? max_e[k] : 0u;
+        h.count = count[k];
+        h.word_offset = place[k];
+        hdrs_out[k] = h;
+    }
+    if (tid == 0) {
+        vgc_pack_status s;
+        s.total_words = total;
+        s.overflow = total > stream_cap ? 1u : 0u;
+        s.plan_mismatch = 0;
+        *status = s;
+    }
 }
 
 int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs,
@@ -109,6 +240,13 @@ int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* gr
                         uint16_t* tile_bytes_out, uint64_t* run_offsets_out, vgc_group_hdr* hdrs_out, vgc_pack_status* status_out,
                         hipStream_t stream) {
     const uint32_t tb = (uint32_t)((n_tiles + 3) / 4);
+    if (n_tiles <= kSmallTiles && n_groups <= kSmallGroups) {
+        hipLaunchKernelGGL(k_compact_count_small, dim3(tb), dim3(256), 0, stream, pc, flags, tiles, (uint32_t)n_tiles, n_groups, hdrs, staging,
+                           tile_bytes_out);
+        hipLaunchKernelGGL(k_compact_emit_small, dim3(tb), dim3(256), 0, stream, pc, flags, tiles, (uint32_t)n_tiles, n_groups, hdrs, staging,
+                           tile_bytes_out, run_offsets_out, stream_out, stream_cap, hdrs_out, status_out);
+        return hip_check(hipGetLastError(), "launch compact pack kernels (few tiles)");
+    }
     const int rc = launch_part_scans(pc, groups, tiles, segs, n_tiles, n_segs, max_group_tiles, hdrs, stmp, stream);
     if (rc != VGC_OK) return rc;
     hipLaunchKernelGGL(k_compact_count, dim3(tb), dim3(256), 0, stream, pc, n_tiles, hdrs, staging, tile_bytes_out);

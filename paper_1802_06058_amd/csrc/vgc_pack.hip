@@ -13,31 +13,12 @@
 //                  position of every segment's and part's first word.
 //   k_emit         one wave per tile: read the staged entries, filter, re-rank, write words.
 //   k_pack_small   all of it in one launch, for parameter sets of few tiles.
-#include "vgc_internal.h"
+#include "vgc_scan.h"
 
 namespace vgc {
 
 __device__ __forceinline__ uint32_t rank_below64(uint64_t mask) {
     return __builtin_amdgcn_mbcnt_hi((uint32_t)(mask >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)mask, 0u));
-}
-
-// Inclusive scan over a workgroup of kWaves waves; returns the inclusive value, total through `total`.
-template <int kWaves>
-__device__ __forceinline__ uint32_t block_scan(uint32_t x, uint32_t* sh /*[kWaves]*/, uint32_t& total) {
-    const uint32_t lane = threadIdx.x & 63u, wave = threadIdx.x >> 6;
-    const uint32_t incl = wave_inclusive_sum(x);
-    __syncthreads();                       // protects sh against the previous use
-    if (lane == 63) sh[wave] = incl;
-    __syncthreads();
-    uint32_t base = 0, tot = 0;
-#pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        const uint32_t c = sh[w];
-        if ((uint32_t)w < wave) base += c;
-        tot += c;
-    }
-    total = tot;
-    return incl + base;
 }
 
 // Workgroup maximum.
@@ -86,20 +67,6 @@ __device__ __forceinline__ Part part_of_block(const PlanGroup* __restrict__ grou
     q.first = (uint64_t)pg.first_tile + in_group;
     q.cnt = in_group < q.group_tiles ? min(kPartTiles, q.group_tiles - in_group) : 0u;
     return q;
-}
-
-// Words of a tile that are encoded in a group of exponent E: entries with rel <= 8 - shift.
-__device__ __forceinline__ uint32_t kept_words(uint4 lo, uint32_t w4, uint32_t E, uint32_t& shift) {
-    shift = E - (w4 >> 16);
-    uint32_t kept = 0;
-    if (E != 0 && shift <= 8) {
-        const uint32_t h[9] = {lo.x & 0xFFFFu, lo.x >> 16, lo.y & 0xFFFFu, lo.y >> 16, lo.z & 0xFFFFu, lo.z >> 16, lo.w & 0xFFFFu,
-                               lo.w >> 16, w4 & 0xFFFFu};
-        const uint32_t lim = 8 - shift;
-#pragma unroll
-        for (int q = 0; q < 9; ++q) kept += ((uint32_t)q <= lim) ? h[q] : 0u;
-    }
-    return kept;
 }
 
 constexpr uint32_t kScanThreads = 256;
@@ -194,20 +161,6 @@ __global__ __launch_bounds__(kScanThreads) void k_part_scan(PlanCheck pc, const 
         prefix += kept[j];
     }
     if (tid == 0 && q.index == 0) stmp[q.seg].exp_field = E;
-}
-
-// An empty message: the plan belongs to another group list.
-__device__ __forceinline__ void empty_message(uint32_t threads, uint32_t n_groups, vgc_group_hdr* __restrict__ hdrs_out, vgc_pack_status* __restrict__ status) {
-    for (uint32_t k = threadIdx.x; k < n_groups; k += threads) {
-        vgc_group_hdr h;
-        h.exp_field = 0; h.count = 0; h.word_offset = 0;
-        hdrs_out[k] = h;
-    }
-    if (threadIdx.x == 0) {
-        vgc_pack_status st;
-        st.total_words = 0; st.overflow = 0; st.plan_mismatch = 1;
-        *status = st;
-    }
 }
 
 // Bytes of a run of the compressed index format: the sum over its tiles (at most 64, of at most 2 kTile bytes each), by one thread.
@@ -404,7 +357,6 @@ __global__ __launch_bounds__(256) void k_emit(PlanCheck pc, const PlanTile* __re
 // from L2) and finds the groups' exponents and its own four tiles' place by itself, so that two launches and the waits between
 // them fall away.  1.8 M elements (880 tiles): 4.7 + 4.0 + 5.2 us in three kernels, 14.2 us a call -> 9.0.  The records every
 // workgroup reads grow with the set: at 4.1 M elements 11.6 against 15.0 us, and there the registers that hold them end it.
-constexpr uint32_t kSmallTiles = 2048, kSmallGroups = 512;
 __global__ __launch_bounds__(256) void k_pack_small(PlanCheck pc, const uint32_t* __restrict__ flags, const PlanTile* __restrict__ tiles,
                                                     uint32_t n_tiles, uint32_t n_groups, const TileHdr* __restrict__ hdrs,
                                                     const uint16_t* __restrict__ staging, uint32_t* __restrict__ words,
