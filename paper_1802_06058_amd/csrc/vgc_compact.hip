@@ -84,37 +84,69 @@ __device__ __forceinline__ uint32_t encode_tile(const TileAhead& a, const uint16
     return bytes;
 }
 
+// kPer: consecutive tiles a wave does, whose first loads it asks for together.  The launches are rounds of waves that wait for memory
+// (8192 are resident), and with two tiles there are half as many: 138 M elements (67569 tiles) at 1.6 bytes a tile to 400, one
+// tile -> two, us: 43.9 -> 38.5, 48.8 -> 45.0 (67 bytes), 61.7 -> 59.3 (210), 112.3 -> 112.6 (620).  With fewer rounds the last ones,
+// partly empty, cost more than that where tiles have many entries (90 M, 43984 tiles: 38.1 -> 37.0, 87.3 -> 90.0); three or four
+// tiles lose there up to 150 M (138 M: 116.0, 121.7) and gain 3 % where few are sent.
+template <uint32_t kPer>
 __global__ __launch_bounds__(256) void k_compact_count(PlanCheck pc, uint64_t n_tiles, const TileHdr* __restrict__ hdrs,
                                                        const uint16_t* __restrict__ staging, uint16_t* __restrict__ tile_bytes) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t t = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= n_tiles || !plan_ok(pc)) return;
-    const uint32_t bytes = encode_tile(tile_ahead(hdrs, staging, t, lane), staging, t, lane, [](const uint32_t* w) { return (w[7] & 0xFFFFu) != 0; },
-                                       [](bool, uint32_t, uint32_t, bool, uint32_t) {});
-    if (lane == 0) tile_bytes[t] = (uint16_t)bytes;
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t t0 = ((uint64_t)blockIdx.x * 4 + wave) * kPer;
+    if (t0 >= n_tiles || !plan_ok(pc)) return;
+    TileAhead a[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) a[q] = tile_ahead(hdrs, staging, min(t0 + q, n_tiles - 1), lane);
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        if (t0 + q >= n_tiles) break;
+        const uint32_t bytes = encode_tile(a[q], staging, t0 + q, lane, [](const uint32_t* w) { return (w[7] & 0xFFFFu) != 0; },
+                                           [](bool, uint32_t, uint32_t, bool, uint32_t) {});
+        if (lane == 0) tile_bytes[t0 + q] = (uint16_t)bytes;
+    }
 }
 
+template <uint32_t kPer>
 __global__ __launch_bounds__(256) void k_compact_emit(PlanCheck pc, const PlanTile* __restrict__ tiles, uint64_t n_tiles,
                                                       const TileHdr* __restrict__ hdrs, const uint16_t* __restrict__ staging,
                                                       const uint16_t* __restrict__ tile_bytes, const uint64_t* __restrict__ run_offsets,
                                                       uint8_t* __restrict__ stream, uint64_t stream_cap) {
-    const uint32_t lane = threadIdx.x & 63u;
-    const uint64_t t = (uint64_t)blockIdx.x * 4 + (threadIdx.x >> 6);
-    if (t >= n_tiles || !plan_ok(pc)) return;
-    const PlanTile pt = tiles[t];
+    const uint32_t lane = threadIdx.x & 63u, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint64_t t0 = ((uint64_t)blockIdx.x * 4 + wave) * kPer;
+    if (t0 >= n_tiles || !plan_ok(pc)) return;
+    TileAhead a[kPer];
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) a[q] = tile_ahead(hdrs, staging, min(t0 + q, n_tiles - 1), lane);
+    // where the first tile's bytes go: the run's offset plus the bytes of the run's earlier tiles; the others' follow
+    const PlanTile pt = tiles[t0];
     uint64_t out = 0;
-    encode_tile(tile_ahead(hdrs, staging, t, lane), staging, t, lane, [&](const uint32_t* w) {
-        if ((w[7] & 0xFFFFu) == 0) return false;
-        // where the tile's bytes go: the run's offset plus the bytes of the run's earlier tiles
+    auto find_place = [&]() {
         const uint32_t in_run = (pt.start >> kTileShift) % kRunTiles;
-        uint32_t x = lane < in_run ? (uint32_t)tile_bytes[t - in_run + lane] : 0u;
+        const uint32_t x = lane < in_run ? (uint32_t)tile_bytes[t0 - in_run + lane] : 0u;
         out = run_offsets[pt.run] + (uint32_t)__builtin_amdgcn_readlane((int)wave_inclusive_sum(x), 63);
-        return true;
-    }, [&](bool keep, uint32_t b0, uint32_t b1, bool is_long, uint32_t offset) {
-        const uint64_t o = out + offset;
-        if (keep && o < stream_cap) stream[o] = (uint8_t)b0;
-        if (is_long && o + 1 < stream_cap) stream[o + 1] = (uint8_t)b1;
-    });
+    };
+    uint32_t run[kPer] = {pt.run};
+    uint64_t run_at[kPer] = {};
+#pragma unroll
+    for (uint32_t q = 1; q < kPer; ++q) run[q] = tiles[min(t0 + q, n_tiles - 1)].run;
+#pragma unroll
+    for (uint32_t q = 1; q < kPer; ++q) run_at[q] = run_offsets[run[q]];
+    if (kPer > 1) find_place();                            // (one alone: only if it has some)
+#pragma unroll
+    for (uint32_t q = 0; q < kPer; ++q) {
+        if (t0 + q >= n_tiles) break;
+        if (q > 0 && run[q] != run[q - 1]) out = run_at[q];
+        out += encode_tile(a[q], staging, t0 + q, lane, [&](const uint32_t* w) {
+            if ((w[7] & 0xFFFFu) == 0) return false;
+            if (kPer == 1) find_place();
+            return true;
+        }, [&](bool keep, uint32_t b0, uint32_t b1, bool is_long, uint32_t offset) {
+            const uint64_t o = out + offset;
+            if (keep && o < stream_cap) stream[o] = (uint8_t)b0;
+            if (is_long && o + 1 < stream_cap) stream[o + 1] = (uint8_t)b1;
+        });
+    }
 }
 
 // The same for parameter sets of at most kSmallTiles tiles, where the kernels are chains of a few us and the launches between
@@ -234,6 +266,7 @@ __global__ __launch_bounds__(256) void k_compact_emit_small(PlanCheck pc, const 
     }
 }
 
+constexpr uint64_t kTwoTiles = 65536;                       // two tiles a wave from eight rounds of waves on (figures at the kernels)
 int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs,
                         const PlanSeg* segs, uint64_t n_tiles, uint64_t n_runs, uint32_t n_groups, uint32_t n_segs, uint32_t max_group_tiles,
                         TileHdr* hdrs, SegTmp* stmp, const uint16_t* staging, uint8_t* stream_out, uint64_t stream_cap,
@@ -249,13 +282,20 @@ int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* gr
     }
     const int rc = launch_part_scans(pc, groups, tiles, segs, n_tiles, n_segs, max_group_tiles, hdrs, stmp, stream);
     if (rc != VGC_OK) return rc;
-    hipLaunchKernelGGL(k_compact_count, dim3(tb), dim3(256), 0, stream, pc, n_tiles, hdrs, staging, tile_bytes_out);
+    const bool two = n_tiles >= kTwoTiles;
+    const uint32_t blocks = two ? (uint32_t)((n_tiles + 7) / 8) : tb;
+    if (two) hipLaunchKernelGGL(k_compact_count<2>, dim3(blocks), dim3(256), 0, stream, pc, n_tiles, hdrs, staging, tile_bytes_out);
+    else hipLaunchKernelGGL(k_compact_count<1>, dim3(blocks), dim3(256), 0, stream, pc, n_tiles, hdrs, staging, tile_bytes_out);
     const CompactDirectory dir = {tiles, runs, n_runs, tile_bytes_out, run_offsets_out, stream_cap};
     const int rc2 = launch_header_scan(pc, flags, groups, segs, n_groups, n_segs, max_group_tiles, hdrs, stmp, hdrs_out, status_out, ~0ull,
                                        &dir, stream);
     if (rc2 != VGC_OK) return rc2;
-    hipLaunchKernelGGL(k_compact_emit, dim3(tb), dim3(256), 0, stream, pc, tiles, n_tiles, hdrs, staging, tile_bytes_out,
-                       run_offsets_out, stream_out, stream_cap);
+    if (two)
+        hipLaunchKernelGGL(k_compact_emit<2>, dim3(blocks), dim3(256), 0, stream, pc, tiles, n_tiles, hdrs, staging, tile_bytes_out,
+                           run_offsets_out, stream_out, stream_cap);
+    else
+        hipLaunchKernelGGL(k_compact_emit<1>, dim3(blocks), dim3(256), 0, stream, pc, tiles, n_tiles, hdrs, staging, tile_bytes_out,
+                           run_offsets_out, stream_out, stream_cap);
     return hip_check(hipGetLastError(), "launch compact pack kernels");
 }
 

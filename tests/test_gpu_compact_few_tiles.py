@@ -50,3 +50,41 @@ def test_both_forms_match_the_oracle(dev, name, alpha):
         assert np.array_equal(got[:most], stream[:most]) and np.all(got[most:] == 0xEE)
         assert np.array_equal(msg.tile_bytes.cpu().numpy().view(np.uint16), tile_bytes)
         assert np.array_equal(msg.run_offsets.cpu().numpy().view(np.uint64), runs)
+
+
+@pytest.mark.parametrize("alpha", [0.5, 40.0])
+def test_two_tiles_a_wave(dev, alpha):
+    """From 65536 tiles on a wave encodes two, which may belong to different runs and groups; the number is odd.  Against the plain
+    encoder's message: decoded the same, and the directory adds up."""
+    import torch
+    from paper_1802_06058_amd import vgc
+    sizes = [T * 64 * 500 + 7, 3, T * 65, T * 33466 + 1, 2 * T, 1]
+    groups, n = W.groups_from_sizes(sizes), sum(sizes)
+    plan = vgc.Plan(groups, dev)
+    assert plan.n_tiles >= 65536 and plan.n_tiles % 2 == 1
+    gen = torch.Generator(device=dev).manual_seed(int(alpha))
+    g = torch.randn(n, generator=gen, device=dev)
+    g *= torch.exp2(torch.randint(-3, 4, (n,), generator=gen, device=dev).float())
+    g[T * 1000:T * 1100] = 0                                   # tiles without any
+    s, r, v = torch.full((n,), 1.0, device=dev), torch.zeros(n, device=dev), torch.zeros(n, device=dev)
+    scratch, status = plan.new_scratch(), plan.new_status()
+    vgc.accumulate_select(g, s, r, v, plan, alpha, 0.999, scratch)
+    words, hdrs = torch.zeros(n, dtype=torch.int32, device=dev), plan.new_headers()
+    vgc.pack(plan, scratch, words, hdrs, status)
+    count, _ = vgc.read_status(status)
+    msg = compact.CompactMessage(plan, dev, 2 * n)
+    vgc.pack_compact(plan, scratch, msg.stream[:msg.cap], msg.tile_bytes, msg.run_offsets, msg.hdrs, msg.status)
+    total, overflow = vgc.read_status(msg.status)
+    tile_bytes = msg.tile_bytes.long()
+    begin = tile_bytes.cumsum(0) - tile_bytes
+    first, runs = 0, []
+    for size in sizes:
+        tiles = (size + T - 1) // T
+        runs += range(first, first + tiles, 64)
+        first += tiles
+    assert overflow == 0 and count <= total == int(tile_bytes.sum()) and torch.equal(begin[torch.tensor(runs, device=dev)], msg.run_offsets)
+    assert [h[:2] for h in vgc.read_headers(msg.hdrs)] == [h[:2] for h in vgc.read_headers(hdrs)]
+    a, b = g, s                                                # (buffers whose contents are no longer needed)
+    vgc.unpack_add_batch([words], [count], [hdrs], plan, 0.5, a, overwrite=True)
+    vgc.unpack_compact_add_batch([msg.stream], [total], [msg.tile_bytes], [msg.run_offsets], [msg.hdrs], plan, 0.5, b, overwrite=True)
+    assert torch.equal(a.view(torch.int32), b.view(torch.int32)) and bool((msg.stream[msg.cap:] == 0xEE).all())
