@@ -10,7 +10,7 @@
 // latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.66 ms (98 -> 180 TFLOP/s); the 53 layers
 // of ResNet-50 at batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product), 2.17 with
 // k_conv_taps_f32 below.  What bounds it now: the vector instructions that cut the elements (13 per pair, once per filter tap and
-// column tile) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 26 to 33 % busy on ResNet's
+// column tile) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 28 to 41 % busy on ResNet's
 // layers), and on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
 //
 // The bf16 MFMA adds with truncation: chained over all positions, every instruction would cut off a little of the
