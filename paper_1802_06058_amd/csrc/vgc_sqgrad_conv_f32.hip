@@ -80,11 +80,12 @@ template <int W> __device__ __forceinline__ uint32_t lds_piece(uint32_t row, uin
 // element by element of its own operands from memory, and gets what float32 arithmetic gives.  Where all of a tile's sums are NaN
 // already, as they are throughout once a network has diverged, nothing more can change and the walk ends.  3 x 3, 256 -> 256 at
 // 14 x 14, batch 32, through k_conv_f32: 78 us; with an infinity among the activations 181, among the gradients 328, with nothing but NaN 87.
-// x_at(z, p), d_at(z, p): the operands of the lane's row and column (lane % 16) at a position, zero outside; valid(r), at(r):
-// whether row r of the tile is an output in the lane's column, and where it lies.
-template <bool kWantG, typename FX, typename FD, typename FV, typename FO>
-__device__ __forceinline__ void form_again(FX x_at, FD d_at, FV valid, FO at, uint32_t z_begin, uint32_t z_end, uint32_t p_begin,
-                                           uint32_t p_end, bool parts, float fs, float fg, float* __restrict__ so, float* __restrict__ go) {
+// x_at(z, p), d_at(z, p): the operands of the lane's row and column (lane % 16) at a position, zero outside; valid(r): whether row
+// r of the tile is an output in the lane's column.  What is formed, for the rows 4 (lane / 16) .. + 3: the last sample's product,
+// the sum of the samples' squares, and of the products.
+struct Formed { f4v sum, s, g; };
+template <typename FX, typename FD, typename FV>
+__device__ __forceinline__ Formed form_again(FX x_at, FD d_at, FV valid, uint32_t z_begin, uint32_t z_end, uint32_t p_begin, uint32_t p_end) {
     const uint32_t lane = threadIdx.x & 63u;
     // whether the sums at the lane's outputs are all NaN
     auto settled = [&](const f4v& v) {
@@ -93,12 +94,12 @@ __device__ __forceinline__ void form_again(FX x_at, FD d_at, FV valid, FO at, ui
         for (int i = 0; i < 4; ++i) s = s && (v[i] != v[i] || !valid(4u * (lane >> 4) + (uint32_t)i));
         return __ballot(!s) == 0;
     };
-    f4v sum = (f4v){0}, s4 = (f4v){0}, g4 = (f4v){0};
+    Formed F = {};
 #pragma unroll 1
-    for (uint32_t z = z_begin; z < z_end && !settled(s4); ++z) {
-        sum = (f4v){0};
+    for (uint32_t z = z_begin; z < z_end && !settled(F.s); ++z) {
+        F.sum = (f4v){0};
 #pragma unroll 1
-        for (uint32_t p0 = p_begin; p0 < p_end && !settled(sum); p0 += 16) {
+        for (uint32_t p0 = p_begin; p0 < p_end && !settled(F.sum); p0 += 16) {
             float x[4], d[4];
 #pragma unroll
             for (uint32_t k = 0; k < 4; ++k) {
@@ -106,21 +107,34 @@ __device__ __forceinline__ void form_again(FX x_at, FD d_at, FV valid, FO at, ui
                 d[k] = d_at(z, p0 + 4u * k + (lane >> 4));
             }
 #pragma unroll
-            for (int k = 0; k < 4; ++k) sum = __builtin_amdgcn_mfma_f32_16x16x4f32(x[k], d[k], sum, 0, 0, 0);
+            for (int k = 0; k < 4; ++k) F.sum = __builtin_amdgcn_mfma_f32_16x16x4f32(x[k], d[k], F.sum, 0, 0, 0);
         }
 #pragma unroll
-        for (int i = 0; i < 4; ++i) s4[i] = __builtin_fmaf(sum[i], sum[i], s4[i]);
-        g4 = g4 + sum;
+        for (int i = 0; i < 4; ++i) F.s[i] = __builtin_fmaf(F.sum[i], F.sum[i], F.s[i]);
+        F.g = F.g + F.sum;
     }
+    return F;
+}
+// at(r): where row r of the tile lies in the lane's column.
+template <bool kWantG, typename FV, typename FO>
+__device__ __forceinline__ void store_formed(const Formed& F, FV valid, FO at, bool parts, float fs, float fg, float* __restrict__ so, float* __restrict__ go) {
+    const uint32_t lane = threadIdx.x & 63u;
 #pragma unroll
     for (int i = 0; i < 4; ++i) {
         const uint32_t r = 4u * (lane >> 4) + (uint32_t)i;
         if (valid(r)) {
             const size_t o = at(r);
-            __builtin_nontemporal_store(parts ? sum[i] : fs * s4[i], so + o);
-            if (kWantG) __builtin_nontemporal_store(fg * g4[i], go + o);
+            __builtin_nontemporal_store(parts ? F.sum[i] : fs * F.s[i], so + o);
+            if (kWantG) __builtin_nontemporal_store(fg * F.g[i], go + o);
         }
     }
+}
+// Whether one of the wave's sums is an infinity or NaN.
+__device__ __forceinline__ bool not_finite(const f4v& v) {
+    uint32_t most = 0;
+#pragma unroll
+    for (int i = 0; i < 4; ++i) most = max(most, __float_as_uint(v[i]) & 0x7FFFFFFFu);
+    return __ballot(most >= 0x7F800000u) != 0;
 }
 
 // X is [B, P, J], D is [B, P, C], samples z_begin .. z_end-1 of this workgroup's split.
@@ -474,7 +488,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
         const uint32_t tile = (uint32_t)__builtin_ctz(again), m = tile / NTL, n = tile % NTL;
         const uint32_t jt = j0 + wm * (uint32_t)WM + m * 16u, j = jt + (lane & 15u), col = c0 + wn * (uint32_t)WN + n * 16u + (lane & 15u);
         const uint32_t tap = kMode == kPatches ? 0u : j / G.Cin, ky = kMode == kPatches ? 0u : tap / G.kw, kx = tap - ky * G.kw;
-        form_again<kWantG>(
+        auto valid = [&](uint32_t r) { return jt + r < J && col < C; };
+        const Formed F = form_again(
             [&](uint32_t z, uint32_t p) -> float {
                 if (j >= J || p >= p_end) return 0.f;
                 if (kMode == kPatches) return X[((size_t)z * P + p) * J + j];
@@ -482,9 +497,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
                 return iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + (j - tap * G.Cin)] : 0.f;
             },
             [&](uint32_t z, uint32_t p) -> float { return col < C && p < p_end ? D[((size_t)z * P + p) * C + col] : 0.f; },
-            [&](uint32_t r) { return jt + r < J && col < C; },
-            [&](uint32_t r) -> size_t { return (size_t)(jt + r) * C + col; },
-            z_begin, z_end, p_begin, p_end, split_p > 1, fs, fg, so, go);
+            valid, z_begin, z_end, p_begin, p_end);
+        store_formed<kWantG>(F, valid, [&](uint32_t r) -> size_t { return (size_t)(jt + r) * C + col; }, split_p > 1, fs, fg, so, go);
     }
 }
 
@@ -841,10 +855,26 @@ void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, u
         }
     }
 
+    // one bit per tile with a sum that is not finite: of a group's squares each by itself, so that with g as without only that group's
+    // are formed again, and the other's stay (in shS from then on)
+    uint32_t again = 0, again_first = 0;
     if (kWantG && to_second <= 0) {
 #pragma unroll
-        for (int t = 0; t < 9; ++t) s_acc[t][0] = shS[t * 512 + tid] + s_acc[t][0];
+        for (int t = 0; t < 9; ++t) {
+            const f4v first = shS[t * 512 + tid], second = s_acc[t][0];
+            s_acc[t][0] = first + second;
+            again |= (not_finite(second) ? 1u : 0u) << t;
+            if (not_finite(first)) {
+                again_first |= 1u << t;
+                shS[t * 512 + tid] = second;
+            }
+        }
         if (halve_g) each_out([&](int t, int n, int i, size_t o) { g_acc[t][n][i] = go[o] + g_acc[t][n][i]; });
+    } else {
+#pragma unroll
+        for (int t = 0; t < 9; ++t)
+#pragma unroll
+            for (int n = 0; n < NTL; ++n) again |= (not_finite(split_p > 1 ? acc[t][n] : s_acc[t][n]) ? 1u : 0u) << (t * NTL + n);
     }
     each_out([&](int t, int n, int i, size_t o) {
         const float out = split_p > 1 ? kDown * acc[t][n][i] : fs * s_acc[t][n][i];
@@ -855,34 +885,38 @@ void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, u
             else go[o] = fg * g_acc[t][n][i];
         }
     });
-    uint32_t again = 0;                                              // one bit per tile with a sum that is not finite
-#pragma unroll
-    for (int t = 0; t < 9; ++t)
-#pragma unroll
-        for (int n = 0; n < NTL; ++n) {
-            uint32_t most = 0;
-#pragma unroll
-            for (int i = 0; i < 4; ++i) most = max(most, __float_as_uint(split_p > 1 ? acc[t][n][i] : s_acc[t][n][i]) & 0x7FFFFFFFu);
-            again |= (__ballot(most >= 0x7F800000u) ? 1u : 0u) << (t * NTL + n);
-        }
-    if (again == 0) return;
+    if ((again | again_first) == 0) return;
     const uint32_t q_begin = c_begin * kR32, q_end = min((uint32_t)(G.H * Wp), split_p > 1 ? (c_begin + total) * kR32 : G.H * Wp);
 #pragma unroll 1
-    for (; again; again &= again - 1u) {
-        const uint32_t tile = (uint32_t)__builtin_ctz(again), t = tile / NTL, n = tile % NTL, ky = t / 3u, kx = t - 3u * ky;
+    for (uint32_t rest = again | again_first; rest; rest &= rest - 1u) {
+        const uint32_t tile = (uint32_t)__builtin_ctz(rest), t = tile / NTL, n = tile % NTL, ky = t / 3u, kx = t - 3u * ky;
         const uint32_t chm = i0 + wc * 16u, colm = c0 + wn * (uint32_t)(NTL * 16) + n * 16u, ch = chm + (lane & 15u), col = colm + (lane & 15u);
-        form_again<kWantG>(
-            [&](uint32_t z, uint32_t q) -> float {
-                const uint32_t y = q / Wp, x = q - y * Wp, iy = y + ky - 1u, ix = x + kx - 1u;
-                return ch < G.Cin && q < q_end && x < G.W && iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + ch] : 0.f;
-            },
-            [&](uint32_t z, uint32_t q) -> float {
-                const uint32_t y = q / Wp, x = q - y * Wp;
-                return col < C && q < q_end && x < G.W ? D[(((size_t)z * G.H + y) * G.W + x) * C + col] : 0.f;
-            },
-            [&](uint32_t r) { return chm + r < G.Cin && col < C; },
-            [&](uint32_t r) -> size_t { return (size_t)(t * G.Cin + chm + r) * C + col; },
-            z_begin, z_end, q_begin, q_end, split_p > 1, fs, fg, so, go);
+        auto valid = [&](uint32_t r) { return chm + r < G.Cin && col < C; };
+        auto form = [&](uint32_t z0, uint32_t z1) {
+            return form_again(
+                [&](uint32_t z, uint32_t q) -> float {
+                    const uint32_t y = q / Wp, x = q - y * Wp, iy = y + ky - 1u, ix = x + kx - 1u;
+                    return ch < G.Cin && q < q_end && x < G.W && iy < G.H && ix < G.W ? X[(((size_t)z * G.H + iy) * G.W + ix) * G.Cin + ch] : 0.f;
+                },
+                [&](uint32_t z, uint32_t q) -> float {
+                    const uint32_t y = q / Wp, x = q - y * Wp;
+                    return col < C && q < q_end && x < G.W ? D[(((size_t)z * G.H + y) * G.W + x) * C + col] : 0.f;
+                },
+                valid, z0, z1, q_begin, q_end);
+        };
+        Formed F;
+        if (kWantG && to_second <= 0) {
+            const uint32_t z_second = z_of(2u * split + 1u);
+            F = form(z_begin, z_second);
+            Formed second = form(z_second, z_end);
+            if (!(again_first >> t & 1u)) F.s = shS[t * 512 + tid];
+            else if (!(again >> t & 1u)) second.s = shS[t * 512 + tid];
+            F.s = F.s + second.s;
+            F.g = F.g + second.g;
+        } else {
+            F = form(z_begin, z_end);
+        }
+        store_formed<kWantG>(F, valid, [&](uint32_t r) -> size_t { return (size_t)(t * G.Cin + chm + r) * C + col; }, split_p > 1, fs, fg, so, go);
     }
 }
 

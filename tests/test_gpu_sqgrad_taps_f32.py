@@ -106,3 +106,21 @@ def test_sums_that_are_not_finite(dev, shape):
             assert np.array_equal(got[inf], ref[inf].astype(np.float32)) and np.isfinite(got[fin]).all()
             if rtol:
                 assert np.all(np.abs(got[fin] - ref[fin]) <= rtol * ref[fin])
+
+
+@pytest.mark.parametrize("shape", [(32, 14, 14, 256, 256), (8, 7, 7, 512, 1024), (4, 14, 14, 1024, 512)], ids=lambda s: "x".join(map(str, s)))
+def test_s_is_the_same_with_g_beside_sums_that_are_not_finite(dev, shape):
+    """A workgroup has two groups of samples with g and one without.  Where one group's sums are not finite they are formed again, and
+    finite ones share their tiles: s is the same bits whether g is asked for or not.  Infinities in the first, the second and in both
+    groups of a pair, a NaN, and a group whose sum alone overflows."""
+    B, H, W, Cin, C = shape
+    A, D = _inputs(shape)
+    D *= 1e3
+    A[0, 0, 0, 1], A[B // 4 - 1, H // 2, 3, 40], A[B // 2, 1, 1, 70], A[-1, 2, 2, 100], D[1, 3, 3, 20] = np.inf, -np.inf, np.inf, np.inf, np.nan
+    A[B // 2 + 1, 4, 4, 130], D[B // 2 + 1, 4, 4, 200] = 2.0 ** 80, 2.0 ** 20
+    c = float(np.float32(1.0 / B))
+    for use_workspace in (True, False):
+        _, s = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev, False, use_workspace)
+        _, s_with_g = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev, True, use_workspace)
+        assert np.isnan(s).any() and np.isinf(s).any() and np.isfinite(s).any()
+        np.testing.assert_array_equal(s_with_g, s)
