@@ -191,6 +191,7 @@ static void check_compute_errors() {
 namespace vgc {
 bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
 bool compact_thin_streams(const uint64_t* n_bytes, uint32_t p, uint64_t n_tiles);
+bool conv_taps_f32_chosen(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace);
 }
 static void check_dispatch() {
     const uint64_t dense[3] = {100, 8, 1ull << 40}, empty[3] = {100, 0, 8}, few[3] = {0, 100, 7}, one[1] = {1};
@@ -199,6 +200,15 @@ static void check_dispatch() {
     const uint64_t thin[3] = {2000, 0, 1999}, thick[3] = {8, 2001, 0};
     CHECK(vgc::compact_thin_streams(thin, 3, 10) && !vgc::compact_thin_streams(thick, 3, 10) && !vgc::compact_thin_streams(thin, 1, 10));
     CHECK(!vgc::compact_thin_streams(nullptr, 0, 10) && !vgc::compact_thin_streams(dense, 3, ~0u));
+    // The float32 3 x 3 layers that the nine-tap kernel takes, and those where it is slower: with g (two rounds of workgroups there, one
+    // without), and with samples in parts whose sum costs more than they gain.  B, H, W, Cin, C.
+    const uint32_t taken[][5] = {{32, 56, 56, 64, 64}, {32, 28, 28, 128, 128}, {32, 14, 14, 256, 256}, {32, 7, 7, 512, 512}, {64, 14, 14, 512, 512},
+                                 {16, 7, 7, 1024, 1024}, {4, 14, 14, 1024, 512}, {8, 7, 7, 512, 1024}};
+    const uint32_t left[][5] = {{182, 50, 7, 64, 832}, {19, 8, 9, 408, 448}, {50, 24, 25, 392, 312}, {56, 6, 8, 960, 320}, {5, 39, 6, 768, 896},
+                                {12, 88, 7, 976, 796}, {37, 22, 22, 144, 392}, {1, 7, 77, 468, 900}, {32, 14, 79, 256, 256}, {32, 4, 4, 512, 512}};
+    for (const auto& q : taken) CHECK(vgc::conv_taps_f32_chosen(q[0], q[1], q[2], q[3], q[4], true));
+    for (const auto& q : left) CHECK(!vgc::conv_taps_f32_chosen(q[0], q[1], q[2], q[3], q[4], true));
+    CHECK(!vgc::conv_taps_f32_chosen(32, 14, 14, 256, 256, false) && vgc::conv_taps_f32_chosen(16, 7, 7, 1024, 1024, false));
 }
 
 int main() {

@@ -1039,38 +1039,66 @@ static TapsGeom taps_geom(uint32_t H, uint32_t W, uint32_t Cin) {
     }
     return G;
 }
-// About how long a shape takes, in us: 3.5 and rounds of workgroups, each of which begins and ends in 6.5 and takes `step` a chunk, and
-// the planes of a split, written and read again at 5 TB/s with a launch of 4.
-static double f32_us(uint64_t tiles, uint64_t slots, uint32_t n_chunks, double step, uint32_t B, const F32Split& s, uint32_t J, uint32_t C) {
-    const uint64_t rounds = (tiles * s.splits + slots - 1) / slots;
-    const uint64_t chunks = s.split_p > 1 ? (n_chunks + s.split_p - 1) / s.split_p : (uint64_t)((B + s.splits - 1) / s.splits) * n_chunks;
-    return 3.5 + (double)rounds * (6.5 + (double)chunks * step) + (s.splits > 1 ? 4.0 + (double)s.splits * J * C * 8.0 / 5e6 : 0.0);
+// About how long a shape takes, in us: 3.5 and rounds of workgroups, each of which begins and ends in `begin` and takes `step` for each of
+// its chunks, and the planes that it leaves, written and read again at 5 TB/s with a launch of 4; parts of samples are added by 16
+// threads for a sample's four outputs, most of them idle with few samples: 9 per million outputs.
+static double f32_us(uint64_t workgroups, uint64_t slots, uint64_t chunks, double begin, double step, uint32_t planes, bool parts, uint32_t J, uint32_t C) {
+    const double rounds = (double)((workgroups + slots - 1) / slots), JC = (double)J * C;
+    return 3.5 + rounds * (begin + (double)chunks * step) + (planes ? 4.0 + planes * JC * 8.0 / 5e6 : 0.0) + (parts ? JC * 9e-6 : 0.0);
+}
+static uint64_t f32_chunks(const F32Split& s, uint32_t B, uint32_t n_chunks) {           // of a workgroup
+    return s.split_p > 1 ? (n_chunks + s.split_p - 1) / s.split_p : (uint64_t)((B + s.splits - 1) / s.splits) * n_chunks;
 }
 
-// 0 or an error: launched; 1: k_conv_f32 takes the shape.  Which of the two is faster follows from that estimate, whose steps
-// were measured: 1.45 us a chunk with 128 x 128 tiles, 1.55 with two workgroups of half of that per compute unit, 2.35 for the
-// 576 x 64 of k_conv_taps_f32.  Estimated and measured times, k_conv_f32 / k_conv_taps_f32, batch 32: 512 channels at 7 x 7
-// 118 / 67 and 104 / 68; 256 at 14 x 14 71 / 62 and 67 / 58; 128 at 28 x 28 90 / 62 and 81 / 55; 64 at 56 x 56 71 / 65 and 69 / 58; what goes to
+// Which of the two kernels takes a shape follows from that estimate, whose steps were measured: 1.45 us a chunk with 128 x 128 tiles,
+// 1.55 with two workgroups of half of that per compute unit, 2.35 for the 576 x 64 of k_conv_taps_f32, and 1.45 for its 288 x 64 with g.
+// Both forms of a call have to take the same way, so that s is the same: k_conv_taps_f32 where it is 6 % faster without g and not
+// slower with it.  Estimated and measured times, k_conv_f32 / k_conv_taps_f32, batch 32: 512 channels at 7 x 7 118 / 67 and 104 / 68; 256 at
+// 14 x 14 71 / 62 and 67 / 58; 128 at 28 x 28 90 / 63 and 81 / 55; 64 at 56 x 56 71 / 66 and 69 / 58; what goes to
 // k_conv_f32: 256 at 14 x 14, batch 33 71 / 74 and 63 / 67; 192 -> 160 at 14 x 14 51 / 54 and 50 / 51; 256 at 8 x 8, batch 64
-// 50 / 57 and 47 / 57; 128 at 14 x 14, batch 7 26 / 32 and 21 / 28.  With g, which has to take the same way, so that s is the same, the
-// shapes above that come here gain as much or more (256 at 14 x 14, the least, 70 and 67).
+// 50 / 57 and 47 / 57; 128 at 14 x 14, batch 7 26 / 32 and 21 / 28.  With g: 512 at 7 x 7 144 / 77 and 120 / 81; 256 at 14 x 14 78 / 71 and
+// 66 / 63; 64 -> 640 at 30 x 15, batch 111 287 / 261 and 256 / 255.  Half the channels a workgroup often make two rounds of one there:
+// 64 -> 832 at 50 x 7, batch 182 439 / 792 and 406 / 742, 408 -> 448 at 8 x 9, batch 19 75 / 117 and 62 / 117, 960 -> 320 at 6 x 8,
+// batch 56 223 / 261 and 191 / 274, for 10 to 36 % without g.  Of 190 shapes about the line the 96 that come here take 0.45 to 1.03 of
+// k_conv_f32's time with g and 0.50 to 0.96 without; the others would have taken 0.88 to 1.90, 1.15 in the mean.
+static bool conv_taps_f32_way(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool space, TapsGeom& G, F32Split& sp) {
+    if (W > kTapsMaxW || H * W <= kR32 / 2) return false;
+    G = taps_geom(H, W, Cin);
+    const uint32_t J = 9 * Cin, P = H * W, tiles_c = (C + 63) / 64;
+    const uint64_t tiles = (uint64_t)((Cin + 63) / 64) * tiles_c;
+    const F32Tile t = conv_f32_tile(J, C);
+    const size_t asked = conv_f32_workspace_bytes(B, P, J, C);
+    const F32Split none{1, 1}, other = space ? f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked) : none;
+    sp = space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, asked, true) : none;
+    const bool parts = sp.split_p > 1, other_parts = other.split_p > 1;
+    const uint64_t chunks = f32_chunks(sp, B, G.n_chunks), other_chunks = f32_chunks(other, B, (P + kR32 - 1) / kR32);
+    auto general = [&](bool g) {
+        const uint32_t planes = other.splits > 1 ? other.splits * (g && !other_parts ? 2 : 1) : 0;
+        return f32_us(conv_f32_tiles(t, J, C) * other.splits, conv_f32_slots(t), other_chunks, 6.5, t.bm + t.bn == 256 ? 1.45 : 1.55, planes, other_parts, J, C);
+    };
+    if (f32_us(tiles * sp.splits, 256, chunks, 6.5, 2.35, sp.splits > 1 ? sp.splits : 0, parts, J, C) > 0.94 * general(false)) return false;
+    if (parts) return true;                                              // the variant without g serves both
+    const uint32_t blocks = (sp.splits + 1) / 2;
+    return f32_us((uint64_t)((Cin + 31) / 32) * tiles_c * blocks, 256, chunks * (sp.splits > 1 ? 2 : 1), 7.8, 1.45, blocks > 1 ? 2 * blocks : 0, false, J, C) <=
+           general(true);
+}
+bool conv_taps_f32_chosen(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace) {
+    TapsGeom G;
+    F32Split sp;
+    return conv_taps_f32_way(B, H, W, Cin, C, workspace, G, sp);
+}
+
+// 0 or an error: launched; 1: k_conv_f32 takes the shape.
 static int launch_conv_taps_f32(const void* X, const void* D, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, float c,
                                 float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
-    if (W > kTapsMaxW || H * W <= kR32 / 2) return 1;
-    const TapsGeom G = taps_geom(H, W, Cin);
-    const uint32_t J = 9 * Cin, P = H * W, tiles_i = (Cin + 63) / 64;
-    const uint64_t tiles = (uint64_t)tiles_i * ((C + 63) / 64);
-    const F32Tile t = conv_f32_tile(J, C);
-    const size_t JC = (size_t)J * C, asked = conv_f32_workspace_bytes(B, P, J, C);
-    const bool space = workspace && workspace_bytes >= asked;
-    const F32Split none{1, 1}, sp = space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, asked, true) : none;
-    const F32Split other = space ? f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked) : none;
-    if (f32_us(tiles, 256, G.n_chunks, 2.35, B, sp, J, C) >
-        0.94 * f32_us(conv_f32_tiles(t, J, C), conv_f32_slots(t), (P + kR32 - 1) / kR32, t.bm + t.bn == 256 ? 1.45 : 1.55, B, other, J, C))
-        return 1;
+    TapsGeom G;
+    F32Split sp;
+    const uint32_t J = 9 * Cin;
+    if (!conv_taps_f32_way(B, H, W, Cin, C, workspace && workspace_bytes >= conv_f32_workspace_bytes(B, H * W, J, C), G, sp)) return 1;
+    const size_t JC = (size_t)J * C;
     const bool with_g = g_out && sp.split_p == 1;
     const uint32_t blocks = with_g ? (sp.splits + 1) / 2 : sp.splits;
-    const uint64_t nblk = (uint64_t)(with_g ? (Cin + 31) / 32 : tiles_i) * ((C + 63) / 64) * blocks;
+    const uint64_t nblk = (uint64_t)(with_g ? (Cin + 31) / 32 : (Cin + 63) / 64) * ((C + 63) / 64) * blocks;
     if (nblk > 0x7FFFFFFFull) { set_error("vgc_sqgrad: shape exceeds the launch limit"); return VGC_ERR_SIZE; }
     const float cg = c, cs = c * c;
     float* ws = static_cast<float*>(workspace);
