@@ -211,6 +211,26 @@ static void check_dispatch() {
     CHECK(!vgc::conv_taps_f32_chosen(32, 14, 14, 256, 256, false) && vgc::conv_taps_f32_chosen(16, 7, 7, 1024, 1024, false));
 }
 
+// The workspace of a float32 convolution follows from the best number of splits of the batch, found here by looking at every one
+// (the library steps over those that leave the largest number of samples the same).  128 x 128 tiles, 512 of them at once.
+static void check_f32_splits() {
+    for (uint32_t B : {1u, 2u, 3u, 7u, 31u, 64u, 97u, 255u, 256u, 1000u, 4099u})
+        for (uint32_t Cin : {128u, 256u, 512u})
+            for (uint32_t C : {128u, 384u, 1024u}) {
+                const uint32_t J = 9 * Cin, P = 8 * 8;                // (samples too short to be split themselves)
+                const uint64_t tiles = (uint64_t)((J + 127) / 128) * ((C + 127) / 128);
+                uint32_t splits = 1;
+                double best = 1e300;
+                for (uint32_t s = 1; s <= B; ++s) {
+                    const uint32_t zper = (B + s - 1) / s;
+                    if ((B + zper - 1) / zper != s) continue;
+                    const double cost = (double)((tiles * s + 511) / 512) * zper + (s > 1 ? 0.5 * s * (double)tiles / 512 + 0.5 : 0.0);
+                    if (cost < best - 1e-9) { best = cost; splits = s; }
+                }
+                CHECK(vgc_sqgrad_workspace_bytes(VGC_CONV, VGC_F32, B, P, J, C) == (splits > 1 ? (size_t)splits * 2 * J * C * 4 : 0));
+            }
+}
+
 int main() {
     const uint32_t T = vgc_tile_size();
     check_plan({1});
@@ -225,6 +245,7 @@ int main() {
     check_group_errors();
     check_compute_errors();
     check_dispatch();
+    check_f32_splits();
     if (g_failed) { std::fprintf(stderr, "hostcheck: %d check(s) failed\n", g_failed); return 1; }
     std::printf("hostcheck ok\n");
     return 0;

@@ -968,15 +968,16 @@ static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32
         if (r.split_p > 1) { r.splits = B * r.split_p; return r; }
         r.split_p = 1;
     }
+    // of the numbers of splits with the same largest number of samples the smallest; the next has fewer samples
     double best = 1e300;
-    for (uint32_t s = 1; s <= B; ++s) {
-        const uint32_t zper = (B + s - 1) / s, s2 = (B + zper - 1) / zper;
-        if (s2 != s || f32_split_bytes(F32Split{s, 1}, J, C, pairs) > most) continue;
-        const uint64_t rounds = (tiles * s2 + slots - 1) / slots;
-        const double cost = (double)rounds * zper + (s2 > 1 ? 0.5 * s2 * (double)tiles / slots + 0.5 : 0.0);
-        if (cost < best - 1e-9) { best = cost; r.splits = s2; }
+    for (uint32_t s = 1, zper = B;; s = (B + zper - 2) / (zper - 1), zper = (B + s - 1) / s) {
+        if (f32_split_bytes(F32Split{s, 1}, J, C, pairs) <= most) {
+            const uint64_t rounds = (tiles * s + slots - 1) / slots;
+            const double cost = (double)rounds * zper + (s > 1 ? 0.5 * s * (double)tiles / slots + 0.5 : 0.0);
+            if (cost < best - 1e-9) { best = cost; r.splits = s; }
+        }
+        if (zper == 1) return r;
     }
-    return r;
 }
 // The workspace a shape asks for, which is also what vgc_sqgrad_noalloc accepts or refuses it by, is a rule of its own: what
 // two, four or six workgroups per compute unit of 128 x 128, 128 x 64 and 64 x 64 tiles would fill.  The kernel has fewer and
@@ -987,16 +988,21 @@ size_t conv_f32_workspace_bytes(uint32_t B, uint32_t P, uint32_t J, uint32_t C) 
     return f32_split_bytes(f32_split(conv_f32_tiles(t, J, C), slots, 16, B, P, J, C, ~(size_t)0), J, C, false);
 }
 
+// What k_conv_f32 would do with a shape: its tile and split; space: whether the caller's workspace is as large as asked for.
+struct F32Way { F32Tile t; size_t asked; bool space; F32Split sp; };
+static F32Way conv_f32_way(uint32_t B, uint32_t P, uint32_t J, uint32_t C, bool workspace, size_t workspace_bytes) {
+    F32Way w{conv_f32_tile(J, C), conv_f32_workspace_bytes(B, P, J, C), false, {1, 1}};
+    w.space = workspace && workspace_bytes >= w.asked;
+    if (w.space) w.sp = f32_split(conv_f32_tiles(w.t, J, C), conv_f32_slots(w.t), kR32, B, P, J, C, w.asked);
+    return w;
+}
+
 template <int kMode>
-static int launch_conv_f32_any(const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
-                               float* g_out, float* s_out, void* workspace, size_t workspace_bytes, const ConvGeom& G,
-                               hipStream_t stream) {
+static int launch_conv_f32_any(const F32Way& way, const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
+                               float* g_out, float* s_out, void* workspace, const ConvGeom& G, hipStream_t stream) {
     const size_t JC = (size_t)J * C;
-    const F32Tile t = conv_f32_tile(J, C);
-    const size_t asked = conv_f32_workspace_bytes(B, P, J, C);
-    F32Split sp = f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked);
-    if (!workspace || workspace_bytes < asked) sp = F32Split{1, 1};
-    const uint32_t splits = sp.splits, split_p = sp.split_p;
+    const F32Tile t = way.t;
+    const uint32_t splits = way.sp.splits, split_p = way.sp.split_p;
     // with the positions split the partial products are unsquared: the variant without g serves both
     const bool with_g = g_out && split_p == 1;
     const uint64_t nblk = conv_f32_tiles(t, J, C) * splits;
@@ -1061,15 +1067,14 @@ static uint64_t f32_chunks(const F32Split& s, uint32_t B, uint32_t n_chunks) {  
 // 64 -> 832 at 50 x 7, batch 182 439 / 792 and 406 / 742, 408 -> 448 at 8 x 9, batch 19 75 / 117 and 62 / 117, 960 -> 320 at 6 x 8,
 // batch 56 223 / 261 and 191 / 274, for 10 to 36 % without g.  Of 190 shapes about the line the 96 that come here take 0.45 to 1.03 of
 // k_conv_f32's time with g and 0.50 to 0.96 without; the others would have taken 0.88 to 1.90, 1.15 in the mean.
-static bool conv_taps_f32_way(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool space, TapsGeom& G, F32Split& sp) {
+static bool conv_taps_f32_way(const F32Way& way, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, TapsGeom& G, F32Split& sp) {
     if (W > kTapsMaxW || H * W <= kR32 / 2) return false;
     G = taps_geom(H, W, Cin);
     const uint32_t J = 9 * Cin, P = H * W, tiles_c = (C + 63) / 64;
     const uint64_t tiles = (uint64_t)((Cin + 63) / 64) * tiles_c;
-    const F32Tile t = conv_f32_tile(J, C);
-    const size_t asked = conv_f32_workspace_bytes(B, P, J, C);
-    const F32Split none{1, 1}, other = space ? f32_split(conv_f32_tiles(t, J, C), conv_f32_slots(t), kR32, B, P, J, C, asked) : none;
-    sp = space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, asked, true) : none;
+    const F32Tile t = way.t;
+    const F32Split other = way.sp;
+    sp = way.space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, way.asked, true) : F32Split{1, 1};
     const bool parts = sp.split_p > 1, other_parts = other.split_p > 1;
     const uint64_t chunks = f32_chunks(sp, B, G.n_chunks), other_chunks = f32_chunks(other, B, (P + kR32 - 1) / kR32);
     auto general = [&](bool g) {
@@ -1085,17 +1090,16 @@ static bool conv_taps_f32_way(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, 
 bool conv_taps_f32_chosen(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace) {
     TapsGeom G;
     F32Split sp;
-    return conv_taps_f32_way(B, H, W, Cin, C, workspace, G, sp);
+    return conv_taps_f32_way(conv_f32_way(B, H * W, 9 * Cin, C, workspace, ~(size_t)0), B, H, W, Cin, C, G, sp);
 }
 
 // 0 or an error: launched; 1: k_conv_f32 takes the shape.
-static int launch_conv_taps_f32(const void* X, const void* D, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, float c,
-                                float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
+static int launch_conv_taps_f32(const F32Way& way, const void* X, const void* D, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin,
+                                uint32_t C, float c, float* g_out, float* s_out, void* workspace, hipStream_t stream) {
     TapsGeom G;
     F32Split sp;
-    const uint32_t J = 9 * Cin;
-    if (!conv_taps_f32_way(B, H, W, Cin, C, workspace && workspace_bytes >= conv_f32_workspace_bytes(B, H * W, J, C), G, sp)) return 1;
-    const size_t JC = (size_t)J * C;
+    if (!conv_taps_f32_way(way, B, H, W, Cin, C, G, sp)) return 1;
+    const size_t JC = (size_t)9 * Cin * C;
     const bool with_g = g_out && sp.split_p == 1;
     const uint32_t blocks = with_g ? (sp.splits + 1) / 2 : sp.splits;
     const uint64_t nblk = (uint64_t)(with_g ? (Cin + 31) / 32 : (Cin + 63) / 64) * ((C + 63) / 64) * blocks;
@@ -1115,13 +1119,15 @@ static int launch_conv_taps_f32(const void* X, const void* D, uint32_t B, uint32
 
 int launch_conv_f32_tiled(const void* X, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
                           float* g_out, float* s_out, void* workspace, size_t workspace_bytes, hipStream_t stream) {
-    return launch_conv_f32_any<kPatches>(X, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, ConvGeom{}, stream);
+    const F32Way way = conv_f32_way(B, P, J, C, workspace != nullptr, workspace_bytes);
+    return launch_conv_f32_any<kPatches>(way, X, D, B, P, J, C, c, g_out, s_out, workspace, ConvGeom{}, stream);
 }
 
 int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, uint32_t J, uint32_t C, float c,
                       float* g_out, float* s_out, void* workspace, size_t workspace_bytes, ConvGeom G, hipStream_t stream) {
+    const F32Way way = conv_f32_way(B, P, J, C, workspace != nullptr, workspace_bytes);
     if (G.kw == 3 && J == 9 * G.Cin && G.sh == 1 && G.sw == 1 && G.ph == 1 && G.pw == 1) {
-        const int rc = launch_conv_taps_f32(act, D, B, G.H, G.W, G.Cin, C, c, g_out, s_out, workspace, workspace_bytes, stream);
+        const int rc = launch_conv_taps_f32(way, act, D, B, G.H, G.W, G.Cin, C, c, g_out, s_out, workspace, stream);
         if (rc <= 0) return rc;
     }
     if (G.sh == 1 && G.sw == 1 && G.Wo == G.W && P > kR32 / 2) {
@@ -1129,11 +1135,11 @@ int launch_conv2d_f32(const void* act, const void* D, uint32_t B, uint32_t P, ui
         while (b) { const uint32_t m = a % b; a = b; b = m; }
         G.period = G.W / a;
         G.step_x = kR32 % G.W;
-        if (G.period <= 32) return launch_conv_f32_any<kLinear>(act, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, G, stream);
+        if (G.period <= 32) return launch_conv_f32_any<kLinear>(way, act, D, B, P, J, C, c, g_out, s_out, workspace, G, stream);
     }
     G.step_y = kR32 / G.Wo;
     G.step_x = kR32 % G.Wo;
-    return launch_conv_f32_any<kGeneral>(act, D, B, P, J, C, c, g_out, s_out, workspace, workspace_bytes, G, stream);
+    return launch_conv_f32_any<kGeneral>(way, act, D, B, P, J, C, c, g_out, s_out, workspace, G, stream);
 }
 
 }  // namespace vgc
