@@ -191,7 +191,7 @@ static void check_compute_errors() {
 namespace vgc {
 bool compact_short_streams(const uint64_t* n_bytes, uint32_t p);
 bool compact_thin_streams(const uint64_t* n_bytes, uint32_t p, uint64_t n_tiles);
-bool conv_taps_f32_chosen(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace);
+uint32_t conv_taps_f32_splits(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace);
 }
 static void check_dispatch() {
     const uint64_t dense[3] = {100, 8, 1ull << 40}, empty[3] = {100, 0, 8}, few[3] = {0, 100, 7}, one[1] = {1};
@@ -204,11 +204,20 @@ static void check_dispatch() {
     // without), and with samples in parts whose sum costs more than they gain.  B, H, W, Cin, C.
     const uint32_t taken[][5] = {{32, 56, 56, 64, 64}, {32, 28, 28, 128, 128}, {32, 14, 14, 256, 256}, {32, 7, 7, 512, 512}, {64, 14, 14, 512, 512},
                                  {16, 7, 7, 1024, 1024}, {4, 14, 14, 1024, 512}, {8, 7, 7, 512, 1024}};
-    const uint32_t left[][5] = {{182, 50, 7, 64, 832}, {19, 8, 9, 408, 448}, {50, 24, 25, 392, 312}, {56, 6, 8, 960, 320}, {5, 39, 6, 768, 896},
+    const uint32_t left[][5] = {{182, 50, 7, 64, 832}, {19, 8, 9, 408, 448}, {50, 24, 25, 392, 312}, {5, 39, 6, 768, 896},
                                 {12, 88, 7, 976, 796}, {37, 22, 22, 144, 392}, {1, 7, 77, 468, 900}, {32, 14, 79, 256, 256}, {32, 4, 4, 512, 512}};
-    for (const auto& q : taken) CHECK(vgc::conv_taps_f32_chosen(q[0], q[1], q[2], q[3], q[4], true));
-    for (const auto& q : left) CHECK(!vgc::conv_taps_f32_chosen(q[0], q[1], q[2], q[3], q[4], true));
-    CHECK(!vgc::conv_taps_f32_chosen(32, 14, 14, 256, 256, false) && vgc::conv_taps_f32_chosen(16, 7, 7, 1024, 1024, false));
+    for (const auto& q : taken) CHECK(vgc::conv_taps_f32_splits(q[0], q[1], q[2], q[3], q[4], true));
+    for (const auto& q : left) CHECK(!vgc::conv_taps_f32_splits(q[0], q[1], q[2], q[3], q[4], true));
+    CHECK(!vgc::conv_taps_f32_splits(32, 14, 14, 256, 256, false) && vgc::conv_taps_f32_splits(16, 7, 7, 1024, 1024, false));
+    // The number of splits, with a workspace and without: one, or two with g, and the kernel scales and writes the results itself
+    // (layers of tests/test_gpu_sqgrad_taps_f32.py); more where k_conv_f32 adds up fewer samples in a row.
+    const uint32_t split[][7] = {{9, 7, 7, 512, 1024, 2, 1}, {8, 7, 7, 512, 1024, 2, 1}, {5, 14, 14, 1024, 512, 2, 1}, {6, 7, 7, 512, 1024, 2, 1},
+                                 {4, 14, 14, 1024, 512, 1, 1}, {16, 7, 7, 1024, 1024, 4, 1}, {64, 7, 7, 1024, 1024, 4, 1}, {128, 14, 14, 512, 512, 8, 0},
+                                 {57, 13, 13, 456, 464, 12, 0}, {32, 7, 7, 512, 512, 4, 0}, {64, 14, 14, 512, 512, 4, 0}};
+    for (const auto& q : split) {
+        CHECK(vgc::conv_taps_f32_splits(q[0], q[1], q[2], q[3], q[4], true) == q[5]);
+        CHECK(vgc::conv_taps_f32_splits(q[0], q[1], q[2], q[3], q[4], false) == q[6]);
+    }
 }
 
 // The workspace of a float32 convolution follows from the best number of splits of the batch, found here by looking at every one

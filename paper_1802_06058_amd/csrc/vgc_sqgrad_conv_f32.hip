@@ -20,6 +20,8 @@
 // of s against 64 bits over ResNet-50's layers: 0.51e-7 to 0.81e-7 (with the float32 instruction 0.66e-7 to 1.3e-7), of g
 // 0.79e-7 to 1.5e-7 (1.1e-7 to 2.9e-7).  Below 16 positions the last truncation shows: at one position g errs by 0.95e-7
 // (0.73e-7), s by 0.62e-7 (0.57e-7).
+#include <cmath>
+
 #include "vgc_internal.h"
 
 namespace vgc {
@@ -951,13 +953,14 @@ static uint64_t conv_f32_slots(const F32Tile& t) {
 // How a shape's work is divided: the samples over `splits` workgroups per tile, or (split_p > 1) every sample's positions
 // over split_p of them, for `slots` workgroups at once and chunks of `chunk` positions.  most: bytes of workspace; pairs: a
 // split of the samples leaves one plane of [J, C] in it, or with g a pair of them two (see k_conv_taps_f32), else each two.
+// least: of splits of the samples, where the workspace has room for as many; 1 split where it has not.
 struct F32Split { uint32_t splits, split_p; };
 static size_t f32_split_bytes(const F32Split& r, uint32_t J, uint32_t C, bool pairs) {
     const size_t JC = (size_t)J * C * sizeof(float);
     return r.split_p > 1 ? (size_t)r.splits * JC : r.splits > 1 ? (size_t)(pairs ? r.splits + r.splits % 2 : r.splits * 2) * JC : 0;
 }
 static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32_t B, uint32_t P, uint32_t J, uint32_t C, size_t most,
-                          bool pairs = false) {
+                          bool pairs = false, uint32_t least = 1) {
     const uint32_t n_chunks = (P + chunk - 1) / chunk;
     F32Split r{1, 1};
     if (tiles * B * 3 <= slots * 2 && n_chunks >= 256u / chunk) {
@@ -971,7 +974,7 @@ static F32Split f32_split(uint64_t tiles, uint64_t slots, uint32_t chunk, uint32
     // of the numbers of splits with the same largest number of samples the smallest; the next has fewer samples
     double best = 1e300;
     for (uint32_t s = 1, zper = B;; s = (B + zper - 2) / (zper - 1), zper = (B + s - 1) / s) {
-        if (f32_split_bytes(F32Split{s, 1}, J, C, pairs) <= most) {
+        if (s >= least && f32_split_bytes(F32Split{s, 1}, J, C, pairs) <= most) {
             const uint64_t rounds = (tiles * s + slots - 1) / slots;
             const double cost = (double)rounds * zper + (s > 1 ? 0.5 * s * (double)tiles / slots + 0.5 : 0.0);
             if (cost < best - 1e-9) { best = cost; r.splits = s; }
@@ -1064,9 +1067,18 @@ static uint64_t f32_chunks(const F32Split& s, uint32_t B, uint32_t n_chunks) {  
 // k_conv_f32: 256 at 14 x 14, batch 33 71 / 74 and 63 / 67; 192 -> 160 at 14 x 14 51 / 54 and 50 / 51; 256 at 8 x 8, batch 64
 // 50 / 57 and 47 / 57; 128 at 14 x 14, batch 7 26 / 32 and 21 / 28.  With g: 512 at 7 x 7 144 / 77 and 120 / 81; 256 at 14 x 14 78 / 71 and
 // 66 / 63; 64 -> 640 at 30 x 15, batch 111 287 / 261 and 256 / 255.  Half the channels a workgroup often make two rounds of one there:
-// 64 -> 832 at 50 x 7, batch 182 439 / 792 and 406 / 742, 408 -> 448 at 8 x 9, batch 19 75 / 117 and 62 / 117, 960 -> 320 at 6 x 8,
-// batch 56 223 / 261 and 191 / 274, for 10 to 36 % without g.  Of 190 shapes about the line the 96 that come here take 0.45 to 1.03 of
+// 64 -> 832 at 50 x 7, batch 182 439 / 792 and 406 / 742, 408 -> 448 at 8 x 9, batch 19 75 / 117 and 62 / 117, for 10 to 36 %
+// without g.  Of 190 shapes about the line the 96 that come here take 0.45 to 1.03 of
 // k_conv_f32's time with g and 0.50 to 0.96 without; the others would have taken 0.88 to 1.90, 1.15 in the mean.
+//
+// The errors must not grow by that.  The part of them that depends on the split is the rounding of a group's sums, added in a row: for s
+// with n samples in each of m groups about n / (3 m) times one addition's, squared.  The tiles here are larger, so that a layer of many
+// channels fills the chip with fewer and longer groups: 1024 -> 1024 at 7 x 7, batch 64, in one group of 64 had errors of 1.22e-7 (s)
+// and 1.54e-7 (g), k_conv_f32 0.53e-7 and 0.97e-7.  So n / m may be 2 more than there; beyond that the samples are split further:
+// 0.51e-7 and 0.96e-7, 372 us instead of 325 (k_conv_f32 497); 512 -> 512 at 14 x 14, batch 128, 0.57e-7 -> 0.50e-7, 546 -> 558 us (752).
+// Of 107 shapes, 72 of which are split further by this, s errs by 0.83 to 1.05 (mean 0.99) and g by 0.83 to 1.12 (mean 1.01) of what
+// k_conv_f32 does, without the limit by up to 2.29 and 1.59.  Those 72 take 0.65 to 0.98 of its time without g and 0.67 to 1.07 with g
+// (without the limit 0.61 to 0.89 and 0.54 to 2.1).  The layers of ResNet-50 and VGG-16 at batch 32 and 64 keep their splits.
 static bool conv_taps_f32_way(const F32Way& way, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, TapsGeom& G, F32Split& sp) {
     if (W > kTapsMaxW || H * W <= kR32 / 2) return false;
     G = taps_geom(H, W, Cin);
@@ -1074,7 +1086,11 @@ static bool conv_taps_f32_way(const F32Way& way, uint32_t B, uint32_t H, uint32_
     const uint64_t tiles = (uint64_t)((Cin + 63) / 64) * tiles_c;
     const F32Tile t = way.t;
     const F32Split other = way.sp;
-    sp = way.space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, way.asked, true) : F32Split{1, 1};
+    // a group's samples for each group: see above
+    const double samples = other.split_p > 1 ? 0.0 : (double)B / ((double)other.splits * other.splits);
+    const uint32_t least = (uint32_t)std::ceil(std::sqrt(B / (samples + 2.0)) - 1e-9);
+    sp = way.space ? f32_split(tiles, 256, kR32, B, G.n_chunks * kR32, J, C, way.asked, true, least) : F32Split{1, 1};
+    if (sp.split_p == 1 && sp.splits < least) return false;
     const bool parts = sp.split_p > 1, other_parts = other.split_p > 1;
     const uint64_t chunks = f32_chunks(sp, B, G.n_chunks), other_chunks = f32_chunks(other, B, (P + kR32 - 1) / kR32);
     auto general = [&](bool g) {
@@ -1087,10 +1103,11 @@ static bool conv_taps_f32_way(const F32Way& way, uint32_t B, uint32_t H, uint32_
     return f32_us((uint64_t)((Cin + 31) / 32) * tiles_c * blocks, 256, chunks * (sp.splits > 1 ? 2 : 1), 7.8, 1.45, blocks > 1 ? 2 * blocks : 0, false, J, C) <=
            general(true);
 }
-bool conv_taps_f32_chosen(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace) {
+// How many splits k_conv_taps_f32 takes a layer in, 0 where k_conv_f32 takes it.
+uint32_t conv_taps_f32_splits(uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, bool workspace) {
     TapsGeom G;
     F32Split sp;
-    return conv_taps_f32_way(conv_f32_way(B, H * W, 9 * Cin, C, workspace, ~(size_t)0), B, H, W, Cin, C, G, sp);
+    return conv_taps_f32_way(conv_f32_way(B, H * W, 9 * Cin, C, workspace, ~(size_t)0), B, H, W, Cin, C, G, sp) ? sp.splits : 0u;
 }
 
 // 0 or an error: launched; 1: k_conv_f32 takes the shape.

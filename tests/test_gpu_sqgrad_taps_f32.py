@@ -38,6 +38,19 @@ def _inputs(shape):
 
 @pytest.mark.parametrize("shape", SHAPES, ids=lambda s: "x".join(map(str, s)))
 def test_shapes(dev, shape):
+    _check_shape(dev, shape, (True,))
+
+
+# Layers whose results the kernel scales and writes itself: their samples are not split (without a workspace), or in two and g is asked
+# for, when the first half's sums of g wait in g's own buffer from four samples on.  And layers that would have so few groups of
+# samples that sums in a row grow longer than in the general kernel.  (The host check states the splits.)
+@pytest.mark.parametrize("shape", [(9, 7, 7, 512, 1024), (8, 7, 7, 512, 1024), (5, 14, 14, 1024, 512), (6, 7, 7, 512, 1024),
+                                   (16, 7, 7, 1024, 1024), (57, 13, 13, 456, 464)], ids=lambda s: "x".join(map(str, s)))
+def test_few_groups(dev, shape):
+    _check_shape(dev, shape, (True, False) if shape[4] == 1024 or shape[3] == 1024 else (True,))
+
+
+def _check_shape(dev, shape, workspaces):
     import torch
     from paper_1802_06058_amd import vgc
     B, H, W, Cin, C = shape
@@ -54,23 +67,24 @@ def test_shapes(dev, shape):
         s64 += G * G * c * c
         mag += (u.abs() @ e.abs()) * c
     g64, s64, mag = g64.cpu().numpy(), s64.cpu().numpy(), mag.cpu().numpy()
-    g, s = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev)
-    _, s_only = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev, want_g=False)
-    assert np.array_equal(s_only, s)
-    # as for the general kernel: |G_z - exact| <= about (P / 32 + 8) roundings of 2^-24 of the magnitudes summed, s doubles it, and
-    # sums over at least five samples do not cancel below a hundredth of the magnitudes squared
-    assert np.all(np.abs(s - s64) <= 1e-5 * s64)
-    assert np.all(np.abs(g - g64) <= 1e-6 * mag)
-    s_gen, g_gen = torch.empty(J, C, device=dev), torch.empty(J, C, device=dev)
-    nb = vgc.sqgrad_workspace_bytes(vgc.CONV, vgc.F32, B, P, J, C)
-    ws = torch.empty(nb, dtype=torch.uint8, device=dev) if nb else None
-    vgc.sqgrad(vgc.CONV, U, E, c, s_gen, g_gen, workspace=ws)
-    s_gen = s_gen.cpu().numpy()
-    assert not np.array_equal(s_gen, s)                              # another kernel, or this file tests nothing
-    assert np.all(np.abs(s - s_gen) <= 2e-5 * s64)
-    # no further from float64 than the general kernel by more than the spread between inputs
     norm = lambda x: np.sqrt((x.astype(np.float64) ** 2).sum())
-    assert norm(s - s64) <= 1.15 * norm(s_gen - s64)
+    for use_workspace in workspaces:
+        g, s = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev, True, use_workspace)
+        _, s_only = _run(A, D, 3, 3, (1, 1), (1, 1), c, dev, False, use_workspace)
+        assert np.array_equal(s_only, s)
+        # as for the general kernel: |G_z - exact| <= about (P / 32 + 8) roundings of 2^-24 of the magnitudes summed, s doubles it, and
+        # sums over at least five samples do not cancel below a hundredth of the magnitudes squared
+        assert np.all(np.abs(s - s64) <= 1e-5 * s64)
+        assert np.all(np.abs(g - g64) <= 1e-6 * mag)
+        s_gen, g_gen = torch.empty(J, C, device=dev), torch.empty(J, C, device=dev)
+        nb = vgc.sqgrad_workspace_bytes(vgc.CONV, vgc.F32, B, P, J, C) if use_workspace else 0
+        vgc.sqgrad(vgc.CONV, U, E, c, s_gen, g_gen, workspace=torch.empty(nb, dtype=torch.uint8, device=dev) if nb else None)
+        s_gen, g_gen = s_gen.cpu().numpy(), g_gen.cpu().numpy()
+        assert not np.array_equal(s_gen, s)                          # another kernel, or this file tests nothing
+        assert np.all(np.abs(s - s_gen) <= 2 * 1e-5 * s64)
+        # no further from float64 than the general kernel by more than the spread between inputs
+        assert norm(s - s64) <= 1.15 * norm(s_gen - s64)
+        assert norm(g - g64) <= 1.15 * norm(g_gen - g64)
 
 
 @pytest.mark.parametrize("shape", [SHAPES[1], SHAPES[3], SHAPES[4]], ids=lambda s: "x".join(map(str, s)))
