@@ -84,6 +84,20 @@ def test_two_tiles_a_wave(dev, alpha):
         first += tiles
     assert overflow == 0 and count <= total == int(tile_bytes.sum()) and torch.equal(begin[torch.tensor(runs, device=dev)], msg.run_offsets)
     assert [h[:2] for h in vgc.read_headers(msg.hdrs)] == [h[:2] for h in vgc.read_headers(hdrs)]
+    # streams that end inside a wave's second tile, between its two, inside the first, where a run begins, and before the first byte
+    wave = plan.n_tiles // 4
+    at = {k: int(begin[2 * wave + k]) for k in (0, 1, 2)}
+    assert at[0] + 2 < at[1] < at[2] - 2
+    want = [x.clone() for x in (msg.stream, msg.tile_bytes, msg.run_offsets)]
+    run = int(msg.run_offsets[plan.n_runs // 2])
+    for cap in (total, total - 1, at[2] - 1, at[1] + 1, at[1], at[0] + 1, run, run - 1, 1, 0):
+        for x, fill in ((msg.stream, 0xEE), (msg.tile_bytes, -1), (msg.run_offsets, -1)):
+            x.fill_(fill)
+        vgc.pack_compact(plan, scratch, msg.stream[:cap], msg.tile_bytes, msg.run_offsets, msg.hdrs, msg.status)
+        assert vgc.read_status(msg.status) == (total, int(total > cap))
+        assert torch.equal(msg.stream[:cap], want[0][:cap]) and bool((msg.stream[cap:] == 0xEE).all())
+        assert torch.equal(msg.tile_bytes, want[1]) and torch.equal(msg.run_offsets, want[2])
+    msg.stream.copy_(want[0])
     a, b = g, s                                                # (buffers whose contents are no longer needed)
     vgc.unpack_add_batch([words], [count], [hdrs], plan, 0.5, a, overwrite=True)
     vgc.unpack_compact_add_batch([msg.stream], [total], [msg.tile_bytes], [msg.run_offsets], [msg.hdrs], plan, 0.5, b, overwrite=True)
