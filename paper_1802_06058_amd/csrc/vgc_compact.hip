@@ -7,9 +7,9 @@
 // plus a directory: bytes per tile (uint16) and the byte offset of every run of 64 tiles (uint64).  The chain of
 // distances restarts in every tile, so one wave encodes or decodes a tile without looking at any other.
 //
-//   k_compact_count   one wave per tile: bytes the tile's kept entries take -> tile_bytes
+//   k_compact_count   one wave per one or two tiles: bytes the tile's kept entries take -> tile_bytes
 //   (k_run_sums and k_header_scan of vgc_pack.hip add them up: run offsets, group byte offsets, total)
-//   k_compact_emit    one wave per tile: the bytes
+//   k_compact_emit    one wave per one or two tiles: the bytes
 // The encoder waits on memory, for a few entries per tile: what counts is how many loads depend on one another.  Entries asked
 // for before it is known how many there are, a tile's place found from two tables instead of four, and the runs scanned where
 // the segments are: 3 % of 138 M elements 80.5 -> 56 us, 30 % 180 -> 139.  Sums over a wave
@@ -86,10 +86,16 @@ __device__ __forceinline__ uint32_t encode_tile(const TileAhead& a, const uint16
 }
 
 // kPer: consecutive tiles a wave does, whose first loads it asks for together.  The launches are rounds of waves that wait for memory
-// (8192 are resident), and with two tiles there are half as many: 138 M elements (67569 tiles) at 1.6 bytes a tile to 400, one
-// tile -> two, us: 43.9 -> 38.5, 48.8 -> 45.0 (67 bytes), 61.7 -> 59.3 (210), 112.3 -> 112.6 (620).  With fewer rounds the last ones,
-// partly empty, cost more than that where tiles have many entries (90 M, 43984 tiles: 38.1 -> 37.0, 87.3 -> 90.0); three or four
-// tiles lose there up to 150 M (138 M: 116.0, 121.7) and gain 3 % where few are sent.
+// (8192 are resident), and with two tiles there are half as many.  With few rounds the last ones, partly empty, cost more than that
+// where tiles have many entries.  vgc_pack_compact at 3, 109, 293, 650 and 1230 bytes a tile, one tile -> two, us:
+//   43984 tiles   36.4 -> 34.3, 40.8 -> 38.5, 53.0 -> 52.0,  84.5 ->  86.4, 127.7 -> 132.6
+//   56000         44.5 -> 41.9, 50.7 -> 47.0, 64.4 -> 63.3, 103.5 -> 106.0, 158.0 -> 163.4
+//   61000         47.4 -> 44.0, 56.2 -> 49.2, 69.0 -> 66.5, 111.1 -> 112.3, 171.5 -> 174.5
+//   65536         44.6 -> 39.7, 51.3 -> 45.4, 66.7 -> 64.1, 111.9 -> 112.2, 176.2 -> 179.0
+//   82000         52.8 -> 45.2, 59.1 -> 52.7, 77.6 -> 74.2, 133.7 -> 134.7, 219.2 -> 221.4
+//   100000        60.0 -> 52.5, 67.3 -> 59.9, 89.6 -> 85.4, 158.0 -> 157.3, 272.6 -> 269.2
+// So the line is where dense messages lose no more than 1.6 % and thin ones gain a tenth.  Three or four tiles lose up to 150 M elements
+// (138 M at 620 bytes 112.6 -> 116.0, 121.7) and gain 3 % where few are sent.
 template <uint32_t kPer>
 __global__ __launch_bounds__(256) void k_compact_count(PlanCheck pc, uint64_t n_tiles, const TileHdr* __restrict__ hdrs,
                                                        const uint16_t* __restrict__ staging, uint16_t* __restrict__ tile_bytes) {
@@ -267,7 +273,7 @@ __global__ __launch_bounds__(256) void k_compact_emit_small(PlanCheck pc, const 
     }
 }
 
-constexpr uint64_t kTwoTiles = 65536;                       // two tiles a wave from eight rounds of waves on (figures at the kernels)
+constexpr uint64_t kTwoTiles = 65536;                       // tiles from which on a wave does two: eight rounds of waves (figures at the kernels)
 int launch_pack_compact(PlanCheck pc, const uint32_t* flags, const PlanGroup* groups, const PlanTile* tiles, const PlanRun* runs,
                         const PlanSeg* segs, uint64_t n_tiles, uint64_t n_runs, uint32_t n_groups, uint32_t n_segs, uint32_t max_group_tiles,
                         TileHdr* hdrs, SegTmp* stmp, const uint16_t* staging, uint8_t* stream_out, uint64_t stream_cap,
@@ -651,8 +657,12 @@ bool compact_short_streams(const uint64_t* n_bytes, uint32_t p) {
 }
 
 // Whether the messages are so thin that several fit a round in most tiles (at most 256 bytes each; the longest of them decides).
-// The variant that looks for it costs 6 to 14 % where they do not: at 247 bytes a tile (8 % of 138 M elements, 8 messages) it takes
+// The variant that looks for it costs 6 to 15 % where they do not: at 247 bytes a tile (8 % of 138 M elements, 8 messages) it takes
 // 215 us against 187, at 170 165 against 185.  Lengths are what the caller knows: one given as a bound only keeps the other form.
+// They say nothing of how the bytes are spread: with as few in all, but half of the tiles at 12 % and half empty, it takes 217 us
+// against 186, an eighth of them at 24 % 331 against 301, two messages over 25.6 M 24.4 against 21.3.  A loop of either kind in one
+// kernel, chosen by a wave's first tiles, took 199, 311 and 25.8, and where all tiles are thin 1 to 5 % more (8 messages of 0.5 % of
+// 25.6 M: 28.5 -> 29.8): messages of one density are what is usual, so there is one loop.
 bool compact_thin_streams(const uint64_t* n_bytes, uint32_t p, uint64_t n_tiles) {
     uint64_t most = 0;
     for (uint32_t w = 0; w < p; ++w) most = std::max(most, n_bytes[w]);

@@ -271,8 +271,9 @@ __global__ __launch_bounds__(kWaves * 64, 4) void k_fused_fc_select(PlanCheck pc
     // for) and kSteps no branch is left around a load.  With them in branches each of these waits was for everything, the r and v
     // just requested among it.  In bf16, us: 25088 x 4096 at batch 32 363 -> 352, at batch 64 387 -> 385, 9216 x 1024 at 64
     // 72.3 -> 69.6, 4096 x 4096 80.5 -> 77.4, 5000 x 256 at 40 33.2 -> 30.2, 1001 x 512 at 20 29.1 -> 25.6; float32, 25088 x 4096
-    // at 16, 367 -> 357.  With two fragments of float32 it is slower (25088 x 4096 at 32: 391 -> 398): they stay in branches.  With one fragment there are registers left to request the r and v, too, 32 columns ahead (bf16, batch 32:
-    // 354 -> 351; with two: 387 -> 401, spilled).
+    // at 16, 367 -> 357.  With two fragments of float32 it is slower (25088 x 4096 at 32: 391 -> 398): they stay in branches.  With
+    // one fragment there are registers left to request the r and v, too, 32 columns ahead (bf16, batch 32: 354 -> 351; with two:
+    // 387 -> 401, spilled).
     constexpr bool kAhead = kSteps == 1;
     uint2 code[kN][2];                                        // of columns 32 n + tcol .. + 3, row q (n < kParked: in LDS meanwhile)
     auto pass = [&](auto whole_) __attribute__((always_inline)) {

@@ -16,7 +16,6 @@ constexpr uint32_t kTile = 2048;
 constexpr uint32_t kTileShift = 11;
 constexpr uint32_t kThreads = 256;
 constexpr uint32_t kElemsPerThread = kTile / kThreads;   // 8
-constexpr uint32_t kRelBins = 9;                          // staged exponent codes 0..8 (see StagedEntry)
 
 constexpr uint64_t kPlanMagic = 0x34304E414C504756ull;    // "VGPLAN04"
 

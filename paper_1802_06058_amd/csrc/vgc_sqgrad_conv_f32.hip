@@ -7,9 +7,9 @@
 // the same two mantissas it is the same each time.  (With hi cut off instead of rounded: 2^-22 and 2^-25.5.)
 //
 // Why: v_mfma_f32_32x32x2_f32 does 256 multiply-adds a cycle and compute unit, the bf16 instructions 4096, so six of the
-// latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32: 1.21 -> 0.66 ms (98 -> 180 TFLOP/s); the 53 layers
-// of ResNet-50 at batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product), 2.17 with
-// k_conv_taps_f32 below.  What bounds it now: the vector instructions that cut the elements (13 per pair, once per filter tap and
+// latter take 3/8 of the time.  3 x 3, 256 -> 256 at 56 x 56, batch 32, through k_conv_f32: 1.21 -> 0.66 ms (98 -> 180 TFLOP/s;
+// k_conv_taps_f32 below, which takes such layers, 0.52 on a card where this kernel takes 0.70); the 53 layers of ResNet-50 at
+// batch 32: 3.14 -> 2.30 ms in one batch call (1.19 ms at the rate of a large bf16 product), 2.17 with k_conv_taps_f32.  What bounds it now: the vector instructions that cut the elements (13 per pair, once per filter tap and
 // column tile) and those that add up the chunks share the issue slots with the MFMAs (matrix pipes 28 to 41 % busy on ResNet's
 // layers), and on the small layers a workgroup's 14 chunks take 19 us of its kernel's 31.
 //
@@ -514,8 +514,8 @@ void k_conv_f32(const float* __restrict__ X, const float* __restrict__ D, uint32
 // For the shift to be the same for all positions, rows are W + 1 pixels long here, the last one a zero: it is the padding to the
 // right of its row and to the left of the next.  Position q = y (W + 1) + x of a sample reads ring pixel q + (ky - 1)(W + 1) +
 // kx - 1; at x = W the output gradient is zero.  That costs 1 / W more positions (none in whole chunks of 32 at 14 x 14 and 7 x 7).
-// A step multiplies 32 positions and takes in 32 pixels, kLead ahead; samples follow each other in the ring with at least
-// W + 2 zeros between their last and first pixels, which pad one's bottom and the other's top.
+// A step multiplies 32 positions and takes in the 32 pixels behind those that it reads; samples follow each other in the ring with at
+// least W + 2 zeros between their last and first pixels, which pad one's bottom and the other's top.
 //
 // Eight waves: wave w has channels 16 (w % 4) .. + 15 of the block and one half of the columns: nine MFMA tiles of rows times two
 // of columns.  Pieces, products, signs and the sum of a chunk are those of the kernel above; the sign turns on the output
@@ -748,9 +748,6 @@ void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, u
 #pragma unroll
     for (int e = 0; e < 3; ++e) { fetch_a(0, 0, kOrder[e]); fetch_b(0, e); }
 
-    // Step q multiplies chunk q from D buffer q % 2 and takes in the next step's pixels and positions.  The fragments of the next
-    // tap are fetched during this one.  The one barrier of a step stands before its last tap: by then the wave has fetched all
-    // of the step's fragments and stored its share of the next step's input; the fragments of the next step's first tap follow.
     // the sums, the products of a part, or the scaled result go here; the lane's output i of tile (t, n)
     const bool direct = (splits <= (kWantG ? 2u : 1u) && split_p == 1);
     const size_t JC = (size_t)J * C;
@@ -776,6 +773,9 @@ void k_conv_taps_f32(const float* __restrict__ X, const float* __restrict__ D, u
     int32_t to_second = kWantG ? (int32_t)(z_of(2u * split + 1u) - z_begin) : 1;   // samples until the second group; then at most 0
     // from four samples a group on, g is summed by groups too (16 samples in a row, 512 -> 512 at 7 x 7: error 9.3e-8, 8.2e-8 so; 6 us)
     const bool halve_g = to_second >= 4;
+    // Step q multiplies chunk q from D buffer q % 2 and takes in the next step's pixels and positions.  The fragments of the next
+    // tap are fetched during this one.  The one barrier of a step stands before its last tap: by then the wave has fetched all
+    // of the step's fragments and stored its share of the next step's input; the fragments of the next step's first tap follow.
     for (uint32_t q0 = 0; q0 < total; q0 += 2) {
 #pragma unroll
         for (int u = 0; u < 2; ++u) {
@@ -1076,8 +1076,8 @@ static uint64_t f32_chunks(const F32Split& s, uint32_t B, uint32_t n_chunks) {  
 // channels fills the chip with fewer and longer groups: 1024 -> 1024 at 7 x 7, batch 64, in one group of 64 had errors of 1.22e-7 (s)
 // and 1.54e-7 (g), k_conv_f32 0.53e-7 and 0.97e-7.  So n / m may be 2 more than there; beyond that the samples are split further:
 // 0.51e-7 and 0.96e-7, 372 us instead of 325 (k_conv_f32 497); 512 -> 512 at 14 x 14, batch 128, 0.57e-7 -> 0.50e-7, 546 -> 558 us (752).
-// Of 107 shapes, 72 of which are split further by this, s errs by 0.83 to 1.05 (mean 0.99) and g by 0.83 to 1.12 (mean 1.01) of what
-// k_conv_f32 does, without the limit by up to 2.29 and 1.59.  Those 72 take 0.65 to 0.98 of its time without g and 0.67 to 1.07 with g
+// Of 108 shapes, 72 of which are split further by this, s errs by 0.84 to 1.05 (mean 0.99) and g by 0.83 to 1.12 (mean 1.00) of what
+// k_conv_f32 does, without the limit by up to 2.29 and 1.59.  Those 72 take 0.65 to 0.99 of its time without g and 0.67 to 1.07 with g
 // (without the limit 0.61 to 0.89 and 0.54 to 2.1).  The layers of ResNet-50 and VGG-16 at batch 32 and 64 keep their splits.
 static bool conv_taps_f32_way(const F32Way& way, uint32_t B, uint32_t H, uint32_t W, uint32_t Cin, uint32_t C, TapsGeom& G, F32Split& sp) {
     if (W > kTapsMaxW || H * W <= kR32 / 2) return false;

@@ -651,7 +651,9 @@ void launch_sqgrad_reduce_parts(const float* ws, uint32_t B, uint32_t split_p, s
 void launch_sqgrad_reduce(const float* ws, uint32_t splits, size_t JC, float cg, float cs, float* g_out, float* s_out,
                           hipStream_t stream, ReducePlanes planes) {
     const bool pairs = planes == ReducePlanes::kPairs;
-    const uint32_t sums = pairs ? (splits + 1) / 2 : splits, lanes = sums <= (planes == ReducePlanes::kSplits ? 4u : 2u) ? 1u : 4u;        // (16 lanes for more than 16 splits read 256-byte runs: 15 against 12.5 us on 32 planes of 1 MB)
+    const uint32_t sums = pairs ? (splits + 1) / 2 : splits;
+    // (16 lanes for more than 16 splits read 256-byte runs: 15 against 12.5 us on 32 planes of 1 MB)
+    const uint32_t lanes = sums <= (planes == ReducePlanes::kSplits ? 4u : 2u) ? 1u : 4u;
     const uint32_t opb = 256u / lanes;
     const bool vec = reduce_vec4(ws, JC, g_out, s_out);
     const dim3 grid((uint32_t)(((vec ? JC / 4 : JC) + opb - 1) / opb));
